@@ -165,8 +165,7 @@ int adacomp_compress(const adacomp_layer_t *layers, uint32_t n_layers, const flo
  *     graph and waits for the stream); calls that repeat the table only launch kernels and touch
  *     no allocator, host or device.
  *   - All calls on one GPU share that GPU's array, which keeps what the last call left in it.
- *     Nothing in it has to start at zero (every field a kernel reads is written earlier in the
- *     same call), but two calls that overlap in time on one GPU (different streams, different
+ *     Two calls that overlap in time on one GPU (different streams, different
  *     threads) race on it: give them one stream, or use adacomp_compress with workspaces of the
  *     caller's. */
 #define ADACOMP_STATIC_SCRATCH_BYTES (16u << 20)

@@ -27,6 +27,12 @@ int adacomp_debug_keep_gmax(int enable);
 int adacomp_workspace_gmax(const adacomp_layer_t *layers, uint32_t n_layers, size_t *byte_offset,
                            size_t *n_bins_total, size_t *learner_stride);
 
+/* Tables whose layers are small are compressed in one launch, whose workgroups wait for each other's
+ * sums.  A workgroup polls this often for one that is missing before it works it out itself (by
+ * default about 4000 times, some milliseconds).  0 makes every workgroup do so at once: for tests of
+ * that path.  Results do not depend on it.  Per workspace; ADACOMP_EWORKSPACE if it is not registered. */
+int adacomp_debug_wait_polls(void *workspace, uint32_t polls);
+
 /* Plain float4 device copy of n floats (dst, src 16-byte aligned): the reference kernel against
  * which HBM byte counters and the achievable copy bandwidth are calibrated. */
 int adacomp_copy_f32(float *dst, const float *src, size_t n, void *hip_stream);
@@ -55,8 +61,9 @@ int adacomp_selftest_binindex(void);
  * Returns ADACOMP_OK. */
 int adacomp_tuning_unpack_min_groups(uint32_t n_groups);
 
-/* Tuning knob of the compress calls, read at every call.  Tables of up to 512 compress tiles and
- * 16 layers skip the separate scan launch (layer scales, word offsets): the placement kernel works
+/* Tuning knob of the compress calls, read at every call.  Tables whose layers are small are compressed
+ * in one launch, and other tables of up to 512 compress tiles and 16 layers skip the separate scan
+ * launch (layer scales, word offsets): the placement kernel works
  * them out itself.  enable = 0 makes such tables take the three-launch path of the large ones;
  * non-zero restores the default.  Results do not depend on it while the float64 sum of every layer's
  * g_max vector is exact (see "Arithmetic" in adacomp.h); beyond that a layer scale may differ in its

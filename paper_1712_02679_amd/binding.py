@@ -24,6 +24,7 @@ EXPORTS = [
     "adacomp_compress", "adacomp_compress_static", "adacomp_compress_batch", "adacomp_compress_variant",
     "adacomp_compress_batch_lazy", "adacomp_residue_sync",
     "adacomp_unpack_accumulate", "adacomp_unpack_update", "adacomp_strerror", "adacomp_workspace_gmax", "adacomp_debug_keep_gmax",
+    "adacomp_debug_wait_polls",
     "adacomp_copy_f32", "adacomp_triad_f32", "adacomp_triad_resident_f32", "adacomp_fill_f32",
     "adacomp_selftest_binindex", "adacomp_tuning_unpack_min_groups", "adacomp_tuning_fold_scan", "adacomp_tuning_place_tiled", "adacomp_timing_enable", "adacomp_timing_read",
 ]
@@ -93,6 +94,7 @@ def lib():
         L.adacomp_strerror.argtypes = [ctypes.c_int]
         L.adacomp_workspace_gmax.argtypes = [LP, u32, ctypes.POINTER(sz), ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.adacomp_debug_keep_gmax.argtypes = [ctypes.c_int]
+        L.adacomp_debug_wait_polls.argtypes = [vp, u32]
         L.adacomp_copy_f32.argtypes = [vp, vp, sz, vp]
         L.adacomp_triad_f32.argtypes = [vp, vp, sz, vp]
         L.adacomp_triad_resident_f32.argtypes = [vp, vp, sz, ctypes.c_uint32, vp]
@@ -252,6 +254,11 @@ def adacomp_workspace_gmax(layers):
 
 def adacomp_debug_keep_gmax(on: bool):
     _check(lib().adacomp_debug_keep_gmax(1 if on else 0))
+
+
+def adacomp_debug_wait_polls(workspace, polls: int):
+    """How often a workgroup of a one-launch compress polls for a record before it works it out itself."""
+    _check(lib().adacomp_debug_wait_polls(_ptr(workspace), int(polls)))
 
 
 def adacomp_copy_f32(dst, src, n=None):

@@ -118,7 +118,9 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         ld.ctile_start = uint32_t(n_ctiles);
         ld.n_ctiles = nt;
         p.n_class_tiles[cls] += nt;
+        p.layer_tiles_max = std::max(p.layer_tiles_max, nt);
         if (T <= 64u) p.has_short_bins = true;
+        if (T < 4u) p.has_tiny_bins = true;
         // The staging array is indexed by position in the tile table, not by address: a tile's stretch
         // starts where the stretches of the tiles before it end (each rounded up to 4 entries, which keeps
         // every stretch 8-byte aligned), so its size follows the element count whatever holes the table has.
@@ -277,7 +279,24 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     if (off >= (size_t(1) << 32)) return ADACOMP_EINVAL;
     w.stage = off;       off = pad256(off + 2 * size_t(p.stage_entries) + 128);  // slack: k_place reads up to 64 entries from a tile's start
     w.scratch_stride = off;
+    off = 0;             // offsets inside one learner's exchange area
+    w.sync_rec = off;    off = pad256(off + 16 * size_t(p.n_ctiles));
+    w.sync_tile = off;   off = pad256(off + 32 * size_t(p.n_ctiles));
+    w.sync_layer = off;  off = pad256(off + 32 * size_t(n_layers));
+    w.sync_epoch = off;  off = pad256(off + 4 * size_t(p.n_ctiles));
+    if (off >= (size_t(1) << 32)) return ADACOMP_EINVAL;
+    w.sync_stride = off;
     return ADACOMP_OK;
+}
+
+SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes)
+{
+    SyncPlace at;
+    const size_t end = workspace_bytes & ~size_t(255);
+    if (end <= ws.scratch) return at;
+    at.learners = std::min((end - ws.scratch) / (ws.scratch_stride + ws.sync_stride), kSyncLearnersMax);
+    at.offset = end - at.learners * ws.sync_stride;
+    return at;
 }
 
 // Workspaces that adacomp_workspace_init has filled, by address.
@@ -289,6 +308,7 @@ struct Registered {
     size_t bytes = 0;
     std::vector<adacomp_layer_t> table;  // the layer table the tile tables in the workspace were built for
     std::vector<float *> waiting;
+    uint32_t wait_polls = kWaitPolls;
 };
 
 static bool same_table(const std::vector<adacomp_layer_t> &have, const adacomp_layer_t *layers, uint32_t n_layers)
@@ -314,15 +334,17 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     // the kernels index the tile tables in the workspace without further checks: the table of this
     // call must be, entry by entry, the one those tables were built for
     if (!same_table(it->second.table, layers, n_layers)) return ADACOMP_EWORKSPACE;
-    if (workspace_bytes < p.ws.total(n_learners) || it->second.bytes < p.ws.total(n_learners)) return ADACOMP_EWORKSPACE;
+    if (workspace_bytes < p.ws.least(n_learners) || it->second.bytes < p.ws.least(n_learners)) return ADACOMP_EWORKSPACE;
     // copy the scalars only; the tables already live on the device
     out.n_layers = p.n_layers; out.n_ctiles = p.n_ctiles; out.n_utiles = p.n_utiles; out.n_ugroups = p.n_ugroups; out.n_ugroups8 = p.n_ugroups8; out.n_usingles8 = p.n_usingles8;
     out.n_bins_total = p.n_bins_total; out.n_chunks_total = p.n_chunks_total;
     out.elem_span = p.elem_span; out.n_elems_total = p.n_elems_total; out.stage_entries = p.stage_entries;
     out.fixed_bytes = p.fixed_bytes; out.bound_bytes = p.bound_bytes;
     for (int c = 0; c < 2; ++c) out.n_class_tiles[c] = p.n_class_tiles[c];
+    out.layer_tiles_max = p.layer_tiles_max; out.has_tiny_bins = p.has_tiny_bins;
     out.has_short_bins = p.has_short_bins; out.has_shifted_tiles = p.has_shifted_tiles;
     out.ws = p.ws;
+    out.sync = p.sync;
     return ADACOMP_OK;
 }
 
@@ -412,7 +434,7 @@ int adacomp_workspace_init(const adacomp_layer_t *layers, uint32_t n_layers, voi
     int rc = build_plan(layers, n_layers, true, reg.plan);
     if (rc != ADACOMP_OK) return rc;
     Plan &p = reg.plan;
-    if (workspace_bytes < p.ws.total(1)) return ADACOMP_EWORKSPACE;
+    if (workspace_bytes < p.ws.least(1)) return ADACOMP_EWORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (hipStreamSynchronize(s) != hipSuccess) return ADACOMP_EHIP;
     char *ws = static_cast<char *>(workspace);
@@ -422,6 +444,10 @@ int adacomp_workspace_init(const adacomp_layer_t *layers, uint32_t n_layers, voi
         hipMemcpy(ws + p.ws.utiles, p.utiles.data(), sizeof(UTileDev) * p.utiles.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(ws + p.ws.ugroups, p.ugroups.data(), sizeof(UGroupDev) * p.ugroups.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(ws + p.ws.usingles, p.usingles.data(), sizeof(UGroupDev) * p.usingles.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return ADACOMP_EHIP;
+    p.sync = sync_place(p.ws, workspace_bytes);
+    if (p.sync.learners != 0 && (hipMemset(ws + p.sync.offset, 0, p.sync.learners * p.ws.sync_stride) != hipSuccess ||
+                                 hipStreamSynchronize(nullptr) != hipSuccess))
         return ADACOMP_EHIP;
     register_workspace(layers, n_layers, workspace, workspace_bytes, std::move(reg.plan));
     return ADACOMP_OK;
@@ -448,6 +474,18 @@ static bool fold_scan_for(const Plan &p)
     return g_fold_scan.load(std::memory_order_relaxed) && place_lanes_for(p) == 64u && p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;
 }
 
+// One launch for everything, where the tiles of each layer are on the GPU together (see k_pack): tables of
+// the 4096-element tile class (whose tiles are 16-byte aligned), with bins of at least four elements, in a
+// workspace that has exchange areas for all learners of the call.
+static uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes)
+{
+    if (n_learners > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
+    if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
+    if (p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers) return kOneLaunchTable;
+    const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
+    return (p.layer_tiles_max <= most && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
+}
+
 static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uint32_t n_learners,
                            const float *const *grads, float *const *residues, void *const *packets_out,
                            size_t packet_capacity, uint32_t rule, float soft_factor, bool lazy, void *workspace,
@@ -471,10 +509,15 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     // Corrections that wait belong to the residue buffers of the call that left them: a lazy call
     // goes on with exactly those buffers, anything else has to wait for adacomp_residue_sync.
     bool corrections_wait = false;
+    uint32_t wait_polls = kWaitPolls;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_ws.find(workspace);
         if (it == g_ws.end()) return ADACOMP_EWORKSPACE;  // released by another thread meanwhile
+        // more learners than there are exchange areas, in a workspace whose last scratch blocks reach into
+        // those: the areas are lost, and this workspace takes the staged launches from here on
+        if (p.ws.least(n_learners) > p.sync.offset) it->second.plan.sync = p.sync = SyncPlace();
+        wait_polls = it->second.wait_polls;
         const std::vector<float *> &waiting = it->second.waiting;
         if (!waiting.empty()) {
             if (!lazy || waiting.size() != n_learners) return ADACOMP_EPENDING;
@@ -494,6 +537,11 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     a.o_tile_out = uint32_t(p.ws.tile_out); a.o_layer_nsel = uint32_t(p.ws.layer_nsel);
     a.o_layer_scale = uint32_t(p.ws.layer_scale); a.o_gmax = uint32_t(p.ws.gmax);
     a.o_chunk_rel = uint32_t(p.ws.chunk_rel); a.o_stage = p.ws.stage;
+    a.o_sync_rec = uint32_t(p.ws.sync_rec); a.o_sync_tile = uint32_t(p.ws.sync_tile);
+    a.o_sync_layer = uint32_t(p.ws.sync_layer); a.o_sync_epoch = uint32_t(p.ws.sync_epoch);
+    a.one_launch = lazy ? kOneLaunchNever : one_launch_for(p, n_learners, workspace_bytes);
+    a.sync_stride = p.ws.sync_stride;
+    a.wait_polls = wait_polls;
     a.n_tiles = p.n_ctiles;
     a.n_layers = p.n_layers;
     a.keep_gmax = g_keep_gmax.load(std::memory_order_relaxed) ? 1u : 0u;
@@ -524,6 +572,7 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
         const uint32_t now = std::min(n_learners - done, kMaxBatch);
         a.n_learners = now;
         a.scratch = reinterpret_cast<uint8_t *>(ws + p.ws.scratch + p.ws.scratch_stride * done);
+        a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset + p.ws.sync_stride * done);
         for (uint32_t k = 0; k < kMaxBatch; ++k) {
             a.grad[k] = k < now ? grads[done + k] : nullptr;
             a.residue[k] = k < now ? residues[done + k] : nullptr;
@@ -555,6 +604,7 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
             }
             if (ev_end && hipEventRecord(ev_end, s) != hipSuccess) return ADACOMP_EHIP;
         }
+        if (a.one_launch) continue;
         if (!a.fold_scan && (rc = launch_scan(a, hip_stream)) != ADACOMP_OK) return rc;
         if ((rc = launch_place(a, hip_stream)) != ADACOMP_OK) return rc;
     }
@@ -693,7 +743,7 @@ int adacomp_compress_static(const adacomp_layer_t *layers, uint32_t n_layers, co
     Plan p;
     int rc = build_plan(layers, n_layers, false, p);
     if (rc != ADACOMP_OK) return rc;
-    if (p.ws.total(1) > kStaticScratchBytes) return ADACOMP_ETOOBIG;
+    if (p.ws.least(1) > kStaticScratchBytes) return ADACOMP_ETOOBIG;
     if (rc_dev != ADACOMP_OK) return rc_dev;
     if ((rc = adacomp_workspace_init(layers, n_layers, ws, kStaticScratchBytes, hip_stream)) != ADACOMP_OK) return rc;
     return adacomp_compress(layers, n_layers, grad, residue, packet_out, packet_capacity, ws, kStaticScratchBytes,
@@ -853,6 +903,15 @@ int adacomp_selftest_binindex(void)
 int adacomp_debug_keep_gmax(int enable)
 {
     g_keep_gmax = enable != 0;
+    return ADACOMP_OK;
+}
+
+int adacomp_debug_wait_polls(void *workspace, uint32_t polls)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_ws.find(workspace);
+    if (it == g_ws.end()) return ADACOMP_EWORKSPACE;
+    it->second.wait_polls = polls;
     return ADACOMP_OK;
 }
 

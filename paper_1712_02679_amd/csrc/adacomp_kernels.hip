@@ -5,7 +5,8 @@
 // per layer; the soft-threshold factor of the variant entry point adds one multiply per element,
 // the fused optimizer step a handful of separate float32 operations per element.
 //
-// adacomp_compress runs three launches:
+// adacomp_compress runs one launch, k_pack, on tables whose layers are small enough that the tiles of
+// a layer are on the GPU together (see there), and three on the others:
 //   k_fused  (streaming, dominant)  one pass over dW and the residue: G = R + dW, H = G + dW, the
 //            per-bin maximum of |G|, the selection compare, and R <- G, all while the tile sits
 //            in registers (Algorithm 2 of the AdaComp paper, both loops; selection is local to a
@@ -64,6 +65,15 @@ __device__ __forceinline__ vfloat4 buffer_load_stream4(__amdgpu_buffer_rsrc_t rs
 __device__ __forceinline__ void buffer_store_stream4(__amdgpu_buffer_rsrc_t rsrc, uint32_t elem, vfloat4 v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vuint4, v), rsrc, int(elem * 4u), 0, kAuxStream);
+}
+// a slot at byte offset `lane_at` (per lane) + `row_at` (uniform) of a tile
+__device__ __forceinline__ vfloat4 buffer_load_slot(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_at, uint32_t row_at)
+{
+    return __builtin_bit_cast(vfloat4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(lane_at), int(row_at), kAuxStream));
+}
+__device__ __forceinline__ void buffer_store_slot(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_at, uint32_t row_at, vfloat4 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vuint4, v), rsrc, int(lane_at), int(row_at), kAuxStream);
 }
 // one element through the same descriptor (the first and last slot of a tile that is not 16-byte aligned)
 __device__ __forceinline__ float buffer_load1(__amdgpu_buffer_rsrc_t rsrc, uint32_t elem)
@@ -410,6 +420,731 @@ __global__ __launch_bounds__(WAVES * 64) void k_fused(const CompressArgs a)
     }
 }
 
+__device__ __forceinline__ uint64_t pad16_dev(uint64_t x) { return (x + 15u) & ~uint64_t(15); }
+
+// Header, layer records and zero padding of one learner's packet, by one workgroup of WG threads:
+// WG layers at a time, word offsets by a block scan of the padded section sizes (all below 2^32: the
+// packet bound is).  get(l, layer, words, scale) says what layer l sends; it is called by the thread
+// that writes the layer's record.
+template <uint32_t WG, class Get>
+__device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *const packet, Get get)
+{
+    const uint32_t tid = threadIdx.x;
+    __shared__ uint32_t s_wtot[WG / 64u];
+    const uint32_t lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint64_t carry = a.fixed_bytes, nsel_all = 0;
+    for (uint32_t l0 = 0; l0 < a.n_layers; l0 += WG) {
+        const uint32_t l = l0 + tid;
+        const bool live = l < a.n_layers;
+        LayerDev ld;
+        uint32_t nsel = 0u, bytes = 0u;
+        float scale = 0.f;
+        if (live) {
+            ld = a.layers[l];
+            get(l, ld, nsel, scale);
+            bytes = uint32_t(pad16_dev(uint64_t(nsel) * ld.word_bytes));
+        }
+        const uint32_t incl = wave_incl_scan(bytes);
+        uint32_t nsum = wave_sum(nsel);
+        __syncthreads();  // previous round's readers of s_wtot are done
+        if (lane == 63) s_wtot[wave] = incl;
+        __syncthreads();
+        uint64_t before = carry;
+        for (uint32_t wv = 0; wv < wave; ++wv) before += s_wtot[wv];
+        const uint64_t woff = before + incl - bytes;
+        for (uint32_t wv = 0; wv < WG / 64u; ++wv) carry += s_wtot[wv];
+        if (live) {
+            adacomp_packet_layer_t rec;
+            rec.elem_offset = ld.elem_offset; rec.n_elems = ld.n_elems;
+            rec.L_T = ld.L_T; rec.n_bins = ld.n_bins; rec.word_bits = ld.word_bytes * 8u;
+            rec.scale = scale;
+            rec.n_selected = nsel;
+            rec.counts_offset = ld.counts_offset; rec.chunks_offset = ld.chunks_offset; rec.words_offset = woff;
+            reinterpret_cast<adacomp_packet_layer_t *>(packet + sizeof(adacomp_packet_header_t))[l] = rec;
+            for (uint64_t b = ld.counts_offset + uint64_t(ld.n_bins) * ld.word_bytes; b < ld.chunks_offset; ++b) packet[b] = 0;
+            const uint64_t chunks_end = ld.chunks_offset + 4ull * ld.n_chunks;
+            for (uint64_t b = chunks_end; b < pad16_dev(chunks_end); ++b) packet[b] = 0;
+            const uint64_t words_end = woff + uint64_t(nsel) * ld.word_bytes;
+            for (uint64_t b = words_end; b < pad16_dev(words_end); ++b)
+                if (b < a.capacity) packet[b] = 0;
+        }
+        // total word count: per-wave sums through the same LDS slots
+        __syncthreads();
+        if (lane == 0) s_wtot[wave] = nsum;
+        __syncthreads();
+        for (uint32_t wv = 0; wv < WG / 64u; ++wv) nsel_all += s_wtot[wv];
+    }
+    if (tid == 0) {
+        adacomp_packet_header_t h;
+        h.magic = ADACOMP_PACKET_MAGIC; h.version = ADACOMP_PACKET_VERSION;
+        h.status = carry > a.capacity ? ADACOMP_STATUS_TRUNCATED : ADACOMP_STATUS_COMPLETE;
+        h.n_layers = a.n_layers; h.total_bytes = carry; h.n_selected = nsel_all;
+        *reinterpret_cast<adacomp_packet_header_t *>(packet) = h;
+    }
+}
+
+// ==============================================================================================
+// The one-launch compress: k_pack does all of Algorithm 2, for tables whose layers are small enough
+// that the tiles of a layer are on the GPU together.
+//
+// What forces a second launch is the layer's scale: it is known when all tiles of the layer have their
+// g_max, and the residue and the place of a word in the packet need it (or the word counts, which
+// come with it).  Written as two launches the residue is stored, fetched again and corrected; here a
+// workgroup keeps its G in registers and its words in LDS, publishes its tile's record (sum of
+// g_max, word count), waits until the layer's records are there, and then writes residue and words
+// once, in their final form.  ResNet-50's table (25.5 M elements, L_T 50, 8 % of the elements sent)
+// moved 12 bytes per element in k_fused and 6 more in the placement.
+//
+// Who adds up the records:
+//   kOneTable   (at most kFoldTiles tiles and kFoldLayers layers) every workgroup reads the records of
+//               the whole table: one hop from the last record to everybody, which is what counts
+//               where the launch is a few microseconds long.
+//   kOneLayers  the workgroup of a layer's last tile reads the layer's records and publishes the scale,
+//               the size of the layer's words and every tile's first word; the others wait for those.
+//
+// Published words carry their own validity: every 8-byte word holds 32 bits of value and, in the rest,
+// the number of the call (the tile's epoch, kept in the scratch block and raised by one by the tile's
+// workgroup in every call), and is read and written with relaxed device-scope atomics.  No fence (a
+// device-scope release writes back the L2), no counter, nothing to clear between calls, and a call
+// replayed from a graph counts on like any other.
+//
+// No workgroup depends on another one being scheduled.  A wait is bounded (CompressArgs::wait_polls);
+// when it runs out, the workgroup works out the missing records itself: a tile's record follows from
+// dW and the residue, and the residue of a tile is written only after all records of its layer are
+// published, so whoever finds a record missing may read the tile's inputs.  Should the owner have
+// moved on while the helper was reading, the helper's compare-and-swap finds the record there and
+// drops what it computed; otherwise the two hold the same bits, being the same operations in the same
+// order.  So two calls on different streams that hold each other's compute units finish, late.
+// ==============================================================================================
+constexpr int kOneTable = int(kOneLaunchTable), kOneLayers = int(kOneLaunchLayers);
+
+// One element of Algorithm 2: the bits of G = R + dW (sign included) and of what is compared with
+// g_max, max(|G|, |H|) with H = G + dW (VARIANT: by the rule and the factor of the call).
+template <bool VARIANT>
+__device__ __forceinline__ void element_bits(const CompressArgs &a, const float r, const float w, uint32_t &gb, uint32_t &mb)
+{
+    const float G = r + w;
+    float H;
+    if (VARIANT) {
+        const float extra = a.soft_factor_minus_1 * w;  // residue + f dW = G + (f - 1) dW
+        H = G + extra;
+    } else {
+        H = G + w;
+    }
+    gb = __float_as_uint(G);
+    const uint32_t ag = gb & 0x7FFFFFFFu, ah = __float_as_uint(H) & 0x7FFFFFFFu;
+    if (VARIANT && a.rule == ADACOMP_RULE_PRINTED_COMPARE) mb = ah;          // |H| alone
+    else if (VARIANT && a.rule == ADACOMP_RULE_LOCAL_SELECTION) mb = ag;     // bin maxima only
+    else mb = ag > ah ? ag : ah;
+}
+
+// The selection: sent iff G != 0 and max(|H|, |G|) >= g_max; the printed compare alone also sends
+// elements whose G is zero.
+template <bool VARIANT>
+__device__ __forceinline__ bool element_sent(const CompressArgs &a, const uint32_t gb, const uint32_t mb, const uint32_t gm)
+{
+    const bool nonzero = (gb & 0x7FFFFFFFu) != 0u || (VARIANT && a.rule == ADACOMP_RULE_PRINTED_COMPARE);
+    return nonzero && (mb >= gm);
+}
+
+struct SyncArea {
+    uint64_t *rec;     // 2 per tile: high half of the tile's g_max sum | epoch; low half | word count, epoch
+    uint64_t *tile;    // 4 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch; unused
+    uint64_t *layer;   // 4 per layer: scale | epoch; padded bytes of its words | epoch; its words | epoch; unused
+    uint32_t *epoch;   // per tile: number of the last call, written by the tile's own workgroup only
+};
+
+// LDS of a workgroup that waits
+struct OneShared {
+    uint64_t old_rec[2];
+    uint32_t w[16];
+    double d[16];
+    uint32_t any[3][16];
+    uint32_t missing, base, at, bytes;
+    float scale;
+};
+
+// Whether any thread of the workgroup says so; a barrier.  `slot`: 16 words of LDS that nobody has read since
+// the barrier before this one.  (__syncthreads_or does the same with hidden kernel arguments.)
+template <uint32_t WG>
+__device__ __forceinline__ bool block_any(const bool mine, uint32_t *slot)
+{
+    const bool in_wave = __builtin_amdgcn_ballot_w64(mine) != 0ull;
+    if ((threadIdx.x & 63u) == 0u) slot[threadIdx.x >> 6] = in_wave ? 1u : 0u;
+    __syncthreads();
+    uint32_t any = 0u;
+#pragma unroll
+    for (uint32_t wv = 0; wv < WG / 64u; ++wv) any |= slot[wv];
+    return any != 0u;
+}
+
+__device__ __forceinline__ uint64_t sync_load(const uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void sync_store(uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ uint64_t sync_word(uint32_t value, uint32_t epoch) { return (uint64_t(value) << 32) | epoch; }
+
+// a word count is at most 16384: 15 bits, and 17 for the epoch.  Every tile's record is written in
+// every call, so a stale one is always exactly one call old.
+constexpr uint32_t kRecEpochMask = (1u << 17) - 1u;
+__device__ __forceinline__ uint64_t rec_high(double sum, uint32_t epoch) { return (__builtin_bit_cast(uint64_t, sum) & 0xFFFFFFFF00000000ull) | epoch; }
+__device__ __forceinline__ uint64_t rec_low(double sum, uint32_t count, uint32_t epoch)
+{
+    return (__builtin_bit_cast(uint64_t, sum) << 32) | (count << 17) | (epoch & kRecEpochMask);
+}
+__device__ __forceinline__ bool rec_valid(uint64_t hi, uint64_t lo, uint32_t epoch)
+{
+    return uint32_t(hi) == epoch && (uint32_t(lo) & kRecEpochMask) == (epoch & kRecEpochMask);
+}
+__device__ __forceinline__ double rec_sum(uint64_t hi, uint64_t lo) { return __builtin_bit_cast(double, (hi & 0xFFFFFFFF00000000ull) | (lo >> 32)); }
+__device__ __forceinline__ uint32_t rec_count(uint64_t lo) { return uint32_t(lo) >> 17; }
+
+// Sum of a tile's g_max values by a whole workgroup, in the one order that the tile's owner and a
+// helper both use; the result is in thread 0.  Has a barrier; `d` is free again after the next one.
+template <uint32_t WG>
+__device__ __forceinline__ double tile_gmax_sum(const uint32_t *s_gmax, const uint32_t nb, double *d)
+{
+    const uint32_t tid = threadIdx.x;
+    double part = 0.0;
+    if ((tid & ~63u) < nb) {   // uniform in a wave
+        for (uint32_t i = tid; i < nb; i += WG) part += double(__uint_as_float(s_gmax[i]));
+        part = wave_sum_f64(part);
+    }
+    if ((tid & 63u) == 0u) d[tid >> 6] = part;
+    __syncthreads();
+    double sum = d[0];
+    for (uint32_t wv = 1; wv < WG / 64u; ++wv) sum += d[wv];
+    return sum;
+}
+
+// Works out and publishes the record of a tile whose workgroup has not done it, by the whole
+// workgroup; does nothing if the record is there.  Begins and ends with a barrier.
+template <uint32_t WG, bool VARIANT>
+__device__ __forceinline__ void help_tile(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t tile,
+                                          const uint32_t epoch, uint32_t *s_gmax, OneShared &sh)
+{
+    const uint32_t tid = threadIdx.x;
+    __syncthreads();
+    if (tid == 0) {
+        sh.old_rec[0] = sync_load(sy.rec + 2u * tile);
+        sh.old_rec[1] = sync_load(sy.rec + 2u * tile + 1u);
+        sh.missing = rec_valid(sh.old_rec[0], sh.old_rec[1], epoch) ? 0u : 1u;
+        sh.base = 0u;
+    }
+    __syncthreads();
+    if (sh.missing != 0u) {   // uniform over the workgroup
+        const TileDev td = a.tiles[tile];
+        const uint32_t n = td.n_elems, T = td.L_T, M = td.magic, nb = td.n_bins;
+        const float *gr = a.grad[lr] + td.elem_base, *rs = a.residue[lr] + td.elem_base;
+        for (uint32_t i = tid; i < nb; i += WG) s_gmax[i] = 0u;
+        __syncthreads();
+        uint32_t gb, mb, count = 0u;
+        for (uint32_t e = tid; e < n; e += WG) {
+            element_bits<VARIANT>(a, rs[e], gr[e], gb, mb);
+            atomicMax(&s_gmax[bin_of(e, T, M)], gb & 0x7FFFFFFFu);
+        }
+        __syncthreads();
+        for (uint32_t e = tid; e < n; e += WG) {
+            element_bits<VARIANT>(a, rs[e], gr[e], gb, mb);
+            count += element_sent<VARIANT>(a, gb, mb, s_gmax[bin_of(e, T, M)]) ? 1u : 0u;
+        }
+        count = wave_sum(count);
+        if ((tid & 63u) == 0u) atomicAdd(&sh.base, count);
+        const double sum = tile_gmax_sum<WG>(s_gmax, nb, sh.d);
+        if (tid == 0) {
+            const uint32_t total = sh.base;
+            if (uint32_t(sh.old_rec[0]) != epoch)
+                __hip_atomic_compare_exchange_strong(sy.rec + 2u * tile, &sh.old_rec[0], rec_high(sum, epoch), __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t(sh.old_rec[1]) & kRecEpochMask) != (epoch & kRecEpochMask))
+                __hip_atomic_compare_exchange_strong(sy.rec + 2u * tile + 1u, &sh.old_rec[1], rec_low(sum, total, epoch), __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+}
+
+// One thread's records, tiles ts + tid, ts + tid + WG, ...: HOLD of them.
+template <uint32_t HOLD>
+struct Records {
+    uint64_t hi[HOLD], lo[HOLD];
+};
+
+// Polls for the thread's records of tiles ts .. ts + nt - 1; says whether they all came.
+template <uint32_t WG, uint32_t HOLD>
+__device__ __forceinline__ bool poll_records(const SyncArea &sy, const uint32_t ts, const uint32_t nt,
+                                             const uint32_t epoch, const uint32_t most_polls, Records<HOLD> &rec)
+{
+    bool all = true;
+#pragma unroll
+    for (uint32_t h = 0; h < HOLD; ++h) {
+        rec.hi[h] = 0u;
+        rec.lo[h] = 0u;
+        const uint32_t i = h * WG + threadIdx.x;
+        const uint64_t *src = sy.rec + 2u * (ts + i);
+        bool ok = i >= nt;
+        for (uint32_t polls = 0; !ok && polls <= most_polls; ++polls) {
+            if (polls != 0u) __builtin_amdgcn_s_sleep(1);
+            rec.hi[h] = sync_load(src);
+            rec.lo[h] = sync_load(src + 1);
+            ok = rec_valid(rec.hi[h], rec.lo[h], epoch);
+        }
+        all = all && ok;
+    }
+    return all;
+}
+
+// before[h]: words of the tiles before the thread's h-th; adds the thread's g_max sums to `part`; returns
+// the words of all tiles.  Begins behind a barrier (sh.w is free) and ends with one.
+template <uint32_t WG, uint32_t HOLD>
+__device__ __forceinline__ uint32_t scan_records(const uint32_t nt, const Records<HOLD> &rec, OneShared &sh, uint32_t (&before)[HOLD], double &part)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t run = 0u;
+#pragma unroll
+    for (uint32_t h = 0; h < HOLD; ++h) {
+        before[h] = 0u;
+        if (h != 0u && h * WG >= nt) continue;   // uniform
+        const bool live = h * WG + tid < nt;
+        const uint32_t count = live ? rec_count(rec.lo[h]) : 0u;
+        if (live) part += rec_sum(rec.hi[h], rec.lo[h]);
+        const uint32_t incl = wave_incl_scan(count);
+        if (lane == 63u) sh.w[wave] = incl;
+        __syncthreads();
+        before[h] = run + incl - count;
+        for (uint32_t wv = 0; wv < WG / 64u; ++wv) {
+            const uint32_t t = sh.w[wv];
+            before[h] += wv < wave ? t : 0u;
+            run += t;
+        }
+        __syncthreads();
+    }
+    return run;
+}
+
+// One wave: waits for the words of `sy.layer` numbered `first`, first + 4, ... (one per layer) of the
+// layers below n_layers and adds up their values; ok: in, whether to wait at all; out, whether all came.
+__device__ __forceinline__ uint32_t poll_layer_words(const SyncArea &sy, const uint32_t first, const uint32_t n_layers, const uint32_t epoch,
+                                                     const uint32_t most_polls, const uint32_t lane, bool &ok)
+{
+    uint32_t sum = 0u;
+    for (uint32_t m = lane; ok && m < n_layers; m += 64u) {
+        uint64_t v = 0u;
+        ok = false;
+        for (uint32_t polls = 0; !ok && polls <= most_polls; ++polls) {
+            if (polls != 0u) __builtin_amdgcn_s_sleep(4);
+            v = sync_load(sy.layer + 4u * m + first);
+            ok = uint32_t(v) == epoch;
+        }
+        sum += uint32_t(v >> 32);
+    }
+    return wave_sum(sum);
+}
+
+// Adds up the records of layer l and publishes what its tiles (and the layers behind it) wait for.  Says
+// whether everything came in time; HELP: works out the records that did not.
+template <uint32_t WG, bool VARIANT, bool HELP>
+__device__ __forceinline__ bool complete_layer(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t l,
+                                               const uint32_t epoch, uint32_t *s_gmax, OneShared &sh)
+{
+    constexpr uint32_t HOLD = (kOneLaunchTiles + WG - 1u) / WG;
+    const uint32_t most_polls = HELP ? kWaitPolls : a.wait_polls;   // (with help everything comes)
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t ts = a.layers[l].ctile_start, nt = a.layers[l].n_ctiles, wbytes = a.layers[l].word_bytes;
+    Records<HOLD> rec;
+    if (block_any<WG>(!poll_records<WG>(sy, ts, nt, epoch, a.wait_polls, rec), sh.any[0])) {
+        if (!HELP) return false;
+        for (uint32_t q = 0; q < nt; ++q) help_tile<WG, VARIANT>(a, sy, lr, ts + q, epoch, s_gmax, sh);
+        poll_records<WG>(sy, ts, nt, epoch, most_polls, rec);   // published now, by whomever
+    }
+    uint32_t before[HOLD];
+    double part = 0.0;
+    const uint32_t words = scan_records<WG>(nt, rec, sh, before, part);
+    part = wave_sum_f64(part);
+    if (lane == 0u) sh.d[tid >> 6] = part;
+    __syncthreads();
+    double total = 0.0;
+    for (uint32_t wv = 0; wv < WG / 64u; ++wv) total += sh.d[wv];   // fixed order
+    const uint32_t scale = __float_as_uint(float(total / double(a.layers[l].n_bins)));
+    if (tid == 0) {
+        uint64_t *out = sy.layer + 4u * l;
+        sync_store(out + 1, sync_word(uint32_t(pad16_dev(uint64_t(words) * wbytes)), epoch));
+        sync_store(out, sync_word(scale, epoch));
+        sync_store(out + 2, sync_word(words, epoch));
+    }
+    bool ok = true;
+    if (tid < 64u) {   // the layers before: their words come first in the packet
+        const uint32_t bytes = poll_layer_words(sy, 1u, l, epoch, most_polls, lane, ok);
+        if (lane == 0u) sh.bytes = bytes;
+    }
+    if (block_any<WG>(!ok, sh.any[1])) return false;
+    const uint32_t woff = uint32_t(a.fixed_bytes) + sh.bytes;   // below 2^32 like the packet
+#pragma unroll
+    for (uint32_t h = 0; h < HOLD; ++h) {
+        if (h * WG + tid < nt) {
+            uint64_t *out = sy.tile + 4u * (ts + h * WG + tid);
+            sync_store(out, sync_word(scale, epoch));
+            sync_store(out + 1, sync_word(woff + before[h] * wbytes, epoch));
+            sync_store(out + 2, sync_word(before[h], epoch));
+        }
+    }
+    return true;
+}
+
+// scale = average of the layer's g_max values, from the sums of its tiles, by one wave in a fixed order
+__device__ __forceinline__ float layer_scale_of(const double *sum, const uint32_t n_ctiles, const uint32_t n_bins, const uint32_t lane)
+{
+    double s = 0.0;
+    for (uint32_t t = lane; t < n_ctiles; t += 64u) s += sum[t];
+    s = wave_sum_f64(s);          // lane 0 holds the sum
+    s = __shfl(s, 0, 64);
+    return float(s / double(n_bins));
+}
+
+// ==============================================================================================
+// k_pack: a tile of at most 4096 elements, 256 threads with four 16-byte slots each.  Tiles of this
+// class start on 16-byte boundaries; bins have at least four elements, so that a slot lies in one bin
+// or two.  Bound by HBM at 12 bytes per element plus the packet, and short of that by the wait, about
+// 8 us of a workgroup's life of 17 us on ResNet-50's table, which other workgroups have to cover:
+// hence eight of them on a compute unit, which takes 64 registers (7 spilled ones cost 10 %) and is why
+// several values are worked out anew below instead of being kept.
+// Measured, before (k_fused, k_scan, k_place or k_place_tiled) and now, in us: ResNet-50's table
+// 98 -> 67, a mini-batch of 8 learners with its unpack 697 -> 532; 23 layers with odd bins, 9.4 M
+// elements, 2 learners 72 -> 50; 397 k elements 12.2 -> 10.2; the CIFAR table, 4 learners with unpack,
+// 33 -> 24.
+// ==============================================================================================
+// values the compiler is not to connect with what they were before
+template <int N>
+__device__ __forceinline__ void keep_apart(uint32_t (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+// max(v, v of the lane CTRL says, 8 or fewer lanes below in the same row of 16), where `from` holds
+template <int CTRL>
+__device__ __forceinline__ uint32_t take_max_from(const uint32_t v, const bool from)
+{
+    const uint32_t o = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, true));   // 0 past the row's start
+    return from && o > v ? o : v;
+}
+
+template <bool VARIANT, int ONE>
+__global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const CompressArgs a)
+{
+    constexpr int J = 4;             // 16-byte slots of a thread: slot j of thread t is number j * kWG + t of the tile
+    constexpr uint32_t kRow = kWG * 4u;
+    const uint32_t lq = blockIdx.x / a.class_count;   // learner-major, and within runs of 64 transposed, as in k_fused
+    uint32_t tile = blockIdx.x - lq * a.class_count;
+    const uint32_t lr = a.fused_first + lq;
+    if (tile < (a.class_count & ~63u)) tile = (tile & ~63u) | ((tile & 7u) << 3) | ((tile >> 3) & 7u);
+    const TileDev td = a.tiles[tile];
+    const LayerDev ld = a.layers[td.layer()];
+    uint8_t *const packet = a.packet[lr];
+    SyncArea sy;
+    {
+        uint8_t *const area = a.sync + uint64_t(lr) * a.sync_stride;
+        sy.rec = reinterpret_cast<uint64_t *>(area + a.o_sync_rec);
+        sy.tile = reinterpret_cast<uint64_t *>(area + a.o_sync_tile);
+        sy.layer = reinterpret_cast<uint64_t *>(area + a.o_sync_layer);
+        sy.epoch = reinterpret_cast<uint32_t *>(area + a.o_sync_epoch);
+    }
+    const uint32_t epoch = sy.epoch[tile] + 1u;
+
+    __shared__ uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kMaxTileBins + 4u];
+    __shared__ uint32_t s_words[kWG * J * 2u + 4u];  // the tile's words, in their final form, one byte or two each
+    __shared__ __attribute__((aligned(16))) uint32_t s_rows[8];   // words per wave and row, two rows to an entry
+    __shared__ uint32_t s_chunk[kMaxTileBins / 64u];
+    __shared__ OneShared sh;
+
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t n = td.n_elems, T = td.L_T, M = td.magic, nb = td.n_bins, l = td.layer();
+    float *const rs = a.residue[lr] + td.elem_base;
+    const float *const gr = a.grad[lr] + td.elem_base;
+    // whole slots only: what lies past the tile is read as zero and not stored, without a branch
+    const __amdgpu_buffer_rsrc_t r_buf = tile_buffer(rs, n & ~3u), w_buf = tile_buffer(gr, n & ~3u);
+
+    uint32_t gb[J][4];  // bits of G (sign included)
+    uint32_t mb[J][4];  // bits of max(|G|, |H|): what is compared with g_max
+    vfloat4 r[J], w[J];
+    auto load_slots = [&]() {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            r[j] = buffer_load_slot(r_buf, tid * 16u, uint32_t(j) * kRow * 4u);
+            w[j] = buffer_load_slot(w_buf, tid * 16u, uint32_t(j) * kRow * 4u);
+        }
+        if ((n & 3u) != 0u) {   // the layer's last elements, which do not fill a slot
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                if (uint32_t(j) * kWG + tid == (n >> 2)) {
+                    for (uint32_t c = 0; c < (n & 3u); ++c) { r[j][c] = rs[(n & ~3u) + c]; w[j][c] = gr[(n & ~3u) + c]; }
+                }
+        }
+    };
+    load_slots();
+    for (uint32_t i = tid; i < nb + 1u; i += kWG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
+    if (ONE == kOneTable) __builtin_amdgcn_s_setprio(2);   // until the record is out: others wait for it (6 % of a small mini-batch; slower where waves queue for memory)
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) element_bits<VARIANT>(a, r[j][c], w[j][c], gb[j][c], mb[j][c]);
+    // (from here on the inputs are not needed again: without this the compiler kept dW and |G| beside G and
+    // worked H out later, 16 registers more than eight resident workgroups leave)
+#pragma unroll
+    for (int j = 0; j < J; ++j) { keep_apart(gb[j]); keep_apart(mb[j]); }
+    __syncthreads();
+
+    // ---- first loop of Algorithm 2: g_max(i) per bin.  A slot lies in bin b0, its elements from `left` on in
+    // the next one (bins have at least four elements): one division per slot -------------------------
+    uint32_t place[J];   // b0 << 16 | left
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const uint32_t e0 = uint32_t(j) * kRow + tid * 4u;
+        const uint32_t b0 = __umulhi(e0, M);
+        const uint32_t left = T - (e0 - __umul24(b0, T));
+        place[j] = (b0 << 16) | left;
+        uint32_t m0 = gb[j][0] & 0x7FFFFFFFu, m1 = 0u;
+#pragma unroll
+        for (uint32_t c = 1; c < 4u; ++c) {
+            const uint32_t v = gb[j][c] & 0x7FFFFFFFu;
+            const uint32_t v0 = c < left ? v : 0u, v1 = c < left ? 0u : v;
+            m0 = v0 > m0 ? v0 : m0;
+            m1 = v1 > m1 ? v1 : m1;
+        }
+        // Lanes of a row of 16 whose slots lie in one bin bring one maximum to the LDS: `into` is the start of the
+        // slot in its bin, 0 for a slot that begins a new bin on its way (its lane takes nothing over).
+        const bool split = left < 4u;
+        const uint32_t into = split ? 0u : T - left;
+        uint32_t v = split ? m1 : m0;
+        v = take_max_from<0x111>(v, into >= 1u);
+        v = take_max_from<0x112>(v, into >= 5u);
+        v = take_max_from<0x114>(v, into >= 13u);
+        v = take_max_from<0x118>(v, into >= 29u);
+        if (split) atomicMax(&s_gmax[b0], m0);
+        if ((lane & 15u) == 15u || (split ? left + T : left) < 8u) atomicMax(&s_gmax[split ? b0 + 1u : b0], v);
+    }
+    __syncthreads();
+
+    // (what a pass works out from `place` is worked out anew in the next one: kept, it costs more registers
+    // than eight resident workgroups leave)
+    keep_apart(place);
+#pragma unroll
+    for (int j = 0; j < J; ++j) keep_apart(gb[j]);
+    // ---- second loop: the local-max compare, and every sent element's place among the tile's words ----
+    uint32_t sent_mask = 0u;   // bit 4 j + c: element c of slot j is sent
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
+        const uint32_t gm0 = s_gmax[b0], gm1 = s_gmax[b0 + 1u];
+#pragma unroll
+        for (uint32_t c = 0; c < 4u; ++c)
+            sent_mask |= element_sent<VARIANT>(a, gb[j][c], mb[j][c], c < left ? gm0 : gm1) ? 1u << (4 * j + c) : 0u;
+        if (VARIANT) {   // the printed compare sends zeros: not those that stand for what lies past the tile
+            const uint32_t e0 = uint32_t(j) * kRow + tid * 4u;
+            const uint32_t valid = n > e0 ? (n - e0 < 4u ? n - e0 : 4u) : 0u;
+            sent_mask &= ~(0xFu << (4 * j)) | (((1u << valid) - 1u) << (4 * j));
+        }
+    }
+    // words are ordered by (row j, wave, lane, c): counts of two rows to a register, at most 256 each per wave
+    const uint32_t c01 = uint32_t(__popc(sent_mask & 0xFu)) | (uint32_t(__popc(sent_mask & 0xF0u)) << 16);
+    const uint32_t c23 = uint32_t(__popc(sent_mask & 0xF00u)) | (uint32_t(__popc(sent_mask & 0xF000u)) << 16);
+    const uint32_t i01 = wave_incl_scan(c01), i23 = wave_incl_scan(c23);
+    if (lane == 63u) { s_rows[2u * wave] = i01; s_rows[2u * wave + 1u] = i23; }
+    const double gmax_sum = tile_gmax_sum<kWG>(s_gmax, nb, sh.d);   // has the barrier
+    uint32_t all01 = 0u, all23 = 0u, pre01 = i01 - c01, pre23 = i23 - c23;
+#pragma unroll
+    for (uint32_t wv = 0; wv < 4u; ++wv) {
+        const uint32_t t01 = s_rows[2u * wv], t23 = s_rows[2u * wv + 1u];
+        if (wv < wave) { pre01 += t01; pre23 += t23; }
+        all01 += t01;
+        all23 += t23;
+    }
+    const uint32_t row2 = (all01 & 0xFFFFu) + (all01 >> 16), tile_total = row2 + (all23 & 0xFFFFu) + (all23 >> 16);
+    if (tid == 0) {   // first thing: others wait for it
+        sync_store(sy.rec + 2u * tile, rec_high(gmax_sum, epoch));
+        sync_store(sy.rec + 2u * tile + 1u, rec_low(gmax_sum, tile_total, epoch));
+        sy.epoch[tile] = epoch;
+    }
+    if (ONE == kOneTable) __builtin_amdgcn_s_setprio(0);
+
+    // ---- the pack vector of Algorithm 2: the words, and how many each bin sends ----------------------
+    const uint32_t wbytes = ld.word_bytes;
+    keep_apart(place);
+    asm volatile("" : "+v"(sent_mask));
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const uint32_t f = (sent_mask >> (4 * j)) & 0xFu;
+        if (f == 0u) continue;
+        const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
+        uint32_t at = j == 0 ? pre01 & 0xFFFFu : j == 1 ? (pre01 >> 16) + (all01 & 0xFFFFu)
+                    : j == 2 ? (pre23 & 0xFFFFu) + row2 : (pre23 >> 16) + row2 + (all23 & 0xFFFFu);
+#pragma unroll
+        for (uint32_t c = 0; c < 4u; ++c) {
+            if (!((f >> c) & 1u)) continue;
+            const uint32_t idx = c < left ? T - left + c : c - left;   // inside the bin
+            const uint32_t word = (idx << 2) | ((gb[j][c] >> 31) ? 3u : 1u);   // ternary code: -scale / +scale
+            if (wbytes == 1u) reinterpret_cast<uint8_t *>(s_words)[at] = uint8_t(word);
+            else reinterpret_cast<uint16_t *>(s_words)[at] = uint16_t(word);
+            ++at;
+        }
+        const uint32_t f1 = left < 4u ? f >> left : 0u;
+        const uint32_t k1 = uint32_t(__popc(f1)), k0 = uint32_t(__popc(f)) - k1;
+        if (k0) atomicAdd(&s_cnt[b0], k0);
+        if (k1) atomicAdd(&s_cnt[b0 + 1u], k1);
+    }
+    __syncthreads();
+
+    // ---- what does not need the layer: counts per bin, running counts, the optional g_max vector -------
+    if (wbytes == 1u) {
+        uint8_t *cp = packet + ld.counts_offset + td.first_bin;
+        for (uint32_t i = tid; i < nb; i += kWG) cp[i] = uint8_t(s_cnt[i]);
+    } else {
+        uint16_t *cp = reinterpret_cast<uint16_t *>(packet + ld.counts_offset) + td.first_bin;
+        for (uint32_t i = tid; i < nb; i += kWG) cp[i] = uint16_t(s_cnt[i]);
+    }
+    if (a.keep_gmax) {
+        float *gm_out = reinterpret_cast<float *>(a.scratch + uint64_t(lr) * a.scratch_stride + a.o_gmax) + ld.bin_start + td.first_bin;
+        for (uint32_t i = tid; i < nb; i += kWG) gm_out[i] = __uint_as_float(s_gmax[i]);
+    }
+    const uint32_t t0 = (64u - (td.first_bin & 63u)) & 63u;   // first bin of the tile that starts a chunk of 64
+    for (uint32_t t = t0 + 64u * wave; t < nb; t += 256u) {
+        uint32_t sum = 0u;
+        for (uint32_t i = lane; i < t; i += 64u) sum += s_cnt[i];
+        sum = wave_sum(sum);
+        if (lane == 0u) s_chunk[t >> 6] = sum;
+    }
+
+    // A workgroup that waits in vain (see wait_polls) does all that is missing itself; it then takes its
+    // own G from memory again (nobody has written this tile's residue yet) instead of holding sixteen
+    // registers through that code.
+    auto take_again = [&]() {
+        load_slots();
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) gb[j][c] = __float_as_uint(r[j][c] + w[j][c]);
+    };
+    // ---- wait for the layer: its scale, the words before this tile --------------------------------------
+    uint32_t first_at, base;   // place of the tile's first word in the packet; words of the layer before the tile
+    float scale;
+    __shared__ uint32_t s_excl[ONE == kOneTable ? kFoldTiles + 1u : 1u];   // kOneTable: words of all tiles before tile t
+    double *const s_sum = reinterpret_cast<double *>(s_cnt);               // kOneTable: g_max sum of tile t (the counts are in the packet)
+    if (ONE == kOneTable) {
+        uint32_t l_ts = 0u, l_nt = 0u, l_wb = 0u;   // lane m keeps layer m's tiles and word width
+        if (lane < a.n_layers) { l_ts = a.layers[lane].ctile_start; l_nt = a.layers[lane].n_ctiles; l_wb = a.layers[lane].word_bytes; }
+        constexpr uint32_t HOLD = kFoldTiles / kWG;
+        Records<HOLD> rec;
+        if (block_any<kWG>(!poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec), sh.any[0])) {
+            for (uint32_t q = 0; q < a.n_tiles; ++q) help_tile<kWG, VARIANT>(a, sy, lr, q, epoch, s_gmax, sh);
+            poll_records<kWG>(sy, 0u, a.n_tiles, epoch, kWaitPolls, rec);   // published now, by whomever
+            take_again();
+        }
+        uint32_t excl[HOLD];
+        double part = 0.0;
+        const uint32_t all = scan_records<kWG>(a.n_tiles, rec, sh, excl, part);
+#pragma unroll
+        for (uint32_t h = 0; h < HOLD; ++h)
+            if (h * kWG + tid < a.n_tiles) { s_excl[h * kWG + tid] = excl[h]; s_sum[h * kWG + tid] = rec_sum(rec.hi[h], rec.lo[h]); }
+        if (tid == 0) s_excl[a.n_tiles] = all;
+        __syncthreads();
+        base = s_excl[tile] - s_excl[ld.ctile_start];
+        scale = layer_scale_of(s_sum + ld.ctile_start, ld.n_ctiles, ld.n_bins, lane);
+        const uint32_t bytes = lane < l ? uint32_t(pad16_dev(uint64_t(s_excl[l_ts + l_nt] - s_excl[l_ts]) * l_wb)) : 0u;   // l < kFoldLayers
+        first_at = uint32_t(a.fixed_bytes) + wave_sum(bytes) + base * wbytes;   // below 2^32 like the packet
+    } else {
+        // A layer's last workgroup adds up its layer; all wait for what that one says about their tile.
+        auto poll_tile = [&](bool ok, const uint32_t most_polls) {
+            if (wave == 0u && lane < 3u) {
+                uint64_t v = 0u;
+                const uint64_t *src = sy.tile + 4u * tile + lane;
+                for (uint32_t polls = 0; ok; ++polls) {
+                    v = sync_load(src);
+                    if (uint32_t(v) == epoch) break;
+                    ok = polls < most_polls;
+                    __builtin_amdgcn_s_sleep(8);
+                }
+                const uint32_t value = uint32_t(v >> 32);
+                if (lane == 0u) sh.scale = __uint_as_float(value);
+                else if (lane == 1u) sh.at = value;
+                else sh.base = value;
+            }
+            if (wave == 0u && tile == a.n_tiles - 1u) {   // the header needs scale and word count of every layer
+                poll_layer_words(sy, 0u, a.n_layers, epoch, most_polls, lane, ok);
+                poll_layer_words(sy, 2u, a.n_layers, epoch, most_polls, lane, ok);
+            }
+            return ok;
+        };
+        bool ok = true;
+        if (tile == ld.ctile_start + ld.n_ctiles - 1u) ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, s_gmax, sh);
+        if (block_any<kWG>(!poll_tile(ok, a.wait_polls), sh.any[2])) {
+            for (uint32_t m = 0; m <= l; ++m) complete_layer<kWG, VARIANT, true>(a, sy, lr, m, epoch, s_gmax, sh);
+            __syncthreads();
+            poll_tile(true, kWaitPolls);   // all there now
+            take_again();
+            __syncthreads();
+        }
+        base = sh.base;
+        scale = sh.scale;
+        first_at = sh.at;
+    }
+
+    asm volatile("" : "+v"(sent_mask));
+    uint32_t tid_r = threadIdx.x;   // (the slots' place is worked out anew, not kept through the wait)
+    asm volatile("" : "+v"(tid_r));
+    // ---- the residue, in its final form: G - Gq at the sent elements, G elsewhere ---------------------------
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        vfloat4 R;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float G = __uint_as_float(gb[j][c]);
+            const float corrected = G - __builtin_copysignf(scale, G);
+            R[c] = ((sent_mask >> (4 * j + c)) & 1u) ? corrected : G;
+        }
+        buffer_store_slot(r_buf, tid_r * 16u, uint32_t(j) * kRow * 4u, R);
+        if ((n & 3u) != 0u && uint32_t(j) * kWG + tid_r == (n >> 2))
+            for (uint32_t c = 0; c < (n & 3u); ++c) rs[(n & ~3u) + c] = R[c];
+    }
+    // ---- the words, at their place in the packet, four bytes at a time ---------------------------------------
+    const uint32_t n_bytes = tile_total * wbytes, skew = first_at & 3u;
+    const uint64_t limit = a.capacity & ~uint64_t(wbytes - 1u);   // no part of a word that does not fit
+    for (uint32_t d = tid; 4u * d < skew + n_bytes; d += kWG) {
+        const uint64_t at = uint64_t(first_at - skew) + 4u * d;
+        const uint32_t o = 4u * d - skew;   // first byte of the four among the tile's words; wraps below zero in the first
+        if (4u * d >= skew && o + 4u <= n_bytes && at + 4u <= limit) {
+            const uint32_t lo = s_words[o >> 2], hi = s_words[(o >> 2) + 1u];
+            *reinterpret_cast<uint32_t *>(packet + at) = __builtin_amdgcn_alignbyte(hi, lo, o & 3u);
+        } else {
+            for (uint32_t c = 0; c < 4u; ++c)
+                if (o + c < n_bytes && at + c < limit) packet[at + c] = reinterpret_cast<const uint8_t *>(s_words)[o + c];
+        }
+    }
+    // chunks[c] = words of the layer in bins < 64 c, for the chunk starts inside this tile
+    for (uint32_t t = t0 + 64u * tid; t < nb; t += 64u * kWG)
+        reinterpret_cast<uint32_t *>(packet + ld.chunks_offset)[(td.first_bin + t) >> 6] = base + s_chunk[t >> 6];
+    if (tile != a.n_tiles - 1u) return;
+    // ---- header and layer records: the workgroup of the table's last tile ------------------------------------
+    if (ONE == kOneTable) {
+        __shared__ float s_lscale[kFoldLayers];
+        for (uint32_t m = wave; m < a.n_layers; m += 4u) {
+            const float sc = layer_scale_of(s_sum + a.layers[m].ctile_start, a.layers[m].n_ctiles, a.layers[m].n_bins, lane);
+            if (lane == 0u) s_lscale[m] = sc;
+        }
+        __syncthreads();
+        place_header<kWG>(a, packet, [&](uint32_t m, const LayerDev &lm, uint32_t &nsel, float &sc) {
+            nsel = s_excl[lm.ctile_start + lm.n_ctiles] - s_excl[lm.ctile_start];
+            sc = s_lscale[m];
+        });
+    } else {
+        place_header<kWG>(a, packet, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
+            nsel = uint32_t(sync_load(sy.layer + 4u * m + 2u) >> 32);
+            sc = __uint_as_float(uint32_t(sync_load(sy.layer + 4u * m) >> 32));
+        });
+    }
+}
+
 // ==============================================================================================
 // k_scan: per layer, scale = (sum of g_max) / n_bins in float64 rounded once to float32, and the
 // exclusive scan of the tiles' word counts.  One workgroup of 1024 threads per layer; a thread
@@ -489,8 +1224,6 @@ __global__ __launch_bounds__(kScanWG) void k_scan(const CompressArgs a)
 // set by the scattered read-modify-writes of the residue: a bare kernel that does nothing else
 // needs as long for the same number of words.
 // ==============================================================================================
-__device__ __forceinline__ uint64_t pad16_dev(uint64_t x) { return (x + 15u) & ~uint64_t(15); }
-
 // LANES lanes serve a tile: 16 where bins are long and a tile sends a few dozen words, 64 for tables
 // with short bins, whose tiles send several hundred (5 % off the compress time of the ResNet-50
 // table, 23 % off the small CIFAR table; 64 lanes cost the 125 M-element table half a percent).
@@ -511,85 +1244,6 @@ __device__ __forceinline__ float fold_layer_scale(const TileOut *tile_out, const
     s = wave_sum_f64(s);          // lane 0 holds the sum
     s = __shfl(s, 0, 64);
     return float(s / double(n_bins));
-}
-
-// Header, layer records and zero padding of one learner's packet, by one workgroup of kWG threads
-// (the extra workgroup of a placement launch): 256 layers at a time, word offsets by a block scan
-// of the padded section sizes (all below 2^32: the packet bound is).  FOLD: the layer totals come
-// from s_excl (words of all tiles before each tile) and the scales are worked out here.
-template <bool FOLD>
-__device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *const packet, const TileOut *const tile_out,
-                                             uint32_t *const layer_nsel, float *const layer_scale, const uint32_t *const s_excl)
-{
-    const uint32_t tid = threadIdx.x;
-    __shared__ uint32_t s_wtot[4];
-    __shared__ float s_fscale[FOLD ? kFoldLayers : 1u];
-    const uint32_t lane = tid & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (FOLD) {
-        for (uint32_t l = wave; l < a.n_layers; l += 4u) {
-            const float sc = fold_layer_scale(tile_out, a.layers[l].ctile_start, a.layers[l].n_ctiles, a.layers[l].n_bins, lane);
-            if (lane == 0u) s_fscale[l] = sc;
-        }
-        __syncthreads();
-    }
-    uint64_t carry = a.fixed_bytes, nsel_all = 0;
-    for (uint32_t l0 = 0; l0 < a.n_layers; l0 += kWG) {
-        const uint32_t l = l0 + tid;
-        const bool live = l < a.n_layers;
-        LayerDev ld;
-        uint32_t nsel = 0u, bytes = 0u;
-        float scale = 0.f;
-        if (live) {
-            ld = a.layers[l];
-            if (FOLD) {   // and left in the scratch block for whoever applies the corrections later
-                nsel = s_excl[ld.ctile_start + ld.n_ctiles] - s_excl[ld.ctile_start];
-                scale = s_fscale[l];
-                layer_nsel[l] = nsel;
-                layer_scale[l] = scale;
-            } else {
-                nsel = layer_nsel[l];
-                scale = layer_scale[l];
-            }
-            bytes = uint32_t(pad16_dev(uint64_t(nsel) * ld.word_bytes));
-        }
-        const uint32_t incl = wave_incl_scan(bytes);
-        uint32_t nsum = wave_sum(nsel);
-        __syncthreads();  // previous round's readers of s_wtot are done
-        if (lane == 63) s_wtot[wave] = incl;
-        __syncthreads();
-        uint64_t before = carry;
-        for (uint32_t wv = 0; wv < wave; ++wv) before += s_wtot[wv];
-        const uint64_t woff = before + incl - bytes;
-        carry += uint64_t(s_wtot[0]) + s_wtot[1] + s_wtot[2] + s_wtot[3];
-        if (live) {
-            adacomp_packet_layer_t rec;
-            rec.elem_offset = ld.elem_offset; rec.n_elems = ld.n_elems;
-            rec.L_T = ld.L_T; rec.n_bins = ld.n_bins; rec.word_bits = ld.word_bytes * 8u;
-            rec.scale = scale;
-            rec.n_selected = nsel;
-            rec.counts_offset = ld.counts_offset; rec.chunks_offset = ld.chunks_offset; rec.words_offset = woff;
-            reinterpret_cast<adacomp_packet_layer_t *>(packet + sizeof(adacomp_packet_header_t))[l] = rec;
-            for (uint64_t b = ld.counts_offset + uint64_t(ld.n_bins) * ld.word_bytes; b < ld.chunks_offset; ++b) packet[b] = 0;
-            const uint64_t chunks_end = ld.chunks_offset + 4ull * ld.n_chunks;
-            for (uint64_t b = chunks_end; b < pad16_dev(chunks_end); ++b) packet[b] = 0;
-            const uint64_t words_end = woff + uint64_t(nsel) * ld.word_bytes;
-            for (uint64_t b = words_end; b < pad16_dev(words_end); ++b)
-                if (b < a.capacity) packet[b] = 0;
-        }
-        // total word count: per-wave sums through the same LDS slots
-        __syncthreads();
-        if (lane == 0) s_wtot[wave] = nsum;
-        __syncthreads();
-        nsel_all += uint64_t(s_wtot[0]) + s_wtot[1] + s_wtot[2] + s_wtot[3];
-    }
-    if (tid == 0) {
-        adacomp_packet_header_t h;
-        h.magic = ADACOMP_PACKET_MAGIC; h.version = ADACOMP_PACKET_VERSION;
-        h.status = carry > a.capacity ? ADACOMP_STATUS_TRUNCATED : ADACOMP_STATUS_COMPLETE;
-        h.n_layers = a.n_layers; h.total_bytes = carry; h.n_selected = nsel_all;
-        *reinterpret_cast<adacomp_packet_header_t *>(packet) = h;
-    }
 }
 
 template <uint32_t LANES, uint32_t MODE, bool FOLD>
@@ -638,7 +1292,24 @@ __global__ __launch_bounds__(kWG) void k_place(const CompressArgs a)
 
     if (MODE == kPlaceResidue && blockIdx.x == gridDim.x - 1) return;
     if (MODE != kPlaceResidue && blockIdx.x == gridDim.x - 1) {
-        place_header<FOLD>(a, packet, tile_out, layer_nsel, layer_scale, s_excl);
+        if (FOLD) {
+            __shared__ float s_fscale[FOLD ? kFoldLayers : 1u];
+            const uint32_t lane = tid & 63u;
+            const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+            for (uint32_t l = wave; l < a.n_layers; l += 4u) {
+                const float sc = fold_layer_scale(tile_out, a.layers[l].ctile_start, a.layers[l].n_ctiles, a.layers[l].n_bins, lane);
+                if (lane == 0u) s_fscale[l] = sc;
+            }
+            __syncthreads();
+            place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &ld, uint32_t &nsel, float &sc) {
+                nsel = s_excl[ld.ctile_start + ld.n_ctiles] - s_excl[ld.ctile_start];
+                sc = s_fscale[l];
+                layer_nsel[l] = nsel;   // and left in the scratch block for whoever applies the corrections later
+                layer_scale[l] = sc;
+            });
+        } else {
+            place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
+        }
         return;
     }
 
@@ -751,7 +1422,7 @@ __global__ __launch_bounds__(kWG) void k_place_tiled(const CompressArgs a)
     uint8_t *const packet = a.packet[lr];
 
     if (blockIdx.x == gridDim.x - 1) {
-        place_header<false>(a, packet, tile_out, layer_nsel, layer_scale, nullptr);
+        place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
         return;
     }
     const uint32_t tile = blockIdx.x;   // the grid has one workgroup per tile and one for the header
@@ -1327,6 +1998,19 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
     // 51-55 % of the HBM peak instead of 75-80 %.)
     const dim3 grid(a.class_count * a.fused_count), wg(jcode == 0 ? 256 : 1024);
     const bool variant = a.rule != ADACOMP_RULE_ADACOMP || a.soft_factor_minus_1 != 1.0f;
+    if (a.one_launch) {   // the host picks it for eager calls on tables of one tile class whose layers are small
+        if (jcode != 0 || a.lazy || a.class_tiles || a.place_mode != kPlaceEager) return ADACOMP_EINVAL;
+        const bool table = a.one_launch == kOneLaunchTable;
+        if (table && (a.n_tiles > kFoldTiles || a.n_layers > kFoldLayers)) return ADACOMP_EINVAL;
+        if (!variant) {
+            if (table) hipLaunchKernelGGL((k_pack<false, kOneTable>), grid, wg, 0, s, a);
+            else hipLaunchKernelGGL((k_pack<false, kOneLayers>), grid, wg, 0, s, a);
+        } else {
+            if (table) hipLaunchKernelGGL((k_pack<true, kOneTable>), grid, wg, 0, s, a);
+            else hipLaunchKernelGGL((k_pack<true, kOneLayers>), grid, wg, 0, s, a);
+        }
+        return check_launch();
+    }
     if (a.lazy) {  // the host offers lazy residues for the default method only
         if (jcode == 0) hipLaunchKernelGGL((k_fused<4, 4, false, true>), grid, wg, 0, s, a);
         else hipLaunchKernelGGL((k_fused<4, 16, false, true>), grid, wg, 0, s, a);

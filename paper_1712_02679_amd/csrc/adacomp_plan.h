@@ -100,8 +100,22 @@ struct WorkspaceLayout {
     size_t layer_nsel = 0, layer_scale = 0;             // per layer
     size_t gmax = 0, chunk_rel = 0;                     // per bin / per chunk
     size_t stage = 0;                                   // uint16 per element of the layers (not of the address span): words before placement
-    size_t total(size_t n_learners) const { return scratch + scratch_stride * n_learners; }
+    // The exchange areas of the one-launch compress, one per learner, lie at the end of the workspace
+    // (SyncPlace); offsets inside one.  A workspace without room for them takes the staged launches.
+    size_t sync_rec = 0, sync_tile = 0, sync_layer = 0, sync_epoch = 0;
+    size_t sync_stride = 0;
+    size_t least(size_t n_learners) const { return scratch + scratch_stride * n_learners; }   // what a call needs
+    size_t total(size_t n_learners) const { return least(n_learners) + sync_stride * n_learners; }
 };
+
+// Where a registered workspace keeps its exchange areas: `learners` of them, as many as fit behind as
+// many scratch blocks.  They are cleared when the workspace is initialised and from then on belong to
+// the kernels.
+constexpr size_t kSyncLearnersMax = 1024;
+struct SyncPlace {
+    size_t offset = 0, learners = 0;
+};
+SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes);
 
 struct Plan {
     uint32_t n_layers = 0;
@@ -116,8 +130,11 @@ struct Plan {
     uint32_t n_class_tiles[2] = {0, 0};  // compress tiles of 4096 / of 16384 elements
     std::vector<uint32_t> cclass;        // compress tile indices, the 4096-element ones first (tables with both kinds)
     bool has_short_bins = false;  // some layer has L_T <= 64 (8-bit words, many words per tile)
+    uint32_t layer_tiles_max = 0;  // compress tiles of the layer that has most
+    bool has_tiny_bins = false;    // some layer has L_T < 4
     bool has_shifted_tiles = false;  // some tile of the larger class has skip != 0
     WorkspaceLayout ws;
+    SyncPlace sync;   // of a registered workspace
     std::vector<LayerDev> layers;
     std::vector<TileDev> ctiles;
     std::vector<UTileDev> utiles;
@@ -152,11 +169,29 @@ constexpr uint64_t kSplitElems = 32u * 1000u * 1000u;  // gradients at least thi
 constexpr uint32_t kFusedIdleLds = 18000;
 constexpr uint32_t kFusedIdleMinLearners = 8;
 
+// How adacomp_compress covers a table in one launch (see k_pack): not at all, with every workgroup
+// reading the records of the whole table, or with one workgroup per layer doing so.
+constexpr uint32_t kOneLaunchNever = 0, kOneLaunchTable = 1, kOneLaunchLayers = 2;
+// Tiles of a layer up to which its workgroups wait for each other: 2048 are resident, and the longer a
+// layer, the longer its first tiles hold their place.  One layer of 1000 tiles, one launch / three, in us:
+// L_T 50, 1 learner 19.5 / 29.3, 8 learners 94 / 119; L_T 500, 1 learner 19.0 / 22.4, but 8 learners
+// 90.5 / 83.5, since the placement it saves is cheap where little is sent; hence the second line, which
+// holds for tables without short bins in calls of several learners (525 tiles: 75.0 / 75.2).
+constexpr uint32_t kOneLaunchTiles = 1024;
+constexpr uint32_t kOneLaunchTilesLong = 512;
+// Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
+constexpr uint32_t kOneLaunchLayersMax = 512;
+constexpr uint32_t kWaitPolls = 4096;        // polls (a microsecond or so each) before a workgroup works out what it waits for
+
 struct CompressArgs {
     const TileDev *tiles;
     const LayerDev *layers;
     uint8_t *scratch;         // scratch block of learner 0 of this launch
     uint64_t scratch_stride;
+    uint8_t *sync;            // exchange area of learner 0 of this launch (one-launch calls)
+    uint64_t sync_stride;
+    uint32_t o_sync_rec, o_sync_tile, o_sync_layer, o_sync_epoch;
+    uint32_t one_launch, wait_polls;    // kOneLaunch*; polls before a waiting workgroup helps itself
     uint32_t o_tile_out, o_layer_nsel, o_layer_scale, o_gmax, o_chunk_rel;
     uint32_t n_tiles, n_layers, n_learners, keep_gmax;
     uint32_t fused_first, fused_count;  // learners covered by one k_fused launch
@@ -178,6 +213,10 @@ struct CompressArgs {
     float *residue[kMaxBatch];
     uint8_t *packet[kMaxBatch];
 };
+
+// Kernel arguments beyond 1 KB (these and the hidden ones that blockDim or __syncthreads_or bring along)
+// make a launch wait on the host, 30 to 150 us, when many other launches went before.
+static_assert(sizeof(CompressArgs) <= 1024, "kernel arguments");
 
 struct UnpackArgs {
     const UTileDev *tiles;

@@ -122,6 +122,18 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
     if (w.usingles + sizeof(UGroupDev) * size_t(p.n_utiles) > w.scratch) return 141;
     if (w.stage + 2 * size_t(p.stage_entries) + 128 > w.scratch_stride) return 142;  // k_place reads 64 entries from a tile's start
     if (p.stage_entries > p.n_elems_total + 3ull * p.n_ctiles) return 145;       // the array follows the element count, not the address span
+    // exchange areas of the one-launch compress: sections in order, behind the scratch blocks of as many
+    // learners, inside the workspace, and none where there is no room; k_pack takes aligned tiles only
+    if (!(w.sync_rec + 16 * size_t(p.n_ctiles) <= w.sync_tile && w.sync_tile + 32 * size_t(p.n_ctiles) <= w.sync_layer &&
+          w.sync_layer + 32 * size_t(p.n_layers) <= w.sync_epoch && w.sync_epoch + 4 * size_t(p.n_ctiles) <= w.sync_stride))
+        return 148;
+    for (size_t bytes : {w.least(1), w.total(1) - 1, w.total(1), w.total(3), w.total(5) + 1000}) {
+        const SyncPlace at = sync_place(w, bytes);
+        if (at.learners != (bytes < w.total(1) ? 0u : bytes < w.total(3) ? 1u : bytes < w.total(4) ? 3u : at.learners) || at.learners > 1024) return 149;
+        if (at.learners && (at.offset % 256 || at.offset < w.least(at.learners) || at.offset + at.learners * w.sync_stride > bytes)) return 150;
+    }
+    for (const TileDev &td : p.ctiles)
+        if (td.jcode() == 0 && !td.aligned()) return 151;
     if (w.total(3) != adacomp_workspace_bytes_batch(t.data(), uint32_t(t.size()), 3)) return 143;
     g_tiles_checked += p.n_ctiles + p.n_utiles;
     g_groups_checked += p.n_ugroups;

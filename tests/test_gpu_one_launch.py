@@ -1,0 +1,161 @@
+"""The one-launch compress (k_pack) on tables that reach both of its forms, with and without the wait for
+other workgroups succeeding, against the CPU oracle bit for bit.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import adacomp_workloads as W  # noqa: E402
+
+f32 = np.float32
+
+# up to 16 layers and 512 tiles: every workgroup reads all records; beyond: a workgroup per layer does.
+# Bin lengths from the shortest the kernel takes (4) to the longest of its tile class, slots that straddle
+# bins (lengths that are no multiple of 4), both word widths, layers that end inside a 16-byte slot
+FEW_LAYERS = [("a", 4 * 1025 + 3, 4), ("b", 5 * 2111 + 1, 5), ("c", 50 * 203 + 2, 50), ("d", 64 * 130 + 5, 64), ("e", 65 * 130 + 7, 65),
+              ("f", 500 * 61 + 216, 500), ("g", 1023 * 9 + 1, 1023), ("h", 4096 * 3 + 9, 4096), ("i", 1, 500), ("j", 6, 7)]
+TABLES = {
+    "one_tile": [("a", 777, 50)],
+    "few_layers": FEW_LAYERS,
+    "many_layers": FEW_LAYERS + [(f"m{i}", 1 + (i * 613) % 9001, (4, 7, 50, 63, 500, 1001)[i % 6]) for i in range(60)],
+    "one_long_layer": [("a", 4000 * 520 + 37, 500)],        # 521 tiles: beyond the 512 of the first form
+    "two_long_layers_short_bins": [("a", 4000 * 700 + 11, 50), ("b", 4032 * 300 + 5, 64)],
+}
+
+
+@pytest.fixture(scope="module")
+def H():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_harness
+    return gpu_harness
+
+
+class _Impatient:
+    """Every GpuSide made inside polls once and then works out what is missing itself."""
+
+    def __init__(self, H):
+        self.H = H
+
+    def __enter__(self):
+        import paper_1712_02679_amd as A
+        self.real = self.H.GpuSide
+
+        class Side(self.real):
+            def __init__(side, *args, **kw):
+                super().__init__(*args, **kw)
+                A.adacomp_debug_wait_polls(side.ws, 0)
+        self.H.GpuSide = Side
+
+    def __exit__(self, *exc):
+        self.H.GpuSide = self.real
+
+
+@pytest.mark.parametrize("name,batch,impatient", [(n, b, False) for n in sorted(TABLES) for b in (False, True)] +
+                         [(n, b, True) for n in ("few_layers", "many_layers", "one_tile") for b in (False, True)])
+def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
+    wl = W.custom(name, TABLES[name], dist="normal_outliers")
+    say = f"one launch: {name}, batch {batch}, impatient {impatient}"
+    if impatient:
+        with _Impatient(H):
+            H.run_parity(oracle_lib, wl, 3, 3, seed=31, label=say, batch=batch)
+    else:
+        H.run_parity(oracle_lib, wl, 3, 3, seed=31, label=say, batch=batch)
+
+
+@pytest.mark.parametrize("rule,factor", [(1, 2.0), (2, 2.0), (0, 1.5)])
+@pytest.mark.parametrize("name", ["few_layers", "many_layers"])
+def test_one_launch_variants(H, oracle_lib, name, rule, factor):
+    """The other rules, with gradients that hold zeros and all-zero bins (the printed compare sends those, but
+    nothing that lies past a tile)."""
+    wl = W.custom(name, TABLES[name], dist="normal")
+    zeros = lambda k, t: (W.gradient(wl, k, t, seed=5) * ((np.arange(wl.n_total) // 97 + k) % 3 != 0)).astype(f32)
+    H.run_parity(oracle_lib, wl, 2, 3, grads=zeros, rule=rule, soft_factor=factor, label=f"one launch: {name} rule {rule}", batch=True)
+
+
+def test_one_launch_beside_staged_calls(H, oracle_lib):
+    """One workspace: one-launch calls, three-launch calls (the tuning knob) and lazy calls in turn, then more
+    learners than the workspace has exchange areas for: the residues go on as if nothing had changed."""
+    import paper_1712_02679_amd as A
+    wl = W.custom("turns", TABLES["many_layers"], dist="normal")
+    table, n = wl.table(), wl.n_total
+    ws1 = torch.zeros(A.adacomp_workspace_bytes_batch(table, 2), dtype=torch.uint8, device="cuda:0")
+    A.adacomp_workspace_init(table, ws1)
+    bound = A.adacomp_packet_bound(table)
+    R = [np.zeros(n, f32) for _ in range(2)]
+    res = [torch.zeros(n, device="cuda:0") for _ in range(2)]
+    pk = [torch.zeros(bound, dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    try:
+        for t in range(8):
+            g = [W.gradient(wl, k, t, seed=3) for k in range(2)]
+            gd = [torch.from_numpy(x).cuda() for x in g]
+            kind = t % 4
+            A.adacomp_tuning_fold_scan(kind != 1)
+            if kind == 2:
+                A.adacomp_compress_batch_lazy(table, gd, res, pk, ws1)
+                A.adacomp_residue_sync(ws1)
+            elif kind == 3:
+                for k in range(2):
+                    A.adacomp_compress(table, gd[k], res[k], pk[k], ws1)
+                    torch.cuda.synchronize()
+            else:
+                A.adacomp_compress_batch(table, gd, res, pk, ws1)
+            torch.cuda.synchronize()
+            for k in range(2):
+                want = oracle_lib.compress(table, g[k], R[k])
+                assert np.array_equal(pk[k][:want.size].cpu().numpy(), want), (t, k)
+                assert np.array_equal(res[k].cpu().numpy(), R[k]), (t, k)
+    finally:
+        A.adacomp_tuning_fold_scan(True)
+        A.adacomp_workspace_release(ws1)
+
+
+def test_workspace_without_room_for_exchange_areas(H, oracle_lib):
+    """The least a call needs is what it was before there were exchange areas: such a workspace is accepted and
+    takes the staged launches, with the same results."""
+    import paper_1712_02679_amd as A
+    wl = W.custom("least", TABLES["few_layers"], dist="normal")
+    table, n = wl.table(), wl.n_total
+    areas = A.adacomp_workspace_bytes_batch(table, 2) - A.adacomp_workspace_bytes(table) - A.adacomp_workspace_gmax(table)[2]
+    assert areas > 0
+    ws = torch.zeros(A.adacomp_workspace_bytes(table) - areas, dtype=torch.uint8, device="cuda:0")
+    A.adacomp_workspace_init(table, ws)
+    g = W.gradient(wl, 0, 0, seed=9)
+    R, res = np.zeros(n, f32), torch.zeros(n, device="cuda:0")
+    pk = torch.zeros(A.adacomp_packet_bound(table), dtype=torch.uint8, device="cuda:0")
+    A.adacomp_compress(table, torch.from_numpy(g).cuda(), res, pk, ws)
+    torch.cuda.synchronize()
+    want = oracle_lib.compress(table, g, R)
+    assert np.array_equal(pk[:want.size].cpu().numpy(), want) and np.array_equal(res.cpu().numpy(), R)
+    A.adacomp_workspace_release(ws)
+
+
+@pytest.mark.parametrize("name", ["few_layers", "many_layers"])
+def test_one_launch_in_a_graph(H, oracle_lib, name):
+    """Captured and replayed five times with eager calls in between: every replay counts on."""
+    import paper_1712_02679_amd as A
+    wl = W.custom(name, TABLES[name], dist="normal_outliers")
+    table, n = wl.table(), wl.n_total
+    ws = torch.zeros(A.adacomp_workspace_bytes(table), dtype=torch.uint8, device="cuda:0")
+    A.adacomp_workspace_init(table, ws)
+    pk = torch.zeros(A.adacomp_packet_bound(table), dtype=torch.uint8, device="cuda:0")
+    res, gd, R = torch.zeros(n, device="cuda:0"), torch.zeros(n, device="cuda:0"), np.zeros(n, f32)
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        A.adacomp_compress(table, gd, res, pk, ws)
+    for t in range(10):
+        g = W.gradient(wl, 0, t, seed=4)
+        gd.copy_(torch.from_numpy(g))
+        torch.cuda.synchronize()
+        if t % 2 == 0:
+            graph.replay()
+        else:
+            A.adacomp_compress(table, gd, res, pk, ws)
+        torch.cuda.synchronize()
+        want = oracle_lib.compress(table, g, R)
+        assert np.array_equal(pk[:want.size].cpu().numpy(), want), t
+        assert np.array_equal(res.cpu().numpy(), R), t
+    A.adacomp_workspace_release(ws)
