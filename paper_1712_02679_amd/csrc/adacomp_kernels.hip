@@ -1290,8 +1290,9 @@ __global__ __launch_bounds__(kWG) void k_place(const CompressArgs a)
         __syncthreads();
     }
 
-    if (MODE == kPlaceResidue && blockIdx.x == gridDim.x - 1) return;
-    if (MODE != kPlaceResidue && blockIdx.x == gridDim.x - 1) {
+    const bool header_block = blockIdx.x == (a.n_tiles + kPlaceTiles - 1u) / kPlaceTiles;   // the last one (gridDim would be a hidden argument)
+    if (MODE == kPlaceResidue && header_block) return;
+    if (MODE != kPlaceResidue && header_block) {
         if (FOLD) {
             __shared__ float s_fscale[FOLD ? kFoldLayers : 1u];
             const uint32_t lane = tid & 63u;
@@ -1421,7 +1422,7 @@ __global__ __launch_bounds__(kWG) void k_place_tiled(const CompressArgs a)
     const uint16_t *const stage_all = reinterpret_cast<const uint16_t *>(sb + a.o_stage);
     uint8_t *const packet = a.packet[lr];
 
-    if (blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.x == a.n_tiles) {   // the grid has one workgroup per tile and this one
         place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
         return;
     }
