@@ -119,7 +119,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         ld.n_ctiles = nt;
         p.n_class_tiles[cls] += nt;
         p.layer_tiles_max = std::max(p.layer_tiles_max, nt);
-        if (T <= 64u) p.has_short_bins = true;
+        if (T <= 64u) { p.has_short_bins = true; p.short_bin_max = std::max(p.short_bin_max, T); }
         if (T < 4u) p.has_tiny_bins = true;
         // The staging array is indexed by position in the tile table, not by address: a tile's stretch
         // starts where the stretches of the tiles before it end (each rounded up to 4 entries, which keeps
@@ -341,7 +341,7 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     out.elem_span = p.elem_span; out.n_elems_total = p.n_elems_total; out.stage_entries = p.stage_entries;
     out.fixed_bytes = p.fixed_bytes; out.bound_bytes = p.bound_bytes;
     for (int c = 0; c < 2; ++c) out.n_class_tiles[c] = p.n_class_tiles[c];
-    out.layer_tiles_max = p.layer_tiles_max; out.has_tiny_bins = p.has_tiny_bins;
+    out.layer_tiles_max = p.layer_tiles_max; out.has_tiny_bins = p.has_tiny_bins; out.short_bin_max = p.short_bin_max;
     out.has_short_bins = p.has_short_bins; out.has_shifted_tiles = p.has_shifted_tiles;
     out.ws = p.ws;
     out.sync = p.sync;
@@ -750,6 +750,22 @@ int adacomp_compress_static(const adacomp_layer_t *layers, uint32_t n_layers, co
                             hip_stream);
 }
 
+// Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack (a workgroup)?  A wave
+// adds learner after learner, about a microsecond each, which pays where there are chunks enough to
+// cover it: 3072 are resident at L_T 50.  k_unpack / k_unpack8 in us, L_T 50, plain sum: 313 chunks 7.3 / 6.2
+// with 1 packet, 9.5 / 14.3 with 8; 1250 chunks 10.1 / 7.9 and 13.3 / 16.4; 2500 chunks 15.4 / 9.8 and
+// 20.8 / 17.4.  With the optimizer a wave also has its tile's traffic to itself: 2500 chunks, 8 packets,
+// SGD 34.8 / 36.9, and small tables lose 20 to 40 %.  ResNet-50's table (7300 chunks): 39 / 22 with 1
+// packet, 57 / 41 with 8, SGD and Adam with 8 packets 101 / 100 and 141 / 138.  Those packets have 1.8 words
+// to a bin; with 4.6, as after some mini-batches, the two meet at 8 learners and k_unpack is ahead beyond
+// (a mini-batch of 4, 8, 16: 290 / 279, 533 / 532, 1033 / 1039), except where bins are so short that a
+// workgroup of k_unpack has little to do: L_T 20, 8 packets, 100 / 37.
+static bool unpack8_for(const Plan &p, uint32_t n_chunks, uint32_t n_learners, uint32_t mode)
+{
+    if (n_learners > 8u && p.short_bin_max > 32u) return false;
+    return n_chunks >= 3072u || (mode == 0u && (n_learners <= 2u || n_chunks >= 2048u));
+}
+
 static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const void *const *packets,
                          uint32_t n_learners, float *dense_out, float *weights, float *state1, float *state2,
                          const adacomp_optimizer_t *opt, void *workspace, size_t workspace_bytes, void *hip_stream)
@@ -800,7 +816,14 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         const uint32_t n_all = a.mode == 0u ? p.n_ugroups : p.n_utiles, n8 = a.mode == 0u ? p.n_ugroups8 : p.n_usingles8;
         a.groups = table;
         a.n_groups = n_all;
-        if (n8 == 0u || n8 == n_all) {  // one word width
+        if (n8 != 0u && unpack8_for(p, n8, now, a.mode)) {
+            a.groups8 = reinterpret_cast<const UGroupDev *>(ws + p.ws.ugroups);
+            a.n_groups8 = n8;
+            a.chunk_elems = 64u * p.short_bin_max;
+            a.groups = table + n8;
+            a.n_groups = n_all - n8;
+            if ((rc = launch_unpack(a, 3, hip_stream)) != ADACOMP_OK) return rc;
+        } else if (n8 == 0u || n8 == n_all) {  // one word width
             if ((rc = launch_unpack(a, n8 ? 1 : 0, hip_stream)) != ADACOMP_OK) return rc;
         } else if (p.n_utiles <= kUnpackSplitTiles) {  // small and mixed: one launch that handles both
             if ((rc = launch_unpack(a, 2, hip_stream)) != ADACOMP_OK) return rc;

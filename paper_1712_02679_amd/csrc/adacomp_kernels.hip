@@ -25,7 +25,8 @@
 // adacomp_compress_batch_lazy runs the same three, but k_place leaves that read-modify-write out
 // and the next call's k_fused applies the corrections to the residue values while it has them in
 // registers (same arithmetic, same results; adacomp_residue_sync writes them on request).
-// adacomp_unpack_accumulate is one launch per word width, k_unpack: a workgroup owns a tile of the dense output
+// adacomp_unpack_accumulate is one launch, k_unpack (or k_unpack8 for large tables with short bins; with
+// many learners one launch per word width): a workgroup owns a tile of the dense output
 // in LDS, a lane group owns each bin and adds the learners' +-scale in learner order, then the
 // tile is written out once with coalesced float4 stores; neighbouring tiles share a workgroup
 // and the per-bin bookkeeping.
@@ -1802,6 +1803,16 @@ __device__ __forceinline__ void apply_update(const UnpackArgs &a, float sum, flo
     }
 }
 
+// LDS of a group of 16-bit layers inside k_unpack8 (k_unpack has the same arrays of its own: laid out in a
+// structure they cost it 2 %)
+struct UnpackLds {
+    __attribute__((aligned(16))) float acc[kUnpackTileElems];
+    __attribute__((aligned(16))) uint32_t off[64][kOffStride];  // first word of (bin, learner), counted from the packet start
+    __attribute__((aligned(16))) uint16_t cnt[64][kCntStride];
+    __attribute__((aligned(16))) float scale[kLearnerGroup];
+    uint32_t cmax;                                              // largest word count of a (bin, learner) in the tables
+};
+
 // MODE 0: dense_out <- sum.  MODE 1 / 2: also (or only) the SGD / Adam step on weights and state.
 // KIND 0 / 1: all groups of this launch belong to layers with 16-bit / 8-bit words; 2: either (the
 // layer says which).  Large tables get one launch per kind: each path alone needs fewer registers
@@ -1810,12 +1821,12 @@ __device__ __forceinline__ void apply_update(const UnpackArgs &a, float sum, flo
 // the kernel that holds both.  The single-width kernels are held to 80 registers (6 waves per
 // SIMD, what the LDS tile allows; the 16-bit path spills two).
 template <int MODE, int KIND>
-__global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const UnpackArgs a)
+__device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride],
+                                             uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
     // A workgroup serves a group of consecutive tiles that lie in one 64-bin chunk (or are slices
     // of one long bin).  With up to 16 learners the tables of phase 1 are built once for the group.
-    if (blockIdx.x >= a.n_groups) return;
-    const UGroupDev grp = a.groups[blockIdx.x];
+    const UGroupDev grp = a.groups[group];
     const UTileDev ut0 = a.tiles[grp.first_tile];
     const UTileDev ut_last = a.tiles[grp.first_tile + grp.n_tiles - 1u];
     const uint32_t layer = ut0.layer();
@@ -1825,11 +1836,6 @@ __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const Unpac
     const bool tables_once = a.n_learners <= kLearnerGroup;
     const bool w8 = KIND == 2 ? ld.word_bytes == 1u : KIND == 1;
 
-    __shared__ float s_acc[kUnpackTileElems];
-    __shared__ __attribute__((aligned(16))) uint32_t s_off[64][kOffStride];  // first word of (bin, learner), counted from the packet start
-    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64][kCntStride];
-    __shared__ __attribute__((aligned(16))) float s_scale[kLearnerGroup];
-    __shared__ uint32_t s_cmax;                                                // largest word count of a (bin, learner) in the tables
 
   for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
     const UTileDev ut = ti == 0u ? ut0 : a.tiles[grp.first_tile + ti];
@@ -1929,6 +1935,195 @@ __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const Unpac
         }
     }
   }  // tiles of the group
+}
+
+template <int MODE, int KIND>
+__global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const UnpackArgs a)
+{
+    if (blockIdx.x >= a.n_groups) return;
+    __shared__ float s_acc[kUnpackTileElems];
+    __shared__ __attribute__((aligned(16))) uint32_t s_off[64][kOffStride];  // first word of (bin, learner), counted from the packet start
+    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64][kCntStride];
+    __shared__ __attribute__((aligned(16))) float s_scale[kLearnerGroup];
+    __shared__ uint32_t s_cmax;                                                // largest word count of a (bin, learner) in the tables
+    unpack_group<MODE, KIND>(a, blockIdx.x, s_acc, s_off, s_cnt, s_scale, s_cmax);
+}
+
+// ==============================================================================================
+// k_unpack8: layers with 8-bit words (L_T <= 64), several words to a bin.  One wave owns a chunk of 64
+// bins, a lane owns a bin: it knows the bin's word count for every learner, a wave scan says where the
+// words start, and the lane fetches its words, sixteen bytes at a time, and adds them to the chunk's
+// accumulators in LDS, learner after learner.  Nothing is shared between waves, so there are no tables
+// and no barriers.  What bounded the scheme before this one (four lanes to a bin, 16 word slots each, of
+// which four were in use) was the issue of those slots: without the adds the launch took 20 us, with them
+// 33 us for 1 packet of ResNet-50's table, 46 for 8 and 78 for 16; now 15, 33 and 66 (with the 16-bit layer's
+// groups 22, 41 and 73, against 39, 57 and 92 for the two launches before).  What bounds it now is the
+// LDS: every word is a load and a store at a random bank.  A workgroup is four such waves, three
+// are on a compute unit at L_T 50 (LDS), and the groups of the 16-bit layers ride in the same launch (a
+// launch of their own cost 7 us).
+// All adds to one element come from one lane in program order, and the LDS unit executes a wave's
+// operations in order: the sum is taken learner 0 first.
+// ==============================================================================================
+// A record of a table that does not change while a kernel runs, the same for all threads: scalar loads.
+// (Behind a store the compiler takes a vector register per word otherwise.)
+typedef uint32_t vuint2 __attribute__((ext_vector_type(2)));
+typedef uint32_t vuint8 __attribute__((ext_vector_type(8)));
+typedef uint32_t vuint16 __attribute__((ext_vector_type(16)));
+template <class V, class T>
+__device__ __forceinline__ T table_record(const T *p)
+{
+    static_assert(sizeof(V) == sizeof(T), "record size");
+    return __builtin_bit_cast(T, *(const __attribute__((address_space(4))) V *)p);
+}
+template <class V>
+__device__ __forceinline__ V packet_field(const uint8_t *p) { return *(const __attribute__((address_space(4))) V *)p; }
+
+template <int MODE>
+__device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_t group, float *acc_chunk)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const UTileDev ut = table_record<vuint8>(a.tiles + table_record<vuint2>(a.groups8 + group).first_tile);
+    const uint32_t layer = ut.layer(), n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
+    const LayerDev ld = table_record<vuint16>(a.layers + layer);
+    float *const out = a.dense + ut.elem_base;
+    const uint32_t chunk = ut.first_bin >> 6;
+
+    for (uint32_t e = lane * 4u; e < n; e += 256u) {   // zero, or the partial sum of an earlier launch
+        vfloat4 v = {0.f, 0.f, 0.f, 0.f};
+        if (a.accumulate)
+            for (uint32_t k = 0; k < 4u && e + k < n; ++k) v[k] = out[e + k];
+        *reinterpret_cast<vfloat4 *>(&acc_chunk[e]) = v;   // the chunk's LDS has room for the rounded-up tail
+    }
+    volatile lds_float *const acc = lds_volatile(acc_chunk + lane * T);
+    const uint32_t span = lane < nb ? (T < n - lane * T ? T : n - lane * T) : 0u;   // elements of this lane's bin
+
+    constexpr uint32_t kBatch = 8;   // learners whose counts and words are in flight together
+    for (uint32_t h0 = 0; h0 < a.n_learners; h0 += kBatch) {
+        const uint32_t nk = a.n_learners - h0 < kBatch ? a.n_learners - h0 : kBatch;
+        uint32_t c[kBatch], off[kBatch], got[kBatch][4];   // got: the 16 bytes from the aligned 4 that hold the first word on
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            c[k] = 0u;
+            if (k < nk && lane < nb) c[k] = (a.packets[h0 + k] + ld.counts_offset)[ut.first_bin + lane];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            off[k] = got[k][0] = got[k][1] = got[k][2] = got[k][3] = 0u;
+            if (k >= nk) continue;   // uniform
+            const uint8_t *const pk = a.packets[h0 + k];
+            const vuint4 hv = packet_field<vuint4>(pk);        // magic, version, status, n_layers
+            const vuint2 tb = packet_field<vuint2>(pk + 16);   // total_bytes
+            const bool ok = (hv.x == ADACOMP_PACKET_MAGIC) & (hv.y == ADACOMP_PACKET_VERSION) & (hv.z == ADACOMP_STATUS_COMPLETE) &
+                            (hv.w == a.n_layers) & (tb.y == 0u);
+            const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
+            const uint32_t words = packet_field<uint32_t>(rec + offsetof(adacomp_packet_layer_t, words_offset));   // packets stay below 2^32 bytes (host check)
+            const uint32_t before = packet_field<uint32_t>(pk + ld.chunks_offset + 4u * chunk);
+            const uint32_t ck = ok ? c[k] : 0u;   // a packet that does not match contributes nothing
+            // a bin whose words would lie past the packet's total_bytes contributes nothing either
+            const uint64_t first = uint64_t(words) + before + (wave_incl_scan(ck) - ck);
+            const bool inside = first + ck <= tb.x;
+            c[k] = inside ? ck : 0u;
+            off[k] = uint32_t(first);
+            if (c[k] != 0u) {
+                // word sections start on 16-byte boundaries and are padded to them, so the aligned 4 bytes
+                // around any word of the run lie inside the packet
+                const uint32_t *const src = reinterpret_cast<const uint32_t *>(pk) + (off[k] >> 2);
+                const uint32_t end = (off[k] & 3u) + c[k];
+#pragma unroll
+                for (uint32_t i = 0; i < 4u; ++i)
+                    if (end > 4u * i) got[k][i] = src[i];
+            }
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            if (k >= nk) break;   // uniform
+            __builtin_amdgcn_sched_barrier(0);   // one learner at a time: keeps the register count down
+            const uint8_t *const pk = a.packets[h0 + k];
+            const float scale = packet_field<float>(pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer + offsetof(adacomp_packet_layer_t, scale));
+            const uint32_t skew = off[k] & 3u;
+#pragma unroll
+            for (uint32_t i = 0; i < 4u; ++i) {
+                // words 4 i .. 4 i + 3 of the run, as far as they have been fetched
+                const uint32_t left = c[k] > 4u * i ? c[k] - 4u * i : 0u;
+                const uint32_t here = i < 3u ? left : left < 4u - skew ? left : 4u - skew;
+                if (__builtin_amdgcn_ballot_w64(here != 0u) == 0ull) break;
+                const uint32_t word = __builtin_amdgcn_alignbyte(i < 3u ? got[k][i < 3u ? i + 1u : 3u] : 0u, got[k][i], skew);
+                // one learner's words name different elements: all loads of the accumulators, then the stores
+                float cur[4];
+                bool on[4];
+#pragma unroll
+                for (uint32_t j = 0; j < 4u; ++j) {
+                    const uint32_t w = (word >> (8u * j)) & 0xFFu;
+                    on[j] = j < here && (w & 1u) != 0u && (w >> 2) < span;
+                    cur[j] = 0.f;
+                    if (on[j]) cur[j] = acc[w >> 2];
+                }
+#pragma unroll
+                for (uint32_t j = 0; j < 4u; ++j) {
+                    const uint32_t w = (word >> (8u * j)) & 0xFFu;
+                    if (on[j]) acc[w >> 2] = cur[j] + ((w & 2u) ? -scale : scale);
+                }
+            }
+            for (uint32_t q = 16u - skew; q < c[k]; ++q) {   // bins that send more than that
+                const uint32_t w = pk[off[k] + q];
+                if ((w & 1u) && (w >> 2) < span) acc[w >> 2] = acc[w >> 2] + ((w & 2u) ? -scale : scale);
+            }
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+
+    const __amdgpu_buffer_rsrc_t w_buf = tile_buffer(MODE != 0 ? a.weights + ut.elem_base : out, MODE != 0 ? n : 0u);
+    const __amdgpu_buffer_rsrc_t s1_buf = tile_buffer(MODE != 0 ? a.state1 + ut.elem_base : out, MODE != 0 ? n : 0u);
+    const __amdgpu_buffer_rsrc_t s2_buf = tile_buffer(MODE == 2 ? a.state2 + ut.elem_base : out, MODE == 2 ? n : 0u);
+#pragma unroll 4
+    for (uint32_t e = lane * 4u; e < (n & ~3u); e += 256u) {
+        const vfloat4 sum = *reinterpret_cast<const vfloat4 *>(&acc_chunk[e]);
+        if (a.write_dense) store_stream4(out + e, sum);
+        if (MODE != 0) {
+            vfloat4 w = buffer_load_stream4(w_buf, e), s1 = buffer_load_stream4(s1_buf, e), s2 = {0.f, 0.f, 0.f, 0.f};
+            if (MODE == 2) s2 = buffer_load_stream4(s2_buf, e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float wk = w[k], s1k = s1[k], s2k = s2[k];
+                apply_update<MODE>(a, sum[k], wk, s1k, s2k);
+                w[k] = wk; s1[k] = s1k; s2[k] = s2k;
+            }
+            buffer_store_stream4(w_buf, e, w);
+            buffer_store_stream4(s1_buf, e, s1);
+            if (MODE == 2) buffer_store_stream4(s2_buf, e, s2);
+        }
+    }
+    if (lane < (n & 3u)) {   // the layer's last elements
+        const uint32_t e = (n & ~3u) + lane;
+        const float sum = acc_chunk[e];
+        if (a.write_dense) out[e] = sum;
+        if (MODE != 0) {
+            float w = buffer_load1(w_buf, e), s1 = buffer_load1(s1_buf, e), s2 = 0.f;
+            if (MODE == 2) s2 = buffer_load1(s2_buf, e);
+            apply_update<MODE>(a, sum, w, s1, s2);
+            buffer_store1(w_buf, e, w);
+            buffer_store1(s1_buf, e, s1);
+            if (MODE == 2) buffer_store1(s2_buf, e, s2);
+        }
+    }
+}
+
+// The first n_groups workgroups take a group of the 16-bit layers each, the others four chunks of the
+// 8-bit ones.  Dynamic LDS: launch_unpack.
+template <int MODE>
+__global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
+    if (blockIdx.x < a.n_groups) {
+        UnpackLds &lds = *reinterpret_cast<UnpackLds *>(s_dyn);
+        unpack_group<MODE, 0>(a, blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+        return;
+    }
+    uint32_t r = blockIdx.x - a.n_groups;
+    const uint32_t n_runs = (a.n_groups8 + 3u) / 4u;
+    if (r < (n_runs & ~63u)) r = (r & ~63u) | ((r & 7u) << 3) | ((r >> 3) & 7u);   // neighbouring chunks share an XCD's L2
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (4u * r + wave < a.n_groups8) unpack8_chunk<MODE>(a, 4u * r + wave, reinterpret_cast<float *>(s_dyn) + wave * a.chunk_elems);
 }
 
 // ==============================================================================================
@@ -2064,9 +2259,16 @@ int launch_place(const CompressArgs &a, void *stream)
 int launch_unpack(const UnpackArgs &a, int kind, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (a.n_groups == 0) return ADACOMP_OK;
+    if (a.n_groups == 0 && kind != 3) return ADACOMP_OK;
     const dim3 grid(a.n_groups), wg(kWG);
-    if (kind == 1) {
+    if (kind == 3) {
+        if (a.n_groups8 == 0 || a.chunk_elems == 0 || a.chunk_elems > 64u * 64u) return ADACOMP_EINVAL;
+        const dim3 both(a.n_groups + (a.n_groups8 + 3u) / 4u);
+        const uint32_t lds = std::max(uint32_t(sizeof(UnpackLds)), 4u * a.chunk_elems * 4u);
+        if (a.mode == 1) hipLaunchKernelGGL((k_unpack8<1>), both, wg, lds, s, a);
+        else if (a.mode == 2) hipLaunchKernelGGL((k_unpack8<2>), both, wg, lds, s, a);
+        else hipLaunchKernelGGL((k_unpack8<0>), both, wg, lds, s, a);
+    } else if (kind == 1) {
         if (a.mode == 1) hipLaunchKernelGGL((k_unpack<1, 1>), grid, wg, 0, s, a);
         else if (a.mode == 2) hipLaunchKernelGGL((k_unpack<2, 1>), grid, wg, 0, s, a);
         else hipLaunchKernelGGL((k_unpack<0, 1>), grid, wg, 0, s, a);

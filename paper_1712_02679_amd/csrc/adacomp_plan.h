@@ -131,6 +131,7 @@ struct Plan {
     std::vector<uint32_t> cclass;        // compress tile indices, the 4096-element ones first (tables with both kinds)
     bool has_short_bins = false;  // some layer has L_T <= 64 (8-bit words, many words per tile)
     uint32_t layer_tiles_max = 0;  // compress tiles of the layer that has most
+    uint32_t short_bin_max = 0;    // longest L_T <= 64
     bool has_tiny_bins = false;    // some layer has L_T < 4
     bool has_shifted_tiles = false;  // some tile of the larger class has skip != 0
     WorkspaceLayout ws;
@@ -225,6 +226,8 @@ struct UnpackArgs {
     const LayerDev *layers;
     float *dense;
     uint32_t n_groups;
+    const UGroupDev *groups8;          // kind 3: the groups of the layers with 8-bit words, single chunks in table order; `groups` holds the others
+    uint32_t n_groups8, chunk_elems;   // chunk_elems: floats of LDS per chunk, 64 times the longest of their bins
     uint32_t n_tiles, n_layers, n_learners, accumulate;
     uint32_t write_dense;              // 0: the sum is only consumed by the update
     uint32_t mode;                     // 0: sum only; 1: SGD with momentum; 2: Adam (applied by this launch)
@@ -240,7 +243,7 @@ int launch_place(const CompressArgs &a, void *stream);
 // what a k_place launch does: everything (the default); the words, offsets and header only, leaving
 // the residue corrections waiting; or those corrections only
 constexpr uint32_t kPlaceEager = 0, kPlaceWords = 1, kPlaceResidue = 2;
-int launch_unpack(const UnpackArgs &a, int kind, void *stream);  // kind 0: 16-bit words, 1: 8-bit, 2: both
+int launch_unpack(const UnpackArgs &a, int kind, void *stream);  // kind 0: 16-bit words, 1: 8-bit, 2: both, 3: both, k_unpack8
 int launch_copy(float *dst, const float *src, size_t n, void *stream);
 int launch_triad(float *x, const float *y, size_t n, uint32_t resident, void *stream);   // n a multiple of 4, below 2^44; resident 3 .. 8
 int launch_fill(float *x, float value, size_t n, void *stream);
