@@ -113,7 +113,9 @@ size_t adacomp_packet_bound(const adacomp_layer_t *layers, uint32_t n_layers);
 size_t adacomp_packet_fixed_bytes(const adacomp_layer_t *layers, uint32_t n_layers);
 
 /* Bytes of workspace adacomp_workspace_init / compress / unpack need for this table (device
- * tables, per-bin g_max, per-tile counters, staging for unplaced words). 0 if the table is invalid. */
+ * tables, per-bin g_max, per-tile counters, staging for unplaced words, and an area in which the
+ * workgroups of a one-launch compress exchange their sums; a workspace short of that area alone is
+ * accepted, and its calls take more launches). 0 if the table is invalid. */
 size_t adacomp_workspace_bytes(const adacomp_layer_t *layers, uint32_t n_layers);
 
 /* Same, for adacomp_compress_batch with up to n_learners learners per call: the tables once plus
