@@ -751,19 +751,27 @@ int adacomp_compress_static(const adacomp_layer_t *layers, uint32_t n_layers, co
 }
 
 // Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack (a workgroup)?  A wave
-// adds learner after learner, about a microsecond each, which pays where there are chunks enough to
-// cover it: 3072 are resident at L_T 50.  k_unpack / k_unpack8 in us, L_T 50, plain sum: 313 chunks 7.3 / 6.2
-// with 1 packet, 9.5 / 14.3 with 8; 1250 chunks 10.1 / 7.9 and 13.3 / 16.4; 2500 chunks 15.4 / 9.8 and
-// 20.8 / 17.4.  With the optimizer a wave also has its tile's traffic to itself: 2500 chunks, 8 packets,
-// SGD 34.8 / 36.9, and small tables lose 20 to 40 %.  ResNet-50's table (7300 chunks): 39 / 22 with 1
-// packet, 57 / 41 with 8, SGD and Adam with 8 packets 101 / 100 and 141 / 138.  Those packets have 1.8 words
-// to a bin; with 4.6, as after some mini-batches, the two meet at 8 learners and k_unpack is ahead beyond
-// (a mini-batch of 4, 8, 16: 290 / 279, 533 / 532, 1033 / 1039), except where bins are so short that a
-// workgroup of k_unpack has little to do: L_T 20, 8 packets, 100 / 37.
+// adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
+// it: 256 bytes of LDS to each element of L_T and three workgroups to a CU leave 3072 resident up to L_T 53,
+// 2048 beyond.  k_unpack / k_unpack8 in us:
+//   plain sum, L_T 50, 1 packet: 313 chunks 7.3 / 6.2, 1250 10.1 / 7.9, 2500 15.4 / 9.8, 7300 39 / 22;
+//   4 packets, 20 M elements: L_T 16 92 / 30, 32 51 / 27, 40 43 / 28, 50 36 / 28, 56 33 / 28, 64 30.5 / 27.9;
+//   8 packets: 10 M elements, L_T 16 61 / 29, 32 36 / 26, 40 31 / 26.5, but 50 25.6 / 28.2 (3277 chunks) and
+//     64 21.2 / 27.8 (2560), whose chunks are too few; 7300 chunks of L_T 50 57 / 41;
+//   16 packets: with 4.6 words to a bin k_unpack is ahead (1033 / 1039) except at short bins (L_T 20, 8
+//     packets, 100 / 37).
+// With the optimizer a wave also has its tile's weights and moments to carry, with too few loads in flight:
+//   20 M elements, SGD with 4 packets, L_T 16 109 / 77, 32 75 / 84, 50 77 / 93, 64 74 / 86; 48 M elements, SGD
+//   with 8, L_T 16 308 / 203, 32 197 / 202, 50 191 / 223; Adam with 1, L_T 16 117 / 111, 32 99 / 120: k_unpack
+//   above L_T 16.
 static bool unpack8_for(const Plan &p, uint32_t n_chunks, uint32_t n_learners, uint32_t mode)
 {
-    if (n_learners > 8u && p.short_bin_max > 32u) return false;
-    return n_chunks >= 3072u || (mode == 0u && (n_learners <= 2u || n_chunks >= 2048u));
+    if (mode != 0u) return p.short_bin_max <= 16u && n_learners <= 8u && n_chunks >= 3072u;
+    if (n_learners <= 2u) return true;
+    if (p.short_bin_max <= 32u) return n_chunks >= 3072u;
+    if (n_learners <= 4u) return n_chunks >= 5120u;
+    if (n_learners <= 8u) return p.short_bin_max <= 40u ? n_chunks >= 4096u : p.short_bin_max <= 53u && n_chunks >= 6144u;
+    return false;
 }
 
 static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const void *const *packets,

@@ -1,6 +1,6 @@
 """k_unpack8 (layers with 8-bit words, a wave per chunk of 64 bins) at the edges of its rule: one or two
-packets on tables of any size, from 2048 chunks on for the plain sum, from 3072 on with the optimizer; up
-to 8 packets, or any number where all such bins have at most 32 elements.
+packets on tables of any size; up to 4 packets from 5120 chunks on; any number where all such bins have at
+most 32 elements, from 3072 chunks on; with the optimizer where they have at most 16.
 Against the CPU oracle, bit for bit.  Needs an MI355X."""
 import numpy as np
 import pytest
@@ -19,9 +19,9 @@ LAYERS = [("a", 64 * 700 + 13, 1), ("b", 1, 64), ("c", 3 * 64 * 300 + 5, 3), ("d
           ("f", 5, 50), ("g", 50 * 64 * 90 + 49, 50), ("h", 64 * 64 * 40 + 63, 64), ("i", 5000 * 3 + 1, 5000), ("j", 2, 9)]
 TABLES = {
     "small": LAYERS[1:6] + LAYERS[8:],                           # below every threshold: one or two packets only
-    "2100_chunks": LAYERS + [("k", 2 * 64 * 570 + 1, 2)],        # plain sum
-    "2100_chunks_up_to_32": [l for l in LAYERS if l[2] <= 32 or l[2] > 64] + [("k", 2 * 64 * 670 + 1, 2), ("l", 32 * 64 * 40 + 3, 32)],   # plain sum of any number
-    "3100_chunks": LAYERS + [("k", 2 * 64 * 1570 + 1, 2)],       # plain sum and optimizer
+    "5200_chunks": LAYERS + [("k", 2 * 64 * 3670 + 1, 2)],       # up to 4 packets
+    "3100_chunks_up_to_32": [l for l in LAYERS if l[2] <= 32 or l[2] > 64] + [("k", 2 * 64 * 1670 + 1, 2), ("l", 32 * 64 * 40 + 3, 32)],   # any number
+    "3100_chunks_up_to_16": [l for l in LAYERS if l[2] <= 16 or l[2] > 64] + [("k", 2 * 64 * 1670 + 1, 2), ("l", 16 * 64 * 40 + 3, 16)],   # the optimizer too
 }
 
 
@@ -36,14 +36,14 @@ def H():
 @pytest.mark.parametrize("dense", [False, True])
 @pytest.mark.parametrize("name", sorted(TABLES))
 def test_sums(H, oracle_lib, name, dense):
-    """1, 2, 8, 9, 17 and 70 packets (batches of 8 in flight, sums carried over launches of 64); dense: every
+    """1, 2, 4, 8, 9, 17 and 70 packets (batches of 8 in flight, sums carried over launches of 64); dense: every
     element sent, so that bins send up to 64 words."""
     wl = W.custom(name, TABLES[name], dist="normal")
     table, n = wl.table(), wl.n_total
     chunks = sum(-(-(-(-m // lt)) // 64) for _, m, lt in table if lt <= 64)
-    assert chunks < 2048 if name == "small" else 2048 <= chunks < 3072 if name.startswith("2100") else chunks >= 3072
+    assert chunks < 3072 if name == "small" else chunks >= (5120 if name == "5200_chunks" else 3072)
     mask = H.layer_mask(table, n)
-    counts = (1, 2, 8) if dense else (0, 1, 2, 8, 9, 17, 70)
+    counts = (1, 2, 4, 8) if dense else (0, 1, 2, 4, 8, 9, 17, 70)
     gpu = H.GpuSide(table, n, max(counts))
     try:
         cpu = []
@@ -66,13 +66,13 @@ def test_sums(H, oracle_lib, name, dense):
 @pytest.mark.parametrize("kind,with_dense", [(1, False), (2, True)])
 def test_updates(H, oracle_lib, kind, with_dense):
     import test_gpu_parity
-    test_gpu_parity._update_case(oracle_lib, W.custom("unpack8_update", TABLES["3100_chunks"], dist="normal_outliers"), 3, 2, kind, with_dense, seed=6)
+    test_gpu_parity._update_case(oracle_lib, W.custom("unpack8_update", TABLES["3100_chunks_up_to_16"], dist="normal_outliers"), 3, 2, kind, with_dense, seed=6)
 
 
 def test_packets_that_do_not_belong(H, oracle_lib):
     """A packet with a broken header, or whose words would lie past its end, contributes nothing; the others do."""
     import packet_format as pf
-    wl = W.custom("broken", TABLES["2100_chunks"], dist="normal")
+    wl = W.custom("broken", TABLES["5200_chunks"], dist="normal")
     table, n = wl.table(), wl.n_total
     mask = H.layer_mask(table, n)
     cpu = [oracle_lib.compress(table, W.gradient(wl, k, 0, seed=2), np.zeros(n, f32)) for k in range(3)]
