@@ -793,7 +793,6 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
     a.tiles = reinterpret_cast<const UTileDev *>(ws + p.ws.utiles);
     a.layers = reinterpret_cast<const LayerDev *>(ws + p.ws.layers);
     a.dense = dense_out;
-    a.n_tiles = p.n_utiles;
     a.n_layers = p.n_layers;
     a.weights = weights; a.state1 = state1; a.state2 = state2;
     a.n_average = float(n_learners);
@@ -824,12 +823,13 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         const uint32_t n_all = a.mode == 0u ? p.n_ugroups : p.n_utiles, n8 = a.mode == 0u ? p.n_ugroups8 : p.n_usingles8;
         a.groups = table;
         a.n_groups = n_all;
+        a.n_groups8 = a.first16 = a.chunk_lds = 0u;
         if (n8 != 0u && unpack8_for(p, n8, now, a.mode)) {
-            a.groups8 = reinterpret_cast<const UGroupDev *>(ws + p.ws.ugroups);
+            a.groups = reinterpret_cast<const UGroupDev *>(ws + p.ws.ugroups);   // single chunks in either table, here in order
             a.n_groups8 = n8;
-            a.chunk_elems = 64u * p.short_bin_max;
-            a.groups = table + n8;
             a.n_groups = n_all - n8;
+            a.first16 = uint32_t(table - a.groups) + n8;
+            a.chunk_lds = 64u * p.short_bin_max + 2u;
             if ((rc = launch_unpack(a, 3, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
             if ((rc = launch_unpack(a, n8 ? 1 : 0, hip_stream)) != ADACOMP_OK) return rc;

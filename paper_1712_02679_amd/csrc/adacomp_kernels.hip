@@ -1982,7 +1982,7 @@ template <int MODE>
 __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_t group, float *acc_chunk)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const UTileDev ut = table_record<vuint8>(a.tiles + table_record<vuint2>(a.groups8 + group).first_tile);
+    const UTileDev ut = table_record<vuint8>(a.tiles + table_record<vuint2>(a.groups + group).first_tile);
     const uint32_t layer = ut.layer(), n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
     const LayerDev ld = table_record<vuint16>(a.layers + layer);
     float *const out = a.dense + ut.elem_base;
@@ -2116,14 +2116,16 @@ __global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackArgs a)
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
     if (blockIdx.x < a.n_groups) {
         UnpackLds &lds = *reinterpret_cast<UnpackLds *>(s_dyn);
-        unpack_group<MODE, 0>(a, blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+        unpack_group<MODE, 0>(a, a.first16 + blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
         return;
     }
     uint32_t r = blockIdx.x - a.n_groups;
-    const uint32_t n_runs = (a.n_groups8 + 3u) / 4u;
+    const uint32_t wg_log = a.chunk_lds & 63u, wg_chunks = 1u << wg_log;
+    const uint32_t n_runs = (a.n_groups8 + wg_chunks - 1u) >> wg_log;
     if (r < (n_runs & ~63u)) r = (r & ~63u) | ((r & 7u) << 3) | ((r >> 3) & 7u);   // neighbouring chunks share an XCD's L2
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (4u * r + wave < a.n_groups8) unpack8_chunk<MODE>(a, 4u * r + wave, reinterpret_cast<float *>(s_dyn) + wave * a.chunk_elems);
+    const uint32_t chunk = (r << wg_log) + wave;
+    if (wave < wg_chunks && chunk < a.n_groups8) unpack8_chunk<MODE>(a, chunk, reinterpret_cast<float *>(s_dyn) + wave * (a.chunk_lds & ~63u));
 }
 
 // ==============================================================================================
@@ -2262,9 +2264,10 @@ int launch_unpack(const UnpackArgs &a, int kind, void *stream)
     if (a.n_groups == 0 && kind != 3) return ADACOMP_OK;
     const dim3 grid(a.n_groups), wg(kWG);
     if (kind == 3) {
-        if (a.n_groups8 == 0 || a.chunk_elems == 0 || a.chunk_elems > 64u * 64u) return ADACOMP_EINVAL;
-        const dim3 both(a.n_groups + (a.n_groups8 + 3u) / 4u);
-        const uint32_t lds = std::max(uint32_t(sizeof(UnpackLds)), 4u * a.chunk_elems * 4u);
+        const uint32_t wg_log = a.chunk_lds & 63u, chunk_elems = a.chunk_lds & ~63u;
+        if (a.n_groups8 == 0 || chunk_elems == 0 || chunk_elems > 64u * 64u || wg_log > 2u) return ADACOMP_EINVAL;
+        const dim3 both(a.n_groups + ((a.n_groups8 + (1u << wg_log) - 1u) >> wg_log));
+        const uint32_t lds = std::max(uint32_t(sizeof(UnpackLds)), 4u * chunk_elems << wg_log);
         if (a.mode == 1) hipLaunchKernelGGL((k_unpack8<1>), both, wg, lds, s, a);
         else if (a.mode == 2) hipLaunchKernelGGL((k_unpack8<2>), both, wg, lds, s, a);
         else hipLaunchKernelGGL((k_unpack8<0>), both, wg, lds, s, a);

@@ -225,17 +225,22 @@ struct UnpackArgs {
     const UGroupDev *groups;
     const LayerDev *layers;
     float *dense;
-    uint32_t n_groups;
-    const UGroupDev *groups8;          // kind 3: the groups of the layers with 8-bit words, single chunks in table order; `groups` holds the others
-    uint32_t n_groups8, chunk_elems;   // chunk_elems: floats of LDS per chunk, 64 times the longest of their bins
-    uint32_t n_tiles, n_layers, n_learners, accumulate;
+    uint32_t n_groups;                 // workgroups that take a group each (kind 3: of the layers with 16-bit words)
+    uint32_t n_groups8;                // kind 3: groups of the layers with 8-bit words, a chunk each, the first of `groups`
+    uint32_t n_layers, n_learners, accumulate;
     uint32_t write_dense;              // 0: the sum is only consumed by the update
     uint32_t mode;                     // 0: sum only; 1: SGD with momentum; 2: Adam (applied by this launch)
+    uint32_t first16;                  // kind 3: where in `groups` those of the layers with 16-bit words begin
     float *weights, *state1, *state2;  // momentum buffer, or Adam's m and v
     float n_average;                   // learner count the sum is divided by
     float lr, p1, p2, one_minus_p1, one_minus_p2, eps, bias1, bias2;
+    uint32_t chunk_lds;                // kind 3: floats of LDS per chunk, 64 times the longest of the 8-bit layers' bins, + log2 of the chunks per workgroup
     const uint8_t *packets[kMaxPacketArgs];
 };
+// Workgroups start with the scalar loads of these arguments, and the first of a launch wait for every line
+// of them.  With 16 bytes more before `packets`, whose lines then no longer began with it, k_unpack took
+// 1.5 to 2 % longer (4 M elements, 4 packets 8.85 -> 9.04 us; 20 M, 8 packets 31.5 -> 32.1).
+static_assert(sizeof(UnpackArgs) == 640 && offsetof(UnpackArgs, packets) == 128, "kernel arguments");
 
 int launch_fused(const CompressArgs &a, int jcode, void *stream);
 int launch_scan(const CompressArgs &a, void *stream);
