@@ -366,6 +366,55 @@ void register_workspace(const adacomp_layer_t *layers, uint32_t n_layers, const 
     g_ws[workspace] = std::move(reg);
 }
 
+// Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack (a workgroup)?  A wave
+// adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
+// it: 256 bytes of LDS to each element of L_T and three workgroups to a CU leave 3072 resident up to L_T 53,
+// 2048 beyond.  k_unpack / k_unpack8 in us:
+//   plain sum, L_T 50, 1 packet: 313 chunks 7.3 / 6.2, 1250 10.1 / 7.9, 2500 15.4 / 9.8, 7300 39 / 22;
+//   4 packets, 20 M elements: L_T 16 92 / 30, 32 51 / 27, 40 43 / 28, 50 36 / 28, 56 33 / 28, 64 30.5 / 27.9;
+//   8 packets: 10 M elements, L_T 16 61 / 29, 32 36 / 26, 40 31 / 26.5, but 50 25.6 / 28.2 (3277 chunks) and
+//     64 21.2 / 27.8 (2560), whose chunks are too few; 7300 chunks of L_T 50 57 / 41;
+//   16 packets: with 4.6 words to a bin k_unpack is ahead (1033 / 1039) except at short bins (L_T 20, 8
+//     packets, 100 / 37).
+// With the optimizer a wave also has its tile's weights and moments to carry, with too few loads in flight:
+//   20 M elements, SGD with 4 packets, L_T 16 109 / 77, 32 75 / 84, 50 77 / 93, 64 74 / 86; 48 M elements, SGD
+//   with 8, L_T 16 308 / 203, 32 197 / 202, 50 191 / 223; Adam with 1, L_T 16 117 / 111, 32 99 / 120: k_unpack
+//   above L_T 16.
+// Small tables with a few long 8-bit bins among many 16-bit groups stay with the one launch of k_unpack<., 2>:
+//   4 M, 5 %, L_T 64 and 500, 2 packets 8.7 / 9.0.
+static bool unpack8_for(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners, uint32_t mode)
+{
+    if (mode != 0u) return p.short_bin_max <= 16u && n_learners <= 8u && n_chunks >= 3072u;
+    if (n_learners <= 2u) return p.short_bin_max <= 53u || p.n_utiles > kUnpackSplitTiles || n_groups16 <= 8u * n_chunks;
+    if (p.short_bin_max <= 32u) return n_chunks >= 3072u;
+    if (n_learners <= 4u) return n_chunks >= 5120u;
+    if (n_learners <= 8u) return p.short_bin_max <= 40u ? n_chunks >= 4096u : p.short_bin_max <= 53u && n_chunks >= 6144u;
+    return false;
+}
+
+// Chunks (waves at work) per workgroup of k_unpack8, as a power of two.  All workgroups of a launch have the
+// same LDS, so the 16-bit groups that ride along get that of the chunks: with four chunks always (51 KB at
+// L_T 50, 64 KB at 64) they had 3 or 2 workgroups on a compute unit instead of the 6 of k_unpack.
+// k_unpack (two launches, or one on small tables) / four / two / one chunks, in us, 1 packet; elements, share
+// of those with 8-bit words, L_T of both:
+//   4 M, 2 %, 64 and 500:    8.6 / 15.1 / 11.2 / 8.3     60 M, 30 %, 64 and 500:    71.5 / 80.7 / 58.1 / 60.7
+//   60 M, 10 %, 64 and 4272: 74.9 / 161 / 88.6 / 65.8    60 M, 85 %, 64 and 4272:   70.5 / 69.6 / 58.7 / 66.0
+//   30 M, 30 %, 50 and 4272: 45.9 / 52.5 / 34.8 / 37.0   12 M, 15 %, 50 and 500:    20.9 / 21.1 / 14.8 / -
+//   60 M, 15 %, 40 and 4272: 78.3 / 86.2 / 63.9 / -      60 M, 60 %, 40 and 500:    86.4 / 60.6 / 60.5 / -
+// Hence: up to L_T 40, where four chunks still leave 4 workgroups, fewer only if 16-bit groups dominate;
+// beyond, two, and from L_T 54 on, where two leave 5, one if the 16-bit groups are many.  The exception:
+// where those are long runs of tiles, 3 workgroups keep the memory busy and four chunks are 3 to 5 % ahead
+// (60 M, 30, 60 and 85 %, 50 and 500: four 60.0, 59.0 and 55.3, two 63.3, 61.6 and 57.0).
+uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners)
+{
+    const uint64_t n8 = n_chunks, n16 = n_groups16;
+    if (n16 == 0u || 4u * 256u * p.short_bin_max <= kUnpackLdsFull) return 2u;
+    if (p.short_bin_max <= 40u) return n16 > 3u * n8 ? 1u : 2u;
+    const uint64_t tiles16 = p.n_utiles - p.n_usingles8;
+    if (p.short_bin_max <= 53u) return n_learners <= 2u && tiles16 >= 3u * n16 && 4u * n16 <= 3u * n8 ? 2u : 1u;
+    return 2u * n16 > n8 ? 0u : 1u;
+}
+
 // ---- optional event timing of the streaming kernel ---------------------------------------------
 // The records are guarded by g_timing_mu; `on` alone is read without it, so that calls pay nothing
 // while timing is off.
@@ -750,30 +799,6 @@ int adacomp_compress_static(const adacomp_layer_t *layers, uint32_t n_layers, co
                             hip_stream);
 }
 
-// Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack (a workgroup)?  A wave
-// adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
-// it: 256 bytes of LDS to each element of L_T and three workgroups to a CU leave 3072 resident up to L_T 53,
-// 2048 beyond.  k_unpack / k_unpack8 in us:
-//   plain sum, L_T 50, 1 packet: 313 chunks 7.3 / 6.2, 1250 10.1 / 7.9, 2500 15.4 / 9.8, 7300 39 / 22;
-//   4 packets, 20 M elements: L_T 16 92 / 30, 32 51 / 27, 40 43 / 28, 50 36 / 28, 56 33 / 28, 64 30.5 / 27.9;
-//   8 packets: 10 M elements, L_T 16 61 / 29, 32 36 / 26, 40 31 / 26.5, but 50 25.6 / 28.2 (3277 chunks) and
-//     64 21.2 / 27.8 (2560), whose chunks are too few; 7300 chunks of L_T 50 57 / 41;
-//   16 packets: with 4.6 words to a bin k_unpack is ahead (1033 / 1039) except at short bins (L_T 20, 8
-//     packets, 100 / 37).
-// With the optimizer a wave also has its tile's weights and moments to carry, with too few loads in flight:
-//   20 M elements, SGD with 4 packets, L_T 16 109 / 77, 32 75 / 84, 50 77 / 93, 64 74 / 86; 48 M elements, SGD
-//   with 8, L_T 16 308 / 203, 32 197 / 202, 50 191 / 223; Adam with 1, L_T 16 117 / 111, 32 99 / 120: k_unpack
-//   above L_T 16.
-static bool unpack8_for(const Plan &p, uint32_t n_chunks, uint32_t n_learners, uint32_t mode)
-{
-    if (mode != 0u) return p.short_bin_max <= 16u && n_learners <= 8u && n_chunks >= 3072u;
-    if (n_learners <= 2u) return true;
-    if (p.short_bin_max <= 32u) return n_chunks >= 3072u;
-    if (n_learners <= 4u) return n_chunks >= 5120u;
-    if (n_learners <= 8u) return p.short_bin_max <= 40u ? n_chunks >= 4096u : p.short_bin_max <= 53u && n_chunks >= 6144u;
-    return false;
-}
-
 static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const void *const *packets,
                          uint32_t n_learners, float *dense_out, float *weights, float *state1, float *state2,
                          const adacomp_optimizer_t *opt, void *workspace, size_t workspace_bytes, void *hip_stream)
@@ -824,12 +849,12 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         a.groups = table;
         a.n_groups = n_all;
         a.n_groups8 = a.first16 = a.chunk_lds = 0u;
-        if (n8 != 0u && unpack8_for(p, n8, now, a.mode)) {
+        if (n8 != 0u && unpack8_for(p, n8, n_all - n8, now, a.mode)) {
             a.groups = reinterpret_cast<const UGroupDev *>(ws + p.ws.ugroups);   // single chunks in either table, here in order
             a.n_groups8 = n8;
             a.n_groups = n_all - n8;
             a.first16 = uint32_t(table - a.groups) + n8;
-            a.chunk_lds = 64u * p.short_bin_max + 2u;
+            a.chunk_lds = 64u * p.short_bin_max + unpack8_wg_log(p, n8, a.n_groups, now);
             if ((rc = launch_unpack(a, 3, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
             if ((rc = launch_unpack(a, n8 ? 1 : 0, hip_stream)) != ADACOMP_OK) return rc;

@@ -78,6 +78,7 @@ static_assert(sizeof(UGroupDev) == 8, "UGroupDev layout");
 constexpr uint32_t kUnpackGroupTiles = 8;   // at most this many tiles per group
 constexpr uint32_t kUnpackMinGroups = 2048;  // groups of more than one tile only while this many workgroups remain (8 per compute unit)
 constexpr uint32_t kUnpackSplitTiles = 2048;  // tables with both word widths and more tiles than this: one launch per width
+constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workgroups on a compute unit
 constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table that go alone (3 per compute unit)
 
 // What k_fused leaves per tile for k_scan and k_place: one 16-byte record, so that a tile makes one
@@ -242,6 +243,7 @@ struct UnpackArgs {
 // 1.5 to 2 % longer (4 M elements, 4 packets 8.85 -> 9.04 us; 20 M, 8 packets 31.5 -> 32.1).
 static_assert(sizeof(UnpackArgs) == 640 && offsetof(UnpackArgs, packets) == 128, "kernel arguments");
 
+uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);
 int launch_fused(const CompressArgs &a, int jcode, void *stream);
 int launch_scan(const CompressArgs &a, void *stream);
 int launch_place(const CompressArgs &a, void *stream);

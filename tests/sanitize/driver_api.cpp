@@ -1,6 +1,7 @@
 // Exercises the host-only parts of libadacomp (table validation, plan and size arithmetic, error
 // paths that return before any HIP call) under AddressSanitizer / UBSan on the host side.
 // Built and run by tests/test_sanitizers.py; no GPU is touched.
+#include <algorithm>
 #include <cstdio>
 #include <cstdint>
 #include <cstdlib>
@@ -230,6 +231,25 @@ int main()
         if (find_plan(a.data(), 2, fake_ws, bytes, 2, found) != ADACOMP_EWORKSPACE) return 28;  // a prefix of the list
         if (adacomp_workspace_release(fake_ws) != ADACOMP_OK) return 29;
         if (find_plan(a.data(), 3, fake_ws, bytes, 2, found) != ADACOMP_EWORKSPACE) return 30;
+    }
+    {   // k_unpack8: a workgroup's LDS is that of its chunks (256 bytes per element of the longest 8-bit bin each), and
+        // the 16-bit groups beside them have the same: where those are many they keep 5 of the 6 workgroups that
+        // k_unpack has on a compute unit (160 KB), and the launch stays inside the 64 KB of a workgroup
+        using namespace adacomp;
+        Plan p;
+        for (uint32_t T = 1; T <= 64; ++T)
+            for (uint32_t n8 : {1u, 17u, 1000u, 20000u})
+                for (uint32_t n16 : {0u, 1u, 60u, 900u, 3500u, 70000u})
+                    for (uint32_t tiles_per_group : {1u, 2u, 4u}) {
+                        p.short_bin_max = T;
+                        p.n_usingles8 = n8;
+                        p.n_utiles = n8 + n16 * tiles_per_group;
+                        const uint32_t log = unpack8_wg_log(p, n8, n16, 1), lds = std::max(24644u, 256u * T << log);
+                        if (log > 2 || lds > 65536 || (n16 == 0 && log != 2)) return 40;
+                        if (n16 > 3 * n8 && 163840 / lds < 5) return 41;
+                        if (T > 40 && n16 > n8 && 163840 / lds < 5) return 42;
+                        if (163840 / lds < 3) { if (T <= 53 || 2 * n16 > n8) return 43; }
+                    }
     }
     if (adacomp_selftest_binindex() != 0) return 9;
     for (int c = 1; c > -9; --c) if (!adacomp_strerror(c)) return 10;

@@ -20,6 +20,11 @@ LAYERS = [("a", 64 * 700 + 13, 1), ("b", 1, 64), ("c", 3 * 64 * 300 + 5, 3), ("d
 TABLES = {
     "small": LAYERS[1:6] + LAYERS[8:],                           # below every threshold: one or two packets only
     "5200_chunks": LAYERS + [("k", 2 * 64 * 3670 + 1, 2)],       # up to 4 packets
+    # 16-bit groups that outnumber the chunks: two chunks to a workgroup (beyond L_T 26), one (beyond 53); an odd
+    # number of chunks, so that the last workgroup is not full
+    "few_chunks_up_to_27": [("a", 27 * 64 * 2 + 5, 27), ("b", 500 * 120 + 3, 500)],
+    "few_chunks_up_to_53": [("a", 53 * 64 * 4 + 30, 53), ("b", 500 * 60 + 3, 500)],
+    "few_chunks_up_to_64": [("a", 64 * 64 * 4 + 63, 64), ("b", 500 * 60 + 3, 500), ("c", 50, 50)],
     "3100_chunks_up_to_32": [l for l in LAYERS if l[2] <= 32 or l[2] > 64] + [("k", 2 * 64 * 1670 + 1, 2), ("l", 32 * 64 * 40 + 3, 32)],   # any number
     "3100_chunks_up_to_16": [l for l in LAYERS if l[2] <= 16 or l[2] > 64] + [("k", 2 * 64 * 1670 + 1, 2), ("l", 16 * 64 * 40 + 3, 16)],   # the optimizer too
 }
@@ -41,7 +46,7 @@ def test_sums(H, oracle_lib, name, dense):
     wl = W.custom(name, TABLES[name], dist="normal")
     table, n = wl.table(), wl.n_total
     chunks = sum(-(-(-(-m // lt)) // 64) for _, m, lt in table if lt <= 64)
-    assert chunks < 3072 if name == "small" else chunks >= (5120 if name == "5200_chunks" else 3072)
+    assert chunks < 3072 if name == "small" or name.startswith("few") else chunks >= (5120 if name == "5200_chunks" else 3072)
     mask = H.layer_mask(table, n)
     counts = (1, 2, 4, 8) if dense else (0, 1, 2, 4, 8, 9, 17, 70)
     gpu = H.GpuSide(table, n, max(counts))
