@@ -129,7 +129,8 @@ size_t adacomp_workspace_bytes_batch(const adacomp_layer_t *layers, uint32_t n_l
  * workspace and layer table, before the first compress / unpack that uses it.  The tables are
  * copied with a blocking host-to-device copy ordered after the work already on `hip_stream`, so
  * this call is not capturable in a HIP graph; compress and unpack only launch kernels.  The
- * caller must leave the workspace contents alone between calls. */
+ * caller must leave the workspace contents alone between calls.  A call captured in a HIP graph belongs
+ * to the initialisation before it: after another one, capture it again. */
 int adacomp_workspace_init(const adacomp_layer_t *layers, uint32_t n_layers, void *workspace,
                            size_t workspace_bytes, void *hip_stream);
 

@@ -280,21 +280,22 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     w.stage = off;       off = pad256(off + 2 * size_t(p.stage_entries) + 128);  // slack: k_place reads up to 64 entries from a tile's start
     w.scratch_stride = off;
     off = 0;             // offsets inside one learner's exchange area
-    w.sync_rec = off;    off = pad256(off + 16 * size_t(p.n_ctiles));
-    w.sync_tile = off;   off = pad256(off + 32 * size_t(p.n_ctiles));
-    w.sync_layer = off;  off = pad256(off + 32 * size_t(n_layers));
-    w.sync_epoch = off;  off = pad256(off + 4 * size_t(p.n_ctiles));
+    w.sync_rec = off;    off += 16 * size_t(p.n_ctiles);
+    w.sync_tile = off;   off += 32 * size_t(p.n_ctiles);
+    w.sync_layer = off;  off += 32 * size_t(n_layers);
+    w.sync_epoch = off;  off = (off + 4 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
     if (off >= (size_t(1) << 32)) return ADACOMP_EINVAL;
     w.sync_stride = off;
     return ADACOMP_OK;
 }
 
-SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes)
+SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes, size_t most_learners)
 {
     SyncPlace at;
-    const size_t end = workspace_bytes & ~size_t(255);
-    if (end <= ws.scratch) return at;
-    at.learners = std::min((end - ws.scratch) / (ws.scratch_stride + ws.sync_stride), kSyncLearnersMax);
+    const size_t end = workspace_bytes & ~size_t(127);
+    if (end < ws.least(1)) return at;
+    const size_t accepted = std::min((end - ws.scratch) / ws.scratch_stride, most_learners);   // by find_plan
+    at.learners = std::min((end - ws.least(accepted)) / ws.sync_stride, size_t(kMaxBatch));
     at.offset = end - at.learners * ws.sync_stride;
     return at;
 }
@@ -474,8 +475,8 @@ int adacomp_workspace_gmax(const adacomp_layer_t *layers, uint32_t n_layers, siz
     return ADACOMP_OK;
 }
 
-int adacomp_workspace_init(const adacomp_layer_t *layers, uint32_t n_layers, void *workspace,
-                           size_t workspace_bytes, void *hip_stream)
+static int init_workspace(const adacomp_layer_t *layers, uint32_t n_layers, void *workspace, size_t workspace_bytes,
+                          size_t most_learners, void *hip_stream)
 {
     if (!workspace) return ADACOMP_EINVAL;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return ADACOMP_EALIGN;
@@ -494,12 +495,18 @@ int adacomp_workspace_init(const adacomp_layer_t *layers, uint32_t n_layers, voi
         hipMemcpy(ws + p.ws.ugroups, p.ugroups.data(), sizeof(UGroupDev) * p.ugroups.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(ws + p.ws.usingles, p.usingles.data(), sizeof(UGroupDev) * p.usingles.size(), hipMemcpyHostToDevice) != hipSuccess)
         return ADACOMP_EHIP;
-    p.sync = sync_place(p.ws, workspace_bytes);
+    p.sync = sync_place(p.ws, workspace_bytes, most_learners);
     if (p.sync.learners != 0 && (hipMemset(ws + p.sync.offset, 0, p.sync.learners * p.ws.sync_stride) != hipSuccess ||
                                  hipStreamSynchronize(nullptr) != hipSuccess))
         return ADACOMP_EHIP;
     register_workspace(layers, n_layers, workspace, workspace_bytes, std::move(reg.plan));
     return ADACOMP_OK;
+}
+
+int adacomp_workspace_init(const adacomp_layer_t *layers, uint32_t n_layers, void *workspace,
+                           size_t workspace_bytes, void *hip_stream)
+{
+    return init_workspace(layers, n_layers, workspace, workspace_bytes, SIZE_MAX, hip_stream);
 }
 
 int adacomp_workspace_release(void *workspace)
@@ -528,7 +535,7 @@ static bool fold_scan_for(const Plan &p)
 // workspace that has exchange areas for all learners of the call.
 static uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes)
 {
-    if (n_learners > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
+    if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
     if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
     if (p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers) return kOneLaunchTable;
     const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
@@ -563,9 +570,6 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_ws.find(workspace);
         if (it == g_ws.end()) return ADACOMP_EWORKSPACE;  // released by another thread meanwhile
-        // more learners than there are exchange areas, in a workspace whose last scratch blocks reach into
-        // those: the areas are lost, and this workspace takes the staged launches from here on
-        if (p.ws.least(n_learners) > p.sync.offset) it->second.plan.sync = p.sync = SyncPlace();
         wait_polls = it->second.wait_polls;
         const std::vector<float *> &waiting = it->second.waiting;
         if (!waiting.empty()) {
@@ -589,6 +593,7 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     a.o_sync_rec = uint32_t(p.ws.sync_rec); a.o_sync_tile = uint32_t(p.ws.sync_tile);
     a.o_sync_layer = uint32_t(p.ws.sync_layer); a.o_sync_epoch = uint32_t(p.ws.sync_epoch);
     a.one_launch = lazy ? kOneLaunchNever : one_launch_for(p, n_learners, workspace_bytes);
+    a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset);   // the launches of a call take turns with the areas
     a.sync_stride = p.ws.sync_stride;
     a.wait_polls = wait_polls;
     a.n_tiles = p.n_ctiles;
@@ -621,7 +626,6 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
         const uint32_t now = std::min(n_learners - done, kMaxBatch);
         a.n_learners = now;
         a.scratch = reinterpret_cast<uint8_t *>(ws + p.ws.scratch + p.ws.scratch_stride * done);
-        a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset + p.ws.sync_stride * done);
         for (uint32_t k = 0; k < kMaxBatch; ++k) {
             a.grad[k] = k < now ? grads[done + k] : nullptr;
             a.residue[k] = k < now ? residues[done + k] : nullptr;
@@ -794,7 +798,7 @@ int adacomp_compress_static(const adacomp_layer_t *layers, uint32_t n_layers, co
     if (rc != ADACOMP_OK) return rc;
     if (p.ws.least(1) > kStaticScratchBytes) return ADACOMP_ETOOBIG;
     if (rc_dev != ADACOMP_OK) return rc_dev;
-    if ((rc = adacomp_workspace_init(layers, n_layers, ws, kStaticScratchBytes, hip_stream)) != ADACOMP_OK) return rc;
+    if ((rc = init_workspace(layers, n_layers, ws, kStaticScratchBytes, 1, hip_stream)) != ADACOMP_OK) return rc;   // one learner: no other call knows this array
     return adacomp_compress(layers, n_layers, grad, residue, packet_out, packet_capacity, ws, kStaticScratchBytes,
                             hip_stream);
 }

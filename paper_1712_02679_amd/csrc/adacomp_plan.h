@@ -18,6 +18,7 @@ constexpr uint32_t kComputeUnits = 256;  // of an MI355X: what a small table's t
 // elements per unpack tile: 16 KB of LDS accumulators (8192 was 10 % faster for the plain sum but
 // 12 % slower with the optimizer epilogue)
 constexpr uint32_t kUnpackTileElems = 4096;
+constexpr uint32_t kMaxBatch = 32;  // learners per launch of the compress kernels
 constexpr uint32_t kLearnerGroup = 16;   // learners whose bin tables sit in LDS together in unpack
 constexpr uint32_t kMaxPacketArgs = 64;  // packet pointers passed by value per unpack launch
 
@@ -101,22 +102,25 @@ struct WorkspaceLayout {
     size_t layer_nsel = 0, layer_scale = 0;             // per layer
     size_t gmax = 0, chunk_rel = 0;                     // per bin / per chunk
     size_t stage = 0;                                   // uint16 per element of the layers (not of the address span): words before placement
-    // The exchange areas of the one-launch compress, one per learner, lie at the end of the workspace
-    // (SyncPlace); offsets inside one.  A workspace without room for them takes the staged launches.
+    // The exchange areas of the one-launch compress, one per learner of a launch, lie at the end of the
+    // workspace (SyncPlace); offsets inside one.  A workspace without room for them takes the staged launches.
     size_t sync_rec = 0, sync_tile = 0, sync_layer = 0, sync_epoch = 0;
     size_t sync_stride = 0;
     size_t least(size_t n_learners) const { return scratch + scratch_stride * n_learners; }   // what a call needs
-    size_t total(size_t n_learners) const { return least(n_learners) + sync_stride * n_learners; }
+    size_t total(size_t n_learners) const { return least(n_learners) + sync_stride * (n_learners < kMaxBatch ? n_learners : kMaxBatch); }
 };
 
-// Where a registered workspace keeps its exchange areas: `learners` of them, as many as fit behind as
-// many scratch blocks.  They are cleared when the workspace is initialised and from then on belong to
-// the kernels.
-constexpr size_t kSyncLearnersMax = 1024;
+// Where a registered workspace keeps its exchange areas: `learners` of them, which a call's launches of up to
+// kMaxBatch learners use one after the other.  They are cleared when the workspace is initialised and from
+// then on belong to the kernels, also to those of captured calls that are replayed any time later: so they
+// begin behind the scratch block of the last learner that any call on this workspace could have.  (In
+// workspace_bytes_batch(n) bytes that is learner n, and there are areas for all: an area takes 52 bytes per
+// compress tile, a scratch block 2 per element.  Only where layers have some tens of elements and areas are
+// as large as blocks does an (n + 1)st learner fit in their place; calls there may be staged.)
 struct SyncPlace {
     size_t offset = 0, learners = 0;
 };
-SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes);
+SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes, size_t most_learners);
 
 struct Plan {
     uint32_t n_layers = 0;
@@ -155,7 +159,6 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
               size_t n_learners, Plan &out);
 
 // ---- kernel launchers (adacomp_kernels.hip) ---------------------------------------------------
-constexpr uint32_t kMaxBatch = 32;  // learners per launch of the compress kernels
 constexpr uint64_t kSplitElems = 32u * 1000u * 1000u;  // gradients at least this long: one k_fused launch per learner
 
 // Dynamic LDS that no kernel touches, asked for with the launches of the eager 256-thread streaming

@@ -128,11 +128,18 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
     if (!(w.sync_rec + 16 * size_t(p.n_ctiles) <= w.sync_tile && w.sync_tile + 32 * size_t(p.n_ctiles) <= w.sync_layer &&
           w.sync_layer + 32 * size_t(p.n_layers) <= w.sync_epoch && w.sync_epoch + 4 * size_t(p.n_ctiles) <= w.sync_stride))
         return 148;
-    for (size_t bytes : {w.least(1), w.total(1) - 1, w.total(1), w.total(3), w.total(5) + 1000}) {
-        const SyncPlace at = sync_place(w, bytes);
-        if (at.learners != (bytes < w.total(1) ? 0u : bytes < w.total(3) ? 1u : bytes < w.total(4) ? 3u : at.learners) || at.learners > 1024) return 149;
-        if (at.learners && (at.offset % 256 || at.offset < w.least(at.learners) || at.offset + at.learners * w.sync_stride > bytes)) return 150;
-    }
+    // no call that the workspace accepts has a scratch block that reaches an area: a captured call may be
+    // replayed after any of them
+    for (size_t n = 1; n <= 70; n += n < 6 ? 1 : 8)
+        for (size_t bytes : {w.least(n), w.least(n) + w.sync_stride - 1, w.total(n) - 1, w.total(n), w.total(n) + 1000, w.least(n + 1) - 1})
+            for (size_t most : {size_t(1), SIZE_MAX}) {
+                const SyncPlace at = sync_place(w, bytes, most);
+                size_t accepted = 0;   // learners of the largest call
+                while (accepted < most && w.least(accepted + 1) <= bytes) ++accepted;
+                if (at.learners > kMaxBatch || (at.learners && (at.offset % 128 || at.offset < w.least(accepted) || at.offset + at.learners * w.sync_stride > bytes))) return 150;
+                if (accepted == n && bytes >= w.total(n) && at.learners < std::min(n, size_t(kMaxBatch))) return 149;
+                if (accepted == n && bytes < w.least(n) + w.sync_stride && at.learners) return 152;
+            }
     for (const TileDev &td : p.ctiles)
         if (td.jcode() == 0 && !td.aligned()) return 151;
     if (w.total(3) != adacomp_workspace_bytes_batch(t.data(), uint32_t(t.size()), 3)) return 143;
@@ -189,6 +196,18 @@ int main()
         if (adacomp_packet_bound(b.data(), n_layers) != 0) return 7;
         if (n_layers > 1) { b = t; b[1].elem_offset = b[0].elem_offset; if (adacomp_packet_bound(b.data(), n_layers) != 0) return 8; }
     }
+    for (uint64_t elems : {1000ull, 5000ull, 397000ull, 2000000ull})
+        for (uint32_t lt : {50u, 500u}) {   // workspace_bytes_batch has areas for all learners of the call, up to a launch's
+            std::vector<adacomp_layer_t> t = {{0, elems, lt, 0}, {(elems + 3) / 4 * 4, elems / 3, 500, 0}};
+            adacomp::Plan p;
+            if (adacomp::build_plan(t.data(), 2, false, p) != ADACOMP_OK) return 12;
+            for (uint32_t n : {1u, 2u, 8u, 16u, 32u, 56u, 57u, 150u, 300u}) {
+                if (elems <= 5000 && n > 8) continue;   // 32 areas would not fit behind a scratch block
+                const size_t bytes = adacomp_workspace_bytes_batch(t.data(), 2, n);
+                if (adacomp::sync_place(p.ws, bytes, SIZE_MAX).learners < std::min(n, adacomp::kMaxBatch)) return 13;
+                if (p.ws.least(n + 1) <= bytes) return 14;
+            }
+        }
     {   // the 125 M-element table of the benchmark: runs of 8 tiles that shorten towards the end
         std::vector<adacomp_layer_t> t(7);
         uint64_t off = 0;

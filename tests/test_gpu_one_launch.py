@@ -76,8 +76,8 @@ def test_one_launch_variants(H, oracle_lib, name, rule, factor):
 
 
 def test_one_launch_beside_staged_calls(H, oracle_lib):
-    """One workspace: one-launch calls, three-launch calls (the tuning knob) and lazy calls in turn, then more
-    learners than the workspace has exchange areas for: the residues go on as if nothing had changed."""
+    """One workspace: one-launch calls, three-launch calls (the tuning knob) and lazy calls in turn: the residues go
+    on as if nothing had changed."""
     import paper_1712_02679_amd as A
     wl = W.custom("turns", TABLES["many_layers"], dist="normal")
     table, n = wl.table(), wl.n_total
@@ -130,6 +130,59 @@ def test_workspace_without_room_for_exchange_areas(H, oracle_lib):
     want = oracle_lib.compress(table, g, R)
     assert np.array_equal(pk[:want.size].cpu().numpy(), want) and np.array_equal(res.cpu().numpy(), R)
     A.adacomp_workspace_release(ws)
+
+
+@pytest.mark.parametrize("name", ["few_layers", "many_layers"])
+@pytest.mark.parametrize("areas", [0, 1, 2])
+def test_more_learners_than_exchange_areas(H, oracle_lib, name, areas):
+    """A workspace that accepts 3 learners and has exchange areas for fewer: a captured call of one learner,
+    replayed after calls of 2 and 3 learners, staged and lazy ones among them (their scratch blocks are the
+    largest that the workspace takes)."""
+    import paper_1712_02679_amd as A
+    wl = W.custom(name, TABLES[name], dist="normal_outliers")
+    table, n = wl.table(), wl.n_total
+    stride = A.adacomp_workspace_gmax(table)[2]
+    area = A.adacomp_workspace_bytes_batch(table, 2) - A.adacomp_workspace_bytes(table) - stride
+    assert 0 < area < stride // 3
+    ws = torch.zeros(A.adacomp_workspace_bytes(table) - area + 2 * stride + areas * area, dtype=torch.uint8, device="cuda:0")
+    A.adacomp_workspace_init(table, ws)
+    bound = A.adacomp_packet_bound(table)
+    R = [np.zeros(n, f32) for _ in range(3)]
+    res = [torch.zeros(n, device="cuda:0") for _ in range(3)]
+    pk = [torch.zeros(bound, dtype=torch.uint8, device="cuda:0") for _ in range(3)]
+    gd = [torch.zeros(n, device="cuda:0") for _ in range(3)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        A.adacomp_compress(table, gd[0], res[0], pk[0], ws)
+    try:
+        for t in range(8):
+            g = [W.gradient(wl, k, t, seed=8) for k in range(3)]
+            for k in range(3):
+                gd[k].copy_(torch.from_numpy(g[k]))
+            live = 1 if t % 2 == 0 else (3, 2, 3, 3)[t // 2]
+            H.say(f"exchange areas {areas}, {name}, call {t} of {live}")
+            if t % 2 == 0:
+                torch.cuda.synchronize()
+                graph.replay()
+            elif t == 5:
+                A.adacomp_compress_batch_lazy(table, gd, res, pk, ws)
+                A.adacomp_residue_sync(ws)
+            else:
+                A.adacomp_compress_batch(table, gd[:live], res[:live], pk[:live], ws)
+            torch.cuda.synchronize()
+            for k in range(live):
+                want = oracle_lib.compress(table, g[k], R[k])
+                assert np.array_equal(pk[k][:want.size].cpu().numpy(), want), (t, k)
+                assert np.array_equal(res[k].cpu().numpy(), R[k]), (t, k)
+    finally:
+        A.adacomp_workspace_release(ws)
+
+
+@pytest.mark.parametrize("n", [33, 40])
+def test_more_learners_than_a_launch(H, oracle_lib, n):
+    """Calls of more than 32 learners take several launches, which use the same exchange areas in turn."""
+    wl = W.custom("few_layers", TABLES["few_layers"][2:6], dist="normal")
+    H.run_parity(oracle_lib, wl, n, 2, seed=12, label=f"one launch: {n} learners", batch=True)
 
 
 @pytest.mark.parametrize("name", ["few_layers", "many_layers"])
