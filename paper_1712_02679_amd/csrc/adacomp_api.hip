@@ -309,7 +309,6 @@ struct Registered {
     size_t bytes = 0;
     std::vector<adacomp_layer_t> table;  // the layer table the tile tables in the workspace were built for
     std::vector<float *> waiting;
-    uint32_t wait_polls = kWaitPolls;
 };
 
 static bool same_table(const std::vector<adacomp_layer_t> &have, const adacomp_layer_t *layers, uint32_t n_layers)
@@ -346,6 +345,7 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     out.has_short_bins = p.has_short_bins; out.has_shifted_tiles = p.has_shifted_tiles;
     out.ws = p.ws;
     out.sync = p.sync;
+    out.wait_polls = p.wait_polls;
     return ADACOMP_OK;
 }
 
@@ -565,12 +565,10 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     // Corrections that wait belong to the residue buffers of the call that left them: a lazy call
     // goes on with exactly those buffers, anything else has to wait for adacomp_residue_sync.
     bool corrections_wait = false;
-    uint32_t wait_polls = kWaitPolls;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_ws.find(workspace);
         if (it == g_ws.end()) return ADACOMP_EWORKSPACE;  // released by another thread meanwhile
-        wait_polls = it->second.wait_polls;
         const std::vector<float *> &waiting = it->second.waiting;
         if (!waiting.empty()) {
             if (!lazy || waiting.size() != n_learners) return ADACOMP_EPENDING;
@@ -595,7 +593,7 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     a.one_launch = lazy ? kOneLaunchNever : one_launch_for(p, n_learners, workspace_bytes);
     a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset);   // the launches of a call take turns with the areas
     a.sync_stride = p.ws.sync_stride;
-    a.wait_polls = wait_polls;
+    a.wait_polls = p.wait_polls;
     a.n_tiles = p.n_ctiles;
     a.n_layers = p.n_layers;
     a.keep_gmax = g_keep_gmax.load(std::memory_order_relaxed) ? 1u : 0u;
@@ -971,7 +969,7 @@ int adacomp_debug_wait_polls(void *workspace, uint32_t polls)
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_ws.find(workspace);
     if (it == g_ws.end()) return ADACOMP_EWORKSPACE;
-    it->second.wait_polls = polls;
+    it->second.plan.wait_polls = std::min(polls, kWaitPollsMax);   // every wait ends
     return ADACOMP_OK;
 }
 

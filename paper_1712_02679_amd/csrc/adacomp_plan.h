@@ -122,6 +122,9 @@ struct SyncPlace {
 };
 SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes, size_t most_learners);
 
+constexpr uint32_t kWaitPolls = 4096;        // polls (a microsecond or so each) before a workgroup works out what it waits for
+constexpr uint32_t kWaitPollsMax = 1u << 16;   // of adacomp_debug_wait_polls
+
 struct Plan {
     uint32_t n_layers = 0;
     uint32_t n_ctiles = 0, n_utiles = 0, n_ugroups = 0;
@@ -141,6 +144,7 @@ struct Plan {
     bool has_shifted_tiles = false;  // some tile of the larger class has skip != 0
     WorkspaceLayout ws;
     SyncPlace sync;   // of a registered workspace
+    uint32_t wait_polls = kWaitPolls;
     std::vector<LayerDev> layers;
     std::vector<TileDev> ctiles;
     std::vector<UTileDev> utiles;
@@ -186,7 +190,6 @@ constexpr uint32_t kOneLaunchTiles = 1024;
 constexpr uint32_t kOneLaunchTilesLong = 512;
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
-constexpr uint32_t kWaitPolls = 4096;        // polls (a microsecond or so each) before a workgroup works out what it waits for
 
 struct CompressArgs {
     const TileDev *tiles;

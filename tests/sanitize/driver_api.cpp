@@ -248,6 +248,12 @@ int main()
                     return 27;
             }
         if (find_plan(a.data(), 2, fake_ws, bytes, 2, found) != ADACOMP_EWORKSPACE) return 28;  // a prefix of the list
+        // polls before a waiting workgroup helps itself: whatever is asked for, the wait ends
+        for (uint32_t polls : {0u, 7u, kWaitPollsMax, kWaitPollsMax + 1u, 0xFFFFFFFFu}) {
+            if (adacomp_debug_wait_polls(fake_ws, polls) != ADACOMP_OK || find_plan(a.data(), 3, fake_ws, bytes, 2, found) != ADACOMP_OK) return 31;
+            if (found.wait_polls != std::min(polls, kWaitPollsMax)) return 32;
+        }
+        if (adacomp_debug_wait_polls(fake_ws + 16, 1) != ADACOMP_EWORKSPACE) return 33;
         if (adacomp_workspace_release(fake_ws) != ADACOMP_OK) return 29;
         if (find_plan(a.data(), 3, fake_ws, bytes, 2, found) != ADACOMP_EWORKSPACE) return 30;
     }
