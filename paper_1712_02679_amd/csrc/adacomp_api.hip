@@ -1,5 +1,6 @@
 // adacomp_api.hip -- the C ABI of libadacomp: argument checks, the plan (tile tables and
 // workspace layout) and the launch sequences.  No arithmetic of the method lives here.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -416,6 +417,19 @@ uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, u
     return 2u * n16 > n8 ? 0u : 1u;
 }
 
+// One launch for everything, where the tiles of each layer are on the GPU together (see k_pack): tables of
+// the 4096-element tile class (whose tiles are 16-byte aligned), with bins of at least four elements, in a
+// workspace that has exchange areas for all learners of a launch.  compute_units: what the stream may use.
+uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units)
+{
+    if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
+    if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
+    const uint32_t room = kOneLaunchTilesPerUnit * compute_units;
+    if (p.n_ctiles <= std::min(kFoldTiles, room) && p.n_layers <= kFoldLayers) return kOneLaunchTable;
+    const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
+    return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
+}
+
 // ---- optional event timing of the streaming kernel ---------------------------------------------
 // The records are guarded by g_timing_mu; `on` alone is read without it, so that calls pay nothing
 // while timing is off.
@@ -530,16 +544,17 @@ static bool fold_scan_for(const Plan &p)
     return g_fold_scan.load(std::memory_order_relaxed) && place_lanes_for(p) == 64u && p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;
 }
 
-// One launch for everything, where the tiles of each layer are on the GPU together (see k_pack): tables of
-// the 4096-element tile class (whose tiles are 16-byte aligned), with bins of at least four elements, in a
-// workspace that has exchange areas for all learners of the call.
-static uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes)
+// Compute units that work on this stream can get: those of its mask (hipExtStreamCreateWithCUMask; without
+// one, and on the GPU's partitions, all there are).  Asked for at every call, 0.2 us: a stream may be
+// destroyed and another one get its handle.
+static uint32_t compute_units_of(hipStream_t s)
 {
-    if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
-    if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
-    if (p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers) return kOneLaunchTable;
-    const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
-    return (p.layer_tiles_max <= most && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
+    uint32_t mask[32] = {0};
+    // (the runtime has no mask for the handle that stands for the null stream)
+    if (hipExtStreamGetCUMask(s == hipStreamLegacy ? nullptr : s, 32, mask) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    uint32_t n = 0;
+    for (uint32_t m : mask) n += uint32_t(__builtin_popcount(m));
+    return n;
 }
 
 static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uint32_t n_learners,
@@ -579,6 +594,7 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     }
 
     char *ws = static_cast<char *>(workspace);
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
     CompressArgs a;
     a.lazy = corrections_wait ? 1u : 0u;
     a.place_mode = lazy ? kPlaceWords : kPlaceEager;
@@ -590,7 +606,8 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     a.o_chunk_rel = uint32_t(p.ws.chunk_rel); a.o_stage = p.ws.stage;
     a.o_sync_rec = uint32_t(p.ws.sync_rec); a.o_sync_tile = uint32_t(p.ws.sync_tile);
     a.o_sync_layer = uint32_t(p.ws.sync_layer); a.o_sync_epoch = uint32_t(p.ws.sync_epoch);
-    a.one_launch = lazy ? kOneLaunchNever : one_launch_for(p, n_learners, workspace_bytes);
+    a.one_launch = lazy ? kOneLaunchNever : one_launch_for(p, n_learners, workspace_bytes, kComputeUnits);
+    if (a.one_launch != kOneLaunchNever) a.one_launch = one_launch_for(p, n_learners, workspace_bytes, compute_units_of(s));
     a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset);   // the launches of a call take turns with the areas
     a.sync_stride = p.ws.sync_stride;
     a.wait_polls = p.wait_polls;
@@ -609,7 +626,6 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     a.capacity = packet_capacity;
     a.fixed_bytes = p.fixed_bytes;
 
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
     // The streaming kernel runs a few percent faster per byte in launches of one learner than in one
     // launch over 16 learners of the 125 M-element workload (240 vs 246 us per learner), so large
     // gradients get one k_fused launch per learner and small ones share a launch; the scan and

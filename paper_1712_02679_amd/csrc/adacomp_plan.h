@@ -188,6 +188,11 @@ constexpr uint32_t kOneLaunchNever = 0, kOneLaunchTable = 1, kOneLaunchLayers = 
 // holds for tables without short bins in calls of several learners (525 tiles: 75.0 / 75.2).
 constexpr uint32_t kOneLaunchTiles = 1024;
 constexpr uint32_t kOneLaunchTilesLong = 512;
+// ... and per compute unit that the stream may use, half of what is resident there: workgroups of a layer that
+// does not fit wait for others that cannot start until they work those out themselves.  Streams masked to 64 and
+// 32 units, one launch (before there was this line) / three, in us: ResNet-50's table (layers of up to 583
+// tiles) 21400 / 243 and 62000 / 450, the character LSTM's 2060 / 43 and 11300 / 66.
+constexpr uint32_t kOneLaunchTilesPerUnit = 4;
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
 
@@ -249,6 +254,7 @@ struct UnpackArgs {
 // 1.5 to 2 % longer (4 M elements, 4 packets 8.85 -> 9.04 us; 20 M, 8 packets 31.5 -> 32.1).
 static_assert(sizeof(UnpackArgs) == 640 && offsetof(UnpackArgs, packets) == 128, "kernel arguments");
 
+uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units);
 uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);
 int launch_fused(const CompressArgs &a, int jcode, void *stream);
 int launch_scan(const CompressArgs &a, void *stream);

@@ -257,6 +257,26 @@ int main()
         if (adacomp_workspace_release(fake_ws) != ADACOMP_OK) return 29;
         if (find_plan(a.data(), 3, fake_ws, bytes, 2, found) != ADACOMP_EWORKSPACE) return 30;
     }
+    {   // one launch only where half of the workgroups that are resident on the stream's compute units (8 on each)
+        // hold the tiles that wait for each other: one layer, L_T 500, tiles of 4000 elements
+        using namespace adacomp;
+        auto route = [](uint32_t tiles, uint32_t layers, uint32_t lt, size_t learners, uint32_t units) {
+            std::vector<adacomp_layer_t> t(layers);
+            for (uint32_t l = 0; l < layers; ++l) t[l] = adacomp_layer_t{uint64_t(l) * 4000 * tiles, 4000ull * tiles, lt, 0};
+            Plan p;
+            if (build_plan(t.data(), layers, false, p) != ADACOMP_OK) return 99u;
+            if (tiles >= 256 && p.layer_tiles_max != tiles) return 98u;
+            p.sync = sync_place(p.ws, p.ws.total(learners), SIZE_MAX);
+            return one_launch_for(p, learners, p.ws.total(learners), units);
+        };
+        if (route(1024, 1, 500, 1, 256) != kOneLaunchLayers || route(1025, 1, 500, 1, 256) != kOneLaunchNever) return 50;
+        if (route(512, 2, 500, 8, 256) != kOneLaunchLayers || route(513, 2, 500, 8, 256) != kOneLaunchNever) return 51;
+        if (route(512, 1, 500, 1, 128) != kOneLaunchTable || route(513, 1, 500, 1, 128) != kOneLaunchNever) return 52;
+        if (route(512, 4, 500, 1, 128) != kOneLaunchLayers || route(513, 4, 50, 4, 128) != kOneLaunchNever) return 53;
+        if (route(256, 9, 50, 2, 64) != kOneLaunchLayers || route(257, 9, 50, 2, 64) != kOneLaunchNever) return 54;
+        if (route(1024, 1, 50, 1, 32) != kOneLaunchNever || route(300, 2, 500, 1, 32) != kOneLaunchNever) return 55;
+        if (route(300, 2, 500, 1, 0) != kOneLaunchNever) return 56;   // the runtime did not say
+    }
     {   // k_unpack8: a workgroup's LDS is that of its chunks (256 bytes per element of the longest 8-bit bin each), and
         // the 16-bit groups beside them have the same: where those are many they keep 5 of the 6 workgroups that
         // k_unpack has on a compute unit (160 KB), and the launch stays inside the 64 KB of a workgroup

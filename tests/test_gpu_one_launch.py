@@ -185,6 +185,27 @@ def test_more_learners_than_a_launch(H, oracle_lib, n):
     H.run_parity(oracle_lib, wl, n, 2, seed=12, label=f"one launch: {n} learners", batch=True)
 
 
+def _masked_stream(units):
+    """A stream that may use the first `units` compute units only."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    words = (ctypes.c_uint32 * 8)(*[((1 << 32) - 1 if 32 * (i + 1) <= units else 0) for i in range(8)])
+    stream = ctypes.c_void_p()
+    rc = hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, words)
+    assert rc == 0, rc
+    return torch.cuda.ExternalStream(stream.value)
+
+
+@pytest.mark.parametrize("name", ["many_layers", "one_long_layer"])
+@pytest.mark.parametrize("units", [32, 64])
+def test_stream_with_few_compute_units(H, oracle_lib, name, units):
+    """A table whose tiles do not fit the compute units of the stream takes the staged launches there."""
+    wl = W.custom(name, TABLES[name], dist="normal")
+    with torch.cuda.stream(_masked_stream(units)):
+        H.run_parity(oracle_lib, wl, 2, 2, seed=14, label=f"one launch: {name} on {units} compute units", batch=True)
+        torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("name", ["few_layers", "many_layers"])
 def test_one_launch_in_a_graph(H, oracle_lib, name):
     """Captured and replayed five times with eager calls in between: every replay counts on."""
