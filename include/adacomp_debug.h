@@ -29,7 +29,7 @@ int adacomp_workspace_gmax(const adacomp_layer_t *layers, uint32_t n_layers, siz
 
 /* Tables whose layers are small are compressed in one launch, whose workgroups wait for each other's
  * sums.  A workgroup polls this often for one that is missing before it works it out itself (by
- * default about 4000 times, some milliseconds).  0 makes every workgroup do so at once: for tests of
+ * default 256 times, about 0.1 ms).  0 makes every workgroup do so at once: for tests of
  * that path.  Results do not depend on it.  At most 65536: more is
  * taken as that.  Per workspace; ADACOMP_EWORKSPACE if it is not registered. */
 int adacomp_debug_wait_polls(void *workspace, uint32_t polls);

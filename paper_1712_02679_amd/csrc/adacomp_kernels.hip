@@ -562,6 +562,7 @@ struct OneShared {
     uint32_t w[16];
     double d[16];
     uint32_t any[3][16];
+    uint64_t miss[kOneLaunchTiles / 64u];   // bit t: tile t of a layer, or layer t, is not there yet
     uint32_t missing, base, at, bytes;
     float scale;
 };
@@ -694,6 +695,63 @@ __device__ __forceinline__ bool poll_records(const SyncArea &sy, const uint32_t 
     return all;
 }
 
+// Sees to it that the records of tiles ts .. ts + nt - 1 are there, by the whole workgroup: as long as some are
+// missing, works out one of them.  Workgroups that wait in vain do this together, each with its own `seed`, and
+// so come upon different ones: those that cannot start are worked out about as fast as if they ran.  (Every
+// round adds a record or finds that somebody else did; false after more rounds than there are tiles: another
+// call is at work in the same area.)
+template <uint32_t WG, uint32_t HOLD, bool VARIANT>
+__device__ __forceinline__ bool help_records(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t ts, const uint32_t nt,
+                                             const uint32_t epoch, uint32_t seed, uint32_t *s_gmax, OneShared &sh)
+{
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t round = 0; round <= nt; ++round) {
+        __syncthreads();   // nobody reads sh.miss any more
+        for (uint32_t h = 0; h < HOLD; ++h) {
+            const uint32_t i = h * WG + tid;
+            const uint64_t *src = sy.rec + 2u * (ts + i);
+            const bool miss = i < nt && !rec_valid(sync_load(src), sync_load(src + 1), epoch);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(miss);
+            if ((tid & 63u) == 0u) sh.miss[i >> 6] = m;
+        }
+        __syncthreads();
+        uint32_t n_miss = 0u;
+        for (uint32_t w = 0; w < HOLD * WG / 64u; ++w) n_miss += uint32_t(__popcll(sh.miss[w]));
+        if (__builtin_amdgcn_readfirstlane(n_miss) == 0u) return true;
+        seed = (seed ^ (seed >> 15)) * 0x2C1B3C6Du + 0x9E3779B9u;
+        uint32_t k = __umulhi(seed, n_miss), q = 0u;   // the k-th of them
+        for (uint32_t w = 0; w < HOLD * WG / 64u; ++w) {
+            uint64_t m = sh.miss[w];
+            const uint32_t c = uint32_t(__popcll(m));
+            if (k < c) {
+                for (; k != 0u; --k) m &= m - 1u;
+                q = 64u * w + uint32_t(__builtin_ctzll(m));
+                break;
+            }
+            k -= c;
+        }
+        help_tile<WG, VARIANT>(a, sy, lr, ts + __builtin_amdgcn_readfirstlane(q), epoch, s_gmax, sh);
+    }
+    return false;
+}
+
+// The first layer below l that has not published its words' size; l if all have.  By the whole workgroup.
+template <uint32_t WG>
+__device__ __forceinline__ uint32_t first_open_layer(const SyncArea &sy, const uint32_t l, const uint32_t epoch, OneShared &sh)
+{
+    const uint32_t tid = threadIdx.x;
+    __syncthreads();   // nobody reads sh.miss any more
+    for (uint32_t m = tid; m < kOneLaunchLayersMax; m += WG) {
+        const uint64_t open = __builtin_amdgcn_ballot_w64(m < l && uint32_t(sync_load(sy.layer + 4u * m + 1u)) != epoch);
+        if ((tid & 63u) == 0u) sh.miss[m >> 6] = open;
+    }
+    __syncthreads();
+    uint32_t first = l;
+    for (uint32_t w = kOneLaunchLayersMax / 64u; w-- > 0u;)
+        if (sh.miss[w] != 0ull) first = 64u * w + uint32_t(__builtin_ctzll(sh.miss[w]));
+    return __builtin_amdgcn_readfirstlane(first);
+}
+
 // before[h]: words of the tiles before the thread's h-th; adds the thread's g_max sums to `part`; returns
 // the words of all tiles.  Begins behind a barrier (sh.w is free) and ends with one.
 template <uint32_t WG, uint32_t HOLD>
@@ -743,21 +801,18 @@ __device__ __forceinline__ uint32_t poll_layer_words(const SyncArea &sy, const u
 }
 
 // Adds up the records of layer l and publishes what its tiles (and the layers behind it) wait for.  Says
-// whether everything came in time; HELP: works out the records that did not.
+// whether everything came in time; HELP: does not wait for records, but works out those that are missing.
 template <uint32_t WG, bool VARIANT, bool HELP>
 __device__ __forceinline__ bool complete_layer(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t l,
-                                               const uint32_t epoch, uint32_t *s_gmax, OneShared &sh)
+                                               const uint32_t epoch, const uint32_t seed, uint32_t *s_gmax, OneShared &sh)
 {
     constexpr uint32_t HOLD = (kOneLaunchTiles + WG - 1u) / WG;
-    const uint32_t most_polls = HELP ? kWaitPolls : a.wait_polls;   // (with help everything comes)
+    const uint32_t most_polls = HELP ? kWaitPollsKnown : a.wait_polls;   // (the layers before: HELP comes when those are there)
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t ts = a.layers[l].ctile_start, nt = a.layers[l].n_ctiles, wbytes = a.layers[l].word_bytes;
     Records<HOLD> rec;
-    if (block_any<WG>(!poll_records<WG>(sy, ts, nt, epoch, a.wait_polls, rec), sh.any[0])) {
-        if (!HELP) return false;
-        for (uint32_t q = 0; q < nt; ++q) help_tile<WG, VARIANT>(a, sy, lr, ts + q, epoch, s_gmax, sh);
-        poll_records<WG>(sy, ts, nt, epoch, most_polls, rec);   // published now, by whomever
-    }
+    if (HELP && !help_records<WG, HOLD, VARIANT>(a, sy, lr, ts, nt, epoch, seed, s_gmax, sh)) return false;
+    if (block_any<WG>(!poll_records<WG>(sy, ts, nt, epoch, HELP ? 0u : a.wait_polls, rec), sh.any[0])) return false;
     uint32_t before[HOLD];
     double part = 0.0;
     const uint32_t words = scan_records<WG>(nt, rec, sh, before, part);
@@ -1038,8 +1093,8 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         constexpr uint32_t HOLD = kFoldTiles / kWG;
         Records<HOLD> rec;
         if (block_any<kWG>(!poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec), sh.any[0])) {
-            for (uint32_t q = 0; q < a.n_tiles; ++q) help_tile<kWG, VARIANT>(a, sy, lr, q, epoch, s_gmax, sh);
-            poll_records<kWG>(sy, 0u, a.n_tiles, epoch, kWaitPolls, rec);   // published now, by whomever
+            const bool there = help_records<kWG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, tile, s_gmax, sh);
+            if (block_any<kWG>(!(there && poll_records<kWG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return;   // nothing to go by: store nothing
             take_again();
         }
         uint32_t excl[HOLD];
@@ -1078,11 +1133,15 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
             return ok;
         };
         bool ok = true;
-        if (tile == ld.ctile_start + ld.n_ctiles - 1u) ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, s_gmax, sh);
+        if (tile == ld.ctile_start + ld.n_ctiles - 1u) ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
         if (block_any<kWG>(!poll_tile(ok, a.wait_polls), sh.any[2])) {
-            for (uint32_t m = 0; m <= l; ++m) complete_layer<kWG, VARIANT, true>(a, sy, lr, m, epoch, s_gmax, sh);
-            __syncthreads();
-            poll_tile(true, kWaitPolls);   // all there now
+            ok = true;
+            for (uint32_t times = 0; ok; ++times) {   // the layers before this one that are not done, and this one
+                const uint32_t m = first_open_layer<kWG>(sy, l, epoch, sh);
+                ok = times <= l && complete_layer<kWG, VARIANT, true>(a, sy, lr, m, epoch, tile, s_gmax, sh);
+                if (m == l) break;
+            }
+            if (block_any<kWG>(!poll_tile(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
             take_again();
             __syncthreads();
         }

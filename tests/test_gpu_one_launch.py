@@ -1,5 +1,7 @@
 """The one-launch compress (k_pack) on tables that reach both of its forms, with and without the wait for
 other workgroups succeeding, against the CPU oracle bit for bit.  Needs an MI355X."""
+import contextlib
+
 import numpy as np
 import pytest
 
@@ -54,7 +56,7 @@ class _Impatient:
 
 
 @pytest.mark.parametrize("name,batch,impatient", [(n, b, False) for n in sorted(TABLES) for b in (False, True)] +
-                         [(n, b, True) for n in ("few_layers", "many_layers", "one_tile") for b in (False, True)])
+                         [(n, b, True) for n in sorted(TABLES) for b in (False, True)])
 def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
     wl = W.custom(name, TABLES[name], dist="normal_outliers")
     say = f"one launch: {name}, batch {batch}, impatient {impatient}"
@@ -66,13 +68,15 @@ def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
 
 
 @pytest.mark.parametrize("rule,factor", [(1, 2.0), (2, 2.0), (0, 1.5)])
-@pytest.mark.parametrize("name", ["few_layers", "many_layers"])
-def test_one_launch_variants(H, oracle_lib, name, rule, factor):
+@pytest.mark.parametrize("name,impatient", [("few_layers", False), ("many_layers", False), ("few_layers", True), ("many_layers", True)])
+def test_one_launch_variants(H, oracle_lib, name, impatient, rule, factor):
     """The other rules, with gradients that hold zeros and all-zero bins (the printed compare sends those, but
     nothing that lies past a tile)."""
     wl = W.custom(name, TABLES[name], dist="normal")
     zeros = lambda k, t: (W.gradient(wl, k, t, seed=5) * ((np.arange(wl.n_total) // 97 + k) % 3 != 0)).astype(f32)
-    H.run_parity(oracle_lib, wl, 2, 3, grads=zeros, rule=rule, soft_factor=factor, label=f"one launch: {name} rule {rule}", batch=True)
+    with _Impatient(H) if impatient else contextlib.nullcontext():
+        H.run_parity(oracle_lib, wl, 2, 3, grads=zeros, rule=rule, soft_factor=factor, label=f"one launch: {name} rule {rule}, impatient {impatient}",
+                     batch=True)
 
 
 def test_one_launch_beside_staged_calls(H, oracle_lib):
@@ -194,6 +198,38 @@ def _masked_stream(units):
     rc = hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, words)
     assert rc == 0, rc
     return torch.cuda.ExternalStream(stream.value)
+
+
+@pytest.mark.parametrize("name", ["few_layers", "one_long_layer", "two_long_layers_short_bins"])
+@pytest.mark.parametrize("units", [32, 64])
+def test_captured_call_replayed_on_few_compute_units(H, oracle_lib, name, units):
+    """Captured where the whole GPU was there, replayed on a stream where the tiles of a layer do not fit: the
+    workgroups that run work out the records of those that cannot start."""
+    import paper_1712_02679_amd as A
+    wl = W.custom(name, TABLES[name], dist="normal_outliers")
+    table, n = wl.table(), wl.n_total
+    ws = torch.zeros(A.adacomp_workspace_bytes(table), dtype=torch.uint8, device="cuda:0")
+    A.adacomp_workspace_init(table, ws)
+    pk = torch.zeros(A.adacomp_packet_bound(table), dtype=torch.uint8, device="cuda:0")
+    res, gd, R = torch.zeros(n, device="cuda:0"), torch.zeros(n, device="cuda:0"), np.zeros(n, f32)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        A.adacomp_compress(table, gd, res, pk, ws)
+    masked = _masked_stream(units)
+    try:
+        for t in range(4):
+            H.say(f"one launch: {name} replayed on {units} compute units, step {t}")
+            g = W.gradient(wl, 0, t, seed=15)
+            gd.copy_(torch.from_numpy(g))
+            torch.cuda.synchronize()
+            with torch.cuda.stream(masked if t != 2 else torch.cuda.current_stream()):
+                graph.replay()
+            torch.cuda.synchronize()
+            want = oracle_lib.compress(table, g, R)
+            assert np.array_equal(pk[:want.size].cpu().numpy(), want), t
+            assert np.array_equal(res.cpu().numpy(), R), t
+    finally:
+        A.adacomp_workspace_release(ws)
 
 
 @pytest.mark.parametrize("name", ["many_layers", "one_long_layer"])
