@@ -1092,7 +1092,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         if (lane < a.n_layers) { l_ts = a.layers[lane].ctile_start; l_nt = a.layers[lane].n_ctiles; l_wb = a.layers[lane].word_bytes; }
         constexpr uint32_t HOLD = kFoldTiles / kWG;
         Records<HOLD> rec;
-        if (block_any<kWG>(!poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec), sh.any[0])) {
+        if (__builtin_expect(block_any<kWG>(!poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec), sh.any[0]), false)) {
             const bool there = help_records<kWG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, tile, s_gmax, sh);
             if (block_any<kWG>(!(there && poll_records<kWG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return;   // nothing to go by: store nothing
             take_again();
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         };
         bool ok = true;
         if (tile == ld.ctile_start + ld.n_ctiles - 1u) ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
-        if (block_any<kWG>(!poll_tile(ok, a.wait_polls), sh.any[2])) {
+        if (__builtin_expect(block_any<kWG>(!poll_tile(ok, a.wait_polls), sh.any[2]), false)) {
             ok = true;
             for (uint32_t times = 0; ok; ++times) {   // the layers before this one that are not done, and this one
                 const uint32_t m = first_open_layer<kWG>(sy, l, epoch, sh);
