@@ -505,7 +505,7 @@ __device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *con
 //               the size of the layer's words and every tile's first word; the others wait for those.
 //
 // Published words carry their own validity: every 8-byte word holds 32 bits of value and, in the rest,
-// the number of the call (the tile's epoch, kept in the scratch block and raised by one by the tile's
+// the number of the call (the tile's epoch, kept in the exchange area and raised by one by the tile's
 // workgroup in every call), and is read and written with relaxed device-scope atomics.  No fence (a
 // device-scope release writes back the L2), no counter, nothing to clear between calls, and a call
 // replayed from a graph counts on like any other.
@@ -553,7 +553,7 @@ struct SyncArea {
     uint64_t *rec;     // 2 per tile: high half of the tile's g_max sum | epoch; low half | word count, epoch
     uint64_t *tile;    // 4 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch; unused
     uint64_t *layer;   // 4 per layer: scale | epoch; padded bytes of its words | epoch; its words | epoch; unused
-    uint32_t *epoch;   // per tile: number of the last call, written by the tile's own workgroup only
+    uint32_t *epoch;   // per tile: number of calls so far, counted up by the tile's own workgroup
 };
 
 // LDS of a workgroup that waits
@@ -905,7 +905,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         sy.layer = reinterpret_cast<uint64_t *>(area + a.o_sync_layer);
         sy.epoch = reinterpret_cast<uint32_t *>(area + a.o_sync_epoch);
     }
-    const uint32_t epoch = sy.epoch[tile] + 1u;
+    const uint32_t epoch = sy.epoch[tile] + 1u;   // (count_call)
 
     __shared__ uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kMaxTileBins + 4u];
@@ -1021,7 +1021,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     if (tid == 0) {   // first thing: others wait for it
         sync_store(sy.rec + 2u * tile, rec_high(gmax_sum, epoch));
         sync_store(sy.rec + 2u * tile + 1u, rec_low(gmax_sum, tile_total, epoch));
-        sy.epoch[tile] = epoch;
+        count_call(sy.epoch + tile);
     }
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(0);
 

@@ -122,6 +122,19 @@ struct SyncPlace {
 };
 SyncPlace sync_place(const WorkspaceLayout &ws, size_t workspace_bytes, size_t most_learners);
 
+// A tile's workgroup of a one-launch call takes the count of the calls before it, plus one, as its epoch and
+// counts itself at the end of its exchange, wherever it stands then.  Stored instead, the epoch would fall
+// behind that of other tiles for good when two calls overlap on one workspace (which is refused by contract, and
+// spoils both): every later call would wait in vain.
+__host__ __device__ inline void count_call(uint32_t *calls)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    (void)__hip_atomic_fetch_add(calls, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#else
+    (void)__atomic_fetch_add(calls, 1u, __ATOMIC_RELAXED);
+#endif
+}
+
 // Polls (0.4 us each) before a workgroup works out what it waits for; in a call that has the GPU for itself waits
 // are 10 to 20 us long.  Captured on the whole GPU, replayed on 64 / 32 compute units, in us, by 64, 256 and 4096
 // polls: ResNet-50's table 820, 1060, 7700 / 1430, 2090, 15400; one layer of 1000 tiles 196, 263, 1590 / 275, 346, 1680.

@@ -277,6 +277,15 @@ int main()
         if (route(1024, 1, 50, 1, 32) != kOneLaunchNever || route(300, 2, 500, 1, 32) != kOneLaunchNever) return 55;
         if (route(300, 2, 500, 1, 0) != kOneLaunchNever) return 56;   // the runtime did not say
     }
+    {   // the epochs of an exchange area after two calls that overlapped (both refused results, nothing else): in
+        // whatever order the calls read and count, each tile has counted two, and the next call's tiles agree
+        uint32_t calls[3] = {7, 7, 7}, a[3], b[3];
+        a[0] = calls[0] + 1; adacomp::count_call(calls + 0); b[0] = calls[0] + 1; adacomp::count_call(calls + 0);   // one after the other
+        a[1] = calls[1] + 1; b[1] = calls[1] + 1; adacomp::count_call(calls + 1); adacomp::count_call(calls + 1);   // both read first
+        b[2] = calls[2] + 1; a[2] = calls[2] + 1; adacomp::count_call(calls + 2); adacomp::count_call(calls + 2);
+        for (int t = 0; t < 3; ++t)
+            if (calls[t] != 9 || a[t] > 9 || b[t] > 9) return 57;
+    }
     {   // k_unpack8: a workgroup's LDS is that of its chunks (256 bytes per element of the longest 8-bit bin each), and
         // the 16-bit groups beside them have the same: where those are many they keep 5 of the 6 workgroups that
         // k_unpack has on a compute unit (160 KB), and the launch stays inside the 64 KB of a workgroup
