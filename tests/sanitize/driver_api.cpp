@@ -276,6 +276,12 @@ int main()
         if (route(256, 9, 50, 2, 64) != kOneLaunchLayers || route(257, 9, 50, 2, 64) != kOneLaunchNever) return 54;
         if (route(1024, 1, 50, 1, 32) != kOneLaunchNever || route(300, 2, 500, 1, 32) != kOneLaunchNever) return 55;
         if (route(300, 2, 500, 1, 0) != kOneLaunchNever) return 56;   // the runtime did not say
+        // more workgroups than are resident: not the form that reads all records, and none with small tiles
+        if (route(256, 2, 500, 4, 256) != kOneLaunchTable || route(256, 2, 500, 5, 256) != kOneLaunchLayers) return 58;
+        if (route(512, 1, 500, 4, 256) != kOneLaunchTable || route(512, 1, 50, 40, 256) != kOneLaunchLayers) return 59;
+        if (route(60, 1, 500, 8, 256) != kOneLaunchTable || route(60, 1, 500, 9, 256) != kOneLaunchNever) return 60;   // 240,000 elements: 240 tiles of 1000
+        if (route(120, 1, 50, 7, 256) != kOneLaunchTable || route(120, 1, 50, 8, 256) != kOneLaunchLayers) return 61;    // 267 tiles of 1800
+        if (route(120, 1, 500, 6, 256) != kOneLaunchTable || route(120, 1, 500, 7, 256) != kOneLaunchNever) return 62;   // 320 of 1500
     }
     {   // the epochs of an exchange area after two calls that overlapped (both refused results, nothing else): in
         // whatever order the calls read and count, each tile has counted two, and the next call's tiles agree

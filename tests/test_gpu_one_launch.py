@@ -182,6 +182,12 @@ def test_more_learners_than_exchange_areas(H, oracle_lib, name, areas):
         A.adacomp_workspace_release(ws)
 
 
+def test_more_workgroups_than_are_resident(H, oracle_lib):
+    """A table that every workgroup could read as a whole, with so many learners that a workgroup per layer does."""
+    wl = W.custom("crowd", [("a", 600 * 1000 + 3, 50), ("b", 55 * 1000 + 9, 500)], dist="normal")
+    H.run_parity(oracle_lib, wl, 9, 2, seed=13, label="one launch: 9 learners", batch=True)
+
+
 @pytest.mark.parametrize("n", [33, 40])
 def test_more_learners_than_a_launch(H, oracle_lib, n):
     """Calls of more than 32 learners take several launches, which use the same exchange areas in turn."""
