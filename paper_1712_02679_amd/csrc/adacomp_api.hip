@@ -282,8 +282,8 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     w.scratch_stride = off;
     off = 0;             // offsets inside one learner's exchange area
     w.sync_rec = off;    off += 16 * size_t(p.n_ctiles);
-    w.sync_tile = off;   off += 32 * size_t(p.n_ctiles);
-    w.sync_layer = off;  off += 32 * size_t(n_layers);
+    w.sync_tile = off;   off += 24 * size_t(p.n_ctiles);
+    w.sync_layer = off;  off += 24 * size_t(n_layers);
     w.sync_epoch = off;  off = (off + 4 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
     if (off >= (size_t(1) << 32)) return ADACOMP_EINVAL;
     w.sync_stride = off;
