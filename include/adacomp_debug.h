@@ -30,8 +30,8 @@ int adacomp_workspace_gmax(const adacomp_layer_t *layers, uint32_t n_layers, siz
 /* Tables whose layers are small are compressed in one launch, whose workgroups wait for each other's
  * sums.  A workgroup polls this often for one that is missing before it works it out itself (by
  * default 256 times, about 0.1 ms).  0 makes every workgroup do so at once: for tests of
- * that path.  Results do not depend on it.  At most 65536: more is
- * taken as that.  Per workspace; ADACOMP_EWORKSPACE if it is not registered. */
+ * that path.  Results do not depend on it.  At most 65536: more is taken as that.  Per workspace;
+ * ADACOMP_EWORKSPACE if it is not registered. */
 int adacomp_debug_wait_polls(void *workspace, uint32_t polls);
 
 /* Plain float4 device copy of n floats (dst, src 16-byte aligned): the reference kernel against
@@ -78,8 +78,8 @@ int adacomp_tuning_fold_scan(int enable);
  * restores the default.  Results do not depend on it.  Returns ADACOMP_OK. */
 int adacomp_tuning_place_tiled(int enable);
 
-/* Per-kernel timing of the streaming kernel (k_fused) of adacomp_compress / adacomp_compress_batch
- * with HIP events on the caller's stream.  enable = k > 0 starts recording every k-th launch (and
+/* Per-kernel timing of the streaming kernel of adacomp_compress / adacomp_compress_batch (k_fused, or on
+ * tables that are compressed in one launch that launch, k_pack, with its wait and its placement) with HIP events on the caller's stream.  enable = k > 0 starts recording every k-th launch (and
  * clears earlier records; an event pair costs a few microseconds between back-to-back launches, so
  * a timed run samples); 0 stops.  adacomp_timing_read synchronises the recorded events and returns their
  * summed duration, the number of launches and the number of learners those launches covered. */

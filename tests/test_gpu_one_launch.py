@@ -25,6 +25,15 @@ TABLES = {
     "one_long_layer": [("a", 4000 * 520 + 37, 500)],        # 521 tiles: beyond the 512 of the first form
     "two_long_layers_short_bins": [("a", 4000 * 700 + 11, 50), ("b", 4032 * 300 + 5, 64)],
 }
+# the longest layer that goes in one launch (four records to a thread of the workgroup that adds them up), and one
+# tile more; the most layers, and one more
+EDGES = {
+    "1024_tiles": [("a", 4000 * 1023 + 5, 50)],
+    "1025_tiles": [("a", 4000 * 1024 + 5, 50)],
+    "1024_tiles_long_bins": [("a", 4000 * 1024 - 500, 500)],
+    "512_layers": [(f"l{i}", 1 + (i * 389) % 2500, (50, 500, 9, 64)[i % 4]) for i in range(512)],
+    "513_layers": [(f"l{i}", 1 + (i * 389) % 2500, (50, 500, 9, 64)[i % 4]) for i in range(513)],
+}
 
 
 @pytest.fixture(scope="module")
@@ -65,6 +74,71 @@ def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
             H.run_parity(oracle_lib, wl, 3, 3, seed=31, label=say, batch=batch)
     else:
         H.run_parity(oracle_lib, wl, 3, 3, seed=31, label=say, batch=batch)
+
+
+@pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(EDGES)] + [("1024_tiles", True), ("512_layers", True)])
+def test_one_launch_edges(H, oracle_lib, name, impatient):
+    with _Impatient(H) if impatient else contextlib.nullcontext():
+        H.run_parity(oracle_lib, W.custom(name, EDGES[name], dist="normal_outliers"), 2, 2, seed=32, label=f"one launch: {name}, impatient {impatient}")
+
+
+@pytest.mark.parametrize("name", ["few_layers", "many_layers"])
+def test_one_launch_non_finite(H, name):
+    """NaN and infinite gradients in both forms: the packet keeps its structure and its length, nothing is written
+    behind it or outside the layers, and what has no such gradient in its layer is what it was."""
+    import packet_format as pf
+    wl = W.custom(name, TABLES[name], dist="normal_outliers")
+    table, n = wl.table(), wl.n_total
+    mask = H.layer_mask(table, n)
+    gpu, clean = H.GpuSide(table, n, 1), H.GpuSide(table, n, 1)
+    try:
+        rng = np.random.default_rng(405)
+        off, m, _ = table[2]                       # a layer that stays finite
+        for t in range(3):
+            H.say(f"one launch: {name}, not finite, step {t}")
+            g = W.gradient(wl, 0, t, seed=405)
+            want = pf.parse(clean.compress(0, g)[:int(pf.header(clean.packets[0].cpu().numpy())["total_bytes"])], check=False)[1][2]
+            bad = rng.choice(n, 400, replace=False)
+            bad = bad[(bad < off) | (bad >= off + m)]
+            g[bad[0::3]], g[bad[1::3]], g[bad[2::3]] = np.nan, np.inf, -np.inf
+            buf = gpu.compress(0, g)
+            h = pf.header(buf)
+            total = int(h["total_bytes"])
+            assert int(h["status"]) == 0 and total <= gpu.bound and np.all(buf[total:] == H.POISON)
+            got = pf.parse(buf[:total])[1][2]
+            assert got["rec"]["scale"] == want["rec"]["scale"] and got["rec"]["n_selected"] == want["rec"]["n_selected"]
+            r, r_clean = gpu.residue[0].cpu().numpy(), clean.residue[0].cpu().numpy()
+            assert np.all(r[~mask] == 0) and np.array_equal(r[off:off + m], r_clean[off:off + m])
+    finally:
+        clean.close()
+        gpu.close()
+
+
+@pytest.mark.parametrize("name", ["few_layers", "many_layers"])
+def test_one_launch_truncated(H, oracle_lib, name):
+    """A capacity in the middle of the words, in both forms: the oracle's bytes up to there, nothing past it."""
+    import packet_format as pf
+    import paper_1712_02679_amd as A
+    wl = W.custom(name, TABLES[name], dist="normal")
+    table, n = wl.table(), wl.n_total
+    g, R = W.gradient(wl, 0, 0, seed=33), np.zeros(n, f32)
+    want = oracle_lib.compress(table, g, R)
+    fixed = A.adacomp_packet_fixed_bytes(table)
+    for cap in (fixed, fixed + (want.size - fixed) // 2 // 16 * 16 + 7, want.size - 1):
+        gpu = H.GpuSide(table, n, 1, capacity=cap)
+        try:
+            H.say(f"one launch: {name}, truncated at {cap}")
+            buf = gpu.compress(0, g)
+            h = pf.header(buf)
+            assert h["status"] == 1 and h["total_bytes"] == want.size and np.all(buf[cap:] == H.POISON)
+            same = buf[:cap] == want[:cap]
+            same[8:12] = True                      # the status word itself
+            if cap % 2:
+                same[cap - 1] = True               # half of a 16-bit word is not written
+            assert np.all(same)
+            assert np.array_equal(gpu.residue[0].cpu().numpy(), R)
+        finally:
+            gpu.close()
 
 
 @pytest.mark.parametrize("rule,factor", [(1, 2.0), (2, 2.0), (0, 1.5)])

@@ -1,6 +1,7 @@
 """k_unpack8 (layers with 8-bit words, a wave per chunk of 64 bins) at the edges of its rule: one or two
-packets on tables of any size; up to 4 packets from 5120 chunks on; any number where all such bins have at
-most 32 elements, from 3072 chunks on; with the optimizer where they have at most 16.
+packets on tables of any size; up to 4 packets from 5120 chunks on; up to 8 from 4096 on where all such bins have
+at most 40 elements, from 6144 on where they have at most 53; any number where they have at most 32, from 3072
+chunks on; with the optimizer where they have at most 16.
 Against the CPU oracle, bit for bit.  Needs an MI355X."""
 import numpy as np
 import pytest
@@ -25,6 +26,11 @@ TABLES = {
     "few_chunks_up_to_27": [("a", 27 * 64 * 2 + 5, 27), ("b", 500 * 120 + 3, 500)],
     "few_chunks_up_to_53": [("a", 53 * 64 * 4 + 30, 53), ("b", 500 * 60 + 3, 500)],
     "few_chunks_up_to_64": [("a", 64 * 64 * 4 + 63, 64), ("b", 500 * 60 + 3, 500), ("c", 50, 50)],
+    # up to 8 packets, on both sides of the two lines
+    "4090_chunks_up_to_40": [("a", 2 * 64 * 4050 + 1, 2), ("b", 40 * 64 * 38 + 7, 40), ("c", 500 * 70 + 3, 500)],
+    "4100_chunks_up_to_40": [("a", 2 * 64 * 4060 + 1, 2), ("b", 40 * 64 * 38 + 7, 40), ("c", 500 * 70 + 3, 500)],
+    "6140_chunks_up_to_53": [("a", 2 * 64 * 6100 + 1, 2), ("b", 53 * 64 * 38 + 7, 53), ("c", 500 * 70 + 3, 500)],
+    "6150_chunks_up_to_53": [("a", 2 * 64 * 6110 + 1, 2), ("b", 53 * 64 * 38 + 7, 53), ("c", 500 * 70 + 3, 500)],
     "3100_chunks_up_to_32": [l for l in LAYERS if l[2] <= 32 or l[2] > 64] + [("k", 2 * 64 * 1670 + 1, 2), ("l", 32 * 64 * 40 + 3, 32)],   # any number
     "3100_chunks_up_to_16": [l for l in LAYERS if l[2] <= 16 or l[2] > 64] + [("k", 2 * 64 * 1670 + 1, 2), ("l", 16 * 64 * 40 + 3, 16)],   # the optimizer too
 }
@@ -41,14 +47,14 @@ def H():
 @pytest.mark.parametrize("dense", [False, True])
 @pytest.mark.parametrize("name", sorted(TABLES))
 def test_sums(H, oracle_lib, name, dense):
-    """1, 2, 4, 8, 9, 17 and 70 packets (batches of 8 in flight, sums carried over launches of 64); dense: every
+    """1, 2, 4, 5, 8, 9, 17 and 70 packets (batches of 8 in flight, sums carried over launches of 64); dense: every
     element sent, so that bins send up to 64 words."""
     wl = W.custom(name, TABLES[name], dist="normal")
     table, n = wl.table(), wl.n_total
     chunks = sum(-(-(-(-m // lt)) // 64) for _, m, lt in table if lt <= 64)
     assert chunks < 3072 if name == "small" or name.startswith("few") else chunks >= (5120 if name == "5200_chunks" else 3072)
     mask = H.layer_mask(table, n)
-    counts = (1, 2, 4, 8) if dense else (0, 1, 2, 4, 8, 9, 17, 70)
+    counts = (1, 2, 4, 8) if dense else (0, 1, 2, 4, 5, 8, 9, 17, 70)
     gpu = H.GpuSide(table, n, max(counts))
     try:
         cpu = []
