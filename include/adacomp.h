@@ -114,8 +114,11 @@ size_t adacomp_packet_fixed_bytes(const adacomp_layer_t *layers, uint32_t n_laye
 
 /* Bytes of workspace adacomp_workspace_init / compress / unpack need for this table (device
  * tables, per-bin g_max, per-tile counters, staging for unplaced words, and an area in which the
- * workgroups of a one-launch compress exchange their sums; a workspace short of that area alone is
- * accepted, and its calls take more launches). 0 if the table is invalid. */
+ * workgroups of a one-launch compress exchange their sums).  0 if the table is invalid.
+ * A workspace a little smaller (one byte is enough) has no such area, is accepted, and its calls take
+ * several launches: somewhat slower on an idle GPU, but no workgroup of theirs then waits for another.
+ * That is the choice for calls that run beside kernels which hold most of the GPU for long; for
+ * streams with a mask of compute units and partitions of a GPU the library makes it itself. */
 size_t adacomp_workspace_bytes(const adacomp_layer_t *layers, uint32_t n_layers);
 
 /* Same, for adacomp_compress_batch with up to n_learners learners per call: the tables once plus
@@ -159,18 +162,18 @@ int adacomp_compress(const adacomp_layer_t *layers, uint32_t n_layers, const flo
  * holds in the memory of every GPU it runs on until the process ends; there is no
  * adacomp_workspace_init to call.  No device memory is allocated or freed by this call, or by
  * anything it calls.
- *   - A layer table whose adacomp_workspace_bytes exceeds the array (about 2.1 bytes per gradient
- *     element: tables beyond roughly 7.5 M elements) is refused with ADACOMP_ETOOBIG before
- *     anything is enqueued.
+ *   - A layer table whose adacomp_workspace_bytes, less the exchange area of a one-launch compress,
+ *     exceeds the array (about 2.1 bytes per gradient element: tables beyond roughly 7.5 M elements)
+ *     is refused with ADACOMP_ETOOBIG before anything is enqueued.
  *   - The first call on a device, and every call whose layer table differs from the previous
  *     call's on that device, writes the tile tables into the array with blocking host-to-device
  *     copies ordered after the work already on hip_stream (so that call is not capturable in a
  *     graph and waits for the stream); calls that repeat the table only launch kernels and touch
  *     no allocator, host or device.
  *   - All calls on one GPU share that GPU's array, which keeps what the last call left in it.
- *     Two calls that overlap in time on one GPU (different streams, different
- *     threads) race on it: give them one stream, or use adacomp_compress with workspaces of the
- *     caller's. */
+ *     Two calls that overlap in time on one GPU (different streams, different threads) race on it,
+ *     and the results of both are undefined (those of later calls are not): give them one stream, or
+ *     use adacomp_compress with workspaces of the caller's. */
 #define ADACOMP_STATIC_SCRATCH_BYTES (16u << 20)
 int adacomp_compress_static(const adacomp_layer_t *layers, uint32_t n_layers, const float *grad,
                             float *residue, void *packet_out, size_t packet_capacity, void *hip_stream);

@@ -370,14 +370,14 @@ void register_workspace(const adacomp_layer_t *layers, uint32_t n_layers, const 
 
 // Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack (a workgroup)?  A wave
 // adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
-// it: 256 bytes of LDS to each element of L_T and three workgroups to a CU leave 3072 resident up to L_T 53,
-// 2048 beyond.  k_unpack / k_unpack8 in us:
+// it (256 bytes of LDS to each element of L_T: 12 chunks are on a compute unit at L_T 50, 10 at 64, more
+// below).  k_unpack / k_unpack8 with four chunks to a workgroup, in us:
 //   plain sum, L_T 50, 1 packet: 313 chunks 7.3 / 6.2, 1250 10.1 / 7.9, 2500 15.4 / 9.8, 7300 39 / 22;
 //   4 packets, 20 M elements: L_T 16 92 / 30, 32 51 / 27, 40 43 / 28, 50 36 / 28, 56 33 / 28, 64 30.5 / 27.9;
 //   8 packets: 10 M elements, L_T 16 61 / 29, 32 36 / 26, 40 31 / 26.5, but 50 25.6 / 28.2 (3277 chunks) and
 //     64 21.2 / 27.8 (2560), whose chunks are too few; 7300 chunks of L_T 50 57 / 41;
-//   16 packets: with 4.6 words to a bin k_unpack is ahead (1033 / 1039) except at short bins (L_T 20, 8
-//     packets, 100 / 37).
+//   16 packets of ResNet-50's table: 92 / 73 at 1.8 words to a bin, but with 4.6 (first mini-batches) a whole
+//     mini-batch 1033 / 1039, and beyond 32 elements left with k_unpack; L_T 20, 8 packets 100 / 37.
 // With the optimizer a wave also has its tile's weights and moments to carry, with too few loads in flight:
 //   20 M elements, SGD with 4 packets, L_T 16 109 / 77, 32 75 / 84, 50 77 / 93, 64 74 / 86; 48 M elements, SGD
 //   with 8, L_T 16 308 / 203, 32 197 / 202, 50 191 / 223; Adam with 1, L_T 16 117 / 111, 32 99 / 120: k_unpack

@@ -25,8 +25,8 @@
 // adacomp_compress_batch_lazy runs the same three, but k_place leaves that read-modify-write out
 // and the next call's k_fused applies the corrections to the residue values while it has them in
 // registers (same arithmetic, same results; adacomp_residue_sync writes them on request).
-// adacomp_unpack_accumulate is one launch, k_unpack (or k_unpack8 for large tables with short bins; with
-// many learners one launch per word width): a workgroup owns a tile of the dense output
+// adacomp_unpack_accumulate is one launch, k_unpack (or k_unpack8 for layers with short bins: one or two
+// packets, or many chunks; large tables of both word widths otherwise take one launch of k_unpack for each): a workgroup owns a tile of the dense output
 // in LDS, a lane group owns each bin and adds the learners' +-scale in learner order, then the
 // tile is written out once with coalesced float4 stores; neighbouring tiles share a workgroup
 // and the per-bin bookkeeping.
@@ -516,7 +516,8 @@ __device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *con
 // published, so whoever finds a record missing may read the tile's inputs.  Should the owner have
 // moved on while the helper was reading, the helper's compare-and-swap finds the record there and
 // drops what it computed; otherwise the two hold the same bits, being the same operations in the same
-// order.  So two calls on different streams that hold each other's compute units finish, late.
+// order.  So two calls on different streams that hold each other's compute units finish, late; those who
+// wait in vain share the missing tiles (help_records).
 // ==============================================================================================
 constexpr int kOneTable = int(kOneLaunchTable), kOneLayers = int(kOneLaunchLayers);
 
@@ -865,9 +866,9 @@ __device__ __forceinline__ float layer_scale_of(const double *sum, const uint32_
 // hence eight of them on a compute unit, which takes 64 registers (7 spilled ones cost 10 %) and is why
 // several values are worked out anew below instead of being kept.
 // Measured, before (k_fused, k_scan, k_place or k_place_tiled) and now, in us: ResNet-50's table
-// 98 -> 67, a mini-batch of 8 learners with its unpack 697 -> 532; 23 layers with odd bins, 9.4 M
-// elements, 2 learners 72 -> 50; 397 k elements 12.2 -> 10.2; the CIFAR table, 4 learners with unpack,
-// 33 -> 24.
+// 98 -> 65, a mini-batch of 8 learners with its unpack 700 -> 524; 23 layers with odd bins, 9.4 M
+// elements, 2 learners 71 -> 49; 397 k elements 12.1 -> 9.6; the CIFAR table, 4 learners with unpack,
+// 33 -> 23.
 // ==============================================================================================
 // values the compiler is not to connect with what they were before
 template <int N>
@@ -2015,11 +2016,11 @@ __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const Unpac
 // accumulators in LDS, learner after learner.  Nothing is shared between waves, so there are no tables
 // and no barriers.  What bounded the scheme before this one (four lanes to a bin, 16 word slots each, of
 // which four were in use) was the issue of those slots: without the adds the launch took 20 us, with them
-// 33 us for 1 packet of ResNet-50's table, 46 for 8 and 78 for 16; now 15, 33 and 66 (with the 16-bit layer's
-// groups 22, 41 and 73, against 39, 57 and 92 for the two launches before).  What bounds it now is the
-// LDS: every word is a load and a store at a random bank.  A workgroup is four such waves, three
-// are on a compute unit at L_T 50 (LDS), and the groups of the 16-bit layers ride in the same launch (a
-// launch of their own cost 7 us).
+// 33 us for 1 packet of ResNet-50's table and 46 for 8; now 15 and 33, and with the 16-bit layer's groups,
+// which ride in the same launch (one of their own cost 7 us), 21 and 39, against 38 and 56 for the two
+// launches before.  What bounds it now is the LDS: every word is a load and a store at a random bank.  A
+// workgroup is up to four such waves: all workgroups of the launch have the LDS of the chunks, and how many
+// of those a workgroup takes decides how many 16-bit groups are resident (unpack8_wg_log).
 // All adds to one element come from one lane in program order, and the LDS unit executes a wave's
 // operations in order: the sum is taken learner 0 first.
 // ==============================================================================================

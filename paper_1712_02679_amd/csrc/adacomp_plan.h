@@ -208,7 +208,7 @@ constexpr uint32_t kOneLaunchNever = 0, kOneLaunchTable = 1, kOneLaunchLayers = 
 // layer, the longer its first tiles hold their place.  One layer of 1000 tiles, one launch / three, in us:
 // L_T 50, 1 learner 19.5 / 29.3, 8 learners 94 / 119; L_T 500, 1 learner 19.0 / 22.4, but 8 learners
 // 90.5 / 83.5, since the placement it saves is cheap where little is sent; hence the second line, which
-// holds for tables without short bins in calls of several learners (525 tiles: 75.0 / 75.2).
+// holds for tables without short bins in calls of several learners (525 tiles: 75.0 / 75.2; 500 tiles 40.9 / 48.0).
 constexpr uint32_t kOneLaunchTiles = 1024;
 constexpr uint32_t kOneLaunchTilesLong = 512;
 // ... and per compute unit that the stream may use, half of what is resident there: workgroups of a layer that
