@@ -425,8 +425,11 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
     if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
     const uint32_t room = kOneLaunchTilesPerUnit * compute_units;
-    const bool crowd = std::min(n_learners, size_t(kMaxBatch)) * p.n_ctiles > 2 * size_t(room);   // more workgroups than are resident
-    if (crowd && p.n_elems_total < uint64_t(p.n_ctiles) * (p.has_short_bins ? kOneLaunchCrowdElems : kOneLaunchCrowdElemsLong)) return kOneLaunchNever;
+    const size_t workgroups = std::min(n_learners, size_t(kMaxBatch)) * p.n_ctiles;
+    const bool crowd = workgroups > 2 * size_t(room);   // more than are resident
+    const bool folds = p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;   // two staged launches, not three
+    const uint64_t pays = !p.has_short_bins ? kOneLaunchCrowdElemsLong : folds ? kOneLaunchCrowdElems : 0u;
+    if (2 * workgroups > 5 * size_t(room) && p.n_elems_total < p.n_ctiles * pays) return kOneLaunchNever;
     if (!crowd && p.n_ctiles <= std::min(kFoldTiles, room) && p.n_layers <= kFoldLayers) return kOneLaunchTable;
     const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
     return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;

@@ -217,11 +217,14 @@ constexpr uint32_t kOneLaunchTilesLong = 512;
 // tiles) 21400 / 243 and 62000 / 450, the character LSTM's 2060 / 43 and 11300 / 66.
 constexpr uint32_t kOneLaunchTilesPerUnit = 4;
 // Calls with more workgroups than are resident (8 per compute unit): the form in which every workgroup reads
-// all records is for latency, and costs more than it saves there; with tiles of some thousand elements neither
-// form pays.  Staged / all records / per layer, in us: 6 layers, L_T 50 and 500, 16 learners: 227 k elements
+// all records is for latency, and costs more than it saves there; with a quarter as many again and small tiles
+// neither form pays, but where staged calls of tables with short bins take three launches.  Staged / all records / per layer, in us: 6 layers, L_T 50 and 500, 16 learners: 227 k elements
 // (1000 a tile) 24.9 / 24.4 / 25.6, 14 layers 26.8 / 31.8 / 26.9; 500 k (1900) 37.7 / 49.2 / 34.0; 1.5 M 80 / 87 / 57.
-// L_T 500, 32 learners: 500 k 59.5 / 96.8 / 65.0, 943 k (3500) 82 / 121 / 71; L_T 3608, 8 learners, 1.5 M 36 / 48 / 33.
-constexpr uint32_t kOneLaunchCrowdElems = 1536, kOneLaunchCrowdElemsLong = 2560;   // elements per tile from which on one launch pays
+// L_T 500, 32 learners: 500 k 59.5 / 96.8 / 65.0, 943 k (3500) 82 / 121 / 71; L_T 3608, 8 learners, 1.5 M 36 / 48 / 33;
+// 20 layers, L_T 2240, 1.1 M (2200 a tile), 4 learners (2060 workgroups) 24.9 / - / 21.0; 20 layers, L_T 50 and
+// 500, 227 k, 16 learners 31.9 / - / 29.0, but L_T 500 alone, 14 learners 24.9 / - / 26.7, 12 (2800 workgroups), 14
+// layers 21.8 / - / 23.0.
+constexpr uint32_t kOneLaunchCrowdElems = 1536, kOneLaunchCrowdElemsLong = 2048;   // elements per tile from which on one launch pays
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
 

@@ -281,9 +281,10 @@ int main()
         // more workgroups than are resident: not the form that reads all records, and none with small tiles
         if (route(256, 2, 500, 4, 256) != kOneLaunchTable || route(256, 2, 500, 5, 256) != kOneLaunchLayers) return 58;
         if (route(512, 1, 500, 4, 256) != kOneLaunchTable || route(512, 1, 50, 40, 256) != kOneLaunchLayers) return 59;
-        if (route(60, 1, 500, 8, 256) != kOneLaunchTable || route(60, 1, 500, 9, 256) != kOneLaunchNever) return 60;   // 240,000 elements: 240 tiles of 1000
-        if (route(120, 1, 50, 7, 256) != kOneLaunchTable || route(120, 1, 50, 8, 256) != kOneLaunchLayers) return 61;    // 267 tiles of 1800
-        if (route(120, 1, 500, 6, 256) != kOneLaunchTable || route(120, 1, 500, 7, 256) != kOneLaunchNever) return 62;   // 320 of 1500
+        if (route(60, 1, 500, 8, 256) != kOneLaunchTable || route(60, 1, 500, 10, 256) != kOneLaunchLayers || route(60, 1, 500, 11, 256) != kOneLaunchNever) return 60;   // 240,000 elements: 240 tiles of 1000
+        if (route(120, 1, 50, 7, 256) != kOneLaunchTable || route(120, 1, 50, 8, 256) != kOneLaunchLayers || route(120, 1, 50, 30, 256) != kOneLaunchLayers) return 61;    // 267 tiles of 1800
+        if (route(120, 1, 500, 6, 256) != kOneLaunchTable || route(120, 1, 500, 8, 256) != kOneLaunchLayers || route(120, 1, 500, 9, 256) != kOneLaunchNever) return 62;   // 320 of 1500
+        if (route(3, 20, 50, 32, 256) != kOneLaunchLayers || route(3, 16, 50, 32, 256) != kOneLaunchNever) return 63;   // three staged launches or two
     }
     {   // the epochs of an exchange area after two calls that overlapped (both refused results, nothing else): in
         // whatever order the calls read and count, each tile has counted two, and the next call's tiles agree
