@@ -281,9 +281,9 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     w.stage = off;       off = pad256(off + 2 * size_t(p.stage_entries) + 128);  // slack: k_place reads up to 64 entries from a tile's start
     w.scratch_stride = off;
     off = 0;             // offsets inside one learner's exchange area
-    w.sync_rec = off;    off += 16 * size_t(p.n_ctiles);
-    w.sync_tile = off;   off += 24 * size_t(p.n_ctiles);
-    w.sync_layer = off;  off += 24 * size_t(n_layers);
+    w.sync_rec = off;    off = (off + 16 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
+    w.sync_tile = off;   off = (off + 32 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
+    w.sync_layer = off;  off = (off + 32 * size_t(n_layers) + 127u) & ~size_t(127);
     w.sync_epoch = off;  off = (off + 4 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
     if (off >= (size_t(1) << 32)) return ADACOMP_EINVAL;
     w.sync_stride = off;

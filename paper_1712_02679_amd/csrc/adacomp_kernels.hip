@@ -552,8 +552,8 @@ __device__ __forceinline__ bool element_sent(const CompressArgs &a, const uint32
 
 struct SyncArea {
     uint64_t *rec;     // 2 per tile: high half of the tile's g_max sum | epoch; low half | word count, epoch
-    uint64_t *tile;    // 3 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch
-    uint64_t *layer;   // 3 per layer: scale | epoch; padded bytes of its words | epoch; its words | epoch
+    uint64_t *tile;    // 4 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch; unused
+    uint64_t *layer;   // 4 per layer: scale | epoch; padded bytes of its words | epoch; its words | epoch; unused
     uint32_t *epoch;   // per tile: number of calls so far, counted up by the tile's own workgroup
 };
 
@@ -743,7 +743,7 @@ __device__ __forceinline__ uint32_t first_open_layer(const SyncArea &sy, const u
     const uint32_t tid = threadIdx.x;
     __syncthreads();   // nobody reads sh.miss any more
     for (uint32_t m = tid; m < kOneLaunchLayersMax; m += WG) {
-        const uint64_t open = __builtin_amdgcn_ballot_w64(m < l && uint32_t(sync_load(sy.layer + 3u * m + 1u)) != epoch);
+        const uint64_t open = __builtin_amdgcn_ballot_w64(m < l && uint32_t(sync_load(sy.layer + 4u * m + 1u)) != epoch);
         if ((tid & 63u) == 0u) sh.miss[m >> 6] = open;
     }
     __syncthreads();
@@ -782,7 +782,7 @@ __device__ __forceinline__ uint32_t scan_records(const uint32_t nt, const Record
     return run;
 }
 
-// One wave: waits for the words of `sy.layer` numbered `first`, first + 3, ... (one per layer) of the
+// One wave: waits for the words of `sy.layer` numbered `first`, first + 4, ... (one per layer) of the
 // layers below n_layers and adds up their values; ok: in, whether to wait at all; out, whether all came.
 __device__ __forceinline__ uint32_t poll_layer_words(const SyncArea &sy, const uint32_t first, const uint32_t n_layers, const uint32_t epoch,
                                                      const uint32_t most_polls, const uint32_t lane, bool &ok)
@@ -793,7 +793,7 @@ __device__ __forceinline__ uint32_t poll_layer_words(const SyncArea &sy, const u
         ok = false;
         for (uint32_t polls = 0; !ok && polls <= most_polls; ++polls) {
             if (polls != 0u) __builtin_amdgcn_s_sleep(4);
-            v = sync_load(sy.layer + 3u * m + first);
+            v = sync_load(sy.layer + 4u * m + first);
             ok = uint32_t(v) == epoch;
         }
         sum += uint32_t(v >> 32);
@@ -824,7 +824,7 @@ __device__ __forceinline__ bool complete_layer(const CompressArgs &a, const Sync
     for (uint32_t wv = 0; wv < WG / 64u; ++wv) total += sh.d[wv];   // fixed order
     const uint32_t scale = __float_as_uint(float(total / double(a.layers[l].n_bins)));
     if (tid == 0) {
-        uint64_t *out = sy.layer + 3u * l;
+        uint64_t *out = sy.layer + 4u * l;
         sync_store(out + 1, sync_word(uint32_t(pad16_dev(uint64_t(words) * wbytes)), epoch));
         sync_store(out, sync_word(scale, epoch));
         sync_store(out + 2, sync_word(words, epoch));
@@ -839,7 +839,7 @@ __device__ __forceinline__ bool complete_layer(const CompressArgs &a, const Sync
 #pragma unroll
     for (uint32_t h = 0; h < HOLD; ++h) {
         if (h * WG + tid < nt) {
-            uint64_t *out = sy.tile + 3u * (ts + h * WG + tid);
+            uint64_t *out = sy.tile + 4u * (ts + h * WG + tid);
             sync_store(out, sync_word(scale, epoch));
             sync_store(out + 1, sync_word(woff + before[h] * wbytes, epoch));
             sync_store(out + 2, sync_word(before[h], epoch));
@@ -1115,7 +1115,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         auto poll_tile = [&](bool ok, const uint32_t most_polls) {
             if (wave == 0u && lane < 3u) {
                 uint64_t v = 0u;
-                const uint64_t *src = sy.tile + 3u * tile + lane;
+                const uint64_t *src = sy.tile + 4u * tile + lane;
                 for (uint32_t polls = 0; ok; ++polls) {
                     v = sync_load(src);
                     if (uint32_t(v) == epoch) break;
@@ -1200,8 +1200,8 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         });
     } else {
         place_header<kWG>(a, packet, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
-            nsel = uint32_t(sync_load(sy.layer + 3u * m + 2u) >> 32);
-            sc = __uint_as_float(uint32_t(sync_load(sy.layer + 3u * m) >> 32));
+            nsel = uint32_t(sync_load(sy.layer + 4u * m + 2u) >> 32);
+            sc = __uint_as_float(uint32_t(sync_load(sy.layer + 4u * m) >> 32));
         });
     }
 }
