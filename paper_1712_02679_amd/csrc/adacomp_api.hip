@@ -284,7 +284,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     w.sync_rec = off;    off = (off + 16 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
     w.sync_tile = off;   off = (off + 32 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
     w.sync_layer = off;  off = (off + 32 * size_t(n_layers) + 127u) & ~size_t(127);
-    w.sync_epoch = off;  off = (off + 4 * size_t(p.n_ctiles) + 127u) & ~size_t(127);
+    w.sync_epoch = off;  off = (off + 4 * (size_t(p.n_ctiles) + 1u) + 127u) & ~size_t(127);
     if (off >= (size_t(1) << 32)) return ADACOMP_EINVAL;
     w.sync_stride = off;
     return ADACOMP_OK;

@@ -86,6 +86,18 @@ __device__ __forceinline__ void buffer_store1(__amdgpu_buffer_rsrc_t rsrc, uint3
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rsrc, int(elem * 4u), 0, 0);
 }
 
+// A record of a table that does not change while a kernel runs, the same for all threads: scalar loads.
+// (Behind a store the compiler takes a vector register per word otherwise.)
+typedef uint32_t vuint2 __attribute__((ext_vector_type(2)));
+typedef uint32_t vuint8 __attribute__((ext_vector_type(8)));
+typedef uint32_t vuint16 __attribute__((ext_vector_type(16)));
+template <class V, class T>
+__device__ __forceinline__ T table_record(const T *p)
+{
+    static_assert(sizeof(V) == sizeof(T), "record size");
+    return __builtin_bit_cast(T, *(const __attribute__((address_space(4))) V *)p);
+}
+
 __device__ __forceinline__ uint32_t bin_of(uint32_t e, uint32_t L_T, uint32_t magic)
 {
     return L_T == 1u ? e : __umulhi(e, magic);
@@ -442,9 +454,9 @@ __device__ __forceinline__ uint64_t pad16_dev(uint64_t x) { return (x + 15u) & ~
 // Header, layer records and zero padding of one learner's packet, by one workgroup of WG threads:
 // WG layers at a time, word offsets by a block scan of the padded section sizes (all below 2^32: the
 // packet bound is).  get(l, layer, words, scale) says what layer l sends; it is called by the thread
-// that writes the layer's record.
+// that writes the layer's record.  `first`: the record of layer number threadIdx.x, if there is one.
 template <uint32_t WG, class Get>
-__device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *const packet, Get get)
+__device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *const packet, const LayerDev &first, Get get)
 {
     const uint32_t tid = threadIdx.x;
     __shared__ uint32_t s_wtot[WG / 64u];
@@ -454,11 +466,11 @@ __device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *con
     for (uint32_t l0 = 0; l0 < a.n_layers; l0 += WG) {
         const uint32_t l = l0 + tid;
         const bool live = l < a.n_layers;
-        LayerDev ld;
+        LayerDev ld = first;
         uint32_t nsel = 0u, bytes = 0u;
         float scale = 0.f;
         if (live) {
-            ld = a.layers[l];
+            if (l0 != 0u) ld = a.layers[l];
             get(l, ld, nsel, scale);
             bytes = uint32_t(pad16_dev(uint64_t(nsel) * ld.word_bytes));
         }
@@ -501,6 +513,9 @@ __device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *con
     }
 }
 
+// The thread's first layer record for place_header.
+__device__ __forceinline__ LayerDev header_layer(const CompressArgs &a) { return a.layers[threadIdx.x < a.n_layers ? threadIdx.x : 0u]; }
+
 // ==============================================================================================
 // The one-launch compress: k_pack does all of Algorithm 2, for tables whose layers are small enough
 // that the tiles of a layer are on the GPU together.
@@ -519,6 +534,13 @@ __device__ __forceinline__ void place_header(const CompressArgs &a, uint8_t *con
 //               where the launch is a few microseconds long.
 //   kOneLayers  the workgroup of a layer's last tile reads the layer's records and publishes the scale,
 //               the size of the layer's words and every tile's first word; the others wait for those.
+//               It does so as soon as its own record is out and before it goes on with its own words, which
+//               takes it 3.5 us (ResNet-50's table 62.5 -> 60.2 us, 8 learners with unpack 512 -> 500).  A
+//               workgroup per learner that adds up all layers, a wave each in turn, takes 71 and 557: 54 layers
+//               at some 3 us each are too many for it.
+// Each learner has a workgroup of its own for the packet's header and layer records, the last of its
+// workgroups.  (That of the last tile, after its own words, was the end of the launch, by 2 us: 397 k
+// elements 8.9 -> 8.2 us, the CIFAR table 10.6 -> 9.9.)
 //
 // Published words carry their own validity: every 8-byte word holds 32 bits of value and, in the rest,
 // the number of the call (the tile's epoch, kept in the exchange area and raised by one by the tile's
@@ -570,7 +592,7 @@ struct SyncArea {
     uint64_t *rec;     // 2 per tile: high half of the tile's g_max sum | epoch; low half | word count, epoch
     uint64_t *tile;    // 4 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch; unused
     uint64_t *layer;   // 4 per layer: scale | epoch; padded bytes of its words | epoch; its words | epoch; unused
-    uint32_t *epoch;   // per tile: number of calls so far, counted up by the tile's own workgroup
+    uint32_t *epoch;   // per tile, and for the header's workgroup: number of calls so far, counted up by that workgroup itself
 };
 
 // LDS of a workgroup that waits
@@ -872,6 +894,51 @@ __device__ __forceinline__ float layer_scale_of(const double *sum, const uint32_
     return float(wave_sum_f64(s) / double(n_bins));
 }
 
+// kOneTable: waits for the records of all tiles and lays them out: s_sum[t] the g_max sum of tile t, s_excl[t] the words
+// of the tiles before t in its run of 64, sh.w[r] the words of run r.  By the whole workgroup, behind a barrier;
+// ends with one.  helped: this workgroup has worked out records itself.  False: another call is at work in the area.
+template <bool VARIANT>
+__device__ __forceinline__ bool table_records(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t epoch, const uint32_t seed,
+                                              uint32_t *s_gmax, uint32_t *const s_excl, double *const s_sum, OneShared &sh, bool &helped)
+{
+    constexpr uint32_t HOLD = kFoldTiles / kWG;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Records<HOLD> rec;
+    auto lay_out = [&]() {
+#pragma unroll
+        for (uint32_t h = 0; h < HOLD; ++h) {
+            const uint32_t i = h * kWG + tid, n = i < a.n_tiles ? rec_count(rec.lo[h]) : 0u;
+            const uint32_t incl = wave_incl_scan(n);
+            s_excl[i] = incl - n;
+            if (i < a.n_tiles) s_sum[i] = rec_sum(rec.hi[h], rec.lo[h]);
+            if (lane == 63u) sh.w[4u * h + wave] = incl;
+        }
+        if (tid == 0) s_excl[kFoldTiles] = 0u;
+    };
+    helped = false;
+    const bool all = poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
+    lay_out();
+    if (__builtin_expect(block_any<kWG>(!all, sh.any[0]), false)) {
+        const bool there = help_records<kWG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, sh);
+        if (block_any<kWG>(!(there && poll_records<kWG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return false;
+        lay_out();
+        __syncthreads();
+        helped = true;
+    }
+    return true;
+}
+// lane r: the words of all runs of 64 tiles before run r; with it, the words of all tiles before tile t
+__device__ __forceinline__ uint32_t words_before_runs(const OneShared &sh, const uint32_t lane)
+{
+    const uint32_t n = lane < kFoldTiles / 64u ? sh.w[lane] : 0u;
+    return wave_incl_scan(n) - n;
+}
+__device__ __forceinline__ uint32_t words_before(const uint32_t *s_excl, const uint32_t run_at, const uint32_t t)
+{
+    return s_excl[t] + uint32_t(__shfl(int(run_at), int(t >> 6), 64));
+}
+
 // ==============================================================================================
 // k_pack: a tile of at most 4096 elements, 256 threads with four 16-byte slots each.  Tiles of this
 // class start on 16-byte boundaries; bins have at least four elements, so that a slot lies in one bin
@@ -882,7 +949,7 @@ __device__ __forceinline__ float layer_scale_of(const double *sum, const uint32_
 // Measured, before (k_fused, k_scan, k_place or k_place_tiled) and now, in us: ResNet-50's table
 // 98 -> 65, a mini-batch of 8 learners with its unpack 700 -> 524; 23 layers with odd bins, 9.4 M
 // elements, 2 learners 71 -> 49; 397 k elements 12.1 -> 9.6; the CIFAR table, 4 learners with unpack,
-// 33 -> 23.
+// 33 -> 23.  (Since then 60, 500, 47, 8.2 and 21.7: see above.)
 // ==============================================================================================
 // values the compiler is not to connect with what they were before
 template <int N>
@@ -905,12 +972,12 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
 {
     constexpr int J = 4;             // 16-byte slots of a thread: slot j of thread t is number j * kWG + t of the tile
     constexpr uint32_t kRow = kWG * 4u;
-    const uint32_t lq = blockIdx.x / a.class_count;   // learner-major, and within runs of 64 transposed, as in k_fused
-    uint32_t tile = blockIdx.x - lq * a.class_count;
+    // learner-major: one workgroup per tile, within runs of 64 transposed as in k_fused, then the one that writes the header
+    const uint32_t lq = blockIdx.x / (a.class_count + 1u);
+    uint32_t tile = blockIdx.x - lq * (a.class_count + 1u);
+    const bool heads = tile == a.class_count;
     const uint32_t lr = a.fused_first + lq;
     if (tile < (a.class_count & ~63u)) tile = (tile & ~63u) | ((tile & 7u) << 3) | ((tile >> 3) & 7u);
-    const TileDev td = a.tiles[tile];
-    const LayerDev ld = a.layers[td.layer()];
     uint8_t *const packet = a.packet[lr];
     SyncArea sy;
     {
@@ -928,9 +995,57 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     __shared__ __attribute__((aligned(16))) uint32_t s_rows[8];   // words per wave and row, two rows to an entry
     __shared__ uint32_t s_chunk[kMaxTileBins / 64u];
     __shared__ OneShared sh;
+    __shared__ uint32_t s_excl[ONE == kOneTable ? kFoldTiles + 1u : 1u];   // kOneTable: words of the tiles before tile t in the same run of 64
+    __shared__ double s_sum[ONE == kOneTable ? kFoldTiles : 1u];           // kOneTable: g_max sum of tile t
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    if (heads) {
+        const LayerDev first = header_layer(a);
+        if (tid == 0) count_call(sy.epoch + a.n_tiles);
+        if (ONE == kOneTable) {
+            float *const s_lscale = reinterpret_cast<float *>(s_words);
+            bool helped;
+            if (!table_records<VARIANT>(a, sy, lr, epoch, a.n_tiles, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by
+            const uint32_t run_at = words_before_runs(sh, lane);
+#pragma unroll
+            for (uint32_t i = 0; i < kFoldLayers / 4u; ++i) {
+                const uint32_t m = wave + 4u * i;
+                if (m >= a.n_layers) continue;   // uniform
+                const float sc = layer_scale_of(s_sum + a.layers[m].ctile_start, a.layers[m].n_ctiles, a.layers[m].n_bins, lane);
+                if (lane == 0u) s_lscale[m] = sc;
+            }
+            const uint32_t ts = first.ctile_start, te = ts + first.n_ctiles;
+            const uint32_t words = words_before(s_excl, run_at, te) - words_before(s_excl, run_at, ts);
+            __syncthreads();
+            place_header<kWG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) { nsel = words; sc = s_lscale[m]; });   // (at most kFoldLayers layers: one round)
+        } else {
+            auto poll_layers = [&](bool ok, const uint32_t most_polls) {   // scale and word count of every layer
+                if (wave == 0u) {
+                    poll_layer_words(sy, 0u, a.n_layers, epoch, most_polls, lane, ok);
+                    poll_layer_words(sy, 2u, a.n_layers, epoch, most_polls, lane, ok);
+                }
+                return ok;
+            };
+            if (__builtin_expect(block_any<kWG>(!poll_layers(true, a.wait_polls), sh.any[2]), false)) {
+                bool ok = true;
+                for (uint32_t times = 0; ok; ++times) {   // the layers that are not done
+                    const uint32_t m = first_open_layer<kWG>(sy, a.n_layers, epoch, sh);
+                    if (m == a.n_layers) break;
+                    ok = times <= a.n_layers && complete_layer<kWG, VARIANT, true>(a, sy, lr, m, epoch, a.n_tiles, s_gmax, sh);
+                }
+                if (block_any<kWG>(!poll_layers(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
+            }
+            place_header<kWG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
+                nsel = uint32_t(sync_load(sy.layer + 4u * m + 2u) >> 32);
+                sc = __uint_as_float(uint32_t(sync_load(sy.layer + 4u * m) >> 32));
+            });
+        }
+        return;
+    }
+
+    const TileDev td = table_record<vuint8>(a.tiles + tile);
     const uint32_t n = td.n_elems, T = td.L_T, M = td.magic, nb = td.n_bins, l = td.layer();
     float *const rs = a.residue[lr] + td.elem_base;
     const float *const gr = a.grad[lr] + td.elem_base;
@@ -955,6 +1070,8 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         }
     };
     load_slots();
+    asm volatile("" ::: "memory");   // the layer's record, which is not needed before the words, is not waited for together with the tile's
+    const LayerDev ld = table_record<vuint16>(a.layers + l);
     for (uint32_t i = tid; i < nb + 1u; i += kWG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(2);   // until the record is out: others wait for it (6 % of a small mini-batch; slower where waves queue for memory)
 #pragma unroll
@@ -1039,6 +1156,9 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         count_call(sy.epoch + tile);
     }
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(0);
+    // A layer's last workgroup adds up its layer, before anything else: all of the layer wait for it.
+    bool layer_ok = true;
+    if (ONE == kOneLayers && tile == ld.ctile_start + ld.n_ctiles - 1u) layer_ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
 
     // ---- the pack vector of Algorithm 2: the words, and how many each bin sends ----------------------
     const uint32_t wbytes = ld.word_bytes;
@@ -1100,32 +1220,18 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     // ---- wait for the layer: its scale, the words before this tile --------------------------------------
     uint32_t first_at, base;   // place of the tile's first word in the packet; words of the layer before the tile
     float scale;
-    __shared__ uint32_t s_excl[ONE == kOneTable ? kFoldTiles + 1u : 1u];   // kOneTable: words of all tiles before tile t
-    double *const s_sum = reinterpret_cast<double *>(s_cnt);               // kOneTable: g_max sum of tile t (the counts are in the packet)
     if (ONE == kOneTable) {
         uint32_t l_ts = 0u, l_nt = 0u, l_wb = 0u;   // lane m keeps layer m's tiles and word width
-        if (lane < a.n_layers) { l_ts = a.layers[lane].ctile_start; l_nt = a.layers[lane].n_ctiles; l_wb = a.layers[lane].word_bytes; }
-        constexpr uint32_t HOLD = kFoldTiles / kWG;
-        Records<HOLD> rec;
-        if (__builtin_expect(block_any<kWG>(!poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec), sh.any[0]), false)) {
-            const bool there = help_records<kWG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, tile, s_gmax, sh);
-            if (block_any<kWG>(!(there && poll_records<kWG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return;   // nothing to go by: store nothing
-            take_again();
-        }
-        uint32_t excl[HOLD];
-        double part = 0.0;
-        const uint32_t all = scan_records<kWG>(a.n_tiles, rec, sh, excl, part);
-#pragma unroll
-        for (uint32_t h = 0; h < HOLD; ++h)
-            if (h * kWG + tid < a.n_tiles) { s_excl[h * kWG + tid] = excl[h]; s_sum[h * kWG + tid] = rec_sum(rec.hi[h], rec.lo[h]); }
-        if (tid == 0) s_excl[a.n_tiles] = all;
-        __syncthreads();
-        base = s_excl[tile] - s_excl[ld.ctile_start];
+        if (lane < l) { l_ts = a.layers[lane].ctile_start; l_nt = a.layers[lane].n_ctiles; l_wb = a.layers[lane].word_bytes; }   // l < kFoldLayers
+        bool helped;
+        if (!table_records<VARIANT>(a, sy, lr, epoch, tile, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by: store nothing
+        if (__builtin_expect(helped, false)) take_again();
+        const uint32_t run_at = words_before_runs(sh, lane);
+        base = words_before(s_excl, run_at, tile) - words_before(s_excl, run_at, ld.ctile_start);
+        const uint32_t words = words_before(s_excl, run_at, l_ts + l_nt) - words_before(s_excl, run_at, l_ts);
         scale = layer_scale_of(s_sum + ld.ctile_start, ld.n_ctiles, ld.n_bins, lane);
-        const uint32_t bytes = lane < l ? uint32_t(pad16_dev(uint64_t(s_excl[l_ts + l_nt] - s_excl[l_ts]) * l_wb)) : 0u;   // l < kFoldLayers
-        first_at = uint32_t(a.fixed_bytes) + wave_sum(bytes) + base * wbytes;   // below 2^32 like the packet
+        first_at = uint32_t(a.fixed_bytes) + wave_sum(uint32_t(pad16_dev(uint64_t(words) * l_wb))) + base * wbytes;   // below 2^32 like the packet
     } else {
-        // A layer's last workgroup adds up its layer; all wait for what that one says about their tile.
         auto poll_tile = [&](bool ok, const uint32_t most_polls) {
             if (wave == 0u && lane < 3u) {
                 uint64_t v = 0u;
@@ -1141,14 +1247,9 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
                 else if (lane == 1u) sh.at = value;
                 else sh.base = value;
             }
-            if (wave == 0u && tile == a.n_tiles - 1u) {   // the header needs scale and word count of every layer
-                poll_layer_words(sy, 0u, a.n_layers, epoch, most_polls, lane, ok);
-                poll_layer_words(sy, 2u, a.n_layers, epoch, most_polls, lane, ok);
-            }
             return ok;
         };
-        bool ok = true;
-        if (tile == ld.ctile_start + ld.n_ctiles - 1u) ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
+        bool ok = layer_ok;
         if (__builtin_expect(block_any<kWG>(!poll_tile(ok, a.wait_polls), sh.any[2]), false)) {
             ok = true;
             for (uint32_t times = 0; ok; ++times) {   // the layers before this one that are not done, and this one
@@ -1199,25 +1300,6 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     // chunks[c] = words of the layer in bins < 64 c, for the chunk starts inside this tile
     for (uint32_t t = t0 + 64u * tid; t < nb; t += 64u * kWG)
         reinterpret_cast<uint32_t *>(packet + ld.chunks_offset)[(td.first_bin + t) >> 6] = base + s_chunk[t >> 6];
-    if (tile != a.n_tiles - 1u) return;
-    // ---- header and layer records: the workgroup of the table's last tile ------------------------------------
-    if (ONE == kOneTable) {
-        __shared__ float s_lscale[kFoldLayers];
-        for (uint32_t m = wave; m < a.n_layers; m += 4u) {
-            const float sc = layer_scale_of(s_sum + a.layers[m].ctile_start, a.layers[m].n_ctiles, a.layers[m].n_bins, lane);
-            if (lane == 0u) s_lscale[m] = sc;
-        }
-        __syncthreads();
-        place_header<kWG>(a, packet, [&](uint32_t m, const LayerDev &lm, uint32_t &nsel, float &sc) {
-            nsel = s_excl[lm.ctile_start + lm.n_ctiles] - s_excl[lm.ctile_start];
-            sc = s_lscale[m];
-        });
-    } else {
-        place_header<kWG>(a, packet, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
-            nsel = uint32_t(sync_load(sy.layer + 4u * m + 2u) >> 32);
-            sc = __uint_as_float(uint32_t(sync_load(sy.layer + 4u * m) >> 32));
-        });
-    }
 }
 
 // ==============================================================================================
@@ -1375,14 +1457,14 @@ __global__ __launch_bounds__(kWG) void k_place(const CompressArgs a)
                 if (lane == 0u) s_fscale[l] = sc;
             }
             __syncthreads();
-            place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &ld, uint32_t &nsel, float &sc) {
+            place_header<kWG>(a, packet, header_layer(a), [&](uint32_t l, const LayerDev &ld, uint32_t &nsel, float &sc) {
                 nsel = s_excl[ld.ctile_start + ld.n_ctiles] - s_excl[ld.ctile_start];
                 sc = s_fscale[l];
                 layer_nsel[l] = nsel;   // and left in the scratch block for whoever applies the corrections later
                 layer_scale[l] = sc;
             });
         } else {
-            place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
+            place_header<kWG>(a, packet, header_layer(a), [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
         }
         return;
     }
@@ -1496,7 +1578,7 @@ __global__ __launch_bounds__(kWG) void k_place_tiled(const CompressArgs a)
     uint8_t *const packet = a.packet[lr];
 
     if (blockIdx.x == a.n_tiles) {   // the grid has one workgroup per tile and this one
-        place_header<kWG>(a, packet, [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
+        place_header<kWG>(a, packet, header_layer(a), [&](uint32_t l, const LayerDev &, uint32_t &nsel, float &sc) { nsel = layer_nsel[l]; sc = layer_scale[l]; });
         return;
     }
     const uint32_t tile = blockIdx.x;   // the grid has one workgroup per tile and one for the header
@@ -2036,17 +2118,6 @@ __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const Unpac
 // All adds to one element come from one lane in program order, and the LDS unit executes a wave's
 // operations in order: the sum is taken learner 0 first.
 // ==============================================================================================
-// A record of a table that does not change while a kernel runs, the same for all threads: scalar loads.
-// (Behind a store the compiler takes a vector register per word otherwise.)
-typedef uint32_t vuint2 __attribute__((ext_vector_type(2)));
-typedef uint32_t vuint8 __attribute__((ext_vector_type(8)));
-typedef uint32_t vuint16 __attribute__((ext_vector_type(16)));
-template <class V, class T>
-__device__ __forceinline__ T table_record(const T *p)
-{
-    static_assert(sizeof(V) == sizeof(T), "record size");
-    return __builtin_bit_cast(T, *(const __attribute__((address_space(4))) V *)p);
-}
 template <class V>
 __device__ __forceinline__ V packet_field(const uint8_t *p) { return *(const __attribute__((address_space(4))) V *)p; }
 
@@ -2266,12 +2337,13 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
     // way a thread holds 16 elements, and a compute unit holds 32 waves of them.  (With 256 threads
     // and 64 elements each the long-bin tiles had two workgroups per compute unit and streamed at
     // 51-55 % of the HBM peak instead of 75-80 %.)
-    const dim3 grid(a.class_count * a.fused_count), wg(jcode == 0 ? 256 : 1024);
+    const dim3 wg(jcode == 0 ? 256 : 1024);
     const bool variant = a.rule != ADACOMP_RULE_ADACOMP || a.soft_factor_minus_1 != 1.0f;
     if (a.one_launch) {   // the host picks it for eager calls on tables of one tile class whose layers are small
         if (jcode != 0 || a.lazy || a.class_tiles || a.place_mode != kPlaceEager) return ADACOMP_EINVAL;
         const bool table = a.one_launch == kOneLaunchTable;
         if (table && (a.n_tiles > kFoldTiles || a.n_layers > kFoldLayers)) return ADACOMP_EINVAL;
+        const dim3 grid((a.class_count + 1u) * a.fused_count);   // a learner's tiles and the workgroup that adds up
         if (!variant) {
             if (table) hipLaunchKernelGGL((k_pack<false, kOneTable>), grid, wg, 0, s, a);
             else hipLaunchKernelGGL((k_pack<false, kOneLayers>), grid, wg, 0, s, a);
@@ -2281,6 +2353,7 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
         }
         return check_launch();
     }
+    const dim3 grid(a.class_count * a.fused_count);
     if (a.lazy) {  // the host offers lazy residues for the default method only
         if (jcode == 0) hipLaunchKernelGGL((k_fused<4, 4, false, true>), grid, wg, 0, s, a);
         else hipLaunchKernelGGL((k_fused<4, 16, false, true>), grid, wg, 0, s, a);

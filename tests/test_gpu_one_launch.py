@@ -28,6 +28,8 @@ TABLES = {
 # the longest layer that goes in one launch (four records to a thread of the workgroup that adds them up), and one
 # tile more; the most layers, and one more
 EDGES = {
+    "512_tiles_16_layers": [(f"l{i}", 4000 * 32 - 3 * i, 500) for i in range(16)],   # the most that every workgroup reads, and half as many
+    "256_tiles_16_layers": [(f"l{i}", 4000 * 16 - i, 500 if i % 2 else 50) for i in range(16)],
     "1024_tiles": [("a", 4000 * 1023 + 5, 50)],
     "1025_tiles": [("a", 4000 * 1024 + 5, 50)],
     "1024_tiles_long_bins": [("a", 4000 * 1024 - 500, 500)],
@@ -76,7 +78,7 @@ def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
         H.run_parity(oracle_lib, wl, 3, 3, seed=31, label=say, batch=batch)
 
 
-@pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(EDGES)] + [("1024_tiles", True), ("512_layers", True)])
+@pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(EDGES)] + [("1024_tiles", True), ("512_layers", True), ("512_tiles_16_layers", True)])
 def test_one_launch_edges(H, oracle_lib, name, impatient):
     with _Impatient(H) if impatient else contextlib.nullcontext():
         H.run_parity(oracle_lib, W.custom(name, EDGES[name], dist="normal_outliers"), 2, 2, seed=32, label=f"one launch: {name}, impatient {impatient}")
