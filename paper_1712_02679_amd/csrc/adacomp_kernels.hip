@@ -636,6 +636,14 @@ __device__ __forceinline__ bool rec_valid(uint64_t hi, uint64_t lo, uint32_t epo
 {
     return uint32_t(hi) == epoch && (uint32_t(lo) & kRecEpochMask) == (epoch & kRecEpochMask);
 }
+// kOneTable: the records three times, where the other form has what it says about tiles.  Every workgroup reads all
+// of them, some hundred times the same lines, and those that publish late wait behind those that already read:
+// 298 tiles 9.0 / 8.7 us, 491 tiles 10.0 / 9.8, 205 7.6 / 7.5.
+constexpr uint32_t kRecCopies = 3;
+__device__ __forceinline__ uint64_t *rec_copy(const SyncArea &sy, const uint32_t n_tiles, const uint32_t copy)
+{
+    return copy == 0u ? sy.rec : sy.tile + 2u * n_tiles * (copy - 1u);
+}
 __device__ __forceinline__ double rec_sum(uint64_t hi, uint64_t lo) { return __builtin_bit_cast(double, (hi & 0xFFFFFFFF00000000ull) | (lo >> 32)); }
 __device__ __forceinline__ uint32_t rec_count(uint64_t lo) { return uint32_t(lo) >> 17; }
 
@@ -897,31 +905,33 @@ __device__ __forceinline__ float layer_scale_of(const double *sum, const uint32_
 // kOneTable: waits for the records of all tiles and lays them out: s_sum[t] the g_max sum of tile t, s_excl[t] the words
 // of the tiles before t in its run of 64, sh.w[r] the words of run r.  By the whole workgroup, behind a barrier;
 // ends with one.  helped: this workgroup has worked out records itself.  False: another call is at work in the area.
-template <bool VARIANT>
+template <uint32_t WG, bool VARIANT>
 __device__ __forceinline__ bool table_records(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t epoch, const uint32_t seed,
                                               uint32_t *s_gmax, uint32_t *const s_excl, double *const s_sum, OneShared &sh, bool &helped)
 {
-    constexpr uint32_t HOLD = kFoldTiles / kWG;
+    constexpr uint32_t HOLD = (kFoldTiles + WG - 1u) / WG;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Records<HOLD> rec;
     auto lay_out = [&]() {
 #pragma unroll
         for (uint32_t h = 0; h < HOLD; ++h) {
-            const uint32_t i = h * kWG + tid, n = i < a.n_tiles ? rec_count(rec.lo[h]) : 0u;
+            const uint32_t i = h * WG + tid, n = i < a.n_tiles ? rec_count(rec.lo[h]) : 0u;
             const uint32_t incl = wave_incl_scan(n);
-            s_excl[i] = incl - n;
+            if (i < kFoldTiles) s_excl[i] = incl - n;
             if (i < a.n_tiles) s_sum[i] = rec_sum(rec.hi[h], rec.lo[h]);
-            if (lane == 63u) sh.w[4u * h + wave] = incl;
+            if (lane == 63u) sh.w[WG / 64u * h + wave] = incl;
         }
         if (tid == 0) s_excl[kFoldTiles] = 0u;
     };
     helped = false;
-    const bool all = poll_records<kWG>(sy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
+    SyncArea copy = sy;   // (whoever helps publishes in the first copy only, and reads that one)
+    copy.rec = rec_copy(sy, a.n_tiles, blockIdx.x % kRecCopies);
+    const bool all = poll_records<WG>(copy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
     lay_out();
-    if (__builtin_expect(block_any<kWG>(!all, sh.any[0]), false)) {
-        const bool there = help_records<kWG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, sh);
-        if (block_any<kWG>(!(there && poll_records<kWG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return false;
+    if (__builtin_expect(block_any<WG>(!all, sh.any[0]), false)) {
+        const bool there = help_records<WG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, sh);
+        if (block_any<WG>(!(there && poll_records<WG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return false;
         lay_out();
         __syncthreads();
         helped = true;
@@ -940,7 +950,8 @@ __device__ __forceinline__ uint32_t words_before(const uint32_t *s_excl, const u
 }
 
 // ==============================================================================================
-// k_pack: a tile of at most 4096 elements, 256 threads with four 16-byte slots each.  Tiles of this
+// k_pack: a tile of at most 4096 elements, 256 threads with four 16-byte slots each, or where every workgroup
+// reads all records and few are at work, 512 with two (kPackWidePerUnit).  Tiles of this
 // class start on 16-byte boundaries; bins have at least four elements, so that a slot lies in one bin
 // or two.  Bound by HBM at 12 bytes per element plus the packet, and short of that by the wait, about
 // 8 us of a workgroup's life of 17 us on ResNet-50's table, which other workgroups have to cover:
@@ -949,7 +960,7 @@ __device__ __forceinline__ uint32_t words_before(const uint32_t *s_excl, const u
 // Measured, before (k_fused, k_scan, k_place or k_place_tiled) and now, in us: ResNet-50's table
 // 98 -> 65, a mini-batch of 8 learners with its unpack 700 -> 524; 23 layers with odd bins, 9.4 M
 // elements, 2 learners 71 -> 49; 397 k elements 12.1 -> 9.6; the CIFAR table, 4 learners with unpack,
-// 33 -> 23.  (Since then 60, 500, 47, 8.2 and 21.7: see above.)
+// 33 -> 23.  (Since then 60, 498, 47, 6.6 and 21.4: the layer added up early, the header's own workgroup, 512 threads.)
 // ==============================================================================================
 // values the compiler is not to connect with what they were before
 template <int N>
@@ -967,32 +978,47 @@ __device__ __forceinline__ uint32_t take_max_from(const uint32_t v, const bool f
     return from && o > v ? o : v;
 }
 
-template <bool VARIANT, int ONE>
-__global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const CompressArgs a)
+template <bool VARIANT, int ONE, int WAVES, int J>
+__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable ? (WAVES == 4 ? 6 : 4) : 8) void k_pack(const CompressArgs a)
 {
-    constexpr int J = 4;             // 16-byte slots of a thread: slot j of thread t is number j * kWG + t of the tile
-    constexpr uint32_t kRow = kWG * 4u;
+    constexpr uint32_t WG = uint32_t(WAVES) * 64u, kRow = WG * 4u;   // J 16-byte slots to a thread: slot j of thread t is number j * WG + t of the tile
+    constexpr int P = (J + 1) / 2;   // pairs of rows
+    static_assert(WG * uint32_t(J) <= 1024u && WG >= kMaxTileBins / 4u, "a tile of at most 4096 elements");
+    // Two rounds of scalar loads: arguments, then what they point to.  (Left to the compiler, which fetches what a
+    // branch needs behind the branch, there are five, 0.25 us each, before the first load of the tile.)
+    const TileDev *tiles = a.tiles;
+    const LayerDev *layers = a.layers;
+    uint8_t *sync = a.sync;
+    uint64_t sync_stride = a.sync_stride;
+    uint32_t o_rec = a.o_sync_rec, o_tile = a.o_sync_tile, o_layer = a.o_sync_layer, o_epoch = a.o_sync_epoch;
+    uint32_t n_tiles = a.class_count, lr = a.fused_first;
+    asm volatile("" : "+s"(tiles), "+s"(layers), "+s"(sync), "+s"(sync_stride), "+s"(o_rec), "+s"(o_tile), "+s"(o_layer), "+s"(o_epoch), "+s"(n_tiles), "+s"(lr));
     // learner-major: one workgroup per tile, within runs of 64 transposed as in k_fused, then the one that writes the header
-    const uint32_t lq = blockIdx.x / (a.class_count + 1u);
-    uint32_t tile = blockIdx.x - lq * (a.class_count + 1u);
-    const bool heads = tile == a.class_count;
-    const uint32_t lr = a.fused_first + lq;
-    if (tile < (a.class_count & ~63u)) tile = (tile & ~63u) | ((tile & 7u) << 3) | ((tile >> 3) & 7u);
-    uint8_t *const packet = a.packet[lr];
+    uint32_t tile = blockIdx.x;
+    const bool heads = tile == n_tiles;
+    lr += blockIdx.y;
+    if (tile < (n_tiles & ~63u)) tile = (tile & ~63u) | ((tile & 7u) << 3) | ((tile >> 3) & 7u);
     SyncArea sy;
     {
-        uint8_t *const area = a.sync + uint64_t(lr) * a.sync_stride;
-        sy.rec = reinterpret_cast<uint64_t *>(area + a.o_sync_rec);
-        sy.tile = reinterpret_cast<uint64_t *>(area + a.o_sync_tile);
-        sy.layer = reinterpret_cast<uint64_t *>(area + a.o_sync_layer);
-        sy.epoch = reinterpret_cast<uint32_t *>(area + a.o_sync_epoch);
+        uint8_t *const area = sync + uint64_t(lr) * sync_stride;
+        sy.rec = reinterpret_cast<uint64_t *>(area + o_rec);
+        sy.tile = reinterpret_cast<uint64_t *>(area + o_tile);
+        sy.layer = reinterpret_cast<uint64_t *>(area + o_layer);
+        sy.epoch = reinterpret_cast<uint32_t *>(area + o_epoch);
     }
-    const uint32_t epoch = sy.epoch[tile] + 1u;   // (count_call)
+    vuint8 tile_words = *(const __attribute__((address_space(4))) vuint8 *)(tiles + (heads ? 0u : tile));
+    uint32_t epoch = *(const __attribute__((address_space(4))) uint32_t *)(sy.epoch + tile);
+    uint8_t *packet = a.packet[lr];
+    float *residue = a.residue[lr];
+    const float *grad = a.grad[lr];
+    asm volatile("" : "+s"(tile_words), "+s"(epoch), "+s"(packet), "+s"(residue), "+s"(grad));
+    ++epoch;   // (count_call)
+    const TileDev td = __builtin_bit_cast(TileDev, tile_words);
 
     __shared__ uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kMaxTileBins + 4u];
-    __shared__ uint32_t s_words[kWG * J * 2u + 4u];  // the tile's words, in their final form, one byte or two each
-    __shared__ __attribute__((aligned(16))) uint32_t s_rows[8];   // words per wave and row, two rows to an entry
+    __shared__ uint32_t s_words[WG * J * 2u + 4u];  // the tile's words, in their final form, one byte or two each
+    __shared__ __attribute__((aligned(16))) uint32_t s_rows[WAVES * P];   // words per wave and row, two rows to an entry
     __shared__ uint32_t s_chunk[kMaxTileBins / 64u];
     __shared__ OneShared sh;
     __shared__ uint32_t s_excl[ONE == kOneTable ? kFoldTiles + 1u : 1u];   // kOneTable: words of the tiles before tile t in the same run of 64
@@ -1007,11 +1033,11 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         if (ONE == kOneTable) {
             float *const s_lscale = reinterpret_cast<float *>(s_words);
             bool helped;
-            if (!table_records<VARIANT>(a, sy, lr, epoch, a.n_tiles, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by
+            if (!table_records<WG, VARIANT>(a, sy, lr, epoch, a.n_tiles, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by
             const uint32_t run_at = words_before_runs(sh, lane);
 #pragma unroll
-            for (uint32_t i = 0; i < kFoldLayers / 4u; ++i) {
-                const uint32_t m = wave + 4u * i;
+            for (uint32_t i = 0; i < kFoldLayers / uint32_t(WAVES); ++i) {
+                const uint32_t m = wave + uint32_t(WAVES) * i;
                 if (m >= a.n_layers) continue;   // uniform
                 const float sc = layer_scale_of(s_sum + a.layers[m].ctile_start, a.layers[m].n_ctiles, a.layers[m].n_bins, lane);
                 if (lane == 0u) s_lscale[m] = sc;
@@ -1019,7 +1045,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
             const uint32_t ts = first.ctile_start, te = ts + first.n_ctiles;
             const uint32_t words = words_before(s_excl, run_at, te) - words_before(s_excl, run_at, ts);
             __syncthreads();
-            place_header<kWG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) { nsel = words; sc = s_lscale[m]; });   // (at most kFoldLayers layers: one round)
+            place_header<WG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) { nsel = words; sc = s_lscale[m]; });   // (at most kFoldLayers layers: one round)
         } else {
             auto poll_layers = [&](bool ok, const uint32_t most_polls) {   // scale and word count of every layer
                 if (wave == 0u) {
@@ -1028,16 +1054,16 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
                 }
                 return ok;
             };
-            if (__builtin_expect(block_any<kWG>(!poll_layers(true, a.wait_polls), sh.any[2]), false)) {
+            if (__builtin_expect(block_any<WG>(!poll_layers(true, a.wait_polls), sh.any[2]), false)) {
                 bool ok = true;
                 for (uint32_t times = 0; ok; ++times) {   // the layers that are not done
-                    const uint32_t m = first_open_layer<kWG>(sy, a.n_layers, epoch, sh);
+                    const uint32_t m = first_open_layer<WG>(sy, a.n_layers, epoch, sh);
                     if (m == a.n_layers) break;
-                    ok = times <= a.n_layers && complete_layer<kWG, VARIANT, true>(a, sy, lr, m, epoch, a.n_tiles, s_gmax, sh);
+                    ok = times <= a.n_layers && complete_layer<WG, VARIANT, true>(a, sy, lr, m, epoch, a.n_tiles, s_gmax, sh);
                 }
-                if (block_any<kWG>(!poll_layers(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
+                if (block_any<WG>(!poll_layers(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
             }
-            place_header<kWG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
+            place_header<WG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
                 nsel = uint32_t(sync_load(sy.layer + 4u * m + 2u) >> 32);
                 sc = __uint_as_float(uint32_t(sync_load(sy.layer + 4u * m) >> 32));
             });
@@ -1045,13 +1071,13 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         return;
     }
 
-    const TileDev td = table_record<vuint8>(a.tiles + tile);
     const uint32_t n = td.n_elems, T = td.L_T, M = td.magic, nb = td.n_bins, l = td.layer();
-    float *const rs = a.residue[lr] + td.elem_base;
-    const float *const gr = a.grad[lr] + td.elem_base;
+    float *const rs = residue + td.elem_base;
+    const float *const gr = grad + td.elem_base;
     // whole slots only: what lies past the tile is read as zero and not stored, without a branch
     const __amdgpu_buffer_rsrc_t r_buf = tile_buffer(rs, n & ~3u), w_buf = tile_buffer(gr, n & ~3u);
 
+    auto skip_row = [&](int j) { return WAVES == 8 && j != 0 && n <= uint32_t(j) * kRow; };   // (uniform: the small tiles of small tables leave a row empty)
     uint32_t gb[J][4];  // bits of G (sign included)
     uint32_t mb[J][4];  // bits of max(|G|, |H|): what is compared with g_max
     vfloat4 r[J], w[J];
@@ -1064,15 +1090,15 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         if ((n & 3u) != 0u) {   // the layer's last elements, which do not fill a slot
 #pragma unroll
             for (int j = 0; j < J; ++j)
-                if (uint32_t(j) * kWG + tid == (n >> 2)) {
+                if (uint32_t(j) * WG + tid == (n >> 2)) {
                     for (uint32_t c = 0; c < (n & 3u); ++c) { r[j][c] = rs[(n & ~3u) + c]; w[j][c] = gr[(n & ~3u) + c]; }
                 }
         }
     };
     load_slots();
     asm volatile("" ::: "memory");   // the layer's record, which is not needed before the words, is not waited for together with the tile's
-    const LayerDev ld = table_record<vuint16>(a.layers + l);
-    for (uint32_t i = tid; i < nb + 1u; i += kWG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
+    const LayerDev ld = table_record<vuint16>(layers + l);
+    for (uint32_t i = tid; i < nb + 1u; i += WG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(2);   // until the record is out: others wait for it (6 % of a small mini-batch; slower where waves queue for memory)
 #pragma unroll
     for (int j = 0; j < J; ++j)
@@ -1089,6 +1115,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     uint32_t place[J];   // b0 << 16 | left
 #pragma unroll
     for (int j = 0; j < J; ++j) {
+        if (skip_row(j)) { place[j] = T; continue; }
         const uint32_t e0 = uint32_t(j) * kRow + tid * 4u;
         const uint32_t b0 = __umulhi(e0, M);
         const uint32_t left = T - (e0 - __umul24(b0, T));
@@ -1124,6 +1151,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     uint32_t sent_mask = 0u;   // bit 4 j + c: element c of slot j is sent
 #pragma unroll
     for (int j = 0; j < J; ++j) {
+        if (skip_row(j)) continue;
         const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
         const uint32_t gm0 = s_gmax[b0], gm1 = s_gmax[b0 + 1u];
 #pragma unroll
@@ -1136,29 +1164,35 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         }
     }
     // words are ordered by (row j, wave, lane, c): counts of two rows to a register, at most 256 each per wave
-    const uint32_t c01 = uint32_t(__popc(sent_mask & 0xFu)) | (uint32_t(__popc(sent_mask & 0xF0u)) << 16);
-    const uint32_t c23 = uint32_t(__popc(sent_mask & 0xF00u)) | (uint32_t(__popc(sent_mask & 0xF000u)) << 16);
-    const uint32_t i01 = wave_incl_scan(c01), i23 = wave_incl_scan(c23);
-    if (lane == 63u) { s_rows[2u * wave] = i01; s_rows[2u * wave + 1u] = i23; }
-    const double gmax_sum = tile_gmax_sum<kWG>(s_gmax, nb, sh.d);   // has the barrier
-    uint32_t all01 = 0u, all23 = 0u, pre01 = i01 - c01, pre23 = i23 - c23;
+    uint32_t pre[P], all[P];   // words of the wave's rows before this lane; of the tile's rows
 #pragma unroll
-    for (uint32_t wv = 0; wv < 4u; ++wv) {
-        const uint32_t t01 = s_rows[2u * wv], t23 = s_rows[2u * wv + 1u];
-        if (wv < wave) { pre01 += t01; pre23 += t23; }
-        all01 += t01;
-        all23 += t23;
+    for (int p = 0; p < P; ++p) {
+        const uint32_t c = uint32_t(__popc((sent_mask >> (8 * p)) & 0xFu)) | (uint32_t(__popc((sent_mask >> (8 * p)) & 0xF0u)) << 16);
+        const uint32_t incl = wave_incl_scan(c);
+        if (lane == 63u) s_rows[uint32_t(P) * wave + uint32_t(p)] = incl;
+        pre[p] = incl - c;
+        all[p] = 0u;
     }
-    const uint32_t row2 = (all01 & 0xFFFFu) + (all01 >> 16), tile_total = row2 + (all23 & 0xFFFFu) + (all23 >> 16);
-    if (tid == 0) {   // first thing: others wait for it
-        sync_store(sy.rec + 2u * tile, rec_high(gmax_sum, epoch));
-        sync_store(sy.rec + 2u * tile + 1u, rec_low(gmax_sum, tile_total, epoch));
-        count_call(sy.epoch + tile);
-    }
+    const double gmax_sum = tile_gmax_sum<WG>(s_gmax, nb, sh.d);   // has the barrier
+#pragma unroll
+    for (uint32_t wv = 0; wv < uint32_t(WAVES); ++wv)
+#pragma unroll
+        for (uint32_t p = 0; p < uint32_t(P); ++p) {
+            const uint32_t t = s_rows[uint32_t(P) * wv + p];
+            if (wv < wave) pre[p] += t;
+            all[p] += t;
+        }
+    uint32_t tile_total = 0u;
+#pragma unroll
+    for (int p = 0; p < P; ++p) tile_total += (all[p] & 0xFFFFu) + (all[p] >> 16);
+    // first thing: others wait for it
+    if (tid < (ONE == kOneTable ? 2u * kRecCopies : 2u))
+        sync_store(rec_copy(sy, a.n_tiles, tid >> 1) + 2u * tile + (tid & 1u), (tid & 1u) ? rec_low(gmax_sum, tile_total, epoch) : rec_high(gmax_sum, epoch));
+    if (tid == 0) count_call(sy.epoch + tile);
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(0);
     // A layer's last workgroup adds up its layer, before anything else: all of the layer wait for it.
     bool layer_ok = true;
-    if (ONE == kOneLayers && tile == ld.ctile_start + ld.n_ctiles - 1u) layer_ok = complete_layer<kWG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
+    if (ONE == kOneLayers && tile == ld.ctile_start + ld.n_ctiles - 1u) layer_ok = complete_layer<WG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
 
     // ---- the pack vector of Algorithm 2: the words, and how many each bin sends ----------------------
     const uint32_t wbytes = ld.word_bytes;
@@ -1169,8 +1203,8 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         const uint32_t f = (sent_mask >> (4 * j)) & 0xFu;
         if (f == 0u) continue;
         const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
-        uint32_t at = j == 0 ? pre01 & 0xFFFFu : j == 1 ? (pre01 >> 16) + (all01 & 0xFFFFu)
-                    : j == 2 ? (pre23 & 0xFFFFu) + row2 : (pre23 >> 16) + row2 + (all23 & 0xFFFFu);
+        uint32_t at = (j & 1) ? (pre[j / 2] >> 16) + (all[j / 2] & 0xFFFFu) : pre[j / 2] & 0xFFFFu;
+        if (j >= 2) at += (all[0] & 0xFFFFu) + (all[0] >> 16);
 #pragma unroll
         for (uint32_t c = 0; c < 4u; ++c) {
             if (!((f >> c) & 1u)) continue;
@@ -1190,17 +1224,17 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     // ---- what does not need the layer: counts per bin, running counts, the optional g_max vector -------
     if (wbytes == 1u) {
         uint8_t *cp = packet + ld.counts_offset + td.first_bin;
-        for (uint32_t i = tid; i < nb; i += kWG) cp[i] = uint8_t(s_cnt[i]);
+        for (uint32_t i = tid; i < nb; i += WG) cp[i] = uint8_t(s_cnt[i]);
     } else {
         uint16_t *cp = reinterpret_cast<uint16_t *>(packet + ld.counts_offset) + td.first_bin;
-        for (uint32_t i = tid; i < nb; i += kWG) cp[i] = uint16_t(s_cnt[i]);
+        for (uint32_t i = tid; i < nb; i += WG) cp[i] = uint16_t(s_cnt[i]);
     }
     if (a.keep_gmax) {
         float *gm_out = reinterpret_cast<float *>(a.scratch + uint64_t(lr) * a.scratch_stride + a.o_gmax) + ld.bin_start + td.first_bin;
-        for (uint32_t i = tid; i < nb; i += kWG) gm_out[i] = __uint_as_float(s_gmax[i]);
+        for (uint32_t i = tid; i < nb; i += WG) gm_out[i] = __uint_as_float(s_gmax[i]);
     }
     const uint32_t t0 = (64u - (td.first_bin & 63u)) & 63u;   // first bin of the tile that starts a chunk of 64
-    for (uint32_t t = t0 + 64u * wave; t < nb; t += 256u) {
+    for (uint32_t t = t0 + 64u * wave; t < nb; t += WG) {
         uint32_t sum = 0u;
         for (uint32_t i = lane; i < t; i += 64u) sum += s_cnt[i];
         sum = wave_sum(sum);
@@ -1224,7 +1258,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         uint32_t l_ts = 0u, l_nt = 0u, l_wb = 0u;   // lane m keeps layer m's tiles and word width
         if (lane < l) { l_ts = a.layers[lane].ctile_start; l_nt = a.layers[lane].n_ctiles; l_wb = a.layers[lane].word_bytes; }   // l < kFoldLayers
         bool helped;
-        if (!table_records<VARIANT>(a, sy, lr, epoch, tile, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by: store nothing
+        if (!table_records<WG, VARIANT>(a, sy, lr, epoch, tile, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by: store nothing
         if (__builtin_expect(helped, false)) take_again();
         const uint32_t run_at = words_before_runs(sh, lane);
         base = words_before(s_excl, run_at, tile) - words_before(s_excl, run_at, ld.ctile_start);
@@ -1250,14 +1284,14 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
             return ok;
         };
         bool ok = layer_ok;
-        if (__builtin_expect(block_any<kWG>(!poll_tile(ok, a.wait_polls), sh.any[2]), false)) {
+        if (__builtin_expect(block_any<WG>(!poll_tile(ok, a.wait_polls), sh.any[2]), false)) {
             ok = true;
             for (uint32_t times = 0; ok; ++times) {   // the layers before this one that are not done, and this one
-                const uint32_t m = first_open_layer<kWG>(sy, l, epoch, sh);
-                ok = times <= l && complete_layer<kWG, VARIANT, true>(a, sy, lr, m, epoch, tile, s_gmax, sh);
+                const uint32_t m = first_open_layer<WG>(sy, l, epoch, sh);
+                ok = times <= l && complete_layer<WG, VARIANT, true>(a, sy, lr, m, epoch, tile, s_gmax, sh);
                 if (m == l) break;
             }
-            if (block_any<kWG>(!poll_tile(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
+            if (block_any<WG>(!poll_tile(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
             take_again();
             __syncthreads();
         }
@@ -1272,6 +1306,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
     // ---- the residue, in its final form: G - Gq at the sent elements, G elsewhere ---------------------------
 #pragma unroll
     for (int j = 0; j < J; ++j) {
+        if (skip_row(j)) continue;
         vfloat4 R;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -1280,13 +1315,13 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
             R[c] = ((sent_mask >> (4 * j + c)) & 1u) ? corrected : G;
         }
         buffer_store_slot(r_buf, tid_r * 16u, uint32_t(j) * kRow * 4u, R);
-        if ((n & 3u) != 0u && uint32_t(j) * kWG + tid_r == (n >> 2))
+        if ((n & 3u) != 0u && uint32_t(j) * WG + tid_r == (n >> 2))
             for (uint32_t c = 0; c < (n & 3u); ++c) rs[(n & ~3u) + c] = R[c];
     }
     // ---- the words, at their place in the packet, four bytes at a time ---------------------------------------
     const uint32_t n_bytes = tile_total * wbytes, skew = first_at & 3u;
     const uint64_t limit = a.capacity & ~uint64_t(wbytes - 1u);   // no part of a word that does not fit
-    for (uint32_t d = tid; 4u * d < skew + n_bytes; d += kWG) {
+    for (uint32_t d = tid; 4u * d < skew + n_bytes; d += WG) {
         const uint64_t at = uint64_t(first_at - skew) + 4u * d;
         const uint32_t o = 4u * d - skew;   // first byte of the four among the tile's words; wraps below zero in the first
         if (4u * d >= skew && o + 4u <= n_bytes && at + 4u <= limit) {
@@ -1298,7 +1333,7 @@ __global__ __launch_bounds__(kWG, ONE == kOneTable ? 6 : 8) void k_pack(const Co
         }
     }
     // chunks[c] = words of the layer in bins < 64 c, for the chunk starts inside this tile
-    for (uint32_t t = t0 + 64u * tid; t < nb; t += 64u * kWG)
+    for (uint32_t t = t0 + 64u * tid; t < nb; t += 64u * WG)
         reinterpret_cast<uint32_t *>(packet + ld.chunks_offset)[(td.first_bin + t) >> 6] = base + s_chunk[t >> 6];
 }
 
@@ -2343,13 +2378,17 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
         if (jcode != 0 || a.lazy || a.class_tiles || a.place_mode != kPlaceEager) return ADACOMP_EINVAL;
         const bool table = a.one_launch == kOneLaunchTable;
         if (table && (a.n_tiles > kFoldTiles || a.n_layers > kFoldLayers)) return ADACOMP_EINVAL;
-        const dim3 grid((a.class_count + 1u) * a.fused_count);   // a learner's tiles and the workgroup that adds up
-        if (!variant) {
-            if (table) hipLaunchKernelGGL((k_pack<false, kOneTable>), grid, wg, 0, s, a);
-            else hipLaunchKernelGGL((k_pack<false, kOneLayers>), grid, wg, 0, s, a);
+        const dim3 grid(a.class_count + 1u, a.fused_count);   // a learner's tiles and the workgroup that writes the header
+        auto launch = [&](auto kernel, uint32_t threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a); };
+        if (!table) {
+            if (!variant) launch((k_pack<false, kOneLayers, 4, 4>), 256u);
+            else launch((k_pack<true, kOneLayers, 4, 4>), 256u);
+        } else if (a.pack_wide) {
+            if (!variant) launch((k_pack<false, kOneTable, 8, 2>), 512u);
+            else launch((k_pack<true, kOneTable, 8, 2>), 512u);
         } else {
-            if (table) hipLaunchKernelGGL((k_pack<true, kOneTable>), grid, wg, 0, s, a);
-            else hipLaunchKernelGGL((k_pack<true, kOneLayers>), grid, wg, 0, s, a);
+            if (!variant) launch((k_pack<false, kOneTable, 4, 4>), 256u);
+            else launch((k_pack<true, kOneTable, 4, 4>), 256u);
         }
         return check_launch();
     }

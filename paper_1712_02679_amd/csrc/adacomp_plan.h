@@ -229,6 +229,12 @@ constexpr uint32_t kOneLaunchCrowdElems = 1536, kOneLaunchCrowdElemsLong = 2048;
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
 
+// A tile by 512 threads instead of 256, up to as many workgroups as leave two to a compute unit: the phases of a
+// workgroup that has a unit to itself are chains of dependent instructions, half as long with half as many slots
+// to a thread.  256 / 512 threads, in us: 32 workgroups 7.2 / 6.7, 205 8.3 / 7.5, 488 (8 learners) 8.8 / 8.3, 596 10.4
+// / 10.4, and 1192, of which 1024 are resident with 512 threads, 13.4 / 17.9.
+constexpr uint32_t kPackWidePerUnit = 2;
+
 struct CompressArgs {
     const TileDev *tiles;
     const LayerDev *layers;
@@ -251,6 +257,7 @@ struct CompressArgs {
     uint32_t shift;                     // the launch over the larger tiles uses the kernel that honours TileDev::skip
     uint32_t fused_idle_lds;            // bytes of dynamic LDS for the eager 256-thread k_fused launches (kFusedIdleLds or 0)
     uint32_t rule;                      // ADACOMP_RULE_*
+    uint32_t pack_wide;                 // one_launch == kOneLaunchTable: 512 threads to a tile instead of 256
     float soft_factor_minus_1;          // 1 for the paper's factor 2
     uint64_t o_stage;
     uint64_t capacity;        // bytes available in each packet buffer

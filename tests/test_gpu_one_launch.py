@@ -155,6 +155,17 @@ def test_one_launch_variants(H, oracle_lib, name, impatient, rule, factor):
                      batch=True)
 
 
+@pytest.mark.parametrize("n,rule,factor", [(1, 0, 2.0), (1, 1, 2.0), (1, 0, 1.5), (2, 0, 2.0), (2, 2, 2.0), (3, 0, 2.0)])
+@pytest.mark.parametrize("name,tiles", [("a", 255), ("b", 511)])
+def test_threads_per_tile(H, oracle_lib, name, tiles, n, rule, factor):
+    """256 or 512 threads to a tile, at the line between them (512 workgroups, one per learner for the header), with
+    tiles that leave the second row of slots empty, by one element or not at all."""
+    per = (2000, 2052, 4000)[n - 1]   # of 2048 elements in a row of 512 threads
+    lt = (500, 54, 50)[n - 1]
+    wl = W.custom(name, [("x", per * (tiles - 9) - 5, lt), ("y", per * 9 - 1, lt)], dist="normal")
+    H.run_parity(oracle_lib, wl, n, 2, rule=rule, soft_factor=factor, seed=6, label=f"one launch: {tiles} tiles of {per}, {n} learners", batch=True)
+
+
 def test_one_launch_beside_staged_calls(H, oracle_lib):
     """One workspace: one-launch calls, three-launch calls (the tuning knob) and lazy calls in turn: the residues go
     on as if nothing had changed."""
