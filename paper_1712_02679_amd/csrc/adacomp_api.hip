@@ -383,28 +383,28 @@ void register_workspace(const adacomp_layer_t *layers, uint32_t n_layers, const 
     g_ws[workspace] = std::move(reg);
 }
 
-// Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack (a workgroup)?  A wave
-// adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
+// Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack and k_unpack_few (a workgroup)?
+// A wave adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
 // it (256 bytes of LDS to each element of L_T: 12 chunks are on a compute unit at L_T 50, 10 at 64, more
-// below).  k_unpack / k_unpack8 with four chunks to a workgroup, in us:
-//   plain sum, L_T 50, 1 packet: 313 chunks 7.3 / 6.2, 1250 10.1 / 7.9, 2500 15.4 / 9.8, 7300 39 / 22;
-//   4 packets, 20 M elements: L_T 16 92 / 30, 32 51 / 27, 40 43 / 28, 50 36 / 28, 56 33 / 28, 64 30.5 / 27.9;
-//   8 packets: 10 M elements, L_T 16 61 / 29, 32 36 / 26, 40 31 / 26.5, but 50 25.6 / 28.2 (3277 chunks) and
-//     64 21.2 / 27.8 (2560), whose chunks are too few; 7300 chunks of L_T 50 57 / 41;
-//   16 packets of ResNet-50's table: 92 / 73 at 1.8 words to a bin, but with 4.6 (first mini-batches) a whole
-//     mini-batch 1033 / 1039, and beyond 32 elements left with k_unpack; L_T 20, 8 packets 100 / 37.
+// below).  A workgroup / a wave per chunk, in us:
+//   plain sum, 1 packet: L_T 16, 700 chunks 5.2 / 5.2, 1500 6.7 / 5.5, 6000 15.8 / 7.9; L_T 32, 700 5.6 / 5.9, 1500 7.2 /
+//     6.9, 6000 16.9 / 11.7; L_T 50, 100 5.0 / 5.7, 700 6.2 / 6.8, 1500 8.4 / 8.1, 3000 11.5 / 11.0, 6000 17.5 / 18.2 (ResNet-50's
+//     table, with 16-bit groups, 22.0 / 20.0); L_T 64, 700 6.3 / 7.3, 3000 11.5 / 13.1, 6000 21.6 / 22.6;
+//   4 packets: L_T 16, 3000 chunks 14.7 / 9.2; L_T 32, 1000 8.2 / 8.8, 3000 15.7 / 10.5, 5000 21.8 / 16.5; L_T 50, 3000
+//     16.8 / 14.0, 5000 23.0 / 21.2, 9000 37.1 / 31.8; L_T 64, 5000 24.0 / 27.9;
+//   8 packets: L_T 16, 1000 9.1 / 11.7, 3000 18.2 / 13.2; L_T 32, 1000 9.6 / 12.9, 3000 19.0 / 14.8, 9000 48 / 34; L_T 50, 3000
+//     20.0 / 18.0, 5000 29.0 / 29.6, 9000 49.9 / 43.5; L_T 64, 9000 51.6 / 62.7;
+//   16 packets, L_T 50, 8000: 87 / 68 at 4 words to a bin, but 129 / 202 with the dense packets of first mini-batches (L_T
+//     32: 101 / 112): beyond 32 elements left with k_unpack, and with fewer packets where chunks are many.
 // With the optimizer a wave also has its tile's weights and moments to carry, with too few loads in flight:
-//   20 M elements, SGD with 4 packets, L_T 16 109 / 77, 32 75 / 84, 50 77 / 93, 64 74 / 86; 48 M elements, SGD
-//   with 8, L_T 16 308 / 203, 32 197 / 202, 50 191 / 223; Adam with 1, L_T 16 117 / 111, 32 99 / 120: k_unpack
-//   above L_T 16.
-// Small tables with a few long 8-bit bins among many 16-bit groups stay with the one launch of k_unpack<., 2>:
-//   4 M, 5 %, L_T 64 and 500, 2 packets 8.7 / 9.0.
-static bool unpack8_for(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners, uint32_t mode)
+//   SGD, L_T 8, 5000 chunks, 1 / 8 packets 14.8 / 9.7 and 27 / 17; L_T 12 16.6 / 13.4 and 29 / 19; L_T 16, 1 packet 5000 18.5 /
+//   18.9, 12000 37.6 / 40.5, 8 packets 29.6 / 24.8 and 62 / 50; 20 M elements, L_T 32 75 / 84, 50 77 / 93.
+static bool unpack8_for(const Plan &p, uint32_t n_chunks, uint32_t n_learners, uint32_t mode)
 {
-    if (mode != 0u) return p.short_bin_max <= 16u && n_learners <= 8u && n_chunks >= 3072u;
-    if (n_learners <= 2u) return p.short_bin_max <= 53u || p.n_utiles > kUnpackSplitTiles || n_groups16 <= 8u * n_chunks;
+    if (mode != 0u) return p.short_bin_max <= (n_learners <= 2u ? 13u : 16u) && n_learners <= 8u && n_chunks >= 3072u;
+    if (n_learners <= 2u) return p.short_bin_max <= 53u && n_chunks >= (p.short_bin_max <= 24u ? 800u : 1300u);
     if (p.short_bin_max <= 32u) return n_chunks >= 3072u;
-    if (n_learners <= 4u) return n_chunks >= 5120u;
+    if (n_learners <= 4u) return n_chunks >= 5120u && p.short_bin_max <= 53u;
     if (n_learners <= 8u) return p.short_bin_max <= 40u ? n_chunks >= 4096u : p.short_bin_max <= 53u && n_chunks >= 6144u;
     return false;
 }
@@ -892,7 +892,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         a.groups = table;
         a.n_groups = n_all;
         a.n_groups8 = a.first16 = a.chunk_lds = 0u;
-        if (n8 != 0u && unpack8_for(p, n8, n_all - n8, now, a.mode)) {
+        if (n8 != 0u && unpack8_for(p, n8, now, a.mode)) {
             a.groups = reinterpret_cast<const UGroupDev *>(ws + p.ws.ugroups);   // single chunks in either table, here in order
             a.n_groups8 = n8;
             a.n_groups = n_all - n8;
@@ -901,7 +901,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
             if ((rc = launch_unpack(a, 3, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
             if ((rc = launch_unpack(a, n8 ? 1 : 0, hip_stream)) != ADACOMP_OK) return rc;
-        } else if (p.n_utiles <= kUnpackSplitTiles) {  // small and mixed: one launch that handles both
+        } else if (p.n_utiles <= kUnpackSplitTiles || (now <= 4u && now != 0u)) {  // mixed, and small or with few registers per path (k_unpack_few): one launch that handles both
             if ((rc = launch_unpack(a, 2, hip_stream)) != ADACOMP_OK) return rc;
         } else {  // large and mixed: the 8-bit groups come first in the table
             a.n_groups = n8;

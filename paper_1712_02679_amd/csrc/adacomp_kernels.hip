@@ -97,6 +97,9 @@ __device__ __forceinline__ T table_record(const T *p)
     static_assert(sizeof(V) == sizeof(T), "record size");
     return __builtin_bit_cast(T, *(const __attribute__((address_space(4))) V *)p);
 }
+template <class V>
+__device__ __forceinline__ V packet_field(const uint8_t *p) { return *(const __attribute__((address_space(4))) V *)p; }
+
 
 __device__ __forceinline__ uint32_t bin_of(uint32_t e, uint32_t L_T, uint32_t magic)
 {
@@ -119,6 +122,19 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 
 // Sum over the 64 lanes, in every lane.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return uint32_t(__builtin_amdgcn_readlane(int(wave_incl_scan(v)), 63)); }
+
+// Maximum over the 64 lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    auto take = [&](int o) { v = uint32_t(o) > v ? uint32_t(o) : v; };
+    take(__builtin_amdgcn_update_dpp(0, int(v), 0x111, 0xF, 0xF, true));   // row_shr:1, 2, 4, 8: lane 15 of a row has the row's
+    take(__builtin_amdgcn_update_dpp(0, int(v), 0x112, 0xF, 0xF, true));
+    take(__builtin_amdgcn_update_dpp(0, int(v), 0x114, 0xF, 0xF, true));
+    take(__builtin_amdgcn_update_dpp(0, int(v), 0x118, 0xF, 0xF, true));
+    take(__builtin_amdgcn_update_dpp(0, int(v), 0x142, 0xA, 0xF, false));  // row_bcast:15 -> rows 1, 3
+    take(__builtin_amdgcn_update_dpp(0, int(v), 0x143, 0xC, 0xF, false));  // row_bcast:31 -> rows 2, 3
+    return uint32_t(__builtin_amdgcn_readlane(int(v), 63));
+}
 
 // Sum of one double per lane, in every lane, in a fixed order: lane i with lane i ^ 32, then ^ 16, ^ 8, ^ 4, ^ 2,
 // ^ 1.  Moves inside the vector registers and no LDS, since a sum stands in every chain that other workgroups wait
@@ -1728,16 +1744,17 @@ __global__ __launch_bounds__(kWG) void k_place_tiled(const CompressArgs a)
 // Row strides of the two LDS tables.  With the natural strides (16 words, 8 words) the 64 lanes of
 // phase 1, which write one row each, would hit 2 and 4 of the 32 banks; 20 and 12 words spread
 // them over 8 banks and keep the rows 16-byte aligned for the wide reads of phase 2.
-constexpr uint32_t kOffStride = 20;  // uint32 per row, 16 used
-constexpr uint32_t kCntStride = 24;  // uint16 per row, 16 used
+template <uint32_t LG>
+constexpr uint32_t kOffStride = LG + 4u;  // uint32 per row, LG used
+constexpr uint32_t kCntStride = 24;  // uint16 per row, LG used
 
-// Phase 1 for learners k0 .. k0 + 15 and the bins [row0_bin, scan_end) of one 64-bin chunk: word
+// Phase 1 for learners k0 .. k0 + LG - 1 (LG = 8 or 16) and the bins [row0_bin, scan_end) of one 64-bin chunk: word
 // count and position of the first word of every (bin, learner), into the LDS tables (row = bin -
 // row0_bin).  The caller has a barrier before (the tables are free) and after (they are filled).
-template <bool W8>
+template <bool W8, uint32_t LG>
 __device__ __forceinline__ void unpack_tables(const UnpackArgs &a, const LayerDev &ld, const uint32_t layer,
                                               const uint32_t row0_bin, const uint32_t scan_end, const uint32_t k0,
-                                              uint32_t (*s_off)[kOffStride], uint16_t (*s_cnt)[kCntStride],
+                                              uint32_t (*s_off)[kOffStride<LG>], uint16_t (*s_cnt)[kCntStride],
                                               float *s_scale, uint32_t *s_cmax)
 {
     typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
@@ -1747,56 +1764,50 @@ __device__ __forceinline__ void unpack_tables(const UnpackArgs &a, const LayerDe
     const uint32_t b = (chunk << 6) + lane;           // the bin this lane looks up
     const bool in_scan = b < scan_end;                // bins of the chunk up to the end of the group
     const bool in_rows = in_scan && b >= row0_bin;
-    constexpr uint32_t kPerWave = kLearnerGroup / 4u;
-    const uint32_t nk = a.n_learners - k0 < kLearnerGroup ? a.n_learners - k0 : kLearnerGroup;
+    constexpr uint32_t kPerWave = LG / 4u;
+    const uint32_t nk = a.n_learners - k0 < LG ? a.n_learners - k0 : LG;
 
     if (tid == 0) *s_cmax = 0u;
     __syncthreads();
 
-    // wave w serves learners w, w + 4, ...; all their loads are issued first
-    uint32_t c[kPerWave], coff[kPerWave], wbase[kPerWave], limit[kPerWave];
-    float sc[kPerWave];
-    bool ok[kPerWave];
+    // Wave w serves learners w, w + 4, ...; all their loads are issued first: without a branch around them (learners
+    // past nk look at the first one's packet), and what is the same for all bins through scalar loads.
+    uint32_t wmax = 0u;
+    uint32_t c[kPerWave];
 #pragma unroll
     for (uint32_t q = 0; q < kPerWave; ++q) {
         const uint32_t kk = wave + 4u * q;
-        c[q] = 0u; coff[q] = 0u; wbase[q] = 0u; limit[q] = 0u; sc[q] = 0.f; ok[q] = false;
-        if (kk < nk) {
-            const uint8_t *pk = a.packets[k0 + kk];
-            const uint4 hv = *reinterpret_cast<const uint4 *>(pk);  // magic, version, status, n_layers
-            const uint2 tb = *reinterpret_cast<const uint2 *>(pk + 16);  // total_bytes
-            ok[q] = (hv.x == ADACOMP_PACKET_MAGIC) & (hv.y == ADACOMP_PACKET_VERSION) &
-                    (hv.z == ADACOMP_STATUS_COMPLETE) & (hv.w == a.n_layers) & (tb.y == 0u);
-            limit[q] = tb.x / uint32_t(sizeof(word_t));  // words that fit in the packet
-            // counts and chunk offsets sit in the fixed part, which every packet buffer holds
-            if (in_scan) c[q] = reinterpret_cast<const word_t *>(pk + ld.counts_offset)[b];
-            coff[q] = reinterpret_cast<const uint32_t *>(pk + ld.chunks_offset)[chunk];
-            const adacomp_packet_layer_t *rec =
-                reinterpret_cast<const adacomp_packet_layer_t *>(pk + sizeof(adacomp_packet_header_t)) + layer;
-            sc[q] = rec->scale;
-            wbase[q] = uint32_t(rec->words_offset / sizeof(word_t));  // packets stay below 2^32 words (host check)
-        }
+        // counts and chunk offsets sit in the fixed part, which every packet buffer holds
+        c[q] = reinterpret_cast<const word_t *>(a.packets[k0 + (kk < nk ? kk : 0u)] + ld.counts_offset)[in_scan ? b : row0_bin];
     }
-    uint32_t wmax = 0u;
 #pragma unroll
     for (uint32_t q = 0; q < kPerWave; ++q) {
-        const uint32_t kk = wave + 4u * q;  // < kLearnerGroup; learners past nk get empty entries
-        const uint32_t cq = ok[q] ? c[q] : 0u;   // a packet that does not match contributes nothing
+        const uint32_t kk = wave + 4u * q;  // < LG; learners past nk get empty entries
+        const uint8_t *const pk = a.packets[k0 + (kk < nk ? kk : 0u)];
+        const vuint4 hv = packet_field<vuint4>(pk);        // magic, version, status, n_layers
+        const vuint2 tb = packet_field<vuint2>(pk + 16);   // total_bytes
+        const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
+        const uint32_t wbase = uint32_t(packet_field<uint64_t>(rec + offsetof(adacomp_packet_layer_t, words_offset)) / sizeof(word_t));  // packets stay below 2^32 words (host check)
+        const uint32_t coff = packet_field<uint32_t>(pk + ld.chunks_offset + 4u * chunk);
+        const float sc = packet_field<float>(rec + offsetof(adacomp_packet_layer_t, scale));
+        const bool ok = (kk < nk) & (hv.x == ADACOMP_PACKET_MAGIC) & (hv.y == ADACOMP_PACKET_VERSION) &
+                        (hv.z == ADACOMP_STATUS_COMPLETE) & (hv.w == a.n_layers) & (tb.y == 0u);
+        const uint32_t limit = tb.x / uint32_t(sizeof(word_t));  // words that fit in the packet
+        const uint32_t cq = ok && in_scan ? c[q] : 0u;   // a packet that does not match contributes nothing
         const uint32_t incl = wave_incl_scan(cq);
         // A bin whose words would lie past the packet's total_bytes (counts or offsets that do not
         // belong together) contributes nothing: no word is read from outside the packet.
-        const uint64_t first = uint64_t(wbase[q]) + coff[q] + (incl - cq);
-        const bool inside = first + cq <= limit[q];
+        const uint64_t first = uint64_t(wbase) + coff + (incl - cq);
+        const bool inside = first + cq <= limit;
         const uint32_t cw = inside ? cq : 0u;
         if (in_rows) {
             s_off[b - row0_bin][kk] = inside ? uint32_t(first) : 0u;
             s_cnt[b - row0_bin][kk] = uint16_t(cw);
         }
-        if (lane == 0) s_scale[kk] = sc[q];
+        if (lane == 0) s_scale[kk] = sc;
         wmax = (in_rows && cw > wmax) ? cw : wmax;
     }
-#pragma unroll
-    for (uint32_t d = 32; d > 0; d >>= 1) { const uint32_t o = __shfl_xor(wmax, d, 64); wmax = o > wmax ? o : wmax; }
+    wmax = wave_max(wmax);
     if (lane == 0) atomicMax(s_cmax, wmax);
 }
 
@@ -1818,15 +1829,15 @@ __device__ __forceinline__ void lds_add(float *acc, const uint32_t idx, const fl
 }
 
 // Phase 2 for one tile: a lane group owns a bin (table row row0 + bin index inside the tile).
-template <bool W8>
+template <bool W8, uint32_t LG>
 __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev &ut, const uint32_t row0, const uint32_t k0,
-                                            float *s_acc, uint32_t (*s_off)[kOffStride],
+                                            float *s_acc, uint32_t (*s_off)[kOffStride<LG>],
                                             uint16_t (*s_cnt)[kCntStride], const float *s_scale, const uint32_t *s_cmax)
 {
     typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
     const uint32_t tid = threadIdx.x;
     const uint32_t n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
-    const uint32_t nk = a.n_learners - k0 < kLearnerGroup ? a.n_learners - k0 : kLearnerGroup;
+    const uint32_t nk = a.n_learners - k0 < LG ? a.n_learners - k0 : LG;
     if (W8) {
         // Short bins (8-bit words) send several words each, about 8 % of the elements on the
         // ResNet-50 table.  Four lanes own a bin and lane j fetches the aligned 4 bytes number j of
@@ -1840,7 +1851,7 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
         // 8 learners at a time, to keep the register count (and with it the number of resident
         // workgroups) where the 16-bit path has it
 #pragma unroll 1
-        for (uint32_t h0 = 0; h0 < kLearnerGroup; h0 += 8u) {
+        for (uint32_t h0 = 0; h0 < LG; h0 += 8u) {
             if (h0 >= nk) break;
             uint32_t cc[8], off[8], packed[8];
             {
@@ -1914,22 +1925,22 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
         const uint32_t row = row0 + lb;
         const uint32_t span = T < n - lb * T ? T : n - lb * T;  // elements of this bin held by the tile
         float *acc = s_acc + lb * T;
-        uint32_t cc[kLearnerGroup], off[kLearnerGroup];
+        uint32_t cc[LG], off[LG];
 #pragma unroll
-        for (uint32_t v = 0; v < kLearnerGroup / 8u; ++v) {
+        for (uint32_t v = 0; v < LG / 8u; ++v) {
             const uint4 t = *reinterpret_cast<const uint4 *>(&s_cnt[row][8u * v]);
             cc[8 * v] = t.x & 0xFFFFu; cc[8 * v + 1] = t.x >> 16; cc[8 * v + 2] = t.y & 0xFFFFu; cc[8 * v + 3] = t.y >> 16;
             cc[8 * v + 4] = t.z & 0xFFFFu; cc[8 * v + 5] = t.z >> 16; cc[8 * v + 6] = t.w & 0xFFFFu; cc[8 * v + 7] = t.w >> 16;
         }
 #pragma unroll
-        for (uint32_t v = 0; v < kLearnerGroup / 4u; ++v) {
+        for (uint32_t v = 0; v < LG / 4u; ++v) {
             const uint4 t = *reinterpret_cast<const uint4 *>(&s_off[row][4u * v]);
             off[4 * v] = t.x; off[4 * v + 1] = t.y; off[4 * v + 2] = t.z; off[4 * v + 3] = t.w;
         }
-        uint32_t word[kLearnerGroup];
+        uint32_t word[LG];
         uint32_t cmax = 0u;
 #pragma unroll
-        for (uint32_t kk = 0; kk < kLearnerGroup; ++kk) {
+        for (uint32_t kk = 0; kk < LG; ++kk) {
             cmax = cc[kk] > cmax ? cc[kk] : cmax;
             word[kk] = 0u;
             if (sub < cc[kk]) {
@@ -1939,7 +1950,7 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
         }
         if (cmax <= gsz) {
 #pragma unroll
-            for (uint32_t kk = 0; kk < kLearnerGroup; ++kk) {
+            for (uint32_t kk = 0; kk < LG; ++kk) {
                 const uint32_t idx = (word[kk] >> 2) - ut.idx_lo;  // wraps to a huge value below idx_lo
                 const uint32_t code = word[kk] & 3u;
                 if ((code & 1u) && idx < span) { const float sck = s_scale[kk]; atomicAdd(&acc[idx], code == 1u ? sck : -sck); }
@@ -1994,46 +2005,19 @@ __device__ __forceinline__ void apply_update(const UnpackArgs &a, float sum, flo
 
 // LDS of a group of 16-bit layers inside k_unpack8 (k_unpack has the same arrays of its own: laid out in a
 // structure they cost it 2 %)
+template <uint32_t LG>
 struct UnpackLds {
     __attribute__((aligned(16))) float acc[kUnpackTileElems];
-    __attribute__((aligned(16))) uint32_t off[64][kOffStride];  // first word of (bin, learner), counted from the packet start
+    __attribute__((aligned(16))) uint32_t off[64][kOffStride<LG>];  // first word of (bin, learner), counted from the packet start
     __attribute__((aligned(16))) uint16_t cnt[64][kCntStride];
-    __attribute__((aligned(16))) float scale[kLearnerGroup];
+    __attribute__((aligned(16))) float scale[LG];
     uint32_t cmax;                                              // largest word count of a (bin, learner) in the tables
 };
 
-// MODE 0: dense_out <- sum.  MODE 1 / 2: also (or only) the SGD / Adam step on weights and state.
-// KIND 0 / 1: all groups of this launch belong to layers with 16-bit / 8-bit words; 2: either (the
-// layer says which).  Large tables get one launch per kind: each path alone needs fewer registers
-// than a kernel that holds both, which buys resident workgroups (8 % of the 16-bit path's time on
-// the 125 M-element table).  Small tables, where a second launch would cost more than that, use
-// the kernel that holds both.  The single-width kernels are held to 80 registers (6 waves per
-// SIMD, what the LDS tile allows; the 16-bit path spills two).
-template <int MODE, int KIND>
-__device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride],
-                                             uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
+// Clears the accumulators of a tile of n elements, or loads the partial sum of an earlier launch.
+__device__ __forceinline__ void unpack_clear(const UnpackArgs &a, const uint32_t n, const bool vec, const float *__restrict__ out, float *const s_acc)
 {
-    // A workgroup serves a group of consecutive tiles that lie in one 64-bin chunk (or are slices
-    // of one long bin).  With up to 16 learners the tables of phase 1 are built once for the group.
-    const UGroupDev grp = a.groups[group];
-    const UTileDev ut0 = a.tiles[grp.first_tile];
-    const UTileDev ut_last = a.tiles[grp.first_tile + grp.n_tiles - 1u];
-    const uint32_t layer = ut0.layer();
-    const LayerDev ld = a.layers[layer];
     const uint32_t tid = threadIdx.x;
-    const uint32_t row0_bin = ut0.first_bin, scan_end = ut_last.first_bin + ut_last.n_bins;
-    const bool tables_once = a.n_learners <= kLearnerGroup;
-    const bool w8 = KIND == 2 ? ld.word_bytes == 1u : KIND == 1;
-
-
-  for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
-    const UTileDev ut = ti == 0u ? ut0 : a.tiles[grp.first_tile + ti];
-    const uint32_t n = ut.n_elems;
-    const bool vec = ut.aligned();
-    float *__restrict__ out = a.dense + ut.elem_base;
-
-    __syncthreads();  // the previous tile has been written out and its adds are done with the tables
-    // ---- tile accumulators: zero, or the partial sum of an earlier launch ----------------------
     for (uint32_t i = tid * 4u; i < n; i += kWG * 4u) {
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (a.accumulate) {
@@ -2047,19 +2031,16 @@ __device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t
         }
         *reinterpret_cast<float4 *>(&s_acc[i]) = v;  // s_acc has room for the rounded-up tail
     }
+}
 
-    for (uint32_t k0 = 0; k0 < a.n_learners; k0 += kLearnerGroup) {
-        if (!tables_once || ti == 0u) {
-            if (k0 != 0u) __syncthreads();  // the adds of the previous 16 learners are done with the tables
-            if (w8) unpack_tables<true>(a, ld, layer, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
-            else unpack_tables<false>(a, ld, layer, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
-        }
-        __syncthreads();  // tables filled, accumulators initialised
-        if (w8) unpack_adds<true>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax);
-        else unpack_adds<false>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax);
-    }
-    __syncthreads();
-
+// Writes a finished tile out: the sum, the optimizer's step, or both.
+template <int MODE>
+__device__ __forceinline__ void unpack_write_out(const UnpackArgs &a, const UTileDev &ut, float *const s_acc)
+{
+    const uint32_t tid = threadIdx.x;
+    const uint32_t n = ut.n_elems;
+    const bool vec = ut.aligned();
+    float *__restrict__ out = a.dense + ut.elem_base;
     float *const W = MODE == 1 ? a.weights + ut.elem_base : nullptr;
     float *const S1 = MODE == 1 ? a.state1 + ut.elem_base : nullptr;
     const __amdgpu_buffer_rsrc_t w_buf = tile_buffer(MODE == 2 ? a.weights + ut.elem_base : out, MODE == 2 ? n : 0u);
@@ -2123,19 +2104,232 @@ __device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t
             }
         }
     }
+}
+
+// MODE 0: dense_out <- sum.  MODE 1 / 2: also (or only) the SGD / Adam step on weights and state.
+// KIND 0 / 1: all groups of this launch belong to layers with 16-bit / 8-bit words; 2: either (the
+// layer says which).  Large tables get one launch per kind: each path alone needs fewer registers
+// than a kernel that holds both, which buys resident workgroups (8 % of the 16-bit path's time on
+// the 125 M-element table).  Small tables, where a second launch would cost more than that, use
+// the kernel that holds both.  The single-width kernels are held to 80 registers (6 waves per
+// SIMD, what the LDS tile allows; the 16-bit path spills two).
+template <int MODE, int KIND, uint32_t LG>
+__device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
+                                             uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
+{
+    // A workgroup serves a group of consecutive tiles that lie in one 64-bin chunk (or are slices
+    // of one long bin).  With up to LG learners the tables of phase 1 are built once for the group.
+    const UGroupDev grp = a.groups[group];
+    const UTileDev ut0 = a.tiles[grp.first_tile];
+    const UTileDev ut_last = a.tiles[grp.first_tile + grp.n_tiles - 1u];
+    const uint32_t layer = ut0.layer();
+    const LayerDev ld = a.layers[layer];
+    const uint32_t row0_bin = ut0.first_bin, scan_end = ut_last.first_bin + ut_last.n_bins;
+    const bool tables_once = a.n_learners <= LG;
+    const bool w8 = KIND == 2 ? ld.word_bytes == 1u : KIND == 1;
+
+
+  for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
+    const UTileDev ut = ti == 0u ? ut0 : a.tiles[grp.first_tile + ti];
+    const uint32_t n = ut.n_elems;
+    const bool vec = ut.aligned();
+    float *__restrict__ out = a.dense + ut.elem_base;
+
+    __syncthreads();  // the previous tile has been written out and its adds are done with the tables
+    unpack_clear(a, n, vec, out, s_acc);
+
+    for (uint32_t k0 = 0; k0 < a.n_learners; k0 += LG) {
+        if (!tables_once || ti == 0u) {
+            if (k0 != 0u) __syncthreads();  // the adds of the previous learners are done with the tables
+            if (w8) unpack_tables<true, LG>(a, ld, layer, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
+            else unpack_tables<false, LG>(a, ld, layer, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
+        }
+        __syncthreads();  // tables filled, accumulators initialised
+        if (w8) unpack_adds<true, LG>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax);
+        else unpack_adds<false, LG>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax);
+    }
+    __syncthreads();
+
+    unpack_write_out<MODE>(a, ut, s_acc);
   }  // tiles of the group
 }
 
-template <int MODE, int KIND>
+template <int MODE, int KIND, uint32_t LG>
 __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const UnpackArgs a)
 {
     if (blockIdx.x >= a.n_groups) return;
     __shared__ float s_acc[kUnpackTileElems];
-    __shared__ __attribute__((aligned(16))) uint32_t s_off[64][kOffStride];  // first word of (bin, learner), counted from the packet start
+    __shared__ __attribute__((aligned(16))) uint32_t s_off[64][kOffStride<LG>];  // first word of (bin, learner), counted from the packet start
     __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64][kCntStride];
-    __shared__ __attribute__((aligned(16))) float s_scale[kLearnerGroup];
+    __shared__ __attribute__((aligned(16))) float s_scale[LG];
     __shared__ uint32_t s_cmax;                                                // largest word count of a (bin, learner) in the tables
-    unpack_group<MODE, KIND>(a, blockIdx.x, s_acc, s_off, s_cnt, s_scale, s_cmax);
+    unpack_group<MODE, KIND, LG>(a, blockIdx.x, s_acc, s_off, s_cnt, s_scale, s_cmax);
+}
+
+// ==============================================================================================
+// k_unpack_few: up to four learners.  Every wave holds what phase 1 of k_unpack puts into tables in LDS in its registers, lane = bin of the
+// chunk, and hands it to the lane groups of its bins with lane permutes: no tables, no barrier between the two phases,
+// and the headers come through scalar loads, all in flight together.  Bound by memory on large tables, by the chain
+// group, tile, layer, counts, words, adds on small ones.  k_unpack / this kernel, in us: 100 k elements, L_T 500, 1
+// packet 5.7 / 4.6; 1 M, Adam, 1 packet 10.8 / 8.2; 8 M, 2 packets 12.3 / 8.9; L_T 133, 4 packets 18.6 / 12.5; ResNet-50's
+// table, SGD with 1 packet 84 / 72, Adam with 4 128 / 116.  With 5 to 8 learners it loses: what every wave does for
+// itself is then most of its work (8 M, 8 packets: 13.0, k_unpack 10.6).
+// ==============================================================================================
+constexpr uint32_t kFewLearners = 4;
+// In the launch of k_unpack8, where they share the LDS and the registers of its chunks, the groups of the 16-bit layers
+// take this form for up to two learners (ResNet-50's table, k_unpack's form / this one: 1 packet 20.3 / 20.0 us, 2 22.1 /
+// 20.9, but 4 25.2 / 26.7).
+constexpr uint32_t kFewInLaunch8 = 2;
+template <int MODE, bool W8>
+__device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGroupDev grp, const UTileDev ut0, const LayerDev ld, float *const s_acc)
+{
+    typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t layer = ut0.layer(), chunk = ut0.first_bin >> 6, bin = (chunk << 6) + lane;
+
+    constexpr uint32_t NK = kFewLearners;
+    // word count and first word (counted from the packet's start) of the lane's bin, for every learner
+    uint32_t c[NK], off[NK];
+    float scale[NK];
+#pragma unroll
+    for (uint32_t k = 0; k < NK; ++k) {
+        const uint8_t *const pk = a.packets[k < a.n_learners ? k : 0u];
+        c[k] = reinterpret_cast<const word_t *>(pk + ld.counts_offset)[bin < ld.n_bins ? bin : 0u];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < NK; ++k) {
+        const uint8_t *const pk = a.packets[k < a.n_learners ? k : 0u];
+        const vuint4 hv = packet_field<vuint4>(pk);        // magic, version, status, n_layers
+        const vuint2 tb = packet_field<vuint2>(pk + 16);   // total_bytes
+        const bool ok = (k < a.n_learners) & (hv.x == ADACOMP_PACKET_MAGIC) & (hv.y == ADACOMP_PACKET_VERSION) &
+                        (hv.z == ADACOMP_STATUS_COMPLETE) & (hv.w == a.n_layers) & (tb.y == 0u);
+        const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
+        const uint32_t words = uint32_t(packet_field<uint64_t>(rec + offsetof(adacomp_packet_layer_t, words_offset)) / sizeof(word_t));
+        const uint32_t before = packet_field<uint32_t>(pk + ld.chunks_offset + 4u * chunk);
+        scale[k] = packet_field<float>(rec + offsetof(adacomp_packet_layer_t, scale));
+        const uint32_t ck = ok && bin < ld.n_bins ? c[k] : 0u;   // a packet that does not match contributes nothing
+        // nor does a bin whose words would lie past the packet's total_bytes
+        const uint64_t first = uint64_t(words) + before + (wave_incl_scan(ck) - ck);
+        c[k] = first + ck <= tb.x / uint32_t(sizeof(word_t)) ? ck : 0u;
+        off[k] = uint32_t(first);
+    }
+
+    for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
+        const UTileDev ut = ti == 0u ? ut0 : table_record<vuint8>(a.tiles + grp.first_tile + ti);
+        const uint32_t n = ut.n_elems, T = ut.L_T, nb = ut.n_bins, bin0 = ut.first_bin & 63u;
+        if (ti != 0u) __syncthreads();   // the previous tile has been written out
+        unpack_clear(a, n, ut.aligned(), a.dense + ut.elem_base, s_acc);
+        __syncthreads();
+        if (W8) {
+            // Four lanes to a bin, lane j fetches the aligned 4 bytes number j of the bin's run of words (what is
+            // beyond these 16 bytes comes byte by byte)
+            const uint32_t lb = tid >> 2, sub = tid & 3u;
+            const uint32_t span = lb < nb ? (T < n - lb * T ? T : n - lb * T) : 0u;   // elements of this bin
+            volatile lds_float *const vacc = lds_volatile(s_acc + lb * T);
+            uint32_t cc[NK], at[NK], packed[NK];
+#pragma unroll
+            for (uint32_t k = 0; k < NK; ++k) {
+                cc[k] = uint32_t(__shfl(int(c[k]), int(lb), 64));
+                at[k] = uint32_t(__shfl(int(off[k]), int(lb), 64));
+                packed[k] = 0u;
+                // word sections start on 16-byte boundaries and are padded to them, so the aligned
+                // 4 bytes around any word of the run lie inside the packet
+                if (cc[k] != 0u && 4u * sub < (at[k] & 3u) + cc[k])
+                    packed[k] = reinterpret_cast<const uint32_t *>(a.packets[k < a.n_learners ? k : 0u])[(at[k] >> 2) + sub];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < NK; ++k) {
+                if (k >= a.n_learners) break;   // uniform
+                __builtin_amdgcn_sched_barrier(0);   // one learner at a time: keeps the register count down
+                // The words of this lane: bytes [beg, end) of its four, moved to the front so that slot j is in use in
+                // every lane that has more than j words and a slot that no lane of the wave uses costs nothing.  One
+                // learner's words name different elements: all loads of the accumulators, then the stores.
+                const uint32_t skew = at[k] & 3u, lo = 4u * sub, end_all = skew + cc[k];
+                const uint32_t beg = skew > lo ? (skew - lo < 4u ? skew - lo : 4u) : 0u;
+                const uint32_t end = end_all > lo ? (end_all - lo < 4u ? end_all - lo : 4u) : 0u;
+                const uint32_t nw = end > beg ? end - beg : 0u;
+                const uint32_t mine = beg < 4u ? packed[k] >> (8u * beg) : 0u;
+                float cur[4];
+                bool on[4];
+#pragma unroll
+                for (uint32_t j = 0; j < 4u; ++j) {
+                    on[j] = false;
+                    cur[j] = 0.f;
+                    if (__builtin_amdgcn_ballot_w64(j < nw) != 0ull) {
+                        const uint32_t w = (mine >> (8u * j)) & 0xFFu;
+                        on[j] = j < nw && (w & 1u) && (w >> 2) < span;
+                        if (on[j]) cur[j] = vacc[w >> 2];
+                    }
+                }
+#pragma unroll
+                for (uint32_t j = 0; j < 4u; ++j) {
+                    const uint32_t w = (mine >> (8u * j)) & 0xFFu;
+                    if (on[j]) vacc[w >> 2] = cur[j] + ((w & 2u) ? -scale[k] : scale[k]);
+                }
+                if (end_all > 16u) {   // the words of this learner beyond the fetched 16 bytes
+                    const uint8_t *const wp = a.packets[k] + at[k];
+                    for (uint32_t q = 16u - skew + sub; q < cc[k]; q += 4u) {
+                        const uint32_t w = wp[q];
+                        if ((w & 1u) && (w >> 2) < span) vacc[w >> 2] = vacc[w >> 2] + ((w & 2u) ? -scale[k] : scale[k]);
+                    }
+                }
+            }
+        } else {
+        uint32_t most = 0u;   // words of the lane's bin from the learner that sends most
+#pragma unroll
+        for (uint32_t k = 0; k < NK; ++k) most = c[k] > most ? c[k] : most;
+        // lanes per bin: what makes use of all threads, more if a bin of the tile has more words
+        uint32_t glog = nb >= 16u ? 4u : nb >= 8u ? 5u : 6u;
+        while (glog < 6u && __builtin_amdgcn_ballot_w64(lane >= bin0 && lane < bin0 + nb && most > (1u << glog)) != 0ull) ++glog;
+        const uint32_t gsz = 1u << glog;
+        for (uint32_t s = tid; s < (((nb << glog) + 63u) & ~63u); s += kWG) {   // (whole waves: the permutes need all lanes)
+            const uint32_t lb = s >> glog, sub = s & (gsz - 1u);
+            const uint32_t from = (bin0 + lb) & 63u;
+            const bool live = lb < nb;
+            const uint32_t span = live ? (T < n - lb * T ? T : n - lb * T) : 0u;   // elements of this bin held by the tile
+            float *const acc = s_acc + lb * T;
+            uint32_t cc[NK], word[NK], cmax = 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < NK; ++k) {
+                cc[k] = uint32_t(__shfl(int(c[k]), int(from), 64));
+                const uint32_t at = uint32_t(__shfl(int(off[k]), int(from), 64)) + sub;
+                cmax = cc[k] > cmax ? cc[k] : cmax;
+                word[k] = 0u;
+                if (live && sub < cc[k]) word[k] = reinterpret_cast<const word_t *>(a.packets[k < a.n_learners ? k : 0u])[at];
+            }
+            if (__builtin_amdgcn_ballot_w64(live && cmax > gsz) == 0ull) {
+#pragma unroll
+                for (uint32_t k = 0; k < NK; ++k) {
+                    const uint32_t idx = (word[k] >> 2) - ut.idx_lo;   // wraps to a huge value below idx_lo
+                    if ((word[k] & 1u) && idx < span) atomicAdd(&acc[idx], (word[k] & 2u) ? -scale[k] : scale[k]);
+                }
+            } else {   // a bin with more words than lanes: one learner after the other
+#pragma unroll
+                for (uint32_t k = 0; k < NK; ++k) {
+                    const word_t *const wp = reinterpret_cast<const word_t *>(a.packets[k < a.n_learners ? k : 0u]) + uint32_t(__shfl(int(off[k]), int(from), 64));
+                    for (uint32_t q = sub; live && q < cc[k]; q += gsz) {
+                        const uint32_t w = wp[q], idx = (w >> 2) - ut.idx_lo;
+                        if ((w & 1u) && idx < span) atomicAdd(&acc[idx], (w & 2u) ? -scale[k] : scale[k]);
+                    }
+                }
+            }
+        }
+        }
+        __syncthreads();
+        unpack_write_out<MODE>(a, ut, s_acc);
+    }
+}
+
+// KIND as in k_unpack
+template <int MODE, int KIND>
+__global__ __launch_bounds__(kWG, 6) void k_unpack_few(const UnpackArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float s_acc[kUnpackTileElems];
+    const UGroupDev grp = table_record<vuint2>(a.groups + blockIdx.x);
+    const UTileDev ut0 = table_record<vuint8>(a.tiles + grp.first_tile);
+    const LayerDev ld = table_record<vuint16>(a.layers + ut0.layer());
+    if (KIND == 1 || (KIND == 2 && ld.word_bytes == 1u)) unpack_group_few<MODE, true>(a, grp, ut0, ld, s_acc);
+    else unpack_group_few<MODE, false>(a, grp, ut0, ld, s_acc);
 }
 
 // ==============================================================================================
@@ -2153,9 +2347,6 @@ __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const Unpac
 // All adds to one element come from one lane in program order, and the LDS unit executes a wave's
 // operations in order: the sum is taken learner 0 first.
 // ==============================================================================================
-template <class V>
-__device__ __forceinline__ V packet_field(const uint8_t *p) { return *(const __attribute__((address_space(4))) V *)p; }
-
 template <int MODE>
 __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_t group, float *acc_chunk)
 {
@@ -2286,15 +2477,21 @@ __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_
     }
 }
 
-// The first n_groups workgroups take a group of the 16-bit layers each, the others four chunks of the
-// 8-bit ones.  Dynamic LDS: launch_unpack.
-template <int MODE>
+// The first n_groups workgroups take a group of the 16-bit layers each, the others up to four chunks of the
+// 8-bit ones.  Dynamic LDS: launch_unpack.  LG: 4 (k_unpack_few), 8 or 16 learners to a group of the former.
+template <int MODE, uint32_t LG>
 __global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
     if (blockIdx.x < a.n_groups) {
-        UnpackLds &lds = *reinterpret_cast<UnpackLds *>(s_dyn);
-        unpack_group<MODE, 0>(a, a.first16 + blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+        if constexpr (LG == kFewLearners) {
+            const UGroupDev grp = table_record<vuint2>(a.groups + a.first16 + blockIdx.x);
+            const UTileDev ut0 = table_record<vuint8>(a.tiles + grp.first_tile);
+            unpack_group_few<MODE, false>(a, grp, ut0, table_record<vuint16>(a.layers + ut0.layer()), reinterpret_cast<float *>(s_dyn));
+        } else {
+            UnpackLds<LG> &lds = *reinterpret_cast<UnpackLds<LG> *>(s_dyn);
+            unpack_group<MODE, 0, LG>(a, a.first16 + blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+        }
         return;
     }
     uint32_t r = blockIdx.x - a.n_groups;
@@ -2447,27 +2644,40 @@ int launch_unpack(const UnpackArgs &a, int kind, void *stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (a.n_groups == 0 && kind != 3) return ADACOMP_OK;
     const dim3 grid(a.n_groups), wg(kWG);
+    uint32_t lds = 0;
+    auto launch = [&](const dim3 &workgroups, auto kernel) { hipLaunchKernelGGL(kernel, workgroups, wg, lds, s, a); };
+    auto with_mode = [&](auto &&go) {
+        if (a.mode == 1) go(std::integral_constant<int, 1>());
+        else if (a.mode == 2) go(std::integral_constant<int, 2>());
+        else go(std::integral_constant<int, 0>());
+    };
+    const bool few = a.n_learners != 0u && a.n_learners <= kFewLearners, eight = a.n_learners <= 8u;
     if (kind == 3) {
         const uint32_t wg_log = a.chunk_lds & 63u, chunk_elems = a.chunk_lds & ~63u;
         if (a.n_groups8 == 0 || chunk_elems == 0 || chunk_elems > 64u * 64u || wg_log > 2u) return ADACOMP_EINVAL;
         const dim3 both(a.n_groups + ((a.n_groups8 + (1u << wg_log) - 1u) >> wg_log));
-        const uint32_t lds = std::max(uint32_t(sizeof(UnpackLds)), 4u * chunk_elems << wg_log);
-        if (a.mode == 1) hipLaunchKernelGGL((k_unpack8<1>), both, wg, lds, s, a);
-        else if (a.mode == 2) hipLaunchKernelGGL((k_unpack8<2>), both, wg, lds, s, a);
-        else hipLaunchKernelGGL((k_unpack8<0>), both, wg, lds, s, a);
-    } else if (kind == 1) {
-        if (a.mode == 1) hipLaunchKernelGGL((k_unpack<1, 1>), grid, wg, 0, s, a);
-        else if (a.mode == 2) hipLaunchKernelGGL((k_unpack<2, 1>), grid, wg, 0, s, a);
-        else hipLaunchKernelGGL((k_unpack<0, 1>), grid, wg, 0, s, a);
-    } else if (kind == 0) {
-        if (a.mode == 1) hipLaunchKernelGGL((k_unpack<1, 0>), grid, wg, 0, s, a);
-        else if (a.mode == 2) hipLaunchKernelGGL((k_unpack<2, 0>), grid, wg, 0, s, a);
-        else hipLaunchKernelGGL((k_unpack<0, 0>), grid, wg, 0, s, a);
-    } else {
-        if (a.mode == 1) hipLaunchKernelGGL((k_unpack<1, 2>), grid, wg, 0, s, a);
-        else if (a.mode == 2) hipLaunchKernelGGL((k_unpack<2, 2>), grid, wg, 0, s, a);
-        else hipLaunchKernelGGL((k_unpack<0, 2>), grid, wg, 0, s, a);
+        const bool two = a.n_learners != 0u && a.n_learners <= kFewInLaunch8;
+        const uint32_t groups = a.n_groups == 0u ? 0u : two ? 4u * kUnpackTileElems : uint32_t(eight ? sizeof(UnpackLds<8>) : sizeof(UnpackLds<16>));
+        lds = std::max(groups, 4u * chunk_elems << wg_log);
+        with_mode([&](auto mode) {
+            constexpr int M = decltype(mode)::value;
+            if (two) launch(both, k_unpack8<M, kFewLearners>);
+            else if (eight) launch(both, k_unpack8<M, 8>);
+            else launch(both, k_unpack8<M, 16>);
+        });
+        return check_launch();
     }
+    with_mode([&](auto mode) {
+        constexpr int M = decltype(mode)::value;
+        auto width = [&](auto k0, auto k1, auto k2) {
+            if (kind == 0) launch(grid, k0);
+            else if (kind == 1) launch(grid, k1);
+            else launch(grid, k2);
+        };
+        if (few) width(k_unpack_few<M, 0>, k_unpack_few<M, 1>, k_unpack_few<M, 2>);
+        else if (eight) width(k_unpack<M, 0, 8>, k_unpack<M, 1, 8>, k_unpack<M, 2, 8>);
+        else width(k_unpack<M, 0, 16>, k_unpack<M, 1, 16>, k_unpack<M, 2, 16>);
+    });
     return check_launch();
 }
 

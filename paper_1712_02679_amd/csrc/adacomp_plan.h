@@ -19,7 +19,6 @@ constexpr uint32_t kComputeUnits = 256;  // of an MI355X: what a small table's t
 // 12 % slower with the optimizer epilogue)
 constexpr uint32_t kUnpackTileElems = 4096;
 constexpr uint32_t kMaxBatch = 32;  // learners per launch of the compress kernels
-constexpr uint32_t kLearnerGroup = 16;   // learners whose bin tables sit in LDS together in unpack
 constexpr uint32_t kMaxPacketArgs = 64;  // packet pointers passed by value per unpack launch
 
 // A layer as the kernels see it (64 bytes).
