@@ -383,6 +383,14 @@ void register_workspace(const adacomp_layer_t *layers, uint32_t n_layers, const 
     g_ws[workspace] = std::move(reg);
 }
 
+// Workgroups per compute unit for launches over the 16-bit layers (see kResidentLds); 0: as many as fit.
+static uint32_t resident_for(uint32_t n_tiles, uint32_t n_learners, uint32_t mode)
+{
+    if (n_tiles < (mode != 0u ? kResidentTiles : kResidentTilesSum)) return 0u;
+    if (mode == 2u) return n_learners <= 8u ? 4u : 5u;
+    return n_learners <= 8u ? 5u : 0u;
+}
+
 // Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack and k_unpack_few (a workgroup)?
 // A wave adds learner after learner, about a microsecond each, which pays where there are chunks enough to cover
 // it (256 bytes of LDS to each element of L_T: 12 chunks are on a compute unit at L_T 50, 10 at 64, more
@@ -889,6 +897,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         // runs of tiles per workgroup for the plain sum, single tiles when the optimizer step follows
         const UGroupDev *table = reinterpret_cast<const UGroupDev *>(ws + (a.mode == 0u ? p.ws.ugroups : p.ws.usingles));
         const uint32_t n_all = a.mode == 0u ? p.n_ugroups : p.n_utiles, n8 = a.mode == 0u ? p.n_ugroups8 : p.n_usingles8;
+        const uint32_t n_tiles16 = p.n_utiles - p.n_usingles8;
         a.groups = table;
         a.n_groups = n_all;
         a.n_groups8 = a.first16 = a.chunk_lds = 0u;
@@ -898,17 +907,17 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
             a.n_groups = n_all - n8;
             a.first16 = uint32_t(table - a.groups) + n8;
             a.chunk_lds = 64u * p.short_bin_max + unpack8_wg_log(p, n8, a.n_groups, now);
-            if ((rc = launch_unpack(a, 3, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 3, 0u, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
-            if ((rc = launch_unpack(a, n8 ? 1 : 0, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, n8 ? 1 : 0, n8 ? 0u : resident_for(n_tiles16, now, a.mode), hip_stream)) != ADACOMP_OK) return rc;
         } else if (p.n_utiles <= kUnpackSplitTiles || (now <= 4u && now != 0u)) {  // mixed, and small or with few registers per path (k_unpack_few): one launch that handles both
-            if ((rc = launch_unpack(a, 2, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 2, 0u, hip_stream)) != ADACOMP_OK) return rc;
         } else {  // large and mixed: the 8-bit groups come first in the table
             a.n_groups = n8;
-            if ((rc = launch_unpack(a, 1, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 1, 0u, hip_stream)) != ADACOMP_OK) return rc;
             a.groups = table + n8;
             a.n_groups = n_all - n8;
-            if ((rc = launch_unpack(a, 0, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 0, resident_for(n_tiles16, now, a.mode), hip_stream)) != ADACOMP_OK) return rc;
         }
         done += now;
     } while (done < n_learners);

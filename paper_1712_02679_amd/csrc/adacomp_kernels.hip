@@ -2639,7 +2639,8 @@ int launch_place(const CompressArgs &a, void *stream)
     return check_launch();
 }
 
-int launch_unpack(const UnpackArgs &a, int kind, void *stream)
+// resident: workgroups per compute unit that the launch is held to (5 or 4), or 0.
+int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (a.n_groups == 0 && kind != 3) return ADACOMP_OK;
@@ -2652,6 +2653,9 @@ int launch_unpack(const UnpackArgs &a, int kind, void *stream)
         else go(std::integral_constant<int, 0>());
     };
     const bool few = a.n_learners != 0u && a.n_learners <= kFewLearners, eight = a.n_learners <= 8u;
+    // what a workgroup of these kernels has (kind 3: for a group of the 16-bit layers)
+    const uint32_t arrays = few ? 4u * kUnpackTileElems : uint32_t(eight ? sizeof(UnpackLds<8>) : sizeof(UnpackLds<16>));
+    if (resident != 0u && arrays < kResidentLds[resident == 4u]) lds = kResidentLds[resident == 4u] - arrays;   // LDS that no kernel touches
     if (kind == 3) {
         const uint32_t wg_log = a.chunk_lds & 63u, chunk_elems = a.chunk_lds & ~63u;
         if (a.n_groups8 == 0 || chunk_elems == 0 || chunk_elems > 64u * 64u || wg_log > 2u) return ADACOMP_EINVAL;

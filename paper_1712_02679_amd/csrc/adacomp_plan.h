@@ -79,6 +79,18 @@ constexpr uint32_t kUnpackGroupTiles = 8;   // at most this many tiles per group
 constexpr uint32_t kUnpackMinGroups = 2048;  // groups of more than one tile only while this many workgroups remain (8 per compute unit)
 constexpr uint32_t kUnpackSplitTiles = 2048;  // tables with both word widths and more tiles than this: one launch per width
 constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workgroups on a compute unit
+// Launches over the 16-bit layers of large tables are bound by HBM, which serves them better with fewer bytes in
+// flight than the workgroups that fit put there (as it does k_fused, below): LDS that no kernel touches holds them to 5
+// or 4 to a compute unit.  As many as fit (8, 7 or 6: up to 4, 8 or more learners) / 5 / 4, in us; L_T 500:
+//   Adam, 1 packet: 8 M 40.0 / 40.0 / 38.8, 24 M 118 / 114 / 112, 60 M 325 / 313 / 300; 8: 8 M 40.2 / 41.4 / 40.4, 24 M
+//     118 / 115 / 113, 60 M 314 / 303 / 286; 16: 12 M 61.9 / 62.0 / 62.8, 24 M 119 / 117 / 116, 125 M 519 / 512 / 520
+//   SGD, 2 packets: 8 M 25.5 / 26.0 / 26.1, 12 M 37.6 / 36.8 / 37.8, 60 M 190 / 174 / 174; 8: 24 M 73.8 / 71.7 / 73.1, 60 M
+//     186 / 175 / 175; 16: 125 M 337 / 338 / 357
+//   sum, 2 packets: 12 M 11.0 / 12.0 / 12.8, 24 M 24.2 / 23.5 / 22.7, 100 M 102 / 98 / 97; 8: 24 M 25.7 / 24.0 / 25.1, 60 M
+//     62.7 / 62.8 / 58.9
+//   L_T 100, 40 M: Adam, 4 packets 192 / 187 / 189; SGD, 8 122 / 124 / 135.
+constexpr uint32_t kResidentLds[2] = {32000, 40900};   // bytes of LDS that leave five, four workgroups on a compute unit
+constexpr uint32_t kResidentTiles = 2900, kResidentTilesSum = 5800;   // tiles from which on, with and without the optimizer
 constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table that go alone (3 per compute unit)
 
 // What k_fused leaves per tile for k_scan and k_place: one 16-byte record, so that a tile makes one
@@ -301,7 +313,7 @@ int launch_place(const CompressArgs &a, void *stream);
 // what a k_place launch does: everything (the default); the words, offsets and header only, leaving
 // the residue corrections waiting; or those corrections only
 constexpr uint32_t kPlaceEager = 0, kPlaceWords = 1, kPlaceResidue = 2;
-int launch_unpack(const UnpackArgs &a, int kind, void *stream);  // kind 0: 16-bit words, 1: 8-bit, 2: both, 3: both, k_unpack8
+int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream);  // kind 0: 16-bit words, 1: 8-bit, 2: both, 3: both, k_unpack8
 int launch_copy(float *dst, const float *src, size_t n, void *stream);
 int launch_triad(float *x, const float *y, size_t n, uint32_t resident, void *stream);   // n a multiple of 4, below 2^44; resident 3 .. 8
 int launch_fill(float *x, float value, size_t n, void *stream);
