@@ -79,6 +79,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     uint32_t small_cap = uint32_t(std::min<uint64_t>(4096u, std::max<uint64_t>(1024u, elems_all / kComputeUnits)));
     // ... and, where a somewhat larger tile does it, as many as there are compute units, less the one for the header:
     // a few more share units with others (397 k elements, 266 tiles of 1500 / 199 of 2000: 7.8 / 6.6 us; 600 k, 9.2 / 7.5).
+    uint64_t tiles_before = 0;
     for (uint32_t cap = small_cap; cap < 4096u || cap == small_cap; cap += cap / 16u) {
         cap = std::min(cap, 4096u);
         uint64_t tiles = 0;
@@ -89,6 +90,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
             if (bpt < a) bpt = a;
             tiles += (bins + bpt / a * a - 1u) / (bpt / a * a);
         }
+        if (tiles_before == 0) tiles_before = tiles;
         if (tiles < kComputeUnits) { small_cap = cap; break; }
         if (cap == 4096u) break;
     }
@@ -220,6 +222,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         if (n_ctiles >= (1u << 31) || n_utiles >= (1u << 31)) return ADACOMP_EINVAL;
     }
     p.n_ctiles = uint32_t(n_ctiles);
+    p.crowd_tiles = std::max(p.n_ctiles, uint32_t(std::min<uint64_t>(tiles_before, UINT32_MAX)));
     p.n_utiles = uint32_t(n_utiles);
     if (tables && p.n_class_tiles[0] && p.n_class_tiles[1]) {
         // both tile sizes: each gets its own k_fused launch over its own tiles
@@ -352,7 +355,7 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     if (!same_table(it->second.table, layers, n_layers)) return ADACOMP_EWORKSPACE;
     if (workspace_bytes < p.ws.least(n_learners) || it->second.bytes < p.ws.least(n_learners)) return ADACOMP_EWORKSPACE;
     // copy the scalars only; the tables already live on the device
-    out.n_layers = p.n_layers; out.n_ctiles = p.n_ctiles; out.n_utiles = p.n_utiles; out.n_ugroups = p.n_ugroups; out.n_ugroups8 = p.n_ugroups8; out.n_usingles8 = p.n_usingles8;
+    out.n_layers = p.n_layers; out.n_ctiles = p.n_ctiles; out.crowd_tiles = p.crowd_tiles; out.n_utiles = p.n_utiles; out.n_ugroups = p.n_ugroups; out.n_ugroups8 = p.n_ugroups8; out.n_usingles8 = p.n_usingles8;
     out.n_bins_total = p.n_bins_total; out.n_chunks_total = p.n_chunks_total;
     out.elem_span = p.elem_span; out.n_elems_total = p.n_elems_total; out.stage_entries = p.stage_entries;
     out.fixed_bytes = p.fixed_bytes; out.bound_bytes = p.bound_bytes;
@@ -448,11 +451,11 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
     if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
     const uint32_t room = kOneLaunchTilesPerUnit * compute_units;
-    const size_t workgroups = std::min(n_learners, size_t(kMaxBatch)) * p.n_ctiles;
+    const size_t workgroups = std::min(n_learners, size_t(kMaxBatch)) * p.crowd_tiles;
     const bool crowd = workgroups > 2 * size_t(room);   // more than are resident
     const bool folds = p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;   // two staged launches, not three
     const uint64_t pays = !p.has_short_bins ? kOneLaunchCrowdElemsLong : folds ? kOneLaunchCrowdElems : 0u;
-    if (2 * workgroups > 5 * size_t(room) && p.n_elems_total < p.n_ctiles * pays) return kOneLaunchNever;
+    if (2 * workgroups > 5 * size_t(room) && p.n_elems_total < p.crowd_tiles * pays) return kOneLaunchNever;
     if (!crowd && p.n_ctiles <= std::min(kFoldTiles, room) && p.n_layers <= kFoldLayers) return kOneLaunchTable;
     const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
     return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;

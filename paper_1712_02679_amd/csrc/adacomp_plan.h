@@ -164,6 +164,8 @@ struct Plan {
     uint32_t n_layers = 0;
     uint32_t n_ctiles = 0, n_utiles = 0, n_ugroups = 0;
     uint32_t n_ugroups8 = 0, n_usingles8 = 0;  // groups of layers with 8-bit words: they come first in both tables
+    uint32_t crowd_tiles = 0;   // compress tiles, for the lines between staged and one-launch calls of many workgroups (kOneLaunchCrowd*): as
+                                // many as a table makes before build_plan rounds them down to the compute units, with which the lines were measured
     uint32_t n_bins_total = 0, n_chunks_total = 0;
     uint64_t elem_span = 0;     // max over layers of elem_offset + n_elems
     uint64_t n_elems_total = 0;
