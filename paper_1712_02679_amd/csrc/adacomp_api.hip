@@ -95,6 +95,23 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         if (cap == 4096u) break;
     }
 
+    // Tables with layers of the larger tile class that can go in one launch (one_launch_for) have all their layers in
+    // tiles of that class: up to a million elements smaller ones, so that there are some.  A 256th / 128th / 64th of
+    // the elements to a tile, in us: 1.2 M elements, L_T 800 and 8000, 1 learner 10.1 / 10.4 / 11.1, 4 learners with unpack
+    // 27.6 / 27.6 / 21.7; 1 M, 50 and 9000, 1 learner 10.6 / 10.0 / 11.9, 4 33.0 / 31.0 / 25.7, 16 108 / 75 / 68; 2 M, 5000, 1 learner
+    // 13.4 / 12.1 / 12.1, 4 50 / 34 / 34 (in staged launches over tiles of both classes 24, 35, 24, 42, 87, 18 and 37).
+    auto large_class = [](uint32_t T) { const uint64_t a = 4u / gcd_u32(T, 4u); return T > 4096u || (a * T > 4096u && a * T <= 16384u); };
+    const uint32_t large_cap = uint32_t(std::min<uint64_t>(16384u, std::max<uint64_t>(4096u, elems_all / 64u)));
+    bool all_large = false, fits = n_layers <= kOneLaunchLayersMax;
+    for (uint32_t l = 0; l < n_layers && fits; ++l) {
+        const uint32_t T = layers[l].L_T;
+        const uint64_t a = 4u / gcd_u32(T, 4u), bpt = std::min<uint64_t>(std::max<uint64_t>(large_cap / T, 1u), kMaxTileBins);
+        const uint64_t at_least = a * T <= 16384u ? (bpt < a ? a : bpt / a * a) : bpt;
+        all_large = all_large || large_class(T);
+        fits = T >= 4u && layers[l].n_elems <= at_least * T * kOneLaunchTilesLarge;
+    }
+    all_large = all_large && fits;
+
     for (uint32_t l = 0; l < n_layers; ++l) {
         const uint32_t T = layers[l].L_T;
         const uint32_t n = uint32_t(layers[l].n_elems);
@@ -125,9 +142,9 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         // 4096 elements take the larger class when they fit there: unaligned tiles fall back to 4-byte
         // accesses, which stream at 44 % of the HBM peak instead of 71-77 %.
         const uint32_t a = 4u / gcd_u32(T, 4u);
-        const int cls = (T > 4096u || (uint64_t(a) * T > 4096u && uint64_t(a) * T <= 16384u)) ? 1 : 0;
+        const int cls = (all_large || large_class(T)) ? 1 : 0;
         const uint32_t cap = cls ? 16384u : 4096u;
-        uint32_t bpt = (cls ? cap : small_cap) / T;
+        uint32_t bpt = (all_large ? large_cap : cls ? cap : small_cap) / T;
         if (bpt == 0) bpt = 1;                        // a bin of up to cap elements always fits its class
         if (bpt > kMaxTileBins) bpt = kMaxTileBins;
         if (bpt < a && uint64_t(a) * T <= cap) bpt = a;
@@ -222,7 +239,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         if (n_ctiles >= (1u << 31) || n_utiles >= (1u << 31)) return ADACOMP_EINVAL;
     }
     p.n_ctiles = uint32_t(n_ctiles);
-    p.crowd_tiles = std::max(p.n_ctiles, uint32_t(std::min<uint64_t>(tiles_before, UINT32_MAX)));
+    p.crowd_tiles = all_large ? p.n_ctiles : std::max(p.n_ctiles, uint32_t(std::min<uint64_t>(tiles_before, UINT32_MAX)));
     p.n_utiles = uint32_t(n_utiles);
     if (tables && p.n_class_tiles[0] && p.n_class_tiles[1]) {
         // both tile sizes: each gets its own k_fused launch over its own tiles
@@ -444,20 +461,22 @@ uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, u
 }
 
 // One launch for everything, where the tiles of each layer are on the GPU together (see k_pack): tables of
-// the 4096-element tile class (whose tiles are 16-byte aligned), with bins of at least four elements, in a
+// one tile class, with bins of at least four elements, in a
 // workspace that has exchange areas for all learners of a launch.  compute_units: what the stream may use.
 uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units)
 {
     if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
-    if (!g_fold_scan.load(std::memory_order_relaxed) || p.n_class_tiles[1] != 0 || p.has_tiny_bins) return kOneLaunchNever;
-    const uint32_t room = kOneLaunchTilesPerUnit * compute_units;
+    if (!g_fold_scan.load(std::memory_order_relaxed) || p.has_tiny_bins || (p.n_class_tiles[0] != 0 && p.n_class_tiles[1] != 0)) return kOneLaunchNever;
+    const bool large = p.n_class_tiles[1] != 0;
+    const uint32_t room = (large ? kOneLaunchTilesLarge / kComputeUnits : kOneLaunchTilesPerUnit) * compute_units;
     const size_t workgroups = std::min(n_learners, size_t(kMaxBatch)) * p.crowd_tiles;
     const bool crowd = workgroups > 2 * size_t(room);   // more than are resident
     const bool folds = p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;   // two staged launches, not three
     const uint64_t pays = !p.has_short_bins ? kOneLaunchCrowdElemsLong : folds ? kOneLaunchCrowdElems : 0u;
+    if (large && !p.has_short_bins && workgroups > 3 * size_t(room)) return kOneLaunchNever;
     if (2 * workgroups > 5 * size_t(room) && p.n_elems_total < p.crowd_tiles * pays) return kOneLaunchNever;
     if (!crowd && p.n_ctiles <= std::min(kFoldTiles, room) && p.n_layers <= kFoldLayers) return kOneLaunchTable;
-    const uint32_t most = (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
+    const uint32_t most = large ? kOneLaunchTilesLarge : (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
     return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
 }
 

@@ -967,8 +967,11 @@ __device__ __forceinline__ uint32_t words_before(const uint32_t *s_excl, const u
 
 // ==============================================================================================
 // k_pack: a tile of at most 4096 elements, 256 threads with four 16-byte slots each, or where every workgroup
-// reads all records and few are at work, 512 with two (kPackWidePerUnit).  Tiles of this
-// class start on 16-byte boundaries; bins have at least four elements, so that a slot lies in one bin
+// reads all records and few are at work, 512 with two (kPackWidePerUnit); a tile of up to 16384 elements, 1024 threads
+// with four slots, of which two workgroups fit a compute unit with at most 64 vector and 80 scalar registers (beyond
+// 80, waves are given 112 of the 800 that a SIMD has, and seven fit: one workgroup).  Tiles of the
+// smaller class start on 16-byte boundaries, those of the larger on 4-byte ones: the buffer accesses of the slots
+// need no more.  Bins have at least four elements, so that a slot lies in one bin
 // or two.  Bound by HBM at 12 bytes per element plus the packet, and short of that by the wait, about
 // 8 us of a workgroup's life of 17 us on ResNet-50's table, which other workgroups have to cover:
 // hence eight of them on a compute unit, which takes 64 registers (7 spilled ones cost 10 %) and is why
@@ -995,11 +998,11 @@ __device__ __forceinline__ uint32_t take_max_from(const uint32_t v, const bool f
 }
 
 template <bool VARIANT, int ONE, int WAVES, int J>
-__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable ? (WAVES == 4 ? 6 : 4) : 8) void k_pack(const CompressArgs a)
+__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVES == 4 ? 6 : 4) : 8) __attribute__((amdgpu_num_sgpr(80))) void k_pack(const CompressArgs a)
 {
     constexpr uint32_t WG = uint32_t(WAVES) * 64u, kRow = WG * 4u;   // J 16-byte slots to a thread: slot j of thread t is number j * WG + t of the tile
     constexpr int P = (J + 1) / 2;   // pairs of rows
-    static_assert(WG * uint32_t(J) <= 1024u && WG >= kMaxTileBins / 4u, "a tile of at most 4096 elements");
+    static_assert(WG * uint32_t(J) <= 4096u && J <= 4, "tiles of at most 16384 elements, words counted in 15 bits");
     // Two rounds of scalar loads: arguments, then what they point to.  (Left to the compiler, which fetches what a
     // branch needs behind the branch, there are five, 0.25 us each, before the first load of the tile.)
     const TileDev *tiles = a.tiles;
@@ -1034,7 +1037,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable ? (WAVES == 4 ? 6 : 4)
     __shared__ uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kMaxTileBins + 4u];
     __shared__ uint32_t s_words[WG * J * 2u + 4u];  // the tile's words, in their final form, one byte or two each
-    __shared__ __attribute__((aligned(16))) uint32_t s_rows[WAVES * P];   // words per wave and row, two rows to an entry
+    __shared__ uint32_t s_rows[WAVES * P * 2];   // words per wave and row, two rows to an entry
     __shared__ uint32_t s_chunk[kMaxTileBins / 64u];
     __shared__ OneShared sh;
     __shared__ uint32_t s_excl[ONE == kOneTable ? kFoldTiles + 1u : 1u];   // kOneTable: words of the tiles before tile t in the same run of 64
@@ -1093,7 +1096,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable ? (WAVES == 4 ? 6 : 4)
     // whole slots only: what lies past the tile is read as zero and not stored, without a branch
     const __amdgpu_buffer_rsrc_t r_buf = tile_buffer(rs, n & ~3u), w_buf = tile_buffer(gr, n & ~3u);
 
-    auto skip_row = [&](int j) { return WAVES == 8 && j != 0 && n <= uint32_t(j) * kRow; };   // (uniform: the small tiles of small tables leave a row empty)
+    auto skip_row = [&](int j) { return WAVES >= 8 && j != 0 && n <= uint32_t(j) * kRow; };   // (uniform: the small tiles of small tables leave a row empty)
     uint32_t gb[J][4];  // bits of G (sign included)
     uint32_t mb[J][4];  // bits of max(|G|, |H|): what is compared with g_max
     vfloat4 r[J], w[J];
@@ -1180,27 +1183,20 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable ? (WAVES == 4 ? 6 : 4)
         }
     }
     // words are ordered by (row j, wave, lane, c): counts of two rows to a register, at most 256 each per wave
-    uint32_t pre[P], all[P];   // words of the wave's rows before this lane; of the tile's rows
+    uint32_t pre[P];   // words of the wave's rows before this lane
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const uint32_t c = uint32_t(__popc((sent_mask >> (8 * p)) & 0xFu)) | (uint32_t(__popc((sent_mask >> (8 * p)) & 0xF0u)) << 16);
         const uint32_t incl = wave_incl_scan(c);
-        if (lane == 63u) s_rows[uint32_t(P) * wave + uint32_t(p)] = incl;
+        if (lane == 63u) { s_rows[2 * p * WAVES + int(wave)] = incl & 0xFFFFu; s_rows[(2 * p + 1) * WAVES + int(wave)] = incl >> 16; }
         pre[p] = incl - c;
-        all[p] = 0u;
     }
     const double gmax_sum = tile_gmax_sum<WG>(s_gmax, nb, sh.d);   // has the barrier
+    const uint32_t row = lane < uint32_t(J * WAVES) ? s_rows[lane] : 0u, rows_incl = wave_incl_scan(row);
+    const uint32_t tile_total = uint32_t(__builtin_amdgcn_readlane(int(rows_incl), J * WAVES - 1));
+    uint32_t row_at[J];   // words of the rows before the wave's row j
 #pragma unroll
-    for (uint32_t wv = 0; wv < uint32_t(WAVES); ++wv)
-#pragma unroll
-        for (uint32_t p = 0; p < uint32_t(P); ++p) {
-            const uint32_t t = s_rows[uint32_t(P) * wv + p];
-            if (wv < wave) pre[p] += t;
-            all[p] += t;
-        }
-    uint32_t tile_total = 0u;
-#pragma unroll
-    for (int p = 0; p < P; ++p) tile_total += (all[p] & 0xFFFFu) + (all[p] >> 16);
+    for (int j = 0; j < J; ++j) row_at[j] = uint32_t(__builtin_amdgcn_readlane(int(rows_incl - row), j * WAVES + int(wave)));
     // first thing: others wait for it
     if (tid < (ONE == kOneTable ? 2u * kRecCopies : 2u))
         sync_store(rec_copy(sy, a.n_tiles, tid >> 1) + 2u * tile + (tid & 1u), (tid & 1u) ? rec_low(gmax_sum, tile_total, epoch) : rec_high(gmax_sum, epoch));
@@ -1219,8 +1215,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable ? (WAVES == 4 ? 6 : 4)
         const uint32_t f = (sent_mask >> (4 * j)) & 0xFu;
         if (f == 0u) continue;
         const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
-        uint32_t at = (j & 1) ? (pre[j / 2] >> 16) + (all[j / 2] & 0xFFFFu) : pre[j / 2] & 0xFFFFu;
-        if (j >= 2) at += (all[0] & 0xFFFFu) + (all[0] >> 16);
+        uint32_t at = row_at[j] + ((j & 1) ? pre[j / 2] >> 16 : pre[j / 2] & 0xFFFFu);
 #pragma unroll
         for (uint32_t c = 0; c < 4u; ++c) {
             if (!((f >> c) & 1u)) continue;
@@ -2572,12 +2567,15 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
     const dim3 wg(jcode == 0 ? 256 : 1024);
     const bool variant = a.rule != ADACOMP_RULE_ADACOMP || a.soft_factor_minus_1 != 1.0f;
     if (a.one_launch) {   // the host picks it for eager calls on tables of one tile class whose layers are small
-        if (jcode != 0 || a.lazy || a.class_tiles || a.place_mode != kPlaceEager) return ADACOMP_EINVAL;
+        if (a.lazy || a.class_tiles || a.place_mode != kPlaceEager) return ADACOMP_EINVAL;
         const bool table = a.one_launch == kOneLaunchTable;
         if (table && (a.n_tiles > kFoldTiles || a.n_layers > kFoldLayers)) return ADACOMP_EINVAL;
         const dim3 grid(a.class_count + 1u, a.fused_count);   // a learner's tiles and the workgroup that writes the header
         auto launch = [&](auto kernel, uint32_t threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a); };
-        if (!table) {
+        if (jcode != 0) {
+            if (!variant) table ? launch((k_pack<false, kOneTable, 16, 4>), 1024u) : launch((k_pack<false, kOneLayers, 16, 4>), 1024u);
+            else table ? launch((k_pack<true, kOneTable, 16, 4>), 1024u) : launch((k_pack<true, kOneLayers, 16, 4>), 1024u);
+        } else if (!table) {
             if (!variant) launch((k_pack<false, kOneLayers, 4, 4>), 256u);
             else launch((k_pack<true, kOneLayers, 4, 4>), 256u);
         } else if (a.pack_wide) {

@@ -239,6 +239,13 @@ constexpr uint32_t kOneLaunchTilesPerUnit = 4;
 // 500, 227 k, 16 learners 31.9 / - / 29.0, but L_T 500 alone, 14 learners 24.9 / - / 26.7, 12 (2800 workgroups), 14
 // layers 21.8 / - / 23.0.
 constexpr uint32_t kOneLaunchCrowdElems = 1536, kOneLaunchCrowdElemsLong = 2048;   // elements per tile from which on one launch pays
+// Tables with bins of the larger tile class have all layers in tiles of that class (build_plan), if none takes more of
+// them than there are compute units (two workgroups are resident on each).  Three staged launches or more (one over
+// each class) / one, in us: 4 M elements, L_T 50 and 9000, 1 learner 36.5 / 19.7, 16 with unpack 242 / 201; 9 M, 1 learner 51 /
+// 30; 20 M in 40 layers, 50 and 7000 86 / 60; 8 M, 64 and 1501, another rule 55 / 31.  Without short bins the staged
+// calls are the shorter ones from 3 workgroups per unit on: L_T 5000, 2 M, 4 learners (536 workgroups) 36.8 / 34.2, 16
+// 88 / 96; 5 M, 4 learners 64 / 70; L_T 12001, 300 k, 16 learners (480) 31.7 / 22.8, 5 M, 4 63 / 70.
+constexpr uint32_t kOneLaunchTilesLarge = 256;
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
 

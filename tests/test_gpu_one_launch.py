@@ -166,6 +166,33 @@ def test_threads_per_tile(H, oracle_lib, name, tiles, n, rule, factor):
     H.run_parity(oracle_lib, wl, n, 2, rule=rule, soft_factor=factor, seed=6, label=f"one launch: {tiles} tiles of {per}, {n} learners", batch=True)
 
 
+# bins of the larger tile class, of which one layer is enough for all to have such tiles: starts at every place of a
+# 16-byte slot, bins that fill a tile, one element more than the class takes with its misalignment, bins of four
+LARGE = [("a", 8000 * 5 + 3, 8000), ("b", 5001 * 7 + 1, 5001), ("c", 16384 * 2, 16384), ("d", 1027 * 9 + 5, 1027), ("e", 50 * 1700 + 7, 50),
+         ("f", 16383 * 3 + 5, 16383), ("g", 1, 9000), ("h", 4 * 3000 + 1, 4), ("i", 4099 * 4 + 2, 4099), ("j", 65 * 300 + 3, 65)]
+LARGE_TABLES = {
+    "large_few_layers": LARGE,
+    "large_many_layers": LARGE + [(f"m{i}", 1 + (i * 613) % 30001, (4, 7, 50, 9001, 500, 16381)[i % 6]) for i in range(40)],
+    "256_large_tiles": [("a", 16384 * 255 + 9, 16384), ("b", 50 * 900, 50)],
+    "257_large_tiles": [("a", 16384 * 256 + 9, 16384), ("b", 50 * 900, 50)],
+}
+
+
+@pytest.mark.parametrize("n,rule,factor", [(1, 0, 2.0), (3, 0, 2.0), (2, 1, 2.0), (2, 2, 2.0), (1, 0, 1.5)])
+@pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(LARGE_TABLES)] + [("large_few_layers", True), ("large_many_layers", True)])
+def test_large_tiles(H, oracle_lib, name, impatient, n, rule, factor):
+    wl = W.custom(name, LARGE_TABLES[name], dist="normal_outliers")
+    with _Impatient(H) if impatient else contextlib.nullcontext():
+        H.run_parity(oracle_lib, wl, n, 2, rule=rule, soft_factor=factor, seed=17, label=f"one launch: {name}, {n} learners, rule {rule}, impatient {impatient}",
+                     batch=True)
+
+
+def test_large_tiles_lazy_and_staged(H, oracle_lib, monkeypatch):
+    """The staged and the lazy calls over the same tiles, in turn with one-launch ones."""
+    monkeypatch.setitem(TABLES, "many_layers", LARGE_TABLES["large_many_layers"])
+    test_one_launch_beside_staged_calls(H, oracle_lib)
+
+
 def test_one_launch_beside_staged_calls(H, oracle_lib):
     """One workspace: one-launch calls, three-launch calls (the tuning knob) and lazy calls in turn: the residues go
     on as if nothing had changed."""
