@@ -463,13 +463,15 @@ uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, u
 // One launch for everything, where the tiles of each layer are on the GPU together (see k_pack): tables of
 // one tile class, with bins of at least four elements, in a
 // workspace that has exchange areas for all learners of a launch.  compute_units: what the stream may use.
-uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units)
+uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units, bool lazy)
 {
     if (std::min(n_learners, size_t(kMaxBatch)) > p.sync.learners || workspace_bytes < p.sync.offset + p.sync.learners * p.ws.sync_stride) return kOneLaunchNever;
     if (!g_fold_scan.load(std::memory_order_relaxed) || p.has_tiny_bins || (p.n_class_tiles[0] != 0 && p.n_class_tiles[1] != 0)) return kOneLaunchNever;
     const bool large = p.n_class_tiles[1] != 0;
     const uint32_t room = (large ? kOneLaunchTilesLarge / kComputeUnits : kOneLaunchTilesPerUnit) * compute_units;
     const size_t workgroups = std::min(n_learners, size_t(kMaxBatch)) * p.crowd_tiles;
+    if (lazy && (n_learners * p.n_elems_total > kLazyOneLaunchElems ||
+                 (4 * workgroups > 6 * size_t(room) && p.n_elems_total < p.crowd_tiles * uint64_t(kOneLaunchCrowdElems)))) return kOneLaunchNever;
     const bool crowd = workgroups > 2 * size_t(room);   // more than are resident
     const bool folds = p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;   // two staged launches, not three
     const uint64_t pays = !p.has_short_bins ? kOneLaunchCrowdElemsLong : folds ? kOneLaunchCrowdElems : 0u;
@@ -656,11 +658,11 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     a.o_chunk_rel = uint32_t(p.ws.chunk_rel); a.o_stage = p.ws.stage;
     a.o_sync_rec = uint32_t(p.ws.sync_rec); a.o_sync_tile = uint32_t(p.ws.sync_tile);
     a.o_sync_layer = uint32_t(p.ws.sync_layer); a.o_sync_epoch = uint32_t(p.ws.sync_epoch);
-    a.one_launch = lazy ? kOneLaunchNever : one_launch_for(p, n_learners, workspace_bytes, kComputeUnits);
+    a.one_launch = one_launch_for(p, n_learners, workspace_bytes, kComputeUnits, lazy);
     a.pack_wide = 0u;
     if (a.one_launch != kOneLaunchNever) {
         const uint32_t units = compute_units_of(s);
-        a.one_launch = one_launch_for(p, n_learners, workspace_bytes, units);
+        a.one_launch = one_launch_for(p, n_learners, workspace_bytes, units, lazy);
         a.pack_wide = std::min(n_learners, kMaxBatch) * (p.n_ctiles + 1u) <= kPackWidePerUnit * units ? 1u : 0u;
     }
     a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset);   // the launches of a call take turns with the areas

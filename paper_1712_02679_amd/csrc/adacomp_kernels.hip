@@ -22,9 +22,9 @@
 //            about 0.3-10 % of the elements); one extra workgroup writes header and records.
 //            Large tables with short bins (L_T <= 64), which send several percent of their elements,
 //            use k_place_tiled instead: a workgroup per tile, the residue corrected line by line.
-// adacomp_compress_batch_lazy runs the same three, but k_place leaves that read-modify-write out
-// and the next call's k_fused applies the corrections to the residue values while it has them in
-// registers (same arithmetic, same results; adacomp_residue_sync writes them on request).
+// adacomp_compress_batch_lazy runs the same three, or k_pack on small tables and few learners, but leaves the
+// residue corrections out; the next call's k_fused or k_pack applies them to the residue values while it has
+// them in registers (same arithmetic, same results; adacomp_residue_sync writes them on request).
 // adacomp_unpack_accumulate is one launch, k_unpack (or k_unpack8 for layers with short bins: one or two
 // packets, or many chunks; large tables of both word widths otherwise take one launch of k_unpack for each): a workgroup owns a tile of the dense output
 // in LDS, a lane group owns each bin and adds the learners' +-scale in learner order, then the
@@ -257,8 +257,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_fused(const CompressArgs a)
         // every thread then reads the four codes of each of its slots and corrects its residues:
         // the same single float32 subtraction or addition that the eager placement performs.
         __shared__ __attribute__((aligned(16))) uint8_t s_fix[J * WG * 4];
-        const uint32_t prev_count = tile_out[tile].count;
-        const float prev_scale = reinterpret_cast<const float *>(sb + a.o_layer_scale)[td.layer()];
+        const TileOut prev = tile_out[tile];
+        const uint32_t prev_count = prev.count;
+        const float prev_scale = __uint_as_float(prev.base);
         for (uint32_t i = tid; i < uint32_t(J) * WG / 4u; i += WG) reinterpret_cast<uint4 *>(s_fix)[i] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
         // four entries per load: a tile's stretch of the staging area starts on an 8-byte boundary
@@ -681,11 +682,51 @@ __device__ __forceinline__ double tile_gmax_sum(const uint32_t *s_gmax, const ui
     return sum;
 }
 
+// LAZY: what the previous call left waiting for a tile: its words' number and its layer's scale, and the words as
+// (tile-local index, sign) in the staging area.
+struct Waiting {
+    uint32_t count;
+    float scale;
+    const uint2 *entries;   // four to a load; what lies behind the last one is readable
+};
+__device__ __forceinline__ Waiting waiting_for(const CompressArgs &a, const uint32_t lr, const uint32_t tile, const TileDev &td)
+{
+    uint8_t *const sb = a.scratch + uint64_t(lr) * a.scratch_stride;
+    const TileOut prev = reinterpret_cast<const TileOut *>(sb + a.o_tile_out)[tile];
+    return Waiting{prev.count < td.n_elems ? prev.count : td.n_elems, __uint_as_float(prev.base),
+                   reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(sb + a.o_stage) + td.stage_base)};
+}
+// Two bits for every element of the tile, the code of its word, 0 if it has none: sixteen to a word of `map`, and the four
+// of a slot in one byte.  By the whole workgroup, `first`: the thread's first four entries; begins and ends with a barrier.
+template <uint32_t WG>
+__device__ __forceinline__ void fix_map(const Waiting &wait, const uint2 first, const uint32_t n, uint32_t *const map)
+{
+    const uint32_t tid = threadIdx.x;
+    __syncthreads();
+    for (uint32_t i = tid; i < (n + 15u) / 16u; i += WG) map[i] = 0u;
+    __syncthreads();
+    for (uint32_t q = tid; 4u * q < wait.count; q += WG) {
+        const uint2 v = q == tid ? first : wait.entries[q];
+        const uint32_t entry[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) {
+            const uint32_t e = entry[i] >> 2;
+            if (4u * q + i < wait.count && e < n) atomicOr(&map[e >> 4], (entry[i] & 3u) << (2u * (e & 15u)));
+        }
+    }
+    __syncthreads();
+}
+// residue <- G - Gq of the previous call: the same single float32 operation that the eager placement performs
+__device__ __forceinline__ float fixed_residue(const float r, const uint32_t code, const float scale)
+{
+    return code == 1u ? r - scale : code == 3u ? r + scale : r;
+}
+
 // Works out and publishes the record of a tile whose workgroup has not done it, by the whole
-// workgroup; does nothing if the record is there.  Begins and ends with a barrier.
-template <uint32_t WG, bool VARIANT>
+// workgroup; does nothing if the record is there.  Begins and ends with a barrier.  s_map (LAZY): LDS for fix_map.
+template <uint32_t WG, bool VARIANT, bool LAZY>
 __device__ __forceinline__ void help_tile(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t tile,
-                                          const uint32_t epoch, uint32_t *s_gmax, OneShared &sh)
+                                          const uint32_t epoch, uint32_t *s_gmax, uint32_t *s_map, OneShared &sh)
 {
     const uint32_t tid = threadIdx.x;
     __syncthreads();
@@ -701,15 +742,25 @@ __device__ __forceinline__ void help_tile(const CompressArgs &a, const SyncArea 
         const uint32_t n = td.n_elems, T = td.L_T, M = td.magic, nb = td.n_bins;
         const float *gr = a.grad[lr] + td.elem_base, *rs = a.residue[lr] + td.elem_base;
         for (uint32_t i = tid; i < nb; i += WG) s_gmax[i] = 0u;
+        float wait_scale = 0.f;
+        if (LAZY && a.lazy) {
+            const Waiting wait = waiting_for(a, lr, tile, td);
+            wait_scale = wait.scale;
+            fix_map<WG>(wait, 4u * tid < wait.count ? wait.entries[tid] : make_uint2(0u, 0u), n, s_map);
+        }
+        auto residue_of = [&](uint32_t e) {
+            const float r = rs[e];
+            return LAZY && a.lazy ? fixed_residue(r, (s_map[e >> 4] >> (2u * (e & 15u))) & 3u, wait_scale) : r;
+        };
         __syncthreads();
         uint32_t gb, mb, count = 0u;
         for (uint32_t e = tid; e < n; e += WG) {
-            element_bits<VARIANT>(a, rs[e], gr[e], gb, mb);
+            element_bits<VARIANT>(a, residue_of(e), gr[e], gb, mb);
             atomicMax(&s_gmax[bin_of(e, T, M)], gb & 0x7FFFFFFFu);
         }
         __syncthreads();
         for (uint32_t e = tid; e < n; e += WG) {
-            element_bits<VARIANT>(a, rs[e], gr[e], gb, mb);
+            element_bits<VARIANT>(a, residue_of(e), gr[e], gb, mb);
             count += element_sent<VARIANT>(a, gb, mb, s_gmax[bin_of(e, T, M)]) ? 1u : 0u;
         }
         count = wave_sum(count);
@@ -763,9 +814,9 @@ __device__ __forceinline__ bool poll_records(const SyncArea &sy, const uint32_t 
 // so come upon different ones: those that cannot start are worked out about as fast as if they ran.  (Every
 // round adds a record or finds that somebody else did; false after more rounds than there are tiles: another
 // call is at work in the same area.)
-template <uint32_t WG, uint32_t HOLD, bool VARIANT>
+template <uint32_t WG, uint32_t HOLD, bool VARIANT, bool LAZY>
 __device__ __forceinline__ bool help_records(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t ts, const uint32_t nt,
-                                             const uint32_t epoch, uint32_t seed, uint32_t *s_gmax, OneShared &sh)
+                                             const uint32_t epoch, uint32_t seed, uint32_t *s_gmax, uint32_t *s_map, OneShared &sh)
 {
     const uint32_t tid = threadIdx.x;
     for (uint32_t round = 0; round <= nt; ++round) {
@@ -793,7 +844,7 @@ __device__ __forceinline__ bool help_records(const CompressArgs &a, const SyncAr
             }
             k -= c;
         }
-        help_tile<WG, VARIANT>(a, sy, lr, ts + __builtin_amdgcn_readfirstlane(q), epoch, s_gmax, sh);
+        help_tile<WG, VARIANT, LAZY>(a, sy, lr, ts + __builtin_amdgcn_readfirstlane(q), epoch, s_gmax, s_map, sh);
     }
     return false;
 }
@@ -865,16 +916,16 @@ __device__ __forceinline__ uint32_t poll_layer_words(const SyncArea &sy, const u
 
 // Adds up the records of layer l and publishes what its tiles (and the layers behind it) wait for.  Says
 // whether everything came in time; HELP: does not wait for records, but works out those that are missing.
-template <uint32_t WG, bool VARIANT, bool HELP>
+template <uint32_t WG, bool VARIANT, bool LAZY, bool HELP>
 __device__ __forceinline__ bool complete_layer(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t l,
-                                               const uint32_t epoch, const uint32_t seed, uint32_t *s_gmax, OneShared &sh)
+                                               const uint32_t epoch, const uint32_t seed, uint32_t *s_gmax, uint32_t *s_map, OneShared &sh)
 {
     constexpr uint32_t HOLD = (kOneLaunchTiles + WG - 1u) / WG;
     const uint32_t most_polls = HELP ? kWaitPollsKnown : a.wait_polls;   // (the layers before: HELP comes when those are there)
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t ts = a.layers[l].ctile_start, nt = a.layers[l].n_ctiles, wbytes = a.layers[l].word_bytes;
     Records<HOLD> rec;
-    if (HELP && !help_records<WG, HOLD, VARIANT>(a, sy, lr, ts, nt, epoch, seed, s_gmax, sh)) return false;
+    if (HELP && !help_records<WG, HOLD, VARIANT, LAZY>(a, sy, lr, ts, nt, epoch, seed, s_gmax, s_map, sh)) return false;
     if (block_any<WG>(!poll_records<WG>(sy, ts, nt, epoch, HELP ? 0u : a.wait_polls, rec), sh.any[0])) return false;
     uint32_t before[HOLD];
     double part = 0.0;
@@ -921,9 +972,9 @@ __device__ __forceinline__ float layer_scale_of(const double *sum, const uint32_
 // kOneTable: waits for the records of all tiles and lays them out: s_sum[t] the g_max sum of tile t, s_excl[t] the words
 // of the tiles before t in its run of 64, sh.w[r] the words of run r.  By the whole workgroup, behind a barrier;
 // ends with one.  helped: this workgroup has worked out records itself.  False: another call is at work in the area.
-template <uint32_t WG, bool VARIANT>
+template <uint32_t WG, bool VARIANT, bool LAZY>
 __device__ __forceinline__ bool table_records(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t epoch, const uint32_t seed,
-                                              uint32_t *s_gmax, uint32_t *const s_excl, double *const s_sum, OneShared &sh, bool &helped)
+                                              uint32_t *s_gmax, uint32_t *s_map, uint32_t *const s_excl, double *const s_sum, OneShared &sh, bool &helped)
 {
     constexpr uint32_t HOLD = (kFoldTiles + WG - 1u) / WG;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -946,7 +997,7 @@ __device__ __forceinline__ bool table_records(const CompressArgs &a, const SyncA
     const bool all = poll_records<WG>(copy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
     lay_out();
     if (__builtin_expect(block_any<WG>(!all, sh.any[0]), false)) {
-        const bool there = help_records<WG, HOLD, VARIANT>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, sh);
+        const bool there = help_records<WG, HOLD, VARIANT, LAZY>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, s_map, sh);
         if (block_any<WG>(!(there && poll_records<WG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return false;
         lay_out();
         __syncthreads();
@@ -997,7 +1048,7 @@ __device__ __forceinline__ uint32_t take_max_from(const uint32_t v, const bool f
     return from && o > v ? o : v;
 }
 
-template <bool VARIANT, int ONE, int WAVES, int J>
+template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
 __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVES == 4 ? 6 : 4) : 8) __attribute__((amdgpu_num_sgpr(80))) void k_pack(const CompressArgs a)
 {
     constexpr uint32_t WG = uint32_t(WAVES) * 64u, kRow = WG * 4u;   // J 16-byte slots to a thread: slot j of thread t is number j * WG + t of the tile
@@ -1048,11 +1099,17 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
 
     if (heads) {
         const LayerDev first = header_layer(a);
+        auto leave = [&](uint32_t m, uint32_t nsel, float sc) {   // LAZY: for whoever applies the corrections later
+            if (!LAZY) return;
+            uint8_t *const sb = a.scratch + uint64_t(lr) * a.scratch_stride;
+            reinterpret_cast<uint32_t *>(sb + a.o_layer_nsel)[m] = nsel;
+            reinterpret_cast<float *>(sb + a.o_layer_scale)[m] = sc;
+        };
         if (tid == 0) count_call(sy.epoch + a.n_tiles);
         if (ONE == kOneTable) {
             float *const s_lscale = reinterpret_cast<float *>(s_words);
             bool helped;
-            if (!table_records<WG, VARIANT>(a, sy, lr, epoch, a.n_tiles, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by
+            if (!table_records<WG, VARIANT, LAZY>(a, sy, lr, epoch, a.n_tiles, s_gmax, s_cnt, s_excl, s_sum, sh, helped)) return;   // nothing to go by
             const uint32_t run_at = words_before_runs(sh, lane);
 #pragma unroll
             for (uint32_t i = 0; i < kFoldLayers / uint32_t(WAVES); ++i) {
@@ -1064,7 +1121,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
             const uint32_t ts = first.ctile_start, te = ts + first.n_ctiles;
             const uint32_t words = words_before(s_excl, run_at, te) - words_before(s_excl, run_at, ts);
             __syncthreads();
-            place_header<WG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) { nsel = words; sc = s_lscale[m]; });   // (at most kFoldLayers layers: one round)
+            place_header<WG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) { nsel = words; sc = s_lscale[m]; leave(m, nsel, sc); });   // (at most kFoldLayers layers: one round)
         } else {
             auto poll_layers = [&](bool ok, const uint32_t most_polls) {   // scale and word count of every layer
                 if (wave == 0u) {
@@ -1078,13 +1135,14 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
                 for (uint32_t times = 0; ok; ++times) {   // the layers that are not done
                     const uint32_t m = first_open_layer<WG>(sy, a.n_layers, epoch, sh);
                     if (m == a.n_layers) break;
-                    ok = times <= a.n_layers && complete_layer<WG, VARIANT, true>(a, sy, lr, m, epoch, a.n_tiles, s_gmax, sh);
+                    ok = times <= a.n_layers && complete_layer<WG, VARIANT, LAZY, true>(a, sy, lr, m, epoch, a.n_tiles, s_gmax, s_cnt, sh);
                 }
                 if (block_any<WG>(!poll_layers(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
             }
             place_header<WG>(a, packet, first, [&](uint32_t m, const LayerDev &, uint32_t &nsel, float &sc) {
                 nsel = uint32_t(sync_load(sy.layer + 4u * m + 2u) >> 32);
                 sc = __uint_as_float(uint32_t(sync_load(sy.layer + 4u * m) >> 32));
+                leave(m, nsel, sc);
             });
         }
         return;
@@ -1117,6 +1175,20 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     load_slots();
     asm volatile("" ::: "memory");   // the layer's record, which is not needed before the words, is not waited for together with the tile's
     const LayerDev ld = table_record<vuint16>(layers + l);
+    // LAZY: the residue corrections of the learner's previous call are applied to the values in registers first
+    auto apply_waiting = [&]() {
+        const Waiting wait = waiting_for(a, lr, tile, td);
+        fix_map<WG>(wait, 4u * tid < n ? wait.entries[tid] : make_uint2(0u, 0u), n, s_cnt);   // (fetched together with the count)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (skip_row(j)) continue;
+            const uint32_t codes = uint32_t(j) * kRow + tid * 4u < n ? reinterpret_cast<const uint8_t *>(s_cnt)[uint32_t(j) * WG + tid] : 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[j][c] = fixed_residue(r[j][c], (codes >> (2 * c)) & 3u, wait.scale);
+        }
+        __syncthreads();
+    };
+    if (LAZY && a.lazy) apply_waiting();
     for (uint32_t i = tid; i < nb + 1u; i += WG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(2);   // until the record is out: others wait for it (6 % of a small mini-batch; slower where waves queue for memory)
 #pragma unroll
@@ -1204,7 +1276,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(0);
     // A layer's last workgroup adds up its layer, before anything else: all of the layer wait for it.
     bool layer_ok = true;
-    if (ONE == kOneLayers && tile == ld.ctile_start + ld.n_ctiles - 1u) layer_ok = complete_layer<WG, VARIANT, false>(a, sy, lr, l, epoch, tile, s_gmax, sh);
+    if (ONE == kOneLayers && tile == ld.ctile_start + ld.n_ctiles - 1u) layer_ok = complete_layer<WG, VARIANT, LAZY, false>(a, sy, lr, l, epoch, tile, s_gmax, s_cnt, sh);
 
     // ---- the pack vector of Algorithm 2: the words, and how many each bin sends ----------------------
     const uint32_t wbytes = ld.word_bytes;
@@ -1257,6 +1329,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     // registers through that code.
     auto take_again = [&]() {
         load_slots();
+        if (LAZY && a.lazy) apply_waiting();
 #pragma unroll
         for (int j = 0; j < J; ++j)
 #pragma unroll
@@ -1269,7 +1342,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
         uint32_t l_ts = 0u, l_nt = 0u, l_wb = 0u;   // lane m keeps layer m's tiles and word width
         if (lane < l) { l_ts = a.layers[lane].ctile_start; l_nt = a.layers[lane].n_ctiles; l_wb = a.layers[lane].word_bytes; }   // l < kFoldLayers
         bool helped;
-        if (!table_records<WG, VARIANT>(a, sy, lr, epoch, tile, s_gmax, s_excl, s_sum, sh, helped)) return;   // nothing to go by: store nothing
+        if (!table_records<WG, VARIANT, LAZY>(a, sy, lr, epoch, tile, s_gmax, s_cnt, s_excl, s_sum, sh, helped)) return;   // nothing to go by: store nothing
         if (__builtin_expect(helped, false)) take_again();
         const uint32_t run_at = words_before_runs(sh, lane);
         base = words_before(s_excl, run_at, tile) - words_before(s_excl, run_at, ld.ctile_start);
@@ -1299,7 +1372,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
             ok = true;
             for (uint32_t times = 0; ok; ++times) {   // the layers before this one that are not done, and this one
                 const uint32_t m = first_open_layer<WG>(sy, l, epoch, sh);
-                ok = times <= l && complete_layer<WG, VARIANT, true>(a, sy, lr, m, epoch, tile, s_gmax, sh);
+                ok = times <= l && complete_layer<WG, VARIANT, LAZY, true>(a, sy, lr, m, epoch, tile, s_gmax, s_cnt, sh);
                 if (m == l) break;
             }
             if (block_any<WG>(!poll_tile(ok, kWaitPollsKnown), sh.any[2])) return;   // nothing to go by: store nothing
@@ -1315,6 +1388,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     uint32_t tid_r = threadIdx.x;   // (the slots' place is worked out anew, not kept through the wait)
     asm volatile("" : "+v"(tid_r));
     // ---- the residue, in its final form: G - Gq at the sent elements, G elsewhere ---------------------------
+    // (LAZY: nothing that a helper reads is written before here: residue, staged words, their number and the scale)
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         if (skip_row(j)) continue;
@@ -1322,12 +1396,39 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const float G = __uint_as_float(gb[j][c]);
+            if (LAZY) { R[c] = G; continue; }   // the corrections wait
             const float corrected = G - __builtin_copysignf(scale, G);
             R[c] = ((sent_mask >> (4 * j + c)) & 1u) ? corrected : G;
         }
         buffer_store_slot(r_buf, tid_r * 16u, uint32_t(j) * kRow * 4u, R);
         if ((n & 3u) != 0u && uint32_t(j) * WG + tid_r == (n >> 2))
             for (uint32_t c = 0; c < (n & 3u); ++c) rs[(n & ~3u) + c] = R[c];
+    }
+    if (LAZY) {   // the words for the next call, with tile-local indices, at the places worked out before
+        uint8_t *const sb = a.scratch + uint64_t(lr) * a.scratch_stride;
+        uint16_t *const stage = reinterpret_cast<uint16_t *>(sb + a.o_stage) + td.stage_base;
+        const uint32_t row = lane < uint32_t(J * WAVES) ? s_rows[lane] : 0u, rows_before = wave_incl_scan(row) - row;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const uint32_t c2 = uint32_t(__popc((sent_mask >> (8 * p)) & 0xFu)) | (uint32_t(__popc((sent_mask >> (8 * p)) & 0xF0u)) << 16);
+            const uint32_t before = wave_incl_scan(c2) - c2;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int j = 2 * p + h;
+                if (j >= J) break;
+                uint32_t at = uint32_t(__builtin_amdgcn_readlane(int(rows_before), j * WAVES + int(wave))) + (h ? before >> 16 : before & 0xFFFFu);
+#pragma unroll
+                for (uint32_t c = 0; c < 4u; ++c)
+                    if ((sent_mask >> (4 * j + int(c))) & 1u) stage[at++] = uint16_t(((uint32_t(j) * kRow + tid_r * 4u + c) << 2) | ((gb[j][c] >> 31) ? 3u : 1u));
+            }
+        }
+        if (tid_r == 0u) {
+            TileOut o;
+            o.gmax_sum = 0.0;
+            o.count = tile_total;
+            o.base = __float_as_uint(scale);
+            reinterpret_cast<TileOut *>(sb + a.o_tile_out)[tile] = o;
+        }
     }
     // ---- the words, at their place in the packet, four bytes at a time ---------------------------------------
     const uint32_t n_bytes = tile_total * wbytes, skew = first_at & 3u;
@@ -1588,6 +1689,7 @@ __global__ __launch_bounds__(kWG) void k_place(const CompressArgs a)
         }
     }
     if (MODE == kPlaceResidue) return;
+    if (MODE == kPlaceWords && sub == 0u) tile_out[tile].base = __float_as_uint(scale);   // for the next call, with the count
 
     // chunks[c] = words of the layer in bins < 64 c, for the chunk starts inside this tile
     const uint32_t t0 = (64u - (td.first_bin & 63u)) & 63u;
@@ -2566,25 +2668,25 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
     // 51-55 % of the HBM peak instead of 75-80 %.)
     const dim3 wg(jcode == 0 ? 256 : 1024);
     const bool variant = a.rule != ADACOMP_RULE_ADACOMP || a.soft_factor_minus_1 != 1.0f;
-    if (a.one_launch) {   // the host picks it for eager calls on tables of one tile class whose layers are small
-        if (a.lazy || a.class_tiles || a.place_mode != kPlaceEager) return ADACOMP_EINVAL;
+    if (a.one_launch) {   // the host picks it for tables of one tile class whose layers are small
+        const bool lazy = a.place_mode == kPlaceWords;
+        if (a.class_tiles || a.place_mode == kPlaceResidue || (a.lazy && !lazy) || (lazy && variant)) return ADACOMP_EINVAL;
         const bool table = a.one_launch == kOneLaunchTable;
         if (table && (a.n_tiles > kFoldTiles || a.n_layers > kFoldLayers)) return ADACOMP_EINVAL;
         const dim3 grid(a.class_count + 1u, a.fused_count);   // a learner's tiles and the workgroup that writes the header
-        auto launch = [&](auto kernel, uint32_t threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a); };
-        if (jcode != 0) {
-            if (!variant) table ? launch((k_pack<false, kOneTable, 16, 4>), 1024u) : launch((k_pack<false, kOneLayers, 16, 4>), 1024u);
-            else table ? launch((k_pack<true, kOneTable, 16, 4>), 1024u) : launch((k_pack<true, kOneLayers, 16, 4>), 1024u);
-        } else if (!table) {
-            if (!variant) launch((k_pack<false, kOneLayers, 4, 4>), 256u);
-            else launch((k_pack<true, kOneLayers, 4, 4>), 256u);
-        } else if (a.pack_wide) {
-            if (!variant) launch((k_pack<false, kOneTable, 8, 2>), 512u);
-            else launch((k_pack<true, kOneTable, 8, 2>), 512u);
-        } else {
-            if (!variant) launch((k_pack<false, kOneTable, 4, 4>), 256u);
-            else launch((k_pack<true, kOneTable, 4, 4>), 256u);
-        }
+        auto method = [&](auto waves, auto slots, auto form) {
+            constexpr int W = decltype(waves)::value, J = decltype(slots)::value, F = decltype(form)::value;
+            if (lazy) hipLaunchKernelGGL((k_pack<false, F, W, J, true>), grid, dim3(W * 64), 0, s, a);
+            else if (variant) hipLaunchKernelGGL((k_pack<true, F, W, J, false>), grid, dim3(W * 64), 0, s, a);
+            else hipLaunchKernelGGL((k_pack<false, F, W, J, false>), grid, dim3(W * 64), 0, s, a);
+        };
+        const std::integral_constant<int, 4> four;
+        const std::integral_constant<int, kOneTable> all_records;
+        const std::integral_constant<int, kOneLayers> per_layer;
+        if (jcode != 0) table ? method(std::integral_constant<int, 16>(), four, all_records) : method(std::integral_constant<int, 16>(), four, per_layer);
+        else if (!table) method(four, four, per_layer);
+        else if (a.pack_wide) method(std::integral_constant<int, 8>(), std::integral_constant<int, 2>(), all_records);
+        else method(four, four, all_records);
         return check_launch();
     }
     const dim3 grid(a.class_count * a.fused_count);

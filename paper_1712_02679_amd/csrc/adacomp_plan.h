@@ -98,7 +98,7 @@ constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table th
 struct TileOut {
     double gmax_sum;  // sum of the tile's g_max values
     uint32_t count;   // words the tile sends
-    uint32_t base;    // words of the layer before this tile (written by k_scan)
+    uint32_t base;    // words of the layer before this tile (written by k_scan); after a lazy call the bits of the layer's scale
 };
 static_assert(sizeof(TileOut) == 16, "TileOut layout");
 
@@ -246,6 +246,12 @@ constexpr uint32_t kOneLaunchCrowdElems = 1536, kOneLaunchCrowdElemsLong = 2048;
 // calls are the shorter ones from 3 workgroups per unit on: L_T 5000, 2 M, 4 learners (536 workgroups) 36.8 / 34.2, 16
 // 88 / 96; 5 M, 4 learners 64 / 70; L_T 12001, 300 k, 16 learners (480) 31.7 / 22.8, 5 M, 4 63 / 70.
 constexpr uint32_t kOneLaunchTilesLarge = 256;
+// Lazy calls save the placement's pass over the residue in either form, so that one launch pays by what it does without
+// launches and staged words, not by bytes: up to as many elements in all, and with small tiles up to the 6 workgroups
+// that its registers leave on a compute unit.  Staged / one launch, in us: 100 k elements, L_T 50 and 500, 1 learner 13.4 /
+// 8.3, 16 with unpack (1700 workgroups of 1000) 32.2 / 34.3; 1.2 M, 1 16.4 / 11.2, 16 71 / 70; 4 M, 4 58 / 50, 16 164 / 170;
+// 12 M, 1 40.5 / 33.9, 2 63.4 / 63.0, 4 129 / 140; ResNet-50's table, 1 66.8 / 66.2, 8 415 / 475.
+constexpr uint64_t kLazyOneLaunchElems = 24u * 1000u * 1000u;
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
 
@@ -314,7 +320,7 @@ struct UnpackArgs {
 // 1.5 to 2 % longer (4 M elements, 4 packets 8.85 -> 9.04 us; 20 M, 8 packets 31.5 -> 32.1).
 static_assert(sizeof(UnpackArgs) == 640 && offsetof(UnpackArgs, packets) == 128, "kernel arguments");
 
-uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units);
+uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units, bool lazy = false);
 uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);
 int launch_fused(const CompressArgs &a, int jcode, void *stream);
 int launch_scan(const CompressArgs &a, void *stream);

@@ -193,6 +193,54 @@ def test_large_tiles_lazy_and_staged(H, oracle_lib, monkeypatch):
     test_one_launch_beside_staged_calls(H, oracle_lib)
 
 
+LAZY_TABLES = {**{n: TABLES[n] for n in ("one_tile", "few_layers", "many_layers", "two_long_layers_short_bins")},
+               **{n: LARGE_TABLES[n] for n in ("large_few_layers", "large_many_layers")}, "512_tiles_16_layers": EDGES["512_tiles_16_layers"]}
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("name,n,impatient", [(n, k, False) for n in sorted(LAZY_TABLES) for k in (1, 3)] +
+                         [(n, 2, True) for n in ("few_layers", "many_layers", "large_few_layers", "large_many_layers")])
+def test_lazy_in_one_launch(H, oracle_lib, name, n, impatient, dense):
+    """Lazy calls in one launch and staged ones in turn, the corrections that one leaves applied by the other; the
+    residue as the calls leave it (G everywhere) and after a sync, eager calls behind that."""
+    import paper_1712_02679_amd as A
+    wl = W.custom(name, LAZY_TABLES[name], dist="normal_outliers")
+    table, m = wl.table(), wl.n_total
+    ws = torch.zeros(A.adacomp_workspace_bytes_batch(table, n), dtype=torch.uint8, device="cuda:0")
+    A.adacomp_workspace_init(table, ws)
+    if impatient:
+        A.adacomp_debug_wait_polls(ws, 0)
+    bound = A.adacomp_packet_bound(table)
+    R = [np.zeros(m, f32) for _ in range(n)]
+    res = [torch.zeros(m, device="cuda:0") for _ in range(n)]
+    pk = [torch.zeros(bound, dtype=torch.uint8, device="cuda:0") for _ in range(n)]
+    try:
+        for t in range(9):
+            H.say(f"lazy in one launch: {name}, {n} learners, impatient {impatient}, dense {dense}, step {t}")
+            g = [W.gradient(wl, k, t, seed=3) for k in range(n)]
+            if dense:   # every element of a bin is its maximum
+                g = [(np.where((np.arange(m) + k) % 3 == 0, -0.5, 0.5) * (k + 1)).astype(f32) - R[k] for k in range(n)]
+            gd = [torch.from_numpy(x).cuda() for x in g]
+            A.adacomp_tuning_fold_scan(t not in (2, 4, 5))   # t 2, 4, 5: staged
+            before = [x.copy() for x in R]
+            (A.adacomp_compress_batch if t == 7 else A.adacomp_compress_batch_lazy)(table, gd, res, pk, ws)
+            torch.cuda.synchronize()
+            for k in range(n):
+                want = oracle_lib.compress(table, g[k], R[k])
+                assert np.array_equal(pk[k][:want.size].cpu().numpy(), want), (t, k)
+                left = R[k] if t == 7 else before[k] + g[k]
+                mask = H.layer_mask(table, m)
+                assert np.array_equal(res[k].cpu().numpy()[mask].view(np.uint32), left[mask].view(np.uint32)), (t, k)
+            if t in (6, 8):
+                A.adacomp_residue_sync(ws)
+                torch.cuda.synchronize()
+                for k in range(n):
+                    assert np.array_equal(res[k].cpu().numpy(), R[k]), (t, k)
+    finally:
+        A.adacomp_tuning_fold_scan(True)
+        A.adacomp_workspace_release(ws)
+
+
 def test_one_launch_beside_staged_calls(H, oracle_lib):
     """One workspace: one-launch calls, three-launch calls (the tuning knob) and lazy calls in turn: the residues go
     on as if nothing had changed."""
