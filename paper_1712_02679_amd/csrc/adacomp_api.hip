@@ -934,7 +934,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
             if ((rc = launch_unpack(a, 3, 0u, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
             if ((rc = launch_unpack(a, n8 ? 1 : 0, n8 ? 0u : resident_for(n_tiles16, now, a.mode), hip_stream)) != ADACOMP_OK) return rc;
-        } else if (p.n_utiles <= kUnpackSplitTiles || (now <= 4u && now != 0u)) {  // mixed, and small or with few registers per path (k_unpack_few): one launch that handles both
+        } else if (p.n_utiles <= kUnpackSplitTiles || now <= kUnpackTogether) {  // mixed, and small or of few packets: one launch that handles both
             if ((rc = launch_unpack(a, 2, 0u, hip_stream)) != ADACOMP_OK) return rc;
         } else {  // large and mixed: the 8-bit groups come first in the table
             a.n_groups = n8;

@@ -77,7 +77,12 @@ struct UGroupDev {
 static_assert(sizeof(UGroupDev) == 8, "UGroupDev layout");
 constexpr uint32_t kUnpackGroupTiles = 8;   // at most this many tiles per group
 constexpr uint32_t kUnpackMinGroups = 2048;  // groups of more than one tile only while this many workgroups remain (8 per compute unit)
-constexpr uint32_t kUnpackSplitTiles = 2048;  // tables with both word widths and more tiles than this: one launch per width
+// Tables with both word widths: one launch per width on tables of more tiles than this and with more packets than
+// that.  The kernel for both has registers for both, which costs the one for 16 packets a workgroup or two per compute unit,
+// the others none; and two launches are two ends.  Two / one, in us: ResNet-50's table, SGD, 8 packets 91 / 85, 16 113 / 116, 1
+// 77 / 72; 30 M, L_T 64 and 500, sum of 8 42 / 35; 10 M, 50 and 500, SGD with 8 43.6 / 37.4, sum of 6 18.5 / 13.6.
+constexpr uint32_t kUnpackSplitTiles = 2048;
+constexpr uint32_t kUnpackTogether = 8;
 constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workgroups on a compute unit
 // Launches over the 16-bit layers of large tables are bound by HBM, which serves them better with fewer bytes in
 // flight than the workgroups that fit put there (as it does k_fused, below): LDS that no kernel touches holds them to 5
