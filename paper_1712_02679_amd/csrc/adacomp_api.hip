@@ -478,7 +478,7 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     if (large && !p.has_short_bins && workgroups > 3 * size_t(room)) return kOneLaunchNever;
     if (2 * workgroups > 5 * size_t(room) && p.n_elems_total < p.crowd_tiles * pays) return kOneLaunchNever;
     if (!crowd && p.n_ctiles <= std::min(kFoldTiles, room) && p.n_layers <= kFoldLayers) return kOneLaunchTable;
-    const uint32_t most = large ? kOneLaunchTilesLarge : (n_learners == 1 || p.has_short_bins) ? kOneLaunchTiles : kOneLaunchTilesLong;
+    const uint32_t most = large ? kOneLaunchTilesLarge : (n_learners == 1 || p.has_short_bins || workgroups <= kOneLaunchRounds * 2 * size_t(room)) ? kOneLaunchTiles : kOneLaunchTilesLong;
     return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
 }
 

@@ -224,10 +224,12 @@ constexpr uint32_t kFusedIdleMinLearners = 8;
 // reading the records of the whole table, or with one workgroup per layer doing so.
 constexpr uint32_t kOneLaunchNever = 0, kOneLaunchTable = 1, kOneLaunchLayers = 2;
 // Tiles of a layer up to which its workgroups wait for each other: 2048 are resident, and the longer a
-// layer, the longer its first tiles hold their place.  One layer of 1000 tiles, one launch / three, in us:
-// L_T 50, 1 learner 19.5 / 29.3, 8 learners 94 / 119; L_T 500, 1 learner 19.0 / 22.4, but 8 learners
-// 90.5 / 83.5, since the placement it saves is cheap where little is sent; hence the second line, which
-// holds for tables without short bins in calls of several learners (525 tiles: 75.0 / 75.2; 500 tiles 40.9 / 48.0).
+// layer, the longer its first tiles hold their place.  Three launches / one, in us, one layer: L_T 50, 1000 tiles, 1 learner
+// 29.3 / 19.5, 8 learners 119 / 94; L_T 500, 525 tiles, 2 learners 23.1 / 14.7, 8 50 / 41; 625 tiles, 4 35 / 28; 1000 tiles, 2
+// 30.9 / 20.0, 4 47.9 / 39.5, 8 81 / 78; the character LSTM, 8 learners with unpack 73.4 / 70.3.  Where little is sent the
+// placement that one launch saves is cheap, and the gain shrinks with the rounds of resident workgroups: without short bins
+// half as many tiles from more than four rounds on.
+constexpr size_t kOneLaunchRounds = 4;
 constexpr uint32_t kOneLaunchTiles = 1024;
 constexpr uint32_t kOneLaunchTilesLong = 512;
 // ... and per compute unit that the stream may use, half of what is resident there: workgroups of a layer that
