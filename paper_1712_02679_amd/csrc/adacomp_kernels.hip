@@ -25,9 +25,9 @@
 // adacomp_compress_batch_lazy runs the same three, or k_pack on small tables and few learners, but leaves the
 // residue corrections out; the next call's k_fused or k_pack applies them to the residue values while it has
 // them in registers (same arithmetic, same results; adacomp_residue_sync writes them on request).
-// adacomp_unpack_accumulate is one launch, k_unpack (or k_unpack8 for layers with short bins: one or two
-// packets, or many chunks; large tables of both word widths otherwise take one launch of k_unpack for each): a workgroup owns a tile of the dense output
-// in LDS, a lane group owns each bin and adds the learners' +-scale in learner order, then the
+// adacomp_unpack_accumulate is one launch: k_unpack, up to four packets k_unpack_few, and where layers with short
+// bins have many chunks k_unpack8 (large tables of both word widths and more than eight packets take two launches of
+// k_unpack): a workgroup owns a tile of the dense output in LDS, a lane group owns each bin and adds the learners' +-scale in learner order, then the
 // tile is written out once with coalesced float4 stores; neighbouring tiles share a workgroup
 // and the per-bin bookkeeping.
 #include <hip/hip_runtime.h>
@@ -1204,6 +1204,24 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     // ---- first loop of Algorithm 2: g_max(i) per bin.  A slot lies in bin b0, its elements from `left` on in
     // the next one (bins have at least four elements): one division per slot -------------------------
     uint32_t place[J];   // b0 << 16 | left
+    const bool whole_slots = (T & 3u) == 0u;   // no slot lies in two bins
+    if (whole_slots) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (skip_row(j)) { place[j] = T; continue; }
+            const uint32_t e0 = uint32_t(j) * kRow + tid * 4u;
+            const uint32_t b0 = __umulhi(e0, M), into = e0 - __umul24(b0, T), left = T - into;
+            place[j] = (b0 << 16) | left;
+            uint32_t v = gb[j][0] & 0x7FFFFFFFu;
+#pragma unroll
+            for (uint32_t c = 1; c < 4u; ++c) { const uint32_t g = gb[j][c] & 0x7FFFFFFFu; v = g > v ? g : v; }
+            v = take_max_from<0x111>(v, into >= 4u);   // (as below)
+            v = take_max_from<0x112>(v, into >= 8u);
+            v = take_max_from<0x114>(v, into >= 16u);
+            v = take_max_from<0x118>(v, into >= 32u);
+            if ((lane & 15u) == 15u || left < 8u) atomicMax(&s_gmax[b0], v);
+        }
+    } else
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         if (skip_row(j)) { place[j] = T; continue; }
@@ -1280,27 +1298,50 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
 
     // ---- the pack vector of Algorithm 2: the words, and how many each bin sends ----------------------
     const uint32_t wbytes = ld.word_bytes;
-    keep_apart(place);
     asm volatile("" : "+v"(sent_mask));
+    // Where workgroups are many, a lane goes over the bits of its mask, as many rounds as the lane with most of them, which
+    // takes fewest instructions; where few are at work and the chain counts, slot by slot, which takes the shortest one.
+    // Slots / bits, in us: ResNet-50's table 61.0 / 60.1, bins of 800 and 8000 21.7 / 20.6, but 397 k elements 6.6 / 7.0, the
+    // CIFAR table 9.3 / 9.9, 4 learners 21.3 / 23.8.
+    if constexpr (ONE == kOneLayers || WAVES == 16) {
+        uint32_t signs = 0u;   // bit 4 j + c: G of element c of slot j is negative
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const uint32_t f = (sent_mask >> (4 * j)) & 0xFu;
-        if (f == 0u) continue;
-        const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
-        uint32_t at = row_at[j] + ((j & 1) ? pre[j / 2] >> 16 : pre[j / 2] & 0xFFFFu);
+        for (int k = 4 * J - 1; k >= 0; --k) signs = __builtin_amdgcn_alignbit(signs, gb[k >> 2][k & 3], 31u);
+        uint32_t row_start[P];   // place of the lane's first word of each row, two rows to a register
 #pragma unroll
-        for (uint32_t c = 0; c < 4u; ++c) {
-            if (!((f >> c) & 1u)) continue;
-            const uint32_t idx = c < left ? T - left + c : c - left;   // inside the bin
-            const uint32_t word = (idx << 2) | ((gb[j][c] >> 31) ? 3u : 1u);   // ternary code: -scale / +scale
+        for (int p = 0; p < P; ++p) row_start[p] = pre[p] + (row_at[2 * p] | (2 * p + 1 < J ? row_at[(2 * p + 1) % J] << 16 : 0u));
+        for (uint32_t left = sent_mask; left != 0u; left &= left - 1u) {
+            const uint32_t k = uint32_t(__builtin_ctz(left)), c = k & 3u;
+            const uint32_t e = (k >> 2) * kRow + tid * 4u + c, b = __umulhi(e, M), idx = e - __umul24(b, T);   // idx: inside the bin
+            const uint32_t rows = P == 1 || k < 8u ? row_start[0] : row_start[P - 1];
+            const uint32_t at = ((rows >> ((k & 4u) * 4u)) & 0xFFFFu) + uint32_t(__popc(__builtin_amdgcn_ubfe(sent_mask, k & 12u, c)));
+            const uint32_t word = (idx << 2) | (((signs >> k) & 1u) << 1) | 1u;   // ternary code: 1 +scale, 3 -scale
             if (wbytes == 1u) reinterpret_cast<uint8_t *>(s_words)[at] = uint8_t(word);
             else reinterpret_cast<uint16_t *>(s_words)[at] = uint16_t(word);
-            ++at;
+            atomicAdd(&s_cnt[b], 1u);
         }
-        const uint32_t f1 = left < 4u ? f >> left : 0u;
-        const uint32_t k1 = uint32_t(__popc(f1)), k0 = uint32_t(__popc(f)) - k1;
-        if (k0) atomicAdd(&s_cnt[b0], k0);
-        if (k1) atomicAdd(&s_cnt[b0 + 1u], k1);
+    } else {
+        keep_apart(place);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const uint32_t f = (sent_mask >> (4 * j)) & 0xFu;
+            if (f == 0u) continue;
+            const uint32_t b0 = place[j] >> 16, left = place[j] & 0xFFFFu;
+            uint32_t at = row_at[j] + ((j & 1) ? pre[j / 2] >> 16 : pre[j / 2] & 0xFFFFu);
+#pragma unroll
+            for (uint32_t c = 0; c < 4u; ++c) {
+                if (!((f >> c) & 1u)) continue;
+                const uint32_t idx = c < left ? T - left + c : c - left;   // inside the bin
+                const uint32_t word = (idx << 2) | ((gb[j][c] >> 31) ? 3u : 1u);   // ternary code: -scale / +scale
+                if (wbytes == 1u) reinterpret_cast<uint8_t *>(s_words)[at] = uint8_t(word);
+                else reinterpret_cast<uint16_t *>(s_words)[at] = uint16_t(word);
+                ++at;
+            }
+            const uint32_t f1 = left < 4u ? f >> left : 0u;
+            const uint32_t k1 = uint32_t(__popc(f1)), k0 = uint32_t(__popc(f)) - k1;
+            if (k0) atomicAdd(&s_cnt[b0], k0);
+            if (k1) atomicAdd(&s_cnt[b0 + 1u], k1);
+        }
     }
     __syncthreads();
 
