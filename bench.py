@@ -46,11 +46,16 @@ def log(msg):
 
 def timed_kernel(table, learners):
     """The kernel that the library's timing events bracket: the streaming kernel of the staged launches, or, on
-    tables whose layers are small (up to 1024 tiles of 4000 elements, 512 with several learners and no short
-    bins), the one launch that does everything, its wait and its placement included."""
-    tiles = max(-(-n // 4000) for _, n, _ in table)
-    short = any(lt <= 64 for _, _, lt in table)
-    return "k_pack" if tiles <= (1024 if learners == 1 or short else 512) and all(4 <= lt <= 4096 for _, _, lt in table) else "k_fused"
+    tables whose layers are small, the one launch that does everything, its wait and its placement included: up to
+    1024 tiles of 4000 elements a layer (512 in calls of many tiles of several learners without short bins), or, with
+    bins of the larger tile class among them, 256 tiles of 16384."""
+    if any(lt < 4 for _, _, lt in table):
+        return "k_fused"
+    if any(lt > 4096 or (lt % 4 and 4096 < lt * (2 if lt % 2 == 0 else 4) <= 16384) for _, _, lt in table):
+        return "k_pack" if max(-(-n // (16384 // lt * lt)) for _, n, lt in table) <= 256 else "k_fused"
+    tiles = [-(-n // 4000) for _, n, _ in table]
+    many = learners > 1 and not any(lt <= 64 for _, _, lt in table) and sum(tiles) * learners > 8192
+    return "k_pack" if max(tiles) <= (512 if many else 1024) else "k_fused"
 
 
 def measured_traffic(workload_name):
