@@ -1052,7 +1052,7 @@ __device__ __forceinline__ uint32_t take_max_from(const uint32_t v, const bool f
 }
 
 template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
-__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVES == 4 ? 6 : 4) : 8) __attribute__((amdgpu_num_sgpr(80))) void k_pack(const CompressArgs a)
+__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80))) void k_pack(const CompressArgs a)
 {
     constexpr uint32_t WG = uint32_t(WAVES) * 64u, kRow = WG * 4u;   // J 16-byte slots to a thread: slot j of thread t is number j * WG + t of the tile
     constexpr int P = (J + 1) / 2;   // pairs of rows
@@ -1088,14 +1088,15 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     ++epoch;   // (count_call)
     const TileDev td = __builtin_bit_cast(TileDev, tile_words);
 
-    __shared__ uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
+    __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kMaxTileBins + 4u];
     __shared__ uint32_t s_words[WG * J * 2u + 4u];  // the tile's words, in their final form, one byte or two each
     __shared__ uint32_t s_rows[WAVES * P * 2];   // words per wave and row, two rows to an entry
     __shared__ uint32_t s_chunk[kMaxTileBins / 64u];
     __shared__ OneShared sh;
     __shared__ uint32_t s_excl[ONE == kOneTable ? kFoldTiles + 1u : 1u];   // kOneTable: words of the tiles before tile t in the same run of 64
-    __shared__ double s_sum[ONE == kOneTable ? kFoldTiles : 1u];           // kOneTable: g_max sum of tile t
+    double *const s_sum = reinterpret_cast<double *>(s_gmax);              // kOneTable: g_max sum of tile t, when the tile's own are done with
+    static_assert(8u * kFoldTiles <= sizeof(s_gmax), "LDS of the sums");
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1359,6 +1360,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES != 16 ? (WAVE
     if (a.keep_gmax) {
         float *gm_out = reinterpret_cast<float *>(a.scratch + uint64_t(lr) * a.scratch_stride + a.o_gmax) + ld.bin_start + td.first_bin;
         for (uint32_t i = tid; i < nb; i += WG) gm_out[i] = __uint_as_float(s_gmax[i]);
+        if (ONE == kOneTable) __syncthreads();   // the records' sums come into their place
     }
     const uint32_t t0 = (64u - (td.first_bin & 63u)) & 63u;   // first bin of the tile that starts a chunk of 64
     for (uint32_t t = t0 + 64u * wave; t < nb; t += WG) {
