@@ -1088,8 +1088,8 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LA
     ++epoch;   // (count_call)
     const TileDev td = __builtin_bit_cast(TileDev, tile_words);
 
-    __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kMaxTileBins + 4u];   // bit pattern of max |G| (one bin more than there are: see the selection)
-    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kMaxTileBins + 4u];
+    __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kPackBins];   // bit pattern of max |G| (and of the bins behind the last: pack_bin)
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kPackBins];
     __shared__ uint32_t s_words[WG * J * 2u + 4u];  // the tile's words, in their final form, one byte or two each
     __shared__ uint32_t s_rows[WAVES * P * 2];   // words per wave and row, two rows to an entry
     __shared__ uint32_t s_chunk[kMaxTileBins / 64u];
@@ -1193,7 +1193,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LA
         __syncthreads();
     };
     if (LAZY && a.lazy) apply_waiting();
-    for (uint32_t i = tid; i < nb + 1u; i += WG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
+    for (uint32_t i = tid; i < nb + 2u; i += WG) { s_gmax[i] = 0u; s_cnt[i] = 0u; }
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(2);   // until the record is out: others wait for it (6 % of a small mini-batch; slower where waves queue for memory)
 #pragma unroll
     for (int j = 0; j < J; ++j)
@@ -1214,7 +1214,7 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LA
         for (int j = 0; j < J; ++j) {
             if (skip_row(j)) { place[j] = T; continue; }
             const uint32_t e0 = uint32_t(j) * kRow + tid * 4u;
-            const uint32_t b0 = __umulhi(e0, M), into = e0 - __umul24(b0, T), left = T - into;
+            const uint32_t b = __umulhi(e0, M), into = e0 - __umul24(b, T), left = T - into, b0 = pack_bin<WAVES == 16>(b, nb);
             place[j] = (b0 << 16) | left;
             uint32_t v = gb[j][0] & 0x7FFFFFFFu;
 #pragma unroll
@@ -1230,8 +1230,8 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LA
     for (int j = 0; j < J; ++j) {
         if (skip_row(j)) { place[j] = T; continue; }
         const uint32_t e0 = uint32_t(j) * kRow + tid * 4u;
-        const uint32_t b0 = __umulhi(e0, M);
-        const uint32_t left = T - (e0 - __umul24(b0, T));
+        const uint32_t b = __umulhi(e0, M), b0 = pack_bin<WAVES == 16>(b, nb);
+        const uint32_t left = T - (e0 - __umul24(b, T));
         place[j] = (b0 << 16) | left;
         uint32_t m0 = gb[j][0] & 0x7FFFFFFFu, m1 = 0u;
 #pragma unroll

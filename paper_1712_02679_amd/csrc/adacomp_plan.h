@@ -268,6 +268,18 @@ constexpr uint32_t kOneLaunchLayersMax = 512;
 // / 10.4, and 1192, of which 1024 are resident with 512 threads, 13.4 / 17.9.
 constexpr uint32_t kPackWidePerUnit = 2;
 
+// k_pack takes whole rows of 16-byte slots, its threads times four elements each, as far as the tile has elements in
+// them.  `bin` is what the index of a slot's first element gives; the slots past the tile would lie in bins that it has
+// not (5120 elements in 1024 bins of five: the second row of 1024 threads ends in bin 1637), so the larger class takes
+// them for bin n_bins, which has an entry of its own and no elements.  They send nothing.  In the smaller class 4096
+// elements in bins of four or more are 1024 bins at most, with nothing to look at.
+constexpr uint32_t kPackBins = kMaxTileBins + 4u;   // entries of k_pack's arrays of bins: of a slot, its bin and the one after
+template <bool LARGE>
+__host__ __device__ inline uint32_t pack_bin(const uint32_t bin, const uint32_t n_bins)
+{
+    return LARGE && bin > n_bins ? n_bins : bin;
+}
+
 struct CompressArgs {
     const TileDev *tiles;
     const LayerDev *layers;

@@ -144,6 +144,20 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
             }
     for (const TileDev &td : p.ctiles)
         if (td.jcode() == 0 && !td.aligned()) return 151;
+    // k_pack: the bins of every slot of the rows that a tile begins, those past the tile too, have entries in its
+    // arrays; those of the tile's elements are what their index says
+    for (const TileDev &td : p.ctiles) {
+        if (td.L_T < 4u) continue;   // staged
+        for (const uint32_t threads : {256u, 512u, 1024u}) {
+            if ((threads == 1024u) != (td.jcode() == 1u)) continue;
+            for (uint32_t e0 = 0; e0 < (td.jcode() ? 16384u : 4096u); e0 += 4u) {
+                if (threads > 256u && e0 >= 4u * threads && e0 / (4u * threads) * (4u * threads) >= td.n_elems) break;   // rows that are left out
+                const uint32_t bin = uint32_t((uint64_t(e0) * td.magic) >> 32);
+                const uint32_t b0 = td.jcode() ? pack_bin<true>(bin, td.n_bins) : pack_bin<false>(bin, td.n_bins);
+                if (b0 + 1u >= kPackBins || (e0 < td.n_elems && b0 != bin)) return 154;
+            }
+        }
+    }
     if (w.total(3) != adacomp_workspace_bytes_batch(t.data(), uint32_t(t.size()), 3)) return 143;
     g_tiles_checked += p.n_ctiles + p.n_utiles;
     g_groups_checked += p.n_ugroups;
@@ -210,6 +224,13 @@ int main()
                 if (p.ws.least(n + 1) <= bytes) return 14;
             }
         }
+    for (uint32_t lt = 4; lt <= 50; ++lt) {   // short bins in tiles of the larger class, as many as such a tile takes
+        std::vector<adacomp_layer_t> t = {{0, 9001 * 3 + 1, 9001, 0}, {27008, 1024ull * 70 * lt + 7, lt, 0}};
+        adacomp::Plan p;
+        if (adacomp::build_plan(t.data(), 2, true, p) != ADACOMP_OK || p.n_class_tiles[0] != 0 || (lt <= 16) != (p.ctiles[4].n_bins == adacomp::kMaxTileBins)) return 15;
+        const int pc = check_plan(t);
+        if (pc) { std::printf("plan check failed with %d, bins of %u among long ones\n", pc, lt); return pc; }
+    }
     {   // the 125 M-element table of the benchmark: runs of 8 tiles that shorten towards the end
         std::vector<adacomp_layer_t> t(7);
         uint64_t off = 0;

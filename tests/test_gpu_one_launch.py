@@ -170,16 +170,20 @@ def test_threads_per_tile(H, oracle_lib, name, tiles, n, rule, factor):
 # 16-byte slot, bins that fill a tile, one element more than the class takes with its misalignment, bins of four
 LARGE = [("a", 8000 * 5 + 3, 8000), ("b", 5001 * 7 + 1, 5001), ("c", 16384 * 2, 16384), ("d", 1027 * 9 + 5, 1027), ("e", 50 * 1700 + 7, 50),
          ("f", 16383 * 3 + 5, 16383), ("g", 1, 9000), ("h", 4 * 3000 + 1, 4), ("i", 4099 * 4 + 2, 4099), ("j", 65 * 300 + 3, 65)]
+# tiles of 1024 bins that end inside a row of the threads' slots (of 4096 elements), and such that fill it
+THOUSAND_BINS = [("a", 9000 * 3 + 1, 9000)] + [(f"t{t}", 1024 * t * (16 if t < 9 else 9) + 3 * t + 2, t) for t in (5, 6, 7, 8, 9, 10, 11, 13, 14, 15, 16)]
 LARGE_TABLES = {
     "large_few_layers": LARGE,
     "large_many_layers": LARGE + [(f"m{i}", 1 + (i * 613) % 30001, (4, 7, 50, 9001, 500, 16381)[i % 6]) for i in range(40)],
+    "thousand_bins_few_layers": THOUSAND_BINS,
+    "thousand_bins_many_layers": THOUSAND_BINS + [(f"m{i}", 50 * i + 1, 50) for i in range(6)],
     "256_large_tiles": [("a", 16384 * 255 + 9, 16384), ("b", 50 * 900, 50)],
     "257_large_tiles": [("a", 16384 * 256 + 9, 16384), ("b", 50 * 900, 50)],
 }
 
 
 @pytest.mark.parametrize("n,rule,factor", [(1, 0, 2.0), (3, 0, 2.0), (2, 1, 2.0), (2, 2, 2.0), (1, 0, 1.5)])
-@pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(LARGE_TABLES)] + [("large_few_layers", True), ("large_many_layers", True)])
+@pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(LARGE_TABLES)] + [("large_few_layers", True), ("large_many_layers", True), ("thousand_bins_few_layers", True)])
 def test_large_tiles(H, oracle_lib, name, impatient, n, rule, factor):
     wl = W.custom(name, LARGE_TABLES[name], dist="normal_outliers")
     with _Impatient(H) if impatient else contextlib.nullcontext():
@@ -194,7 +198,7 @@ def test_large_tiles_lazy_and_staged(H, oracle_lib, monkeypatch):
 
 
 LAZY_TABLES = {**{n: TABLES[n] for n in ("one_tile", "few_layers", "many_layers", "two_long_layers_short_bins")},
-               **{n: LARGE_TABLES[n] for n in ("large_few_layers", "large_many_layers")}, "512_tiles_16_layers": EDGES["512_tiles_16_layers"]}
+               **{n: LARGE_TABLES[n] for n in ("large_few_layers", "large_many_layers", "thousand_bins_few_layers", "thousand_bins_many_layers")}, "512_tiles_16_layers": EDGES["512_tiles_16_layers"]}
 
 
 @pytest.mark.parametrize("dense", [False, True])
