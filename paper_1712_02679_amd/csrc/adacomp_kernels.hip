@@ -609,8 +609,8 @@ __device__ __forceinline__ bool element_sent(const CompressArgs &a, const uint32
 }
 
 struct SyncArea {
-    uint64_t *rec;     // 2 per tile: high half of the tile's g_max sum | epoch; low half | word count, epoch
-    uint64_t *tile;    // 4 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch; unused
+    uint64_t *rec;     // 2 per tile: high half of the tile's g_max sum | epoch; low half | word count, epoch (in the order of rec_part)
+    uint64_t *tile;    // 4 per tile: scale | epoch; place of its first word in the packet | epoch; words of the layer before it | epoch; unused (kOneTable: see rec_copy)
     uint64_t *layer;   // 4 per layer: scale | epoch; padded bytes of its words | epoch; its words | epoch; unused
     uint32_t *epoch;   // per tile, and for the header's workgroup: number of calls so far, counted up by that workgroup itself
 };
@@ -644,8 +644,8 @@ __device__ __forceinline__ uint64_t sync_load(const uint64_t *p) { return __hip_
 __device__ __forceinline__ void sync_store(uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ uint64_t sync_word(uint32_t value, uint32_t epoch) { return (uint64_t(value) << 32) | epoch; }
 
-// a word count is at most 16384: 15 bits, and 17 for the epoch.  Every tile's record is written in
-// every call, so a stale one is always exactly one call old.
+// a word count is at most 16384: 15 bits, and 17 for the epoch, which come back after 131072 calls: a low word has to
+// be written in every call (see rec_part), so that a stale one is one call old.
 constexpr uint32_t kRecEpochMask = (1u << 17) - 1u;
 __device__ __forceinline__ uint64_t rec_high(double sum, uint32_t epoch) { return (__builtin_bit_cast(uint64_t, sum) & 0xFFFFFFFF00000000ull) | epoch; }
 __device__ __forceinline__ uint64_t rec_low(double sum, uint32_t count, uint32_t epoch)
@@ -663,6 +663,16 @@ constexpr uint32_t kRecCopies = 3;
 __device__ __forceinline__ uint64_t *rec_copy(const SyncArea &sy, const uint32_t n_tiles, const uint32_t copy)
 {
     return copy == 0u ? sy.rec : sy.tile + 2u * n_tiles * (copy - 1u);
+}
+// Where in its pair of words a record has its low word (part 1).  kOneLayers: behind the high one.  kOneTable: in every
+// second pair before it, so that the low words of the copies stand where kOneLayers has a place or a number of words, in
+// the second and third of the four of a tile, and calls of that form replace them too; of the first and the fourth a call
+// may leave what is any number of calls old, but a high word says in 32 bits which call it is of.  (A fourth word written by
+// kOneLayers instead costs that form 2 %: ResNet-50's table 60.6 / 61.6 us, the character LSTM 70.2 / 71.6.)
+template <int ONE>
+__device__ __forceinline__ uint32_t rec_part(const uint64_t *pair, const uint32_t part)
+{
+    return ONE == kOneTable ? ((uint32_t(reinterpret_cast<uintptr_t>(pair)) >> 4) ^ part) & 1u : part;
 }
 __device__ __forceinline__ double rec_sum(uint64_t hi, uint64_t lo) { return __builtin_bit_cast(double, (hi & 0xFFFFFFFF00000000ull) | (lo >> 32)); }
 __device__ __forceinline__ uint32_t rec_count(uint64_t lo) { return uint32_t(lo) >> 17; }
@@ -727,15 +737,16 @@ __device__ __forceinline__ float fixed_residue(const float r, const uint32_t cod
 
 // Works out and publishes the record of a tile whose workgroup has not done it, by the whole
 // workgroup; does nothing if the record is there.  Begins and ends with a barrier.  s_map (LAZY): LDS for fix_map.
-template <uint32_t WG, bool VARIANT, bool LAZY>
+template <uint32_t WG, bool VARIANT, bool LAZY, int ONE>
 __device__ __forceinline__ void help_tile(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t tile,
                                           const uint32_t epoch, uint32_t *s_gmax, uint32_t *s_map, OneShared &sh)
 {
     const uint32_t tid = threadIdx.x;
     __syncthreads();
     if (tid == 0) {
-        sh.old_rec[0] = sync_load(sy.rec + 2u * tile);
-        sh.old_rec[1] = sync_load(sy.rec + 2u * tile + 1u);
+        const uint64_t *pair = sy.rec + 2u * tile;
+        sh.old_rec[0] = sync_load(pair + rec_part<ONE>(pair, 0u));
+        sh.old_rec[1] = sync_load(pair + rec_part<ONE>(pair, 1u));
         sh.missing = rec_valid(sh.old_rec[0], sh.old_rec[1], epoch) ? 0u : 1u;
         sh.base = 0u;
     }
@@ -771,11 +782,12 @@ __device__ __forceinline__ void help_tile(const CompressArgs &a, const SyncArea 
         const double sum = tile_gmax_sum<WG>(s_gmax, nb, sh.d);
         if (tid == 0) {
             const uint32_t total = sh.base;
+            uint64_t *pair = sy.rec + 2u * tile;
             if (uint32_t(sh.old_rec[0]) != epoch)
-                __hip_atomic_compare_exchange_strong(sy.rec + 2u * tile, &sh.old_rec[0], rec_high(sum, epoch), __ATOMIC_RELAXED,
+                __hip_atomic_compare_exchange_strong(pair + rec_part<ONE>(pair, 0u), &sh.old_rec[0], rec_high(sum, epoch), __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((uint32_t(sh.old_rec[1]) & kRecEpochMask) != (epoch & kRecEpochMask))
-                __hip_atomic_compare_exchange_strong(sy.rec + 2u * tile + 1u, &sh.old_rec[1], rec_low(sum, total, epoch), __ATOMIC_RELAXED,
+                __hip_atomic_compare_exchange_strong(pair + rec_part<ONE>(pair, 1u), &sh.old_rec[1], rec_low(sum, total, epoch), __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -789,7 +801,7 @@ struct Records {
 };
 
 // Polls for the thread's records of tiles ts .. ts + nt - 1; says whether they all came.
-template <uint32_t WG, uint32_t HOLD>
+template <uint32_t WG, int ONE, uint32_t HOLD>
 __device__ __forceinline__ bool poll_records(const SyncArea &sy, const uint32_t ts, const uint32_t nt,
                                              const uint32_t epoch, const uint32_t most_polls, Records<HOLD> &rec)
 {
@@ -803,8 +815,8 @@ __device__ __forceinline__ bool poll_records(const SyncArea &sy, const uint32_t 
         bool ok = i >= nt;
         for (uint32_t polls = 0; !ok && polls <= most_polls; ++polls) {
             if (polls != 0u) __builtin_amdgcn_s_sleep(1);
-            rec.hi[h] = sync_load(src);
-            rec.lo[h] = sync_load(src + 1);
+            rec.hi[h] = sync_load(src + rec_part<ONE>(src, 0u));
+            rec.lo[h] = sync_load(src + rec_part<ONE>(src, 1u));
             ok = rec_valid(rec.hi[h], rec.lo[h], epoch);
         }
         all = all && ok;
@@ -817,7 +829,7 @@ __device__ __forceinline__ bool poll_records(const SyncArea &sy, const uint32_t 
 // so come upon different ones: those that cannot start are worked out about as fast as if they ran.  (Every
 // round adds a record or finds that somebody else did; false after more rounds than there are tiles: another
 // call is at work in the same area.)
-template <uint32_t WG, uint32_t HOLD, bool VARIANT, bool LAZY>
+template <uint32_t WG, uint32_t HOLD, bool VARIANT, bool LAZY, int ONE>
 __device__ __forceinline__ bool help_records(const CompressArgs &a, const SyncArea &sy, const uint32_t lr, const uint32_t ts, const uint32_t nt,
                                              const uint32_t epoch, uint32_t seed, uint32_t *s_gmax, uint32_t *s_map, OneShared &sh)
 {
@@ -827,7 +839,7 @@ __device__ __forceinline__ bool help_records(const CompressArgs &a, const SyncAr
         for (uint32_t h = 0; h < HOLD; ++h) {
             const uint32_t i = h * WG + tid;
             const uint64_t *src = sy.rec + 2u * (ts + i);
-            const bool miss = i < nt && !rec_valid(sync_load(src), sync_load(src + 1), epoch);
+            const bool miss = i < nt && !rec_valid(sync_load(src + rec_part<ONE>(src, 0u)), sync_load(src + rec_part<ONE>(src, 1u)), epoch);
             const uint64_t m = __builtin_amdgcn_ballot_w64(miss);
             if ((tid & 63u) == 0u) sh.miss[i >> 6] = m;
         }
@@ -847,7 +859,7 @@ __device__ __forceinline__ bool help_records(const CompressArgs &a, const SyncAr
             }
             k -= c;
         }
-        help_tile<WG, VARIANT, LAZY>(a, sy, lr, ts + __builtin_amdgcn_readfirstlane(q), epoch, s_gmax, s_map, sh);
+        help_tile<WG, VARIANT, LAZY, ONE>(a, sy, lr, ts + __builtin_amdgcn_readfirstlane(q), epoch, s_gmax, s_map, sh);
     }
     return false;
 }
@@ -928,8 +940,8 @@ __device__ __forceinline__ bool complete_layer(const CompressArgs &a, const Sync
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t ts = a.layers[l].ctile_start, nt = a.layers[l].n_ctiles, wbytes = a.layers[l].word_bytes;
     Records<HOLD> rec;
-    if (HELP && !help_records<WG, HOLD, VARIANT, LAZY>(a, sy, lr, ts, nt, epoch, seed, s_gmax, s_map, sh)) return false;
-    if (block_any<WG>(!poll_records<WG>(sy, ts, nt, epoch, HELP ? 0u : a.wait_polls, rec), sh.any[0])) return false;
+    if (HELP && !help_records<WG, HOLD, VARIANT, LAZY, kOneLayers>(a, sy, lr, ts, nt, epoch, seed, s_gmax, s_map, sh)) return false;
+    if (block_any<WG>(!poll_records<WG, kOneLayers>(sy, ts, nt, epoch, HELP ? 0u : a.wait_polls, rec), sh.any[0])) return false;
     uint32_t before[HOLD];
     double part = 0.0;
     const uint32_t words = scan_records<WG>(nt, rec, sh, before, part);
@@ -997,11 +1009,11 @@ __device__ __forceinline__ bool table_records(const CompressArgs &a, const SyncA
     helped = false;
     SyncArea copy = sy;   // (whoever helps publishes in the first copy only, and reads that one)
     copy.rec = rec_copy(sy, a.n_tiles, blockIdx.x % kRecCopies);
-    const bool all = poll_records<WG>(copy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
+    const bool all = poll_records<WG, kOneTable>(copy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
     lay_out();
     if (__builtin_expect(block_any<WG>(!all, sh.any[0]), false)) {
-        const bool there = help_records<WG, HOLD, VARIANT, LAZY>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, s_map, sh);
-        if (block_any<WG>(!(there && poll_records<WG>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return false;
+        const bool there = help_records<WG, HOLD, VARIANT, LAZY, kOneTable>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, s_map, sh);
+        if (block_any<WG>(!(there && poll_records<WG, kOneTable>(sy, 0u, a.n_tiles, epoch, 0u, rec)), sh.any[1])) return false;
         lay_out();
         __syncthreads();
         helped = true;
@@ -1292,8 +1304,10 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LA
 #pragma unroll
     for (int j = 0; j < J; ++j) row_at[j] = uint32_t(__builtin_amdgcn_readlane(int(rows_incl - row), j * WAVES + int(wave)));
     // first thing: others wait for it
-    if (tid < (ONE == kOneTable ? 2u * kRecCopies : 2u))
-        sync_store(rec_copy(sy, a.n_tiles, tid >> 1) + 2u * tile + (tid & 1u), (tid & 1u) ? rec_low(gmax_sum, tile_total, epoch) : rec_high(gmax_sum, epoch));
+    if (tid < (ONE == kOneTable ? 2u * kRecCopies : 2u)) {
+        uint64_t *pair = rec_copy(sy, a.n_tiles, tid >> 1) + 2u * tile;
+        sync_store(pair + rec_part<ONE>(pair, tid & 1u), (tid & 1u) ? rec_low(gmax_sum, tile_total, epoch) : rec_high(gmax_sum, epoch));
+    }
     if (tid == 0) count_call(sy.epoch + tile);
     if (ONE == kOneTable) __builtin_amdgcn_s_setprio(0);
     // A layer's last workgroup adds up its layer, before anything else: all of the layer wait for it.

@@ -354,6 +354,33 @@ def test_more_workgroups_than_are_resident(H, oracle_lib):
     H.run_parity(oracle_lib, wl, 9, 2, seed=13, label="one launch: 9 learners", batch=True)
 
 
+@pytest.mark.parametrize("odd", [0, 1])
+def test_both_forms_write_the_words_of_an_area(H, odd):
+    """Calls of 1 and of 9 learners on one workspace take the two forms, which share what a learner's exchange area has
+    for its tiles, four words each.  The second and third, where records keep 17 bits of the call's number beside a word
+    count, are written in every call; the others tell calls apart by 32 bits."""
+    import paper_1712_02679_amd as A
+    wl = W.custom("crowd", [("a", 600 * 1000 + 2600 * odd, 50), ("b", 55 * 1000 + 9, 500)], dist="normal")
+    table, n = wl.table(), wl.n_total
+    gpu = H.GpuSide(table, n, 9, batch=True)
+    try:
+        layers = gpu.ws[256:256 + 64 * len(table)].cpu().numpy().view(np.uint32).reshape(len(table), 16)
+        tiles = int(layers[-1][10] + layers[-1][11])   # the last layer's first tile, and how many it has
+        assert tiles % 2 == odd
+        area = A.adacomp_workspace_bytes_batch(table, 2) - A.adacomp_workspace_bytes(table) - A.adacomp_workspace_gmax(table)[2]
+        at = gpu.ws.numel() // 128 * 128 - 9 * area + -(-16 * tiles // 128) * 128
+        for call, live in enumerate((9, 1, 9, 9, 1, 1, 9)):
+            g = [torch.from_numpy(W.gradient(wl, k, call, seed=2)).cuda() for k in range(live)]
+            A.adacomp_compress_batch(table, g, gpu.residue[:live], gpu.packets[:live], gpu.ws, packet_capacity=gpu.capacity)
+            torch.cuda.synchronize()
+            words = gpu.ws[at:at + 32 * tiles].cpu().numpy().view(np.uint64).reshape(tiles, 4)
+            assert np.all(words[:, 1:3] & 0x1FFFF == call + 1), (call, live)
+            whole = (0, 3) if live == 1 else (0, 1, 2)
+            assert np.all(words[:, whole] & 0xFFFFFFFF == call + 1), (call, live)
+    finally:
+        gpu.close()
+
+
 @pytest.mark.parametrize("n", [33, 40])
 def test_more_learners_than_a_launch(H, oracle_lib, n):
     """Calls of more than 32 learners take several launches, which use the same exchange areas in turn."""
