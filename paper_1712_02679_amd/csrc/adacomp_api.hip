@@ -78,10 +78,10 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     for (uint32_t l = 0; l < n_layers; ++l) elems_all += layers[l].n_elems;
     uint32_t small_cap = uint32_t(std::min<uint64_t>(4096u, std::max<uint64_t>(1024u, elems_all / kComputeUnits)));
     // ... and, where a somewhat larger tile does it, as many as there are compute units, less the one for the header:
-    // a few more share units with others (397 k elements, 266 tiles of 1500 / 199 of 2000: 7.8 / 6.6 us; 600 k, 9.2 / 7.5).
+    // a few more share units with others (397 k elements, 266 tiles of 1500 / 199 of 2000: 7.8 / 6.6 us; 600 k, 9.2 / 7.5; 1.02 M, 263 of
+    // 3900 / 255 of 4000: 8.35 / 7.25, 4 learners with unpack 22.5 / 22.1).
     uint64_t tiles_before = 0;
-    for (uint32_t cap = small_cap; cap < 4096u || cap == small_cap; cap += cap / 16u) {
-        cap = std::min(cap, 4096u);
+    for (uint32_t cap = small_cap;; cap = std::min(cap + cap / 16u, 4096u)) {
         uint64_t tiles = 0;
         for (uint32_t l = 0; l < n_layers; ++l) {
             const uint64_t bins = (layers[l].n_elems + layers[l].L_T - 1u) / layers[l].L_T;
@@ -92,7 +92,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         }
         if (tiles_before == 0) tiles_before = tiles;
         if (tiles < kComputeUnits) { small_cap = cap; break; }
-        if (cap == 4096u) break;
+        if (cap >= 4096u) break;
     }
 
     // Tables with layers of the larger tile class that can go in one launch (one_launch_for) have all their layers in

@@ -224,6 +224,14 @@ int main()
                 if (p.ws.least(n + 1) <= bytes) return 14;
             }
         }
+    for (uint64_t elems = 240000; elems < 1100000; elems += 3571)   // fewer tiles than compute units wherever tiles of up to 4096 elements make so few
+        for (uint32_t lt : {50u, 52u, 500u, 1000u}) {
+            const adacomp_layer_t t = {0, elems, lt, 0};
+            adacomp::Plan p;
+            if (adacomp::build_plan(&t, 1, false, p) != ADACOMP_OK) return 16;
+            const uint64_t of_4096 = 4096u / lt / (lt % 4u ? 2u : 1u) * (lt % 4u ? 2u : 1u), least = ((elems + lt - 1u) / lt + of_4096 - 1u) / of_4096;
+            if (least < 256u && p.n_ctiles >= 256u) return 17;
+        }
     for (uint32_t lt = 4; lt <= 50; ++lt) {   // short bins in tiles of the larger class, as many as such a tile takes
         std::vector<adacomp_layer_t> t = {{0, 9001 * 3 + 1, 9001, 0}, {27008, 1024ull * 70 * lt + 7, lt, 0}};
         adacomp::Plan p;
