@@ -128,6 +128,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         ld.bin_start = uint32_t(bins_total);
         ld.chunk_start = uint32_t(chunks_total);
         bins_total += n_bins;
+        if (wb == 2u) { p.n_elems16 += n; p.n_bins16 += n_bins; }
         chunks_total += n_chunks;
         if (bins_total >= (uint64_t(1) << 32)) return ADACOMP_EINVAL;
         p.elem_span = std::max<uint64_t>(p.elem_span, layers[l].elem_offset + n);
@@ -374,6 +375,7 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     // copy the scalars only; the tables already live on the device
     out.n_layers = p.n_layers; out.n_ctiles = p.n_ctiles; out.crowd_tiles = p.crowd_tiles; out.n_utiles = p.n_utiles; out.n_ugroups = p.n_ugroups; out.n_ugroups8 = p.n_ugroups8; out.n_usingles8 = p.n_usingles8;
     out.n_bins_total = p.n_bins_total; out.n_chunks_total = p.n_chunks_total;
+    out.n_elems16 = p.n_elems16; out.n_bins16 = p.n_bins16;
     out.elem_span = p.elem_span; out.n_elems_total = p.n_elems_total; out.stage_entries = p.stage_entries;
     out.fixed_bytes = p.fixed_bytes; out.bound_bytes = p.bound_bytes;
     for (int c = 0; c < 2; ++c) out.n_class_tiles[c] = p.n_class_tiles[c];
@@ -403,12 +405,21 @@ void register_workspace(const adacomp_layer_t *layers, uint32_t n_layers, const 
     g_ws[workspace] = std::move(reg);
 }
 
-// Workgroups per compute unit for launches over the 16-bit layers (see kResidentLds); 0: as many as fit.
-static uint32_t resident_for(uint32_t n_tiles, uint32_t n_learners, uint32_t mode)
+// Workgroups per compute unit for launches over the 16-bit layers, by what those have (see kResidentLds); 0: as many as fit.
+uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint32_t n_learners, uint32_t mode)
 {
-    if (n_tiles < (mode != 0u ? kResidentTiles : kResidentTilesSum)) return 0u;
-    if (mode == 2u) return n_learners <= 8u ? 4u : 5u;
-    return n_learners <= 8u ? 5u : 0u;
+    auto tiles_of = [&](uint32_t at_least) { return n_elems >= at_least * n_tiles; };                    // elements
+    auto bins_of = [&](uint32_t per_learner) { return n_elems >= per_learner * n_learners * n_bins; };   // elements, for every packet
+    const bool few = n_learners <= 4u;
+    if (mode == 2u) {
+        if (n_elems < kResidentElems) return 0u;
+        if ((tiles_of(3800u) && bins_of(60u)) || (tiles_of(2900u) && bins_of(300u))) return 4u;
+        return tiles_of(few ? 2300u : 2900u) && bins_of(25u) ? 5u : 0u;
+    }
+    if (n_learners > 8u || !bins_of(mode == 1u ? 60u : 50u)) return 0u;
+    if (mode == 1u) return n_elems >= kResidentElems && tiles_of(few ? 2700u : 2900u) ? 5u : 0u;
+    if (few) return n_elems >= kResidentElemsSum && (tiles_of(2700u) || (tiles_of(2300u) && bins_of(70u))) ? 5u : 0u;
+    return n_elems >= kResidentElemsSumMany && tiles_of(3800u) ? 5u : 0u;
 }
 
 // Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack and k_unpack_few (a workgroup)?
@@ -921,7 +932,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         // runs of tiles per workgroup for the plain sum, single tiles when the optimizer step follows
         const UGroupDev *table = reinterpret_cast<const UGroupDev *>(ws + (a.mode == 0u ? p.ws.ugroups : p.ws.usingles));
         const uint32_t n_all = a.mode == 0u ? p.n_ugroups : p.n_utiles, n8 = a.mode == 0u ? p.n_ugroups8 : p.n_usingles8;
-        const uint32_t n_tiles16 = p.n_utiles - p.n_usingles8;
+        const uint32_t resident = resident_for(p.n_elems16, p.n_bins16, p.n_utiles - p.n_usingles8, now, a.mode);   // for the 16-bit layers by themselves
         a.groups = table;
         a.n_groups = n_all;
         a.n_groups8 = a.first16 = a.chunk_lds = 0u;
@@ -933,7 +944,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
             a.chunk_lds = 64u * p.short_bin_max + unpack8_wg_log(p, n8, a.n_groups, now);
             if ((rc = launch_unpack(a, 3, 0u, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
-            if ((rc = launch_unpack(a, n8 ? 1 : 0, n8 ? 0u : resident_for(n_tiles16, now, a.mode), hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, n8 ? 1 : 0, n8 ? 0u : resident, hip_stream)) != ADACOMP_OK) return rc;
         } else if (p.n_utiles <= kUnpackSplitTiles || now <= kUnpackTogether) {  // mixed, and small or of few packets: one launch that handles both
             if ((rc = launch_unpack(a, 2, 0u, hip_stream)) != ADACOMP_OK) return rc;
         } else {  // large and mixed: the 8-bit groups come first in the table
@@ -941,7 +952,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
             if ((rc = launch_unpack(a, 1, 0u, hip_stream)) != ADACOMP_OK) return rc;
             a.groups = table + n8;
             a.n_groups = n_all - n8;
-            if ((rc = launch_unpack(a, 0, resident_for(n_tiles16, now, a.mode), hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 0, resident, hip_stream)) != ADACOMP_OK) return rc;
         }
         done += now;
     } while (done < n_learners);

@@ -86,16 +86,21 @@ constexpr uint32_t kUnpackTogether = 8;
 constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workgroups on a compute unit
 // Launches over the 16-bit layers of large tables are bound by HBM, which serves them better with fewer bytes in
 // flight than the workgroups that fit put there (as it does k_fused, below): LDS that no kernel touches holds them to 5
-// or 4 to a compute unit.  As many as fit (8, 7 or 6: up to 4, 8 or more learners) / 5 / 4, in us; L_T 500:
-//   Adam, 1 packet: 8 M 40.0 / 40.0 / 38.8, 24 M 118 / 114 / 112, 60 M 325 / 313 / 300; 8: 8 M 40.2 / 41.4 / 40.4, 24 M
-//     118 / 115 / 113, 60 M 314 / 303 / 286; 16: 12 M 61.9 / 62.0 / 62.8, 24 M 119 / 117 / 116, 125 M 519 / 512 / 520
-//   SGD, 2 packets: 8 M 25.5 / 26.0 / 26.1, 12 M 37.6 / 36.8 / 37.8, 60 M 190 / 174 / 174; 8: 24 M 73.8 / 71.7 / 73.1, 60 M
-//     186 / 175 / 175; 16: 125 M 337 / 338 / 357
-//   sum, 2 packets: 12 M 11.0 / 12.0 / 12.8, 24 M 24.2 / 23.5 / 22.7, 100 M 102 / 98 / 97; 8: 24 M 25.7 / 24.0 / 25.1, 60 M
-//     62.7 / 62.8 / 58.9
-//   L_T 100, 40 M: Adam, 4 packets 192 / 187 / 189; SGD, 8 122 / 124 / 135.
+// or 4 to a compute unit.  That needs full tiles, since a workgroup in one of 2080 elements (L_T 65; 2400 at 150 and 300, 2800 at
+// 700, 3000 at 3000 and 9000, 3200 at 100 and 200, 4000 at 500) has half of them in flight, and few words to each: what hides the
+// adds is other workgroups.  As many as fit (8, 7 or 6: up to 4, 8 or more packets) / 5 / 4, in us, 40 M elements:
+//   sum    L_T 65, 1 packet 34 / 43 / 51, 4 50 / 63 / 74, 8 76 / 86 / 98; 100, 1 38.6 / 35.3 / 36.2, 4 37.9 / 46.9 / 54; 200, 4
+//          42.2 / 39.2 / 39.3, 8 40.6 / 43.4 / 48.7; 300, 4 42.3 / 41.6 / 39.6, 8 41.5 / 44.4 / 51.6; 500, 1 42.2 / 41.5 / 40.5, 4 43.4 /
+//          41.8 / 41.8, 8 46.6 / 42.0 / 42.2, 16 47.9 / 48.8 / 53; 9000, 4 38.5 / 36.3 / 36.1, 8 38.0 / 39.2 / 42.8; 24 M, L_T 500, 4 25.2 /
+//          24.1 / 23.5, 8 25.5 / 26.2 / 28.1; 13 M, 4 11.9 / 12.6 / 14.1
+//   SGD    L_T 65, 1 115 / 123 / 135, 8 127 / 144 / 163; 100, 1 120 / 118 / 122, 8 123 / 126 / 137; 200, 1 121 / 117 / 121, 4 121 / 123 /
+//          128; 300, 4 116 / 121 / 129; 500, 1 126 / 117 / 117, 8 125 / 120 / 122, 16 126 / 127 / 133; 700, 4 117 / 115 / 118, 8 117.5 /
+//          118.5 / 125; 3000, 8 118 / 116 / 119; 13 M, L_T 500, 4 41.8 / 41.1 / 43.1
+//   Adam   L_T 65, 4 185 / 189 / 205, 8 193 / 207 / 228; 100, 4 194 / 189 / 191, 8 191 / 193 / 202; 200, 8 192 / 190 / 194; 300, 4 184 / 182 /
+//          187, 8 183 / 185 / 194; 500, 1 205 / 203 / 188, 8 204 / 195 / 189, 16 202 / 198 / 193 (125 M 519 / 512 / 520); 9000, 8 193 / 189 /
+//          186, 16 194 / 190 / 189; 13 M, L_T 500, 8 65.4 / 64.2 / 65.3
 constexpr uint32_t kResidentLds[2] = {32000, 40900};   // bytes of LDS that leave five, four workgroups on a compute unit
-constexpr uint32_t kResidentTiles = 2900, kResidentTilesSum = 5800;   // tiles from which on, with and without the optimizer
+constexpr uint64_t kResidentElems = 11600000, kResidentElemsSum = 23200000, kResidentElemsSumMany = 32000000;   // from which on: with the optimizer; sums of up to 4 packets; of more
 constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table that go alone (3 per compute unit)
 
 // What k_fused leaves per tile for k_scan and k_place: one 16-byte record, so that a tile makes one
@@ -172,6 +177,7 @@ struct Plan {
     uint32_t crowd_tiles = 0;   // compress tiles, for the lines between staged and one-launch calls of many workgroups (kOneLaunchCrowd*): as
                                 // many as a table makes before build_plan rounds them down to the compute units, with which the lines were measured
     uint32_t n_bins_total = 0, n_chunks_total = 0;
+    uint64_t n_elems16 = 0, n_bins16 = 0;   // of the layers with 16-bit words
     uint64_t elem_span = 0;     // max over layers of elem_offset + n_elems
     uint64_t n_elems_total = 0;
     uint64_t stage_entries = 0; // entries of the staging array: sum over the compress tiles of their element counts rounded up to 4
@@ -340,6 +346,7 @@ struct UnpackArgs {
 static_assert(sizeof(UnpackArgs) == 640 && offsetof(UnpackArgs, packets) == 128, "kernel arguments");
 
 uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units, bool lazy = false);
+uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint32_t n_learners, uint32_t mode);
 uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);
 int launch_fused(const CompressArgs &a, int jcode, void *stream);
 int launch_scan(const CompressArgs &a, void *stream);

@@ -343,6 +343,23 @@ int main()
                         if (163840 / lds < 3) { if (T <= 53 || 2 * n16 > n8) return 43; }
                     }
     }
+    {   // workgroups per compute unit of the launches over 16-bit layers: fewer than fit only where tiles are full and bins
+        // have elements enough for the packets (one layer; n_bins of L_T elements, a power of two of them to a tile of up to 4096)
+        using namespace adacomp;
+        auto held = [](uint64_t elems, uint32_t lt, uint32_t learners, uint32_t mode) {
+            const adacomp_layer_t t = {0, elems, lt, 0};
+            Plan p;
+            if (build_plan(&t, 1, true, p) != ADACOMP_OK || p.n_elems16 != elems || p.n_usingles8 != 0) return 99u;
+            return resident_for(p.n_elems16, p.n_bins16, p.n_utiles, learners, mode);
+        };
+        const uint64_t M = 1000000;
+        if (held(40 * M, 500, 8, 2) != 4 || held(40 * M, 500, 9, 2) != 5 || held(40 * M, 500, 16, 2) != 5 || held(40 * M, 500, 21, 2) != 0 || held(11 * M, 500, 1, 2) != 0) return 70;
+        if (held(40 * M, 100, 4, 2) != 5 || held(40 * M, 100, 5, 2) != 0 || held(40 * M, 65, 1, 2) != 0 || held(40 * M, 300, 4, 2) != 5 || held(40 * M, 300, 5, 2) != 0 || held(40 * M, 9000, 16, 2) != 4 || held(40 * M, 3000, 16, 2) != 5) return 71;
+        if (held(40 * M, 500, 8, 1) != 5 || held(40 * M, 500, 9, 1) != 0 || held(40 * M, 200, 3, 1) != 5 || held(40 * M, 200, 4, 1) != 0 || held(40 * M, 65, 1, 1) != 0) return 72;
+        if (held(40 * M, 700, 4, 1) != 5 || held(40 * M, 700, 5, 1) != 0 || held(40 * M, 3000, 8, 1) != 5 || held(11 * M, 500, 1, 1) != 0 || held(12 * M, 500, 1, 1) != 5) return 73;
+        if (held(24 * M, 500, 4, 0) != 5 || held(24 * M, 500, 5, 0) != 0 || held(40 * M, 500, 8, 0) != 5 || held(40 * M, 500, 9, 0) != 0 || held(23 * M, 500, 4, 0) != 0) return 74;
+        if (held(40 * M, 100, 2, 0) != 5 || held(40 * M, 100, 3, 0) != 0 || held(40 * M, 65, 1, 0) != 0 || held(40 * M, 200, 4, 0) != 5 || held(40 * M, 9000, 5, 0) != 0 || held(40 * M, 300, 4, 0) != 5 || held(40 * M, 150, 4, 0) != 0) return 75;
+    }
     if (adacomp_selftest_binindex() != 0) return 9;
     for (int c = 1; c > -9; --c) if (!adacomp_strerror(c)) return 10;
     std::printf("api sanitizer driver ok, checksum %llu, %llu tiles and %llu groups checked\n", (unsigned long long)checksum,
