@@ -29,7 +29,7 @@ TABLES = {
 # tile more; the most layers, and one more
 EDGES = {
     "512_tiles_16_layers": [(f"l{i}", 4000 * 32 - 3 * i, 500) for i in range(16)],   # the most that every workgroup reads, and half as many
-    "256_tiles_16_layers": [(f"l{i}", 4000 * 16 - i, 500 if i % 2 else 50) for i in range(16)],
+    "256_tiles_16_layers": [(f"l{i}", 4000 * 16, 500 if i % 2 else 50) for i in range(16)],
     "1024_tiles": [("a", 4000 * 1023 + 5, 50)],
     "1025_tiles": [("a", 4000 * 1024 + 5, 50)],
     "1024_tiles_long_bins": [("a", 4000 * 1024 - 500, 500)],
@@ -66,6 +66,23 @@ class _Impatient:
         self.H.GpuSide = self.real
 
 
+def layer_tiles(ws, n_layers):
+    """(first tile, number of tiles) of every layer, from the layer records of an initialised workspace."""
+    records = ws[256:256 + 64 * n_layers].cpu().numpy().view(np.uint32).reshape(n_layers, 16)
+    return [(int(r[10]), int(r[11])) for r in records]
+
+
+def tiles_of(table):
+    """Compress tiles that the library makes of a table."""
+    import paper_1712_02679_amd as A
+    ws = torch.zeros(A.adacomp_workspace_bytes(table), dtype=torch.uint8, device="cuda")
+    A.adacomp_workspace_init(table, ws)
+    torch.cuda.synchronize()
+    tiles = sum(layer_tiles(ws, len(table))[-1])
+    A.adacomp_workspace_release(ws)
+    return tiles
+
+
 @pytest.mark.parametrize("name,batch,impatient", [(n, b, False) for n in sorted(TABLES) for b in (False, True)] +
                          [(n, b, True) for n in sorted(TABLES) for b in (False, True)])
 def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
@@ -80,6 +97,9 @@ def test_one_launch_tables(H, oracle_lib, name, batch, impatient):
 
 @pytest.mark.parametrize("name,impatient", [(n, False) for n in sorted(EDGES)] + [("1024_tiles", True), ("512_layers", True), ("512_tiles_16_layers", True)])
 def test_one_launch_edges(H, oracle_lib, name, impatient):
+    table = W.custom(name, EDGES[name], dist="normal_outliers").table()
+    if "_tiles" in name:
+        assert tiles_of(table) == int(name.split("_")[0])
     with _Impatient(H) if impatient else contextlib.nullcontext():
         H.run_parity(oracle_lib, W.custom(name, EDGES[name], dist="normal_outliers"), 2, 2, seed=32, label=f"one launch: {name}, impatient {impatient}")
 
@@ -155,14 +175,13 @@ def test_one_launch_variants(H, oracle_lib, name, impatient, rule, factor):
                      batch=True)
 
 
-@pytest.mark.parametrize("n,rule,factor", [(1, 0, 2.0), (1, 1, 2.0), (1, 0, 1.5), (2, 0, 2.0), (2, 2, 2.0), (3, 0, 2.0)])
-@pytest.mark.parametrize("name,tiles", [("a", 255), ("b", 511)])
-def test_threads_per_tile(H, oracle_lib, name, tiles, n, rule, factor):
+@pytest.mark.parametrize("rule,factor", [(0, 2.0), (1, 2.0), (2, 2.0), (0, 1.5)])
+@pytest.mark.parametrize("n,tiles,per", [(1, 511, 4000), (1, 512, 4000), (1, 511, 2052), (2, 255, 2048), (2, 255, 2052), (2, 256, 2052), (3, 169, 2048), (3, 170, 4000)])
+def test_threads_per_tile(H, oracle_lib, n, tiles, per, rule, factor):
     """256 or 512 threads to a tile, at the line between them (512 workgroups, one per learner for the header), with
-    tiles that leave the second row of slots empty, by one element or not at all."""
-    per = (2000, 2052, 4000)[n - 1]   # of 2048 elements in a row of 512 threads
-    lt = (500, 54, 50)[n - 1]
-    wl = W.custom(name, [("x", per * (tiles - 9) - 5, lt), ("y", per * 9 - 1, lt)], dist="normal")
+    tiles that leave the second row of slots empty (2048 elements), by one slot (2052) or not at all."""
+    wl = W.custom("line", [("x", per * (tiles - 9) - 5, per), ("y", per * 9 - 1, per)], dist="normal")   # a bin to a tile
+    assert tiles_of(wl.table()) == tiles
     H.run_parity(oracle_lib, wl, n, 2, rule=rule, soft_factor=factor, seed=6, label=f"one launch: {tiles} tiles of {per}, {n} learners", batch=True)
 
 
@@ -364,8 +383,7 @@ def test_both_forms_write_the_words_of_an_area(H, odd):
     table, n = wl.table(), wl.n_total
     gpu = H.GpuSide(table, n, 9, batch=True)
     try:
-        layers = gpu.ws[256:256 + 64 * len(table)].cpu().numpy().view(np.uint32).reshape(len(table), 16)
-        tiles = int(layers[-1][10] + layers[-1][11])   # the last layer's first tile, and how many it has
+        tiles = sum(layer_tiles(gpu.ws, len(table))[-1])   # the last layer's first tile, and how many it has
         assert tiles % 2 == odd
         area = A.adacomp_workspace_bytes_batch(table, 2) - A.adacomp_workspace_bytes(table) - A.adacomp_workspace_gmax(table)[2]
         at = gpu.ws.numel() // 128 * 128 - 9 * area + -(-16 * tiles // 128) * 128
