@@ -572,10 +572,11 @@ __device__ __forceinline__ LayerDev header_layer(const CompressArgs &a) { return
 // when it runs out, the workgroup works out the missing records itself: a tile's record follows from
 // dW and the residue, and the residue of a tile is written only after all records of its layer are
 // published, so whoever finds a record missing may read the tile's inputs.  Should the owner have
-// moved on while the helper was reading, the helper's compare-and-swap finds the record there and
-// drops what it computed; otherwise the two hold the same bits, being the same operations in the same
-// order.  So two calls on different streams that hold each other's compute units finish, late; those who
-// wait in vain share the missing tiles (help_records).
+// moved on while the helper was reading, the helper's compare-and-swap finds the record there (which it
+// is before the owner writes the residue: the owner has read it, or see table_records) and drops what
+// it computed; otherwise the two hold the same bits, being the same operations in the same order.  So
+// two calls on different streams that hold each other's compute units finish, late; those who wait in
+// vain share the missing tiles (help_records).
 // ==============================================================================================
 constexpr int kOneTable = int(kOneLaunchTable), kOneLayers = int(kOneLaunchLayers);
 
@@ -660,6 +661,7 @@ __device__ __forceinline__ bool rec_valid(uint64_t hi, uint64_t lo, uint32_t epo
 // of them, some hundred times the same lines, and those that publish late wait behind those that already read:
 // 298 tiles 9.0 / 8.7 us, 491 tiles 10.0 / 9.8, 205 7.6 / 7.5.
 constexpr uint32_t kRecCopies = 3;
+constexpr int kWaitVmem = 0x0F70;   // s_waitcnt vmcnt(0): until the wave's loads and stores are done
 __device__ __forceinline__ uint64_t *rec_copy(const SyncArea &sy, const uint32_t n_tiles, const uint32_t copy)
 {
     return copy == 0u ? sy.rec : sy.tile + 2u * n_tiles * (copy - 1u);
@@ -1010,6 +1012,10 @@ __device__ __forceinline__ bool table_records(const CompressArgs &a, const SyncA
     SyncArea copy = sy;   // (whoever helps publishes in the first copy only, and reads that one)
     copy.rec = rec_copy(sy, a.n_tiles, blockIdx.x % kRecCopies);
     const bool all = poll_records<WG, kOneTable>(copy, 0u, a.n_tiles, epoch, a.wait_polls, rec);
+    // Who reads another copy does not learn from it that its own record is in the first one, where a helper that has read the
+    // residue after it was written has to find it: the wave that published, the first one, waits for its stores here, and the
+    // others for that wave at the barrier, before any of them writes the residue.  (They are done by then: no time.)
+    __builtin_amdgcn_s_waitcnt(kWaitVmem);
     lay_out();
     if (__builtin_expect(block_any<WG>(!all, sh.any[0]), false)) {
         const bool there = help_records<WG, HOLD, VARIANT, LAZY, kOneTable>(a, sy, lr, 0u, a.n_tiles, epoch, seed, s_gmax, s_map, sh);
