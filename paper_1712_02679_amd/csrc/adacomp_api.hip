@@ -493,6 +493,12 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
 }
 
+// 512 threads to a tile instead of 256 (see kPackWidePerUnit)?
+bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units)
+{
+    return std::min(n_learners, size_t(kMaxBatch)) * (size_t(p.n_ctiles) + 1u) <= size_t(kPackWidePerUnit) * compute_units;
+}
+
 // ---- optional event timing of the streaming kernel ---------------------------------------------
 // The records are guarded by g_timing_mu; `on` alone is read without it, so that calls pay nothing
 // while timing is off.
@@ -674,7 +680,7 @@ static int compress_common(const adacomp_layer_t *layers, uint32_t n_layers, uin
     if (a.one_launch != kOneLaunchNever) {
         const uint32_t units = compute_units_of(s);
         a.one_launch = one_launch_for(p, n_learners, workspace_bytes, units, lazy);
-        a.pack_wide = std::min(n_learners, kMaxBatch) * (p.n_ctiles + 1u) <= kPackWidePerUnit * units ? 1u : 0u;
+        a.pack_wide = pack_wide_for(p, n_learners, units) ? 1u : 0u;
     }
     a.sync = reinterpret_cast<uint8_t *>(ws + p.sync.offset);   // the launches of a call take turns with the areas
     a.sync_stride = p.ws.sync_stride;

@@ -126,7 +126,7 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
     // exchange areas of the one-launch compress: sections in order, behind the scratch blocks of as many
     // learners, inside the workspace, and none where there is no room; k_pack takes aligned tiles only
     if (!(w.sync_rec + 16 * size_t(p.n_ctiles) <= w.sync_tile && w.sync_tile + 32 * size_t(p.n_ctiles) <= w.sync_layer &&
-          w.sync_layer + 32 * size_t(p.n_layers) <= w.sync_epoch && w.sync_epoch + 4 * size_t(p.n_ctiles) <= w.sync_stride))
+          w.sync_layer + 32 * size_t(p.n_layers) <= w.sync_epoch && w.sync_epoch + 4 * (size_t(p.n_ctiles) + 1) <= w.sync_stride))   // (epochs: the header's workgroup has one too)
         return 148;
     // no call that the workspace accepts has a scratch block that reaches an area: a captured call may be
     // replayed after any of them
@@ -291,14 +291,14 @@ int main()
     {   // one launch only where half of the workgroups that are resident on the stream's compute units (8 on each)
         // hold the tiles that wait for each other: one layer, L_T 500, tiles of 4000 elements
         using namespace adacomp;
-        auto route = [](uint32_t tiles, uint32_t layers, uint32_t lt, size_t learners, uint32_t units) {
+        auto route = [](uint32_t tiles, uint32_t layers, uint32_t lt, size_t learners, uint32_t units, bool lazy = false) {
             std::vector<adacomp_layer_t> t(layers);
             for (uint32_t l = 0; l < layers; ++l) t[l] = adacomp_layer_t{uint64_t(l) * 4000 * tiles, 4000ull * tiles, lt, 0};
             Plan p;
             if (build_plan(t.data(), layers, false, p) != ADACOMP_OK) return 99u;
             if (tiles >= 256 && p.layer_tiles_max != tiles) return 98u;
             p.sync = sync_place(p.ws, p.ws.total(learners), SIZE_MAX);
-            return one_launch_for(p, learners, p.ws.total(learners), units);
+            return one_launch_for(p, learners, p.ws.total(learners), units, lazy);
         };
         if (route(1024, 1, 500, 1, 256) != kOneLaunchLayers || route(1025, 1, 500, 1, 256) != kOneLaunchNever) return 50;
         if (route(512, 2, 500, 8, 256) != kOneLaunchLayers || route(513, 2, 500, 8, 256) != kOneLaunchNever) return 51;
@@ -314,6 +314,37 @@ int main()
         if (route(120, 1, 50, 7, 256) != kOneLaunchTable || route(120, 1, 50, 8, 256) != kOneLaunchLayers || route(120, 1, 50, 30, 256) != kOneLaunchLayers) return 61;    // 267 tiles of 1800
         if (route(120, 1, 500, 6, 256) != kOneLaunchTable || route(120, 1, 500, 8, 256) != kOneLaunchLayers || route(120, 1, 500, 9, 256) != kOneLaunchNever) return 62;   // 320 of 1500
         if (route(3, 20, 50, 32, 256) != kOneLaunchLayers || route(3, 16, 50, 32, 256) != kOneLaunchNever) return 63;   // three staged launches or two
+        // several learners without short bins: layers of more than 512 tiles up to four rounds of resident workgroups (8192)
+        if (route(1024, 1, 500, 8, 256) != kOneLaunchLayers || route(1024, 1, 500, 9, 256) != kOneLaunchNever || route(600, 1, 500, 13, 256) != kOneLaunchLayers || route(600, 1, 500, 14, 256) != kOneLaunchNever) return 64;
+        // lazy calls: up to 24 M elements in all, with tiles of fewer than 1536 elements up to 6 workgroups on a compute unit
+        if (route(600, 10, 500, 1, 256, true) != kOneLaunchLayers || route(601, 10, 500, 1, 256, true) != kOneLaunchNever || route(600, 2, 50, 5, 256, true) != kOneLaunchLayers || route(600, 2, 50, 6, 256, true) != kOneLaunchNever) return 65;
+        if (route(60, 1, 500, 6, 256, true) != kOneLaunchTable || route(60, 1, 500, 7, 256, true) != kOneLaunchNever || route(60, 1, 500, 7, 256) != kOneLaunchTable || route(120, 1, 50, 6, 256, true) != kOneLaunchTable || route(120, 1, 50, 10, 256, true) != kOneLaunchLayers) return 66;
+        // tables of the larger tile class: layers of up to 256 tiles and of as many as the stream has compute units; without
+        // short bins up to 3 workgroups on each
+        auto large = [](uint32_t tiles, uint32_t layers, uint32_t lt, size_t learners, uint32_t units, bool lazy = false) {
+            std::vector<adacomp_layer_t> t(layers + 1);
+            for (uint32_t l = 0; l < layers; ++l) t[l] = adacomp_layer_t{uint64_t(l) * 16384 * tiles, 16384ull * tiles, 16384, 0};
+            t[layers] = adacomp_layer_t{uint64_t(layers) * 16384 * tiles, 2 * lt, lt, 0};
+            Plan p;
+            if (build_plan(t.data(), layers + 1, false, p) != ADACOMP_OK) return 99u;
+            p.sync = sync_place(p.ws, p.ws.total(learners), SIZE_MAX);
+            return one_launch_for(p, learners, p.ws.total(learners), units, lazy);
+        };
+        if (large(255, 1, 500, 2, 256) != kOneLaunchTable || large(256, 1, 500, 2, 256) != kOneLaunchLayers || large(257, 1, 500, 1, 256) != kOneLaunchNever) return 76;
+        if (large(255, 3, 500, 1, 256) != kOneLaunchLayers || large(256, 3, 500, 1, 256) != kOneLaunchNever || large(128, 2, 500, 2, 256) != kOneLaunchLayers || large(128, 2, 500, 3, 256) != kOneLaunchNever) return 77;
+        if (large(256, 5, 50, 1, 256) != kOneLaunchLayers || large(257, 5, 50, 1, 256) != kOneLaunchNever || large(100, 3, 50, 32, 256) != kOneLaunchLayers) return 78;
+        if (large(100, 1, 50, 1, 128) != kOneLaunchTable || large(128, 2, 50, 1, 128) != kOneLaunchLayers || large(129, 2, 50, 1, 128) != kOneLaunchNever) return 79;
+        if (large(244, 6, 50, 1, 256, true) != kOneLaunchLayers || large(245, 6, 50, 1, 256, true) != kOneLaunchNever) return 80;   // 24 M elements
+    }
+    {   // 512 threads to a tile up to two workgroups on a compute unit, one per learner for the header; bins of 2052: a tile each
+        using namespace adacomp;
+        auto wide = [](uint64_t tiles, size_t learners, uint32_t units) {
+            const adacomp_layer_t t = {0, 2052 * tiles, 2052, 0};
+            Plan p;
+            return build_plan(&t, 1, false, p) == ADACOMP_OK && p.n_ctiles == tiles && pack_wide_for(p, learners, units);
+        };
+        if (!wide(511, 1, 256) || wide(512, 1, 256) || !wide(255, 2, 256) || wide(256, 2, 256) || !wide(169, 3, 256) || wide(170, 3, 256) || !wide(15, 32, 256) || !wide(15, 40, 256) || wide(16, 32, 256)) return 81;
+        if (!wide(127, 1, 64) || wide(128, 1, 64) || wide(1, 1, 0)) return 82;
     }
     {   // the epochs of an exchange area after two calls that overlapped (both refused results, nothing else): in
         // whatever order the calls read and count, each tile has counted two, and the next call's tiles agree
