@@ -44,20 +44,6 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def timed_kernel(table, learners):
-    """The kernel that the library's timing events bracket: the streaming kernel of the staged launches, or, on
-    tables whose layers are small, the one launch that does everything, its wait and its placement included: up to
-    1024 tiles of 4000 elements a layer (512 in calls of many tiles of several learners without short bins), or, with
-    bins of the larger tile class among them, 256 tiles of 16384."""
-    if any(lt < 4 for _, _, lt in table):
-        return "k_fused"
-    if any(lt > 4096 or (lt % 4 and 4096 < lt * (2 if lt % 2 == 0 else 4) <= 16384) for _, _, lt in table):
-        return "k_pack" if max(-(-n // (16384 // lt * lt)) for _, n, lt in table) <= 256 else "k_fused"
-    tiles = [-(-n // 4000) for _, n, _ in table]
-    many = learners > 1 and not any(lt <= 64 for _, _, lt in table) and sum(tiles) * learners > 8192
-    return "k_pack" if max(tiles) <= (512 if many else 1024) else "k_fused"
-
-
 def measured_traffic(workload_name):
     """HBM bytes per k_fused launch from the committed rocprofv3 --pmc summary, if there is one
     for this workload (lines 'workload: <name>' and 'traffic_bytes_per_launch: <int>')."""
@@ -338,10 +324,13 @@ def main():
     per_launch = fused_learners // fused_n if fused_n else 1  # learners one launch of the timed kernel covers
     alg_bytes_launch = 12 * n_params * per_launch  # read dW, read residue, write residue, 4 B each
     roofline = None
+    # the kernel that the library's timing events bracket: the streaming kernel of the staged launches, or the one launch
+    # that does everything, its wait and its placement included
+    timed_kernel = "k_pack" if A.adacomp_debug_one_launch(ws, 1 if args.no_batch else n_learners) else "k_fused"
     if use_events and fused_n:
         dur_ms = fused_ms / fused_n
         achieved = alg_bytes_launch / (dur_ms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": timed_kernel(table, per_launch), "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+        roofline = {"bound": "hbm", "kernel": timed_kernel, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": (measured_traffic(wl.name) or 0) * per_launch or None,
                     "traffic_source": "committed rocprofv3 --pmc summary profiles/k_fused_hbm_traffic.txt (not a counter of this run)",

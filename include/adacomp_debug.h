@@ -34,6 +34,12 @@ int adacomp_workspace_gmax(const adacomp_layer_t *layers, uint32_t n_layers, siz
  * ADACOMP_EWORKSPACE if it is not registered. */
 int adacomp_debug_wait_polls(void *workspace, uint32_t polls);
 
+/* Whether an eager adacomp_compress_batch of n_learners on this workspace goes in one launch, k_pack (1), or in
+ * several, of which k_fused is the streaming one (0), on a stream that may use the whole GPU; lazy != 0:
+ * adacomp_compress_batch_lazy.  For the benchmark, which names the kernel that it timed.  ADACOMP_EWORKSPACE if the workspace
+ * is not registered or too small. */
+int adacomp_debug_one_launch(const void *workspace, size_t n_learners, int lazy);
+
 /* Plain float4 device copy of n floats (dst, src 16-byte aligned): the reference kernel against
  * which HBM byte counters and the achievable copy bandwidth are calibrated. */
 int adacomp_copy_f32(float *dst, const float *src, size_t n, void *hip_stream);

@@ -24,7 +24,7 @@ EXPORTS = [
     "adacomp_compress", "adacomp_compress_static", "adacomp_compress_batch", "adacomp_compress_variant",
     "adacomp_compress_batch_lazy", "adacomp_residue_sync",
     "adacomp_unpack_accumulate", "adacomp_unpack_update", "adacomp_strerror", "adacomp_workspace_gmax", "adacomp_debug_keep_gmax",
-    "adacomp_debug_wait_polls",
+    "adacomp_debug_wait_polls", "adacomp_debug_one_launch",
     "adacomp_copy_f32", "adacomp_triad_f32", "adacomp_triad_resident_f32", "adacomp_fill_f32",
     "adacomp_selftest_binindex", "adacomp_tuning_unpack_min_groups", "adacomp_tuning_fold_scan", "adacomp_tuning_place_tiled", "adacomp_timing_enable", "adacomp_timing_read",
 ]
@@ -95,6 +95,7 @@ def lib():
         L.adacomp_workspace_gmax.argtypes = [LP, u32, ctypes.POINTER(sz), ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.adacomp_debug_keep_gmax.argtypes = [ctypes.c_int]
         L.adacomp_debug_wait_polls.argtypes = [vp, u32]
+        L.adacomp_debug_one_launch.argtypes = [vp, ctypes.c_size_t, ctypes.c_int]
         L.adacomp_copy_f32.argtypes = [vp, vp, sz, vp]
         L.adacomp_triad_f32.argtypes = [vp, vp, sz, vp]
         L.adacomp_triad_resident_f32.argtypes = [vp, vp, sz, ctypes.c_uint32, vp]
@@ -259,6 +260,14 @@ def adacomp_debug_keep_gmax(on: bool):
 def adacomp_debug_wait_polls(workspace, polls: int):
     """How often a workgroup of a one-launch compress polls for a record before it works it out itself."""
     _check(lib().adacomp_debug_wait_polls(_ptr(workspace), int(polls)))
+
+
+def adacomp_debug_one_launch(workspace, n_learners: int, lazy: bool = False) -> bool:
+    """Whether a compress call of n_learners on this workspace goes in one launch (k_pack) or in several (k_fused ...)."""
+    rc = lib().adacomp_debug_one_launch(_ptr(workspace), int(n_learners), 1 if lazy else 0)
+    if rc < 0:
+        _check(rc)
+    return rc == 1
 
 
 def adacomp_copy_f32(dst, src, n=None):

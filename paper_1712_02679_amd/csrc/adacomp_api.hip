@@ -1064,6 +1064,14 @@ int adacomp_debug_wait_polls(void *workspace, uint32_t polls)
     return ADACOMP_OK;
 }
 
+int adacomp_debug_one_launch(const void *workspace, size_t n_learners, int lazy)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_ws.find(workspace);
+    if (it == g_ws.end() || n_learners == 0 || it->second.bytes < it->second.plan.ws.least(n_learners)) return ADACOMP_EWORKSPACE;
+    return one_launch_for(it->second.plan, n_learners, it->second.bytes, kComputeUnits, lazy != 0) != kOneLaunchNever ? 1 : 0;
+}
+
 int adacomp_tuning_fold_scan(int enable)
 {
     g_fold_scan = enable != 0;
