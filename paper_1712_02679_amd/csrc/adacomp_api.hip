@@ -135,9 +135,11 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         p.n_elems_total += n;
 
         // ---- compress tiles: whole bins, as many as fit the registers of a workgroup ------------
-        // 16 elements per thread (tiles of 4096 elements) unless a bin is longer: then 64 per thread
-        // (16384).  Tiles of 8192 elements streamed at less than half the rate of either on MI355X
-        // (measured on a plain triad), so there is no class in between.
+        // up to 4096 elements (256 threads with 16 each) unless a bin is longer: then up to 16384 (1024 threads).
+        // With all_large every layer takes the larger class, those of short bins too: tiles of up to large_cap
+        // elements, and of up to kMaxTileBins bins like the others, which with bins of fewer than 16 elements end
+        // inside a row of the threads' slots (see pack_bin).  Tiles of 8192 elements streamed at less than half the rate of
+        // either on MI355X (measured on a plain triad), so there is no class in between.
         // Tile starts are float4-aligned when a tile holds a multiple of a = 4 / gcd(L_T, 4) bins.  Bin
         // lengths that are odd (a = 4) or twice an odd number (a = 2) and too long for a such bins to fit
         // 4096 elements take the larger class when they fit there: unaligned tiles fall back to 4-byte

@@ -1047,7 +1047,9 @@ __device__ __forceinline__ uint32_t words_before(const uint32_t *s_excl, const u
 // or two.  Bound by HBM at 12 bytes per element plus the packet, and short of that by the wait, about
 // 8 us of a workgroup's life of 17 us on ResNet-50's table, which other workgroups have to cover:
 // hence eight of them on a compute unit, which takes 64 registers (7 spilled ones cost 10 %) and is why
-// several values are worked out anew below instead of being kept.
+// several values are worked out anew below instead of being kept.  The lazy form for layers spills 19 at that, and is
+// still the faster for it: 8 / 7 / 6 waves, in us, ResNet-50's table, 1 learner 64.5 / 66.5 / 70.8; the character LSTM, 1
+// 14.8 / 14.9 / 14.9, 4 35.8 / 36.6 / 40.9; 12 M elements, L_T 50 and 500, 2 60.9 / 64.1 / 67.0; 4 M, 2 22.2 / 27.6 / 28.7.
 // Measured, before (k_fused, k_scan, k_place or k_place_tiled) and now, in us: ResNet-50's table
 // 98 -> 65, a mini-batch of 8 learners with its unpack 700 -> 524; 23 layers with odd bins, 9.4 M
 // elements, 2 learners 71 -> 49; 397 k elements 12.1 -> 9.6; the CIFAR table, 4 learners with unpack,
@@ -2728,7 +2730,8 @@ static int check_launch() { return hipGetLastError() == hipSuccess ? ADACOMP_OK 
 int launch_fused(const CompressArgs &a, int jcode, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // tiles of 4096 elements: 256 threads; tiles of 16384 (a bin longer than 4096): 1024 threads.  Either
+    // tiles of the smaller class (up to 4096 elements): 256 threads; of the larger (up to 16384: layers with a bin longer
+    // than 4096, and all layers beside those in tables that can go in one launch, of whatever bins): 1024 threads.  Either
     // way a thread holds 16 elements, and a compute unit holds 32 waves of them.  (With 256 threads
     // and 64 elements each the long-bin tiles had two workgroups per compute unit and streamed at
     // 51-55 % of the HBM peak instead of 75-80 %.)

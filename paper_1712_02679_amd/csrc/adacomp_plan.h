@@ -140,8 +140,8 @@ struct WorkspaceLayout {
 // after the other.  They are cleared when the workspace is initialised and from then on belong to the kernels,
 // also to those of captured calls that are replayed any time later: so they begin behind the scratch block of
 // the last learner that any call on this workspace could have.  In workspace_bytes_batch(n) bytes that is learner
-// n.  An area takes 52 bytes per compress tile (44 are used: packed, without sections on lines of their own,
-// calls took 0.8 % longer over 41 tables), a scratch block 2 per element and some: areas for 32 learners fit in
+// n.  An area takes 52 bytes per compress tile (packed to 44, which one of the two forms makes do with, and
+// without sections on lines of their own, calls took 0.8 % longer over 41 tables), a scratch block 2 per element and some: areas for 32 learners fit in
 // less than a block where tiles have a thousand elements and are not few, for 16 where they have 400.  Calls of
 // more learners take the staged launches there (30 k elements in 14 layers, 32 learners: 15.7 us, one launch
 // 14.1, two of 16 learners each 23.5).
