@@ -495,6 +495,19 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     return (p.layer_tiles_max <= std::min(most, room) && p.n_layers <= kOneLaunchLayersMax) ? kOneLaunchLayers : kOneLaunchNever;
 }
 
+// Lanes per tile in k_place: 64 for tables with short bins, whose tiles send several hundred words,
+// and for small tables, where the launch is far from filling the GPU and the words of a tile are
+// better spread over more lanes (the 397 k-element table sends 440 words per tile in its first
+// steps: 37 -> 23 us per compress call); and for tables in tiles of the larger class, of which a tile sends four times
+// the words.  16 otherwise.  The larger class, 16 / 64 lanes, us: bins of 8000 and others, 40 M elements, L_T 100 in half of
+// them, 1 learner 144 / 129, 4 536 / 524; 200 130 / 124, 506 / 499; 500 113 / 109, 457 / 451; 60 M, 100 191 / 181, 826 / 780; bins of 8000
+// alone, 40 M, 97.2 / 96.2, 8 learners 804 / 797.
+uint32_t place_lanes_for(const Plan &p)
+{
+    const bool large = p.n_class_tiles[0] == 0u && p.n_class_tiles[1] != 0u;
+    return (p.has_short_bins || large || p.n_ctiles <= 2048u) ? 64u : 16u;
+}
+
 // 512 threads to a tile instead of 256 (see kPackWidePerUnit)?
 bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units)
 {
@@ -598,15 +611,6 @@ int adacomp_workspace_release(void *workspace)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     return g_ws.erase(workspace) ? ADACOMP_OK : ADACOMP_EINVAL;
-}
-
-// Lanes per tile in k_place: 64 for tables with short bins, whose tiles send several hundred words,
-// and for small tables, where the launch is far from filling the GPU and the words of a tile are
-// better spread over more lanes (the 397 k-element table sends 440 words per tile in its first
-// steps: 37 -> 23 us per compress call); 16 otherwise.
-static uint32_t place_lanes_for(const Plan &p)
-{
-    return (p.has_short_bins || p.n_ctiles <= 2048u) ? 64u : 16u;
 }
 
 // Small tables: no k_scan launch, the placement kernel does the scan itself (see k_place).
@@ -798,6 +802,7 @@ int adacomp_residue_sync(void *workspace, void *hip_stream)
         waiting = it->second.waiting;
         p.n_layers = it->second.plan.n_layers; p.n_ctiles = it->second.plan.n_ctiles;
         p.has_short_bins = it->second.plan.has_short_bins; p.ws = it->second.plan.ws;
+        for (int c = 0; c < 2; ++c) p.n_class_tiles[c] = it->second.plan.n_class_tiles[c];
     }
     char *ws = static_cast<char *>(workspace);
     CompressArgs a = {};

@@ -336,6 +336,16 @@ int main()
         if (large(100, 1, 50, 1, 128) != kOneLaunchTable || large(128, 2, 50, 1, 128) != kOneLaunchLayers || large(129, 2, 50, 1, 128) != kOneLaunchNever) return 79;
         if (large(244, 6, 50, 1, 256, true) != kOneLaunchLayers || large(245, 6, 50, 1, 256, true) != kOneLaunchNever) return 80;   // 24 M elements
     }
+    {   // lanes per tile in the placement: 64 with few tiles, with short bins, and in tables of the larger tile class
+        using namespace adacomp;
+        auto lanes = [](uint64_t elems, uint32_t lt, uint64_t elems_b, uint32_t lt_b) {
+            const adacomp_layer_t t[2] = {{0, elems, lt, 0}, {elems, elems_b, lt_b, 0}};
+            Plan p;
+            return build_plan(t, 2, true, p) == ADACOMP_OK ? place_lanes_for(p) : 0u;
+        };
+        if (lanes(2047 * 4000, 500, 400, 500) != 64 || lanes(2048 * 4000, 500, 400, 500) != 16 || lanes(5000 * 4000, 500, 400, 50) != 64) return 83;
+        if (lanes(3000 * 16000, 8000, 16000, 8000) != 64 || lanes(3000 * 16000, 8000, 5000 * 4000, 500) != 16) return 84;   // (of both classes: layers too long for one launch)
+    }
     {   // 512 threads to a tile up to two workgroups on a compute unit, one per learner for the header; bins of 2052: a tile each
         using namespace adacomp;
         auto wide = [](uint64_t tiles, size_t learners, uint32_t units) {

@@ -216,6 +216,13 @@ def test_large_tiles_lazy_and_staged(H, oracle_lib, monkeypatch):
     test_one_launch_beside_staged_calls(H, oracle_lib)
 
 
+def test_many_large_tiles_staged(H, oracle_lib):
+    """More than 2048 tiles of the larger class in layers that are too long for one launch: eager and lazy."""
+    wl = W.custom("long", [("a", 15000 * 1100 + 7, 5000), ("b", 16382 * 1000 - 5, 16382)], dist="normal_spikes")
+    H.run_parity(oracle_lib, wl, 1, 2, seed=14, label="staged: 2100 large tiles")
+    H.run_lazy_parity(oracle_lib, wl, 1, 3, 2, seed=14, label="staged, lazy: 2100 large tiles")
+
+
 LAZY_TABLES = {**{n: TABLES[n] for n in ("one_tile", "few_layers", "many_layers", "two_long_layers_short_bins")},
                **{n: LARGE_TABLES[n] for n in ("large_few_layers", "large_many_layers", "thousand_bins_few_layers", "thousand_bins_many_layers")}, "512_tiles_16_layers": EDGES["512_tiles_16_layers"]}
 
