@@ -489,6 +489,7 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     const bool folds = p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;   // two staged launches, not three
     const uint64_t pays = !p.has_short_bins ? kOneLaunchCrowdElemsLong : folds ? kOneLaunchCrowdElems : 0u;
     if (large && !p.has_short_bins && workgroups > 3 * size_t(room)) return kOneLaunchNever;
+    if (large && workgroups > kOneLaunchLargePerUnit * size_t(room) && p.n_elems_total < p.crowd_tiles * uint64_t(kOneLaunchLargeFill)) return kOneLaunchNever;
     if (2 * workgroups > 5 * size_t(room) && p.n_elems_total < p.crowd_tiles * pays) return kOneLaunchNever;
     if (!crowd && p.n_ctiles <= std::min(kFoldTiles, room) && p.n_layers <= kFoldLayers) return kOneLaunchTable;
     const uint32_t most = large ? kOneLaunchTilesLarge : (n_learners == 1 || p.has_short_bins || workgroups <= kOneLaunchRounds * 2 * size_t(room)) ? kOneLaunchTiles : kOneLaunchTilesLong;

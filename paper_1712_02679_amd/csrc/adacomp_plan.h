@@ -259,6 +259,13 @@ constexpr uint32_t kOneLaunchCrowdElems = 1536, kOneLaunchCrowdElemsLong = 2048;
 // calls are the shorter ones from 3 workgroups per unit on: L_T 5000, 2 M, 4 learners (536 workgroups) 36.8 / 34.2, 16
 // 88 / 96; 5 M, 4 learners 64 / 70; L_T 12001, 300 k, 16 learners (480) 31.7 / 22.8, 5 M, 4 63 / 70.
 constexpr uint32_t kOneLaunchTilesLarge = 256;
+// ... nor does one launch pay with many workgroups whose tiles are half empty, since one bin fills little more than half
+// of them: a workgroup holds its place for all that a full one waits, and loads less in that time.  Staged / one launch
+// / staged over tiles of both classes, in us: L_T 50 and 9000, 80 % of the elements in long bins (9900 to a tile), 10 M, 1
+// learner 54 / 38 / 48, 2 (2022 workgroups) 79 / 68 / 72, 4 130 / 129 / 122, 8 247 / 258 / 240; 20 M, 2 127 / 133 / 122; 4 M, 16 176 /
+// 196 / 183; 95 %, 20 M, 1 (2170) 76 / 70 / 70, 4 234 / 264 / 230; L_T 8200, 95 %, 4 242 / 283 / 239; but 60 % (11000 to a tile), 10 M, 8
+// 270 / 249 / 249, L_T 11000, 80 %, 8 240 / 230 / 232.
+constexpr uint32_t kOneLaunchLargeFill = 10000, kOneLaunchLargePerUnit = 12;   // elements per tile below which, workgroups per unit beyond which
 // Lazy calls save the placement's pass over the residue in either form, so that one launch pays by what it does without
 // launches and staged words, not by bytes: up to as many elements in all, and with small tiles up to the 6 workgroups
 // that its registers leave on a compute unit.  Staged / one launch, in us: 100 k elements, L_T 50 and 500, 1 learner 13.4 /

@@ -334,6 +334,17 @@ int main()
         if (large(255, 3, 500, 1, 256) != kOneLaunchLayers || large(256, 3, 500, 1, 256) != kOneLaunchNever || large(128, 2, 500, 2, 256) != kOneLaunchLayers || large(128, 2, 500, 3, 256) != kOneLaunchNever) return 77;
         if (large(256, 5, 50, 1, 256) != kOneLaunchLayers || large(257, 5, 50, 1, 256) != kOneLaunchNever || large(100, 3, 50, 32, 256) != kOneLaunchLayers) return 78;
         if (large(100, 1, 50, 1, 128) != kOneLaunchTable || large(128, 2, 50, 1, 128) != kOneLaunchLayers || large(129, 2, 50, 1, 128) != kOneLaunchNever) return 79;
+        // tiles half empty: 11 layers of 9000-element bins, 40 bins of L_T 50
+        auto half = [](uint32_t tiles, uint32_t lt, size_t learners, bool lazy = false) {
+            std::vector<adacomp_layer_t> t(12);
+            for (uint32_t l = 0; l < 11; ++l) t[l] = adacomp_layer_t{uint64_t(l) * lt * tiles, uint64_t(lt) * tiles, lt, 0};
+            t[11] = adacomp_layer_t{11ull * lt * tiles, 2000, 50, 0};
+            Plan p;
+            if (build_plan(t.data(), 12, false, p) != ADACOMP_OK || p.n_ctiles != 11 * tiles + 1) return 99u;
+            p.sync = sync_place(p.ws, p.ws.total(learners), SIZE_MAX);
+            return one_launch_for(p, learners, p.ws.total(learners), 256, lazy);
+        };
+        if (half(139, 9000, 2) != kOneLaunchLayers || half(140, 9000, 2) != kOneLaunchNever || half(140, 10012, 2) != kOneLaunchLayers || half(200, 12000, 4) != kOneLaunchLayers) return 85;
         if (large(244, 6, 50, 1, 256, true) != kOneLaunchLayers || large(245, 6, 50, 1, 256, true) != kOneLaunchNever) return 80;   // 24 M elements
     }
     {   // lanes per tile in the placement: 64 with few tiles, with short bins, and in tables of the larger tile class
