@@ -483,7 +483,8 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
     const bool large = p.n_class_tiles[1] != 0;
     const uint32_t room = (large ? kOneLaunchTilesLarge / kComputeUnits : kOneLaunchTilesPerUnit) * compute_units;
     const size_t workgroups = std::min(n_learners, size_t(kMaxBatch)) * p.crowd_tiles;
-    if (lazy && (n_learners * p.n_elems_total > kLazyOneLaunchElems ||
+    const bool filled = !large || p.n_elems_total >= p.crowd_tiles * uint64_t(kLazyLargeFill);
+    if (lazy && (n_learners * p.n_elems_total > (filled ? kLazyOneLaunchElems : kLazyOneLaunchElems / 2u) ||
                  (4 * workgroups > 6 * size_t(room) && p.n_elems_total < p.crowd_tiles * uint64_t(kOneLaunchCrowdElems)))) return kOneLaunchNever;
     const bool crowd = workgroups > 2 * size_t(room);   // more than are resident
     const bool folds = p.n_ctiles <= kFoldTiles && p.n_layers <= kFoldLayers;   // two staged launches, not three

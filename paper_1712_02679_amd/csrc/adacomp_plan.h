@@ -272,6 +272,11 @@ constexpr uint32_t kOneLaunchLargeFill = 10000, kOneLaunchLargePerUnit = 12;   /
 // 8.3, 16 with unpack (1700 workgroups of 1000) 32.2 / 34.3; 1.2 M, 1 16.4 / 11.2, 16 71 / 70; 4 M, 4 58 / 50, 16 164 / 170;
 // 12 M, 1 40.5 / 33.9, 2 63.4 / 63.0, 4 129 / 140; ResNet-50's table, 1 66.8 / 66.2, 8 415 / 475.
 constexpr uint64_t kLazyOneLaunchElems = 24u * 1000u * 1000u;
+// ... and half as many where tiles of the larger class are a third empty or more.  Staged / one launch / staged over tiles of
+// both classes: L_T 50 and 9000, 60 % of the elements in long bins (11000 to a tile), 4 M in all 27.8 / 20.8 / 31.7, 8 M 40.0 / 35.9 /
+// 40.9, 10 M, 1 learner 46.4 / 44.9 / 45.4, 2 42.0 / 38.2 / 45.7, 16 M 58.5 / 62.2 / 62.3, 20 M, 1 71.2 / 78.6 / 73.8, 2 70.9 / 81.3 /
+// 73.6, 4 66.5 / 74.1 / 73.6; but 20 % (14000 to a tile), 20 M 68 / 66 / 71, L_T 5000 (15000) 68 / 63 / 72.
+constexpr uint32_t kLazyLargeFill = 12288;   // elements per tile
 // Every tile looks at every layer before its own: 300 layers, 8 M elements, 4 learners 86 / 120.
 constexpr uint32_t kOneLaunchLayersMax = 512;
 

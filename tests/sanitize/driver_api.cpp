@@ -344,6 +344,7 @@ int main()
             p.sync = sync_place(p.ws, p.ws.total(learners), SIZE_MAX);
             return one_launch_for(p, learners, p.ws.total(learners), 256, lazy);
         };
+        if (half(121, 9000, 1, true) != kOneLaunchLayers || half(122, 9000, 1, true) != kOneLaunchNever || half(122, 12300, 1, true) != kOneLaunchLayers) return 86;
         if (half(139, 9000, 2) != kOneLaunchLayers || half(140, 9000, 2) != kOneLaunchNever || half(140, 10012, 2) != kOneLaunchLayers || half(200, 12000, 4) != kOneLaunchLayers) return 85;
         if (large(244, 6, 50, 1, 256, true) != kOneLaunchLayers || large(245, 6, 50, 1, 256, true) != kOneLaunchNever) return 80;   // 24 M elements
     }
