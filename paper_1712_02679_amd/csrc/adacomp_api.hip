@@ -102,15 +102,27 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
     // 13.4 / 12.1 / 12.1, 4 50 / 34 / 34 (in staged launches over tiles of both classes 24, 35, 24, 42, 87, 18 and 37).
     auto large_class = [](uint32_t T) { const uint64_t a = 4u / gcd_u32(T, 4u); return T > 4096u || (a * T > 4096u && a * T <= 16384u); };
     const uint32_t large_cap = uint32_t(std::min<uint64_t>(16384u, std::max<uint64_t>(4096u, elems_all / 64u)));
-    bool all_large = false, fits = n_layers <= kOneLaunchLayersMax;
+    bool all_large = false, fits = n_layers <= kOneLaunchLayersMax, short_bins = false;
+    uint64_t large_tiles = 0, long_elems = 0;   // tiles if all have that class; elements of the layers that need it
     for (uint32_t l = 0; l < n_layers && fits; ++l) {
         const uint32_t T = layers[l].L_T;
         const uint64_t a = 4u / gcd_u32(T, 4u), bpt = std::min<uint64_t>(std::max<uint64_t>(large_cap / T, 1u), kMaxTileBins);
         const uint64_t at_least = a * T <= 16384u ? (bpt < a ? a : bpt / a * a) : bpt;
         all_large = all_large || large_class(T);
         fits = T >= 4u && layers[l].n_elems <= at_least * T * kOneLaunchTilesLarge;
+        short_bins = short_bins || T <= 64u;
+        if (large_class(T)) long_elems += layers[l].n_elems;
+        large_tiles += (layers[l].n_elems + at_least * T - 1u) / (at_least * T);
     }
-    all_large = all_large && fits;
+    // Tables that are staged whoever calls, also one learner (one_launch_for), keep the smaller tiles for the bins that fit
+    // them, unless the long bins hold half of the elements and the others are not short: larger tiles save a launch over
+    // one of the classes (7 us), smaller ones stream faster.  Smaller / larger, us: L_T 500 and 8000, a quarter in long bins,
+    // 20 M, 4 learners 212 / 214, 16 869 / 914; 28 M, 1 85 / 83, 4 283 / 297, 8 578 / 610; 200, 4 310 / 342, 8 649 / 711; 60 M, 100, 1 189 / 201;
+    // half: 20 M, 500, 1 69 / 63, 8 395 / 404; 40 M, 1 113 / 109, 8 1004 / 960; 200, 1 122 / 124, 4 495 / 499; three quarters: 40 M, 100, 1
+    // 120 / 115, 4 484 / 464.  L_T 50, tiles half empty, 40 M, four fifths in bins of 9000, 1 learner 123 / 126, of 8200 126 / 131.
+    const bool staged = short_bins ? large_tiles > kOneLaunchLargePerUnit * kComputeUnits && elems_all < large_tiles * kOneLaunchLargeFill
+                                   : large_tiles > 3u * kComputeUnits;
+    all_large = all_large && fits && (!staged || (!short_bins && 2u * long_elems >= elems_all));
 
     for (uint32_t l = 0; l < n_layers; ++l) {
         const uint32_t T = layers[l].L_T;

@@ -348,6 +348,19 @@ int main()
         if (half(139, 9000, 2) != kOneLaunchLayers || half(140, 9000, 2) != kOneLaunchNever || half(140, 10012, 2) != kOneLaunchLayers || half(200, 12000, 4) != kOneLaunchLayers) return 85;
         if (large(244, 6, 50, 1, 256, true) != kOneLaunchLayers || large(245, 6, 50, 1, 256, true) != kOneLaunchNever) return 80;   // 24 M elements
     }
+    {   // tiles of both classes where no call goes in one launch, but not if long bins hold half of the elements of a table without short ones
+        using namespace adacomp;
+        auto both = [](uint32_t layers, uint32_t n_long, uint32_t tiles, uint32_t lt, uint32_t lt_long) {   // the same number of elements to each layer
+            std::vector<adacomp_layer_t> t(layers);
+            for (uint32_t l = 0; l < layers; ++l) t[l] = adacomp_layer_t{16000ull * tiles * l, 16000ull * tiles, l < n_long ? lt_long : lt, 0};
+            Plan p;
+            if (build_plan(t.data(), layers, true, p) != ADACOMP_OK || check_plan(t)) return 99;
+            return p.n_class_tiles[0] != 0u && p.n_class_tiles[1] != 0u ? 1 : p.n_class_tiles[1] != 0u ? 0 : 98;
+        };
+        if (both(4, 1, 192, 500, 8000) != 0 || both(4, 1, 193, 500, 8000) != 1 || both(4, 2, 193, 500, 8000) != 0 || both(7, 3, 193, 500, 8000) != 1) return 87;
+        if (both(4, 1, 193, 50, 8000) != 0 || both(20, 1, 200, 50, 8000) != 0) return 88;
+        if (both(20, 19, 139, 50, 9000) != 1 || both(20, 5, 139, 50, 9000) != 0 || both(10, 9, 139, 50, 9000) != 0) return 89;
+    }
     {   // lanes per tile in the placement: 64 with few tiles, with short bins, and in tables of the larger tile class
         using namespace adacomp;
         auto lanes = [](uint64_t elems, uint32_t lt, uint64_t elems_b, uint32_t lt_b) {
