@@ -115,14 +115,14 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         large_tiles += (layers[l].n_elems + at_least * T - 1u) / (at_least * T);
     }
     // Tables that are staged whoever calls, also one learner (one_launch_for), keep the smaller tiles for the bins that fit
-    // them, unless the long bins hold half of the elements and the others are not short: larger tiles save a launch over
+    // them, unless the long bins hold two fifths of the elements and the others are not short: larger tiles save a launch over
     // one of the classes (7 us), smaller ones stream faster.  Smaller / larger, us: L_T 500 and 8000, a quarter in long bins,
     // 20 M, 4 learners 212 / 214, 16 869 / 914; 28 M, 1 85 / 83, 4 283 / 297, 8 578 / 610; 200, 4 310 / 342, 8 649 / 711; 60 M, 100, 1 189 / 201;
     // half: 20 M, 500, 1 69 / 63, 8 395 / 404; 40 M, 1 113 / 109, 8 1004 / 960; 200, 1 122 / 124, 4 495 / 499; three quarters: 40 M, 100, 1
     // 120 / 115, 4 484 / 464.  L_T 50, tiles half empty, 40 M, four fifths in bins of 9000, 1 learner 123 / 126, of 8200 126 / 131.
     const bool staged = short_bins ? large_tiles > kOneLaunchLargePerUnit * kComputeUnits && elems_all < large_tiles * kOneLaunchLargeFill
                                    : large_tiles > 3u * kComputeUnits;
-    all_large = all_large && fits && (!staged || (!short_bins && 2u * long_elems >= elems_all));
+    all_large = all_large && fits && (!staged || (!short_bins && 5u * long_elems >= 2u * elems_all));
 
     for (uint32_t l = 0; l < n_layers; ++l) {
         const uint32_t T = layers[l].L_T;

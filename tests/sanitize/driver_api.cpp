@@ -348,7 +348,7 @@ int main()
         if (half(139, 9000, 2) != kOneLaunchLayers || half(140, 9000, 2) != kOneLaunchNever || half(140, 10012, 2) != kOneLaunchLayers || half(200, 12000, 4) != kOneLaunchLayers) return 85;
         if (large(244, 6, 50, 1, 256, true) != kOneLaunchLayers || large(245, 6, 50, 1, 256, true) != kOneLaunchNever) return 80;   // 24 M elements
     }
-    {   // tiles of both classes where no call goes in one launch, but not if long bins hold half of the elements of a table without short ones
+    {   // tiles of both classes where no call goes in one launch, but not if long bins hold two fifths of the elements of a table without short ones
         using namespace adacomp;
         auto both = [](uint32_t layers, uint32_t n_long, uint32_t tiles, uint32_t lt, uint32_t lt_long) {   // the same number of elements to each layer
             std::vector<adacomp_layer_t> t(layers);
@@ -357,7 +357,7 @@ int main()
             if (build_plan(t.data(), layers, true, p) != ADACOMP_OK || check_plan(t)) return 99;
             return p.n_class_tiles[0] != 0u && p.n_class_tiles[1] != 0u ? 1 : p.n_class_tiles[1] != 0u ? 0 : 98;
         };
-        if (both(4, 1, 192, 500, 8000) != 0 || both(4, 1, 193, 500, 8000) != 1 || both(4, 2, 193, 500, 8000) != 0 || both(7, 3, 193, 500, 8000) != 1) return 87;
+        if (both(4, 1, 192, 500, 8000) != 0 || both(4, 1, 193, 500, 8000) != 1 || both(4, 2, 193, 500, 8000) != 0 || both(5, 2, 193, 500, 8000) != 0 || both(8, 3, 193, 500, 8000) != 1) return 87;
         if (both(4, 1, 193, 50, 8000) != 0 || both(20, 1, 200, 50, 8000) != 0) return 88;
         if (both(20, 19, 139, 50, 9000) != 1 || both(20, 5, 139, 50, 9000) != 0 || both(10, 9, 139, 50, 9000) != 0) return 89;
     }
