@@ -179,8 +179,8 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 // 16-byte slots.  Slot q of the tile then covers the elements 4 q - skip .. 4 q + 3 - skip: the first
 // slot begins in the tile before (those elements are left alone: loaded as zero, never stored) and
 // everything after it is aligned.  With 4-byte accesses such tiles streamed at 44 % of the HBM peak.
-template <int J, int WAVES, bool VARIANT, bool LAZY, bool SHIFT = false>
-__global__ __launch_bounds__(WAVES * 64) void k_fused(const CompressArgs a)
+template <int J, int WAVES, bool VARIANT, bool LAZY, bool SHIFT>
+__device__ __forceinline__ void fused_tile(const CompressArgs &a)
 {
     static_assert(!(SHIFT && LAZY), "the lazy kernel keeps 4-byte accesses on unaligned tiles");
     constexpr uint32_t WG = uint32_t(WAVES) * 64u;  // threads of the workgroup: a tile is J * WG float4 slots
@@ -467,6 +467,25 @@ __global__ __launch_bounds__(WAVES * 64) void k_fused(const CompressArgs a)
         o.base = 0u;  // filled in by k_scan
         tile_out[tile] = o;  // one 16-byte store
     }
+}
+
+template <int J, int WAVES, bool VARIANT, bool LAZY, bool SHIFT = false>
+__global__ __launch_bounds__(WAVES * 64) void k_fused(const CompressArgs a)
+{
+    fused_tile<J, WAVES, VARIANT, LAZY, SHIFT>(a);
+}
+// Those of 1024 threads that the compiler gives 81 scalar registers are held to 80: beyond them one of these workgroups fits a
+// compute unit, not two (see k_pack).  Another rule, in us, 81 / 80: 40 M elements, L_T 5000, 1 learner 143 / 101, 4 598 / 416; L_T 5001 143 / 101;
+// 20 M, 500 and 8000, 8 594 / 404; 3 M, 200 and 4500, 20 257 / 185.
+template <>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80))) void k_fused<4, 16, true, false, false>(const CompressArgs a)
+{
+    fused_tile<4, 16, true, false, false>(a);
+}
+template <>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80))) void k_fused<4, 16, true, false, true>(const CompressArgs a)
+{
+    fused_tile<4, 16, true, false, true>(a);
 }
 
 __device__ __forceinline__ uint64_t pad16_dev(uint64_t x) { return (x + 15u) & ~uint64_t(15); }
