@@ -1072,7 +1072,7 @@ __device__ __forceinline__ uint32_t words_before(const uint32_t *s_excl, const u
 // Measured, before (k_fused, k_scan, k_place or k_place_tiled) and now, in us: ResNet-50's table
 // 98 -> 65, a mini-batch of 8 learners with its unpack 700 -> 524; 23 layers with odd bins, 9.4 M
 // elements, 2 learners 71 -> 49; 397 k elements 12.1 -> 9.6; the CIFAR table, 4 learners with unpack,
-// 33 -> 23.  (Since then 60, 498, 47, 6.6 and 21.4: the layer added up early, the header's own workgroup, 512 threads.)
+// 33 -> 23.  (Since then 60, 495, 47, 6.6 and 22: the layer added up early, the header's own workgroup, 512 threads.)
 // ==============================================================================================
 // values the compiler is not to connect with what they were before
 template <int N>
