@@ -260,6 +260,7 @@ int main()
         Plan p, found;
         if (build_plan(a.data(), 3, true, p) != ADACOMP_OK) return 20;
         const size_t bytes = p.ws.total(2);
+        p.sync = sync_place(p.ws, bytes, SIZE_MAX);
         register_workspace(a.data(), 3, fake_ws, bytes, std::move(p));
         if (find_plan(a.data(), 3, fake_ws, bytes, 2, found) != ADACOMP_OK) return 21;
         if (found.n_ctiles == 0 || found.ws.total(2) != bytes) return 22;
@@ -285,6 +286,13 @@ int main()
             if (found.wait_polls != std::min(polls, kWaitPollsMax)) return 32;
         }
         if (adacomp_debug_wait_polls(fake_ws + 16, 1) != ADACOMP_EWORKSPACE) return 33;
+        // the route of a call: in one launch, unless that is switched off; nothing for more learners than there is room for
+        if (adacomp_debug_one_launch(fake_ws, 2, 0) != 1 || adacomp_debug_one_launch(fake_ws, 1, 1) != 1 || adacomp_debug_one_launch(fake_ws, 3, 0) != ADACOMP_EWORKSPACE ||
+            adacomp_debug_one_launch(fake_ws, 0, 0) != ADACOMP_EWORKSPACE || adacomp_debug_one_launch(fake_ws + 16, 1, 0) != ADACOMP_EWORKSPACE) return 34;
+        adacomp_tuning_fold_scan(0);
+        const int staged = adacomp_debug_one_launch(fake_ws, 1, 0);
+        adacomp_tuning_fold_scan(1);
+        if (staged != 0) return 35;
         if (adacomp_workspace_release(fake_ws) != ADACOMP_OK) return 29;
         if (find_plan(a.data(), 3, fake_ws, bytes, 2, found) != ADACOMP_EWORKSPACE) return 30;
     }
