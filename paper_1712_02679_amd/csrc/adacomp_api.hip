@@ -221,11 +221,13 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
                     const uint32_t first_bin = t * nb;
                     const uint64_t e0 = uint64_t(first_bin) * T;
                     ut.elem_base = layers[l].elem_offset + e0;
-                    ut.n_elems = uint32_t(std::min<uint64_t>(uint64_t(nb) * T, n - e0));
-                    ut.L_T = T;
-                    ut.n_bins = (ut.n_elems + T - 1) / T;
+                    ut.n_elems = uint16_t(std::min<uint64_t>(uint64_t(nb) * T, n - e0));
+                    ut.L_T = uint16_t(T);
+                    ut.n_bins = uint8_t((ut.n_elems + T - 1) / T);
                     ut.first_bin = first_bin;
                     ut.idx_lo = 0;
+                    ut.chunk_bins = uint8_t(std::min<uint32_t>(ADACOMP_CHUNK_BINS, n_bins - (first_bin & ~(ADACOMP_CHUNK_BINS - 1u))));
+                    ut.counts_offset = uint32_t(ld.counts_offset); ut.chunks_offset = uint32_t(ld.chunks_offset);
                     ut.layer_flags = l | (glog << 24) | ((e0 % 4 == 0) ? 0x80000000u : 0u);
                     p.utiles.push_back(ut);
                 }
@@ -239,11 +241,13 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
                     if (tables) {
                         UTileDev ut;
                         ut.elem_base = layers[l].elem_offset + b0 + lo;
-                        ut.n_elems = std::min(kUnpackTileElems, blen - lo);
-                        ut.L_T = T;
+                        ut.n_elems = uint16_t(std::min(kUnpackTileElems, blen - lo));
+                        ut.L_T = uint16_t(T);
                         ut.n_bins = 1;
                         ut.first_bin = b;
-                        ut.idx_lo = lo;
+                        ut.idx_lo = uint16_t(lo);
+                        ut.chunk_bins = uint8_t(std::min<uint32_t>(ADACOMP_CHUNK_BINS, n_bins - (b & ~(ADACOMP_CHUNK_BINS - 1u))));
+                        ut.counts_offset = uint32_t(ld.counts_offset); ut.chunks_offset = uint32_t(ld.chunks_offset);
                         ut.layer_flags = l | (glog << 24) | (((b0 + lo) % 4 == 0) ? 0x80000000u : 0u);
                         p.utiles.push_back(ut);
                     }
@@ -292,13 +296,10 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         }
         // Single tiles, for the launches that also apply the optimizer: those are bound by the
         // traffic of their epilogue, gain nothing from shared tables, and with runs of tiles they
-        // were up to 15 % slower on some machines.  Workgroups are dealt to the 8 XCDs round-robin,
-        // so inside each 64 the order is transposed and the 8 tiles of a chunk, which read the same
-        // count and offset lines of every packet, share an L2.
+        // were up to 15 % slower on some machines.
         p.usingles.resize(p.n_utiles);
-        const uint32_t whole = p.n_utiles & ~63u;
-        for (uint32_t i = 0; i < p.n_utiles; ++i)
-            p.usingles[i] = UGroupDev{i < whole ? ((i & ~63u) | ((i & 7u) << 3) | ((i >> 3) & 7u)) : i, 1u};
+        for (uint32_t i = 0; i < p.n_utiles; ++i) p.usingles[i] = UGroupDev{single_tile(i, p.n_utiles), 1u};
+        p.groups_single = run_max == 1u;
         if (run_max == 1u) p.ugroups = p.usingles;
         // groups of 8-bit layers first: the two kinds go to different kernels
         auto is8 = [&p](const UGroupDev &g) { return p.utiles[g.first_tile].L_T <= 64u; };
@@ -394,7 +395,7 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     out.fixed_bytes = p.fixed_bytes; out.bound_bytes = p.bound_bytes;
     for (int c = 0; c < 2; ++c) out.n_class_tiles[c] = p.n_class_tiles[c];
     out.layer_tiles_max = p.layer_tiles_max; out.has_tiny_bins = p.has_tiny_bins; out.short_bin_max = p.short_bin_max;
-    out.has_short_bins = p.has_short_bins; out.has_shifted_tiles = p.has_shifted_tiles;
+    out.has_short_bins = p.has_short_bins; out.has_shifted_tiles = p.has_shifted_tiles; out.groups_single = p.groups_single;
     out.ws = p.ws;
     out.sync = p.sync;
     out.wait_polls = p.wait_polls;
@@ -434,6 +435,44 @@ uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint3
     if (mode == 1u) return n_elems >= kResidentElems && tiles_of(few ? 2700u : 2900u) ? 5u : 0u;
     if (few) return n_elems >= kResidentElemsSum && (tiles_of(2700u) || (tiles_of(2300u) && bins_of(70u))) ? 5u : 0u;
     return n_elems >= kResidentElemsSumMany && tiles_of(3800u) ? 5u : 0u;
+}
+
+// Does a launch with the optimizer's step ask for weights and moments when the words have been asked for, ahead of the adds
+// (k_unpack's and k_unpack_few's EARLY), or behind the adds?  Ahead, they are on their way while the adds run, and take 32 or 48 registers
+// through them, which leaves fewer workgroups: 7 instead of 8 with up to 4 packets (Adam 5 / 6), 4 or 5 instead of 6 or 7 with more.  That
+// pays in full tiles with few words, and where there is work for all compute units.  Behind / ahead, in us:
+//   up to 4 packets: 0.4 M elements, L_T 500, SGD, 1 packet 5.9 / 5.9, Adam, 4 8.4 / 8.5; 2 M, 50 and 500, SGD, 4 9.3 / 8.6; 25 M, 500, 1
+//     71.7 / 70.7, 4 73.0 / 70.6, Adam 114.2 / 109.9, 114.0 / 110.8; tiles of 2080 elements (L_T 65), Adam, 4 110.7 / 112.1; of 1280
+//     (L_T 20, and 200), SGD, 4 85.1 / 80.2, Adam, 4 122 / 120, 60 M 286 / 287;
+//   8: 25 M, L_T 500 73.8 / 70.6, L_T 50 85.7 / 75.9, 65 76.1 / 80.4, 20 and 200 106 / 128; Adam 116.6 / 113.8, 123 / 114, 113 / 124, 152 / 165;
+//   16: 25 M, 500 78.4 / 72.8, 250 75.7 / 74.3, 170 75.7 / 82.7, 100 83.6 / 95.6, 50 101 / 122; Adam 121 / 117, 118 / 114, 114 / 115, 121 /
+//     130, 132 / 154; 24 packets, 10 M, 170 45.6 / 52.8.
+bool unpack_early_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, bool words8, uint32_t n_learners, uint32_t mode)
+{
+    if (mode == 0u || n_elems < kEarlyElems) return false;
+    if (n_learners <= 4u) return mode == 1u || n_elems >= 2300u * n_tiles;
+    if (n_learners <= 8u) return n_elems >= 2900u * n_tiles;
+    return n_learners <= 16u && !words8 && n_elems >= 2900u * n_tiles && n_elems >= 200u * n_bins;
+}
+
+// Is a launch with 8-bit words that fetches ahead held to 4 workgroups per compute unit?  Up to 4 packets, whose kernels
+// leave 5 or 6; as many as fit / 4, in us: 25 M elements, L_T 50, SGD, 4 packets 71.8 / 70.3, Adam 111.5 / 109.1; 50 and 500 71.0 / 69.5,
+// 111.0 / 109.3; 60 M, Adam 260 / 256, 260 / 256; tiles of 2080 elements, 25 M, SGD 70.7 / 78.3.
+static bool unpack_hold_early(uint64_t n_elems, uint64_t n_tiles, uint32_t n_learners)
+{
+    return n_learners <= 4u && n_elems >= kResidentElems && n_elems >= 2900u * n_tiles;
+}
+
+// Plain sums of one or two packets over layers with 8-bit words that k_unpack_few takes: how many workgroups per compute unit they
+// are held to.  Full tiles and next to no words to add: the launch is a stream of stores, which HBM takes at a higher rate with fewer
+// in flight.  8 workgroups / 5 / 4, in us: L_T 64, 1 packet, 25 M 22.7 / 21.2 / 19.9, 40 M 34.8 / 33.9 / 29.3, 60 M 52.0 / 50.9 / 41.4; with 30 % of
+// the elements at L_T 200 22.2 / 21.5 / 21.5, 35.9 / 34.4 / 31.6, 53.6 / 53.0 / 45.6; L_T 54 and 4000 21.4 / 21.4 / 22.9, 34.5 / 31.5 / 33.9, 53.2 / 45.5 /
+// 49.2; 13 M, 64, 11.3 / 11.7 / 12.9.  2 packets: 64, 25 M 22.5 / 21.1 / 23.8, 40 M 35.7 / 31.2 / 35.6, 60 M 52.5 / 44.3 / 51.1; 64 and 200
+// 21.6 / 21.8 / 23.5, 35.1 / 33.5 / 35.9, 51.7 / 50.0 / 52.3; 54 and 4000, 40 M 32.7 / 35.8 / 39.4.  4 packets 54.1 / 64.2 / 74.5.
+static uint32_t unpack_hold_sum8(uint64_t elems8, uint64_t tiles8, uint64_t n_elems, uint32_t n_learners)
+{
+    if (n_learners == 1u && n_elems >= kResidentElemsSum) return elems8 >= 3700u * tiles8 ? 4u : 5u;
+    return n_learners == 2u && n_elems >= kResidentElemsSumMany && elems8 >= 3900u * tiles8 ? 5u : 0u;
 }
 
 // Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack and k_unpack_few (a workgroup)?
@@ -959,7 +998,21 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         // runs of tiles per workgroup for the plain sum, single tiles when the optimizer step follows
         const UGroupDev *table = reinterpret_cast<const UGroupDev *>(ws + (a.mode == 0u ? p.ws.ugroups : p.ws.usingles));
         const uint32_t n_all = a.mode == 0u ? p.n_ugroups : p.n_utiles, n8 = a.mode == 0u ? p.n_ugroups8 : p.n_usingles8;
-        const uint32_t resident = resident_for(p.n_elems16, p.n_bins16, p.n_utiles - p.n_usingles8, now, a.mode);   // for the 16-bit layers by themselves
+        // What the launches over one word width or both have, whether they fetch the optimizer's state ahead, and to how many
+        // workgroups per compute unit they are held.
+        const uint64_t tiles16 = p.n_utiles - p.n_usingles8, elems8 = p.n_elems_total - p.n_elems16, bins8 = p.n_bins_total - p.n_bins16;
+        const bool early16 = unpack_early_for(p.n_elems16, p.n_bins16, tiles16, false, now, a.mode), early8 = unpack_early_for(elems8, bins8, p.n_usingles8, true, now, a.mode);
+        const bool early_both = unpack_early_for(p.n_elems_total, p.n_bins_total, p.n_utiles, true, now, a.mode);
+        uint32_t resident16 = resident_for(p.n_elems16, p.n_bins16, tiles16, now, a.mode);
+        if (early16 && resident16 != 0u) resident16 = 4u;
+        uint32_t resident8 = early8 && unpack_hold_early(elems8, p.n_usingles8, now) ? 4u : 0u;
+        uint32_t resident_both = early_both && unpack_hold_early(p.n_elems_total, p.n_utiles, now) && p.n_elems16 >= 60u * uint64_t(now) * p.n_bins16 ? 4u : 0u;
+        if (a.mode == 0u) resident8 = resident_both = unpack_hold_sum8(elems8, p.n_usingles8, p.n_elems_total, now);
+        // Launches over all groups take single tiles without a look at the table, a round of scalar loads; over both word widths only
+        // while every tile has a compute unit to itself, since those of short bins, which take longest, stand first in it (2 M elements,
+        // 50 and 500, 16 packets: by the table 13.8 us, without 14.4; 0.4 M 13.0 / 12.6).
+        const bool singles = a.mode != 0u || p.groups_single;
+        const UGroupDev *const whole_table = singles ? nullptr : table, *const both_table = singles && p.n_utiles <= kComputeUnits ? nullptr : table;
         a.groups = table;
         a.n_groups = n_all;
         a.n_groups8 = a.first16 = a.chunk_lds = 0u;
@@ -969,17 +1022,19 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
             a.n_groups = n_all - n8;
             a.first16 = uint32_t(table - a.groups) + n8;
             a.chunk_lds = 64u * p.short_bin_max + unpack8_wg_log(p, n8, a.n_groups, now);
-            if ((rc = launch_unpack(a, 3, 0u, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 3, 0u, false, hip_stream)) != ADACOMP_OK) return rc;
         } else if (n8 == 0u || n8 == n_all) {  // one word width
-            if ((rc = launch_unpack(a, n8 ? 1 : 0, n8 ? 0u : resident, hip_stream)) != ADACOMP_OK) return rc;
+            a.groups = whole_table;
+            if ((rc = launch_unpack(a, n8 ? 1 : 0, n8 ? resident8 : resident16, n8 ? early8 : early16, hip_stream)) != ADACOMP_OK) return rc;
         } else if (p.n_utiles <= kUnpackSplitTiles || now <= kUnpackTogether) {  // mixed, and small or of few packets: one launch that handles both
-            if ((rc = launch_unpack(a, 2, 0u, hip_stream)) != ADACOMP_OK) return rc;
+            a.groups = both_table;
+            if ((rc = launch_unpack(a, 2, resident_both, early_both, hip_stream)) != ADACOMP_OK) return rc;
         } else {  // large and mixed: the 8-bit groups come first in the table
             a.n_groups = n8;
-            if ((rc = launch_unpack(a, 1, 0u, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 1, resident8, early8, hip_stream)) != ADACOMP_OK) return rc;
             a.groups = table + n8;
             a.n_groups = n_all - n8;
-            if ((rc = launch_unpack(a, 0, resident, hip_stream)) != ADACOMP_OK) return rc;
+            if ((rc = launch_unpack(a, 0, resident16, early16, hip_stream)) != ADACOMP_OK) return rc;
         }
         done += now;
     } while (done < n_learners);

@@ -1932,11 +1932,63 @@ template <uint32_t LG>
 constexpr uint32_t kOffStride = LG + 4u;  // uint32 per row, LG used
 constexpr uint32_t kCntStride = 24;  // uint16 per row, LG used
 
+// What the kernels look up in a packet for one chunk of a layer: the header, where the layer's words begin, how many stand
+// before the chunk, the scale.  The same for all threads: scalar loads.  `settle` behind the loads of all packets keeps the
+// compiler from waiting for one packet before it asks for the next, as it does where registers or branches suggest it (k_unpack_few,
+// 4 packets, 0.4 M elements 4.4 us, one after the other 5.3).
+struct PacketChunk {
+    vuint4 head;          // magic, version, status, n_layers
+    vuint2 total_bytes;
+    vuint2 words_offset;
+    uint32_t before;
+    float scale;
+    __device__ __forceinline__ void fetch(const uint8_t *const pk, const uint32_t layer, const uint32_t chunks_offset, const uint32_t chunk)
+    {
+        const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
+        head = packet_field<vuint4>(pk);
+        total_bytes = packet_field<vuint2>(pk + 16);
+        words_offset = packet_field<vuint2>(rec + offsetof(adacomp_packet_layer_t, words_offset));
+        scale = packet_field<float>(rec + offsetof(adacomp_packet_layer_t, scale));
+        before = packet_field<uint32_t>(pk + chunks_offset + 4u * chunk);
+    }
+    // whether the packet is one that this call can read
+    __device__ __forceinline__ bool fits(const UnpackArgs &a) const
+    {
+        return (head.x == ADACOMP_PACKET_MAGIC) & (head.y == ADACOMP_PACKET_VERSION) & (head.z == ADACOMP_STATUS_COMPLETE) & (head.w == a.n_layers) & (total_bytes.y == 0u);
+    }
+    // words (of `size` bytes each) from the packet's start to the chunk's first one
+    __device__ __forceinline__ uint64_t first_word(const uint32_t size) const
+    {
+        return uint64_t(uint32_t(((uint64_t(words_offset.y) << 32) | words_offset.x) / size)) + before;   // packets stay below 2^32 words (host check)
+    }
+};
+// ... of the headers alone, together with the counts of the lane's bin (which otherwise wait for what says whether they are needed)
+template <uint32_t N>
+__device__ __forceinline__ void settle_heads(PacketChunk (&p)[N], uint32_t (&c)[N])
+{
+    static_assert(N == 2 || N == 4, "operands of one statement");
+    if constexpr (N == 2)
+        asm volatile("" : "+s"(p[0].head), "+s"(p[0].total_bytes), "+s"(p[1].head), "+s"(p[1].total_bytes), "+v"(c[0]), "+v"(c[1]));
+    else
+        asm volatile("" : "+s"(p[0].head), "+s"(p[0].total_bytes), "+s"(p[1].head), "+s"(p[1].total_bytes), "+s"(p[2].head), "+s"(p[2].total_bytes),
+                          "+s"(p[3].head), "+s"(p[3].total_bytes), "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+}
+template <uint32_t N>
+__device__ __forceinline__ void settle(PacketChunk (&p)[N])
+{
+    static_assert(N == 2 || N == 4, "operands of one statement: what is in flight together");
+    asm volatile("" : "+s"(p[0].head), "+s"(p[0].total_bytes), "+s"(p[0].words_offset), "+s"(p[0].before), "+s"(p[0].scale),
+                      "+s"(p[1].head), "+s"(p[1].total_bytes), "+s"(p[1].words_offset), "+s"(p[1].before), "+s"(p[1].scale));
+    if constexpr (N == 4)
+        asm volatile("" : "+s"(p[2].head), "+s"(p[2].total_bytes), "+s"(p[2].words_offset), "+s"(p[2].before), "+s"(p[2].scale),
+                          "+s"(p[3].head), "+s"(p[3].total_bytes), "+s"(p[3].words_offset), "+s"(p[3].before), "+s"(p[3].scale));
+}
+
 // Phase 1 for learners k0 .. k0 + LG - 1 (LG = 8 or 16) and the bins [row0_bin, scan_end) of one 64-bin chunk: word
 // count and position of the first word of every (bin, learner), into the LDS tables (row = bin -
 // row0_bin).  The caller has a barrier before (the tables are free) and after (they are filled).
 template <bool W8, uint32_t LG>
-__device__ __forceinline__ void unpack_tables(const UnpackArgs &a, const LayerDev &ld, const uint32_t layer,
+__device__ __forceinline__ void unpack_tables(const UnpackArgs &a, const UTileDev &ut0,
                                               const uint32_t row0_bin, const uint32_t scan_end, const uint32_t k0,
                                               uint32_t (*s_off)[kOffStride<LG>], uint16_t (*s_cnt)[kCntStride],
                                               float *s_scale, uint32_t *s_cmax)
@@ -1952,36 +2004,34 @@ __device__ __forceinline__ void unpack_tables(const UnpackArgs &a, const LayerDe
     const uint32_t nk = a.n_learners - k0 < LG ? a.n_learners - k0 : LG;
 
     if (tid == 0) *s_cmax = 0u;
-    __syncthreads();
 
     // Wave w serves learners w, w + 4, ...; all their loads are issued first: without a branch around them (learners
     // past nk look at the first one's packet), and what is the same for all bins through scalar loads.
     uint32_t wmax = 0u;
     uint32_t c[kPerWave];
+    PacketChunk pc[kPerWave];
 #pragma unroll
     for (uint32_t q = 0; q < kPerWave; ++q) {
         const uint32_t kk = wave + 4u * q;
+        const uint8_t *const pk = a.packets[k0 + (kk < nk ? kk : 0u)];
         // counts and chunk offsets sit in the fixed part, which every packet buffer holds
-        c[q] = reinterpret_cast<const word_t *>(a.packets[k0 + (kk < nk ? kk : 0u)] + ld.counts_offset)[in_scan ? b : row0_bin];
+        c[q] = reinterpret_cast<const word_t *>(pk + ut0.counts_offset)[in_scan ? b : row0_bin];
+        if (LG == 8u) pc[q].fetch(pk, ut0.layer(), ut0.chunks_offset, chunk);
     }
+    if constexpr (LG == 8u) settle(pc);
+    __syncthreads();   // (s_cmax)
 #pragma unroll
     for (uint32_t q = 0; q < kPerWave; ++q) {
         const uint32_t kk = wave + 4u * q;  // < LG; learners past nk get empty entries
-        const uint8_t *const pk = a.packets[k0 + (kk < nk ? kk : 0u)];
-        const vuint4 hv = packet_field<vuint4>(pk);        // magic, version, status, n_layers
-        const vuint2 tb = packet_field<vuint2>(pk + 16);   // total_bytes
-        const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
-        const uint32_t wbase = uint32_t(packet_field<uint64_t>(rec + offsetof(adacomp_packet_layer_t, words_offset)) / sizeof(word_t));  // packets stay below 2^32 words (host check)
-        const uint32_t coff = packet_field<uint32_t>(pk + ld.chunks_offset + 4u * chunk);
-        const float sc = packet_field<float>(rec + offsetof(adacomp_packet_layer_t, scale));
-        const bool ok = (kk < nk) & (hv.x == ADACOMP_PACKET_MAGIC) & (hv.y == ADACOMP_PACKET_VERSION) &
-                        (hv.z == ADACOMP_STATUS_COMPLETE) & (hv.w == a.n_layers) & (tb.y == 0u);
-        const uint32_t limit = tb.x / uint32_t(sizeof(word_t));  // words that fit in the packet
+        if (LG != 8u) pc[q].fetch(a.packets[k0 + (kk < nk ? kk : 0u)], ut0.layer(), ut0.chunks_offset, chunk);   // (of four at once the registers spill)
+        const float sc = pc[q].scale;
+        const bool ok = (kk < nk) & pc[q].fits(a);
+        const uint32_t limit = pc[q].total_bytes.x / uint32_t(sizeof(word_t));  // words that fit in the packet
         const uint32_t cq = ok && in_scan ? c[q] : 0u;   // a packet that does not match contributes nothing
         const uint32_t incl = wave_incl_scan(cq);
         // A bin whose words would lie past the packet's total_bytes (counts or offsets that do not
         // belong together) contributes nothing: no word is read from outside the packet.
-        const uint64_t first = uint64_t(wbase) + coff + (incl - cq);
+        const uint64_t first = pc[q].first_word(uint32_t(sizeof(word_t))) + (incl - cq);
         const bool inside = first + cq <= limit;
         const uint32_t cw = inside ? cq : 0u;
         if (in_rows) {
@@ -2013,22 +2063,29 @@ __device__ __forceinline__ void lds_add(float *acc, const uint32_t idx, const fl
 }
 
 // Phase 2 for one tile: a lane group owns a bin (table row row0 + bin index inside the tile).
-template <bool W8, uint32_t LG>
+// words_on_their_way: called once by every thread, when the first words that it waits for have been asked for (NoHook: not at all).
+struct NoHook {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <bool W8, uint32_t LG, class Hook>
 __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev &ut, const uint32_t row0, const uint32_t k0,
                                             float *s_acc, uint32_t (*s_off)[kOffStride<LG>],
-                                            uint16_t (*s_cnt)[kCntStride], const float *s_scale, const uint32_t *s_cmax)
+                                            uint16_t (*s_cnt)[kCntStride], const float *s_scale, const uint32_t *s_cmax, Hook words_on_their_way)
 {
     typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
     const uint32_t tid = threadIdx.x;
     const uint32_t n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
     const uint32_t nk = a.n_learners - k0 < LG ? a.n_learners - k0 : LG;
+    constexpr bool kHook = !std::is_same<Hook, NoHook>::value;
     if (W8) {
         // Short bins (8-bit words) send several words each, about 8 % of the elements on the
         // ResNet-50 table.  Four lanes own a bin and lane j fetches the aligned 4 bytes number j of
         // the bin's run of words, for all 16 learners at once (16 words per bin and learner; longer
         // runs are finished with byte loads), then adds learner after learner in program order.
-        const uint32_t lb = tid >> 2, sub = tid & 3u;
-        if (lb >= nb) return;
+        const uint32_t sub = tid & 3u;
+        const bool live = !kHook || (tid >> 2) < nb;   // (the hook is for all threads)
+        if (!kHook && (tid >> 2) >= nb) return;
+        const uint32_t lb = live ? tid >> 2 : 0u;
         const uint32_t row = row0 + lb;
         const uint32_t span = T < n - lb * T ? T : n - lb * T;  // elements of this bin held by the tile
         float *acc = s_acc + lb * T;
@@ -2052,9 +2109,11 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
                 packed[kk] = 0u;
                 // word sections start on 16-byte boundaries and are padded to them, so the aligned
                 // 4 bytes around any word of the run lie inside the packet
+                cc[kk] = live ? cc[kk] : 0u;
                 if (cc[kk] != 0u && 4u * sub < (off[kk] & 3u) + cc[kk])
                     packed[kk] = reinterpret_cast<const uint32_t *>(a.packets[k0 + (h0 + kk < nk ? h0 + kk : 0u)])[(off[kk] >> 2) + sub];
             }
+            if (h0 == 0u) words_on_their_way();
 #pragma unroll
             for (uint32_t kk = 0; kk < 8u; ++kk) {
                 __builtin_amdgcn_sched_barrier(0);  // one learner at a time: keeps the register count down
@@ -2104,11 +2163,10 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
     while (glog < 6u && (1u << glog) < *s_cmax) ++glog;
     const uint32_t gsz = 1u << glog;
 
-    for (uint32_t s = tid; s < (nb << glog); s += kWG) {
-        const uint32_t lb = s >> glog, sub = s & (gsz - 1u);
-        const uint32_t row = row0 + lb;
-        const uint32_t span = T < n - lb * T ? T : n - lb * T;  // elements of this bin held by the tile
-        float *acc = s_acc + lb * T;
+    const uint32_t slots = nb << glog;
+    uint32_t word[LG], cmax;   // of the bin and learners in turn: the lane's word, and how many the bin has at most
+    auto fetch = [&](const uint32_t s) {
+        const uint32_t row = row0 + (!kHook || s < slots ? s >> glog : 0u), sub = s & (gsz - 1u);
         uint32_t cc[LG], off[LG];
 #pragma unroll
         for (uint32_t v = 0; v < LG / 8u; ++v) {
@@ -2121,17 +2179,24 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
             const uint4 t = *reinterpret_cast<const uint4 *>(&s_off[row][4u * v]);
             off[4 * v] = t.x; off[4 * v + 1] = t.y; off[4 * v + 2] = t.z; off[4 * v + 3] = t.w;
         }
-        uint32_t word[LG];
-        uint32_t cmax = 0u;
+        cmax = 0u;
 #pragma unroll
         for (uint32_t kk = 0; kk < LG; ++kk) {
             cmax = cc[kk] > cmax ? cc[kk] : cmax;
             word[kk] = 0u;
-            if (sub < cc[kk]) {
+            if ((!kHook || s < slots) && sub < cc[kk]) {
                 const word_t *wp = reinterpret_cast<const word_t *>(a.packets[k0 + (kk < nk ? kk : 0u)]);
                 word[kk] = wp[off[kk] + sub];
             }
         }
+    };
+    if (kHook) { fetch(tid); words_on_their_way(); }
+    for (uint32_t s = tid; s < slots; s += kWG) {
+        if (!kHook || s != tid) fetch(s);
+        const uint32_t lb = s >> glog, sub = s & (gsz - 1u);
+        const uint32_t row = row0 + lb;
+        const uint32_t span = T < n - lb * T ? T : n - lb * T;  // elements of this bin held by the tile
+        float *acc = s_acc + lb * T;
         if (cmax <= gsz) {
 #pragma unroll
             for (uint32_t kk = 0; kk < LG; ++kk) {
@@ -2217,31 +2282,21 @@ __device__ __forceinline__ void unpack_clear(const UnpackArgs &a, const uint32_t
     }
 }
 
-// Writes a finished tile out: the sum, the optimizer's step, or both.
-template <int MODE>
+// Writes the finished sum of a tile out.
 __device__ __forceinline__ void unpack_write_out(const UnpackArgs &a, const UTileDev &ut, float *const s_acc)
 {
     const uint32_t tid = threadIdx.x;
     const uint32_t n = ut.n_elems;
-    const bool vec = ut.aligned();
     float *__restrict__ out = a.dense + ut.elem_base;
-    float *const W = MODE == 1 ? a.weights + ut.elem_base : nullptr;
-    float *const S1 = MODE == 1 ? a.state1 + ut.elem_base : nullptr;
-    const __amdgpu_buffer_rsrc_t w_buf = tile_buffer(MODE == 2 ? a.weights + ut.elem_base : out, MODE == 2 ? n : 0u);
-    const __amdgpu_buffer_rsrc_t s1_buf = tile_buffer(MODE == 2 ? a.state1 + ut.elem_base : out, MODE == 2 ? n : 0u);
-    const __amdgpu_buffer_rsrc_t s2_buf = tile_buffer(MODE == 2 ? a.state2 + ut.elem_base : out, MODE == 2 ? n : 0u);
     // The write-out moves 16-byte slots of memory whatever the tile's alignment.  A tile that starts
     // `skip` elements past a 16-byte boundary reads its accumulators from the LDS tile at the matching
     // offset (four 4-byte reads per slot instead of one 16-byte read): slot f (a multiple of 4) holds
     // the elements f - skip .. f + 3 - skip; in the first slot that wraps below zero, and `< n` on the
     // wrapped value tells the elements that are the tile's.  (With 4-byte accesses to memory such
     // tiles were written at 3.1 instead of 5 TB/s.)
-    // (The Adam epilogue sits at its register limit and keeps 4-byte accesses on unaligned tiles: the
-    // few registers this costs spilled there and slowed the aligned case by 4 %.)
-    const uint32_t skip = MODE == 2 ? 0u : uint32_t(ut.elem_base) & 3u;
+    const uint32_t skip = uint32_t(ut.elem_base) & 3u;
     for (uint32_t f = tid * 4u; f < n + skip; f += kWG * 4u) {
         const uint32_t e = f - skip;
-        const bool full = (MODE != 2 || vec) && f >= skip && e + 4u <= n;
         float sum[4];
         if (skip == 0u) {
             const float4 v = *reinterpret_cast<const float4 *>(&s_acc[f]);
@@ -2250,44 +2305,103 @@ __device__ __forceinline__ void unpack_write_out(const UnpackArgs &a, const UTil
 #pragma unroll
             for (uint32_t c = 0; c < 4u; ++c) sum[c] = e + c < n ? s_acc[e + c] : 0.f;
         }
-        if (a.write_dense) {
-            if (full) store_stream4(out + e, vfloat4{sum[0], sum[1], sum[2], sum[3]});
-            else {
+        if (f >= skip && e + 4u <= n) store_stream4(out + e, vfloat4{sum[0], sum[1], sum[2], sum[3]});
+        else {
 #pragma unroll
-                for (uint32_t c = 0; c < 4u; ++c)
-                    if (e + c < n) out[e + c] = sum[c];
-            }
-        }
-        if (MODE != 0) {
-            if (full) {
-                vfloat4 w4, s14, s24 = vfloat4{0.f, 0.f, 0.f, 0.f};
-                if (MODE == 2) { w4 = buffer_load_stream4(w_buf, e); s14 = buffer_load_stream4(s1_buf, e); s24 = buffer_load_stream4(s2_buf, e); }
-                else { w4 = load_stream4(W + e); s14 = load_stream4(S1 + e); }
-                float w[4] = {w4.x, w4.y, w4.z, w4.w}, s1[4] = {s14.x, s14.y, s14.z, s14.w}, s2[4] = {s24.x, s24.y, s24.z, s24.w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) apply_update<MODE>(a, sum[c], w[c], s1[c], s2[c]);
-                if (MODE == 2) {
-                    buffer_store_stream4(w_buf, e, vfloat4{w[0], w[1], w[2], w[3]});
-                    buffer_store_stream4(s1_buf, e, vfloat4{s1[0], s1[1], s1[2], s1[3]});
-                    buffer_store_stream4(s2_buf, e, vfloat4{s2[0], s2[1], s2[2], s2[3]});
-                } else {
-                    store_stream4(W + e, vfloat4{w[0], w[1], w[2], w[3]});
-                    store_stream4(S1 + e, vfloat4{s1[0], s1[1], s1[2], s1[3]});
-                }
-            } else {
-                for (uint32_t c = 0; c < 4u; ++c) {
-                    const uint32_t ec = e + c;   // wraps back into the tile for the elements of the first slot that are the tile's
-                    if (ec >= n) continue;
-                    float w, s1, s2 = 0.f;
-                    if (MODE == 2) { w = buffer_load1(w_buf, ec); s1 = buffer_load1(s1_buf, ec); s2 = buffer_load1(s2_buf, ec); }
-                    else { w = W[ec]; s1 = S1[ec]; }
-                    apply_update<MODE>(a, sum[c], w, s1, s2);
-                    if (MODE == 2) { buffer_store1(w_buf, ec, w); buffer_store1(s1_buf, ec, s1); buffer_store1(s2_buf, ec, s2); }
-                    else { W[ec] = w; S1[ec] = s1; }
-                }
-            }
+            for (uint32_t c = 0; c < 4u; ++c)
+                if (e + c < n) out[e + c] = sum[c];
         }
     }
+}
+
+// The optimizer's step on a tile: everything that it reads at once, and the step itself.  Bound by HBM; what it loses is the time
+// in which a workgroup adds words and nothing of its own is on the way.  So weights and moments are asked for ahead of the adds
+// where that pays (unpack_early_for has the line and both sides of it), and behind them all slots together elsewhere.  One slot
+// after the other behind the adds (as before) / all together / ahead, in us: SGD, 25 M elements, L_T 500, 8 packets 78.3 / 73.8 / 70.6, 16
+// 79.4 / 78.4 / 72.8, L_T 50, 16 108 / 101 / 122; ResNet-50's table, 8 packets 86.3 / - / 79.5; Adam, 16 packets of the 125 M-element table
+// 517 / - / 501.
+// Slot j of thread t holds the elements 4 (256 j + t) .. + 3 of the tile; buffer accesses need 4-byte alignment and no more, and
+// leave alone what lies past the tile's whole slots.  The layer's last elements, which do not fill one, go one by one.
+template <int MODE>
+struct TileState {
+    static constexpr uint32_t kSlots = kUnpackTileElems / (4u * kWG);
+    vfloat4 w[kSlots], s1[kSlots], s2[MODE == 2 ? kSlots : 1u];
+
+    __device__ __forceinline__ void fetch(const UnpackArgs &a, const UTileDev &ut)
+    {
+        const uint32_t whole = ut.n_elems & ~3u;
+        const __amdgpu_buffer_rsrc_t wb = tile_buffer(a.weights + ut.elem_base, whole), b1 = tile_buffer(a.state1 + ut.elem_base, whole);
+        const __amdgpu_buffer_rsrc_t b2 = tile_buffer(MODE == 2 ? a.state2 + ut.elem_base : a.weights, MODE == 2 ? whole : 0u);
+#pragma unroll
+        for (uint32_t j = 0; j < kSlots; ++j) {
+            w[j] = buffer_load_slot(wb, threadIdx.x * 16u, j * kWG * 16u);
+            s1[j] = buffer_load_slot(b1, threadIdx.x * 16u, j * kWG * 16u);
+            if (MODE == 2) s2[j] = buffer_load_slot(b2, threadIdx.x * 16u, j * kWG * 16u);
+        }
+    }
+    __device__ __forceinline__ void step(const UnpackArgs &a, const UTileDev &ut, const float *const s_acc)
+    {
+        const uint32_t n = ut.n_elems, whole = n & ~3u;
+        const __amdgpu_buffer_rsrc_t wb = tile_buffer(a.weights + ut.elem_base, whole), b1 = tile_buffer(a.state1 + ut.elem_base, whole);
+        const __amdgpu_buffer_rsrc_t b2 = tile_buffer(MODE == 2 ? a.state2 + ut.elem_base : a.weights, MODE == 2 ? whole : 0u);
+        const __amdgpu_buffer_rsrc_t out = tile_buffer(a.write_dense ? a.dense + ut.elem_base : a.weights, a.write_dense ? whole : 0u);
+#pragma unroll
+        for (uint32_t j = 0; j < kSlots; ++j) {
+            const uint32_t e = (j * kWG + threadIdx.x) * 4u;
+            if (e >= whole) break;
+            const vfloat4 sum = *reinterpret_cast<const vfloat4 *>(&s_acc[e]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float wc = w[j][c], s1c = s1[j][c], s2c = MODE == 2 ? s2[j][c] : 0.f;
+                apply_update<MODE>(a, sum[c], wc, s1c, s2c);
+                w[j][c] = wc; s1[j][c] = s1c;
+                if (MODE == 2) s2[j][c] = s2c;
+            }
+            buffer_store_slot(wb, threadIdx.x * 16u, j * kWG * 16u, w[j]);
+            buffer_store_slot(b1, threadIdx.x * 16u, j * kWG * 16u, s1[j]);
+            if (MODE == 2) buffer_store_slot(b2, threadIdx.x * 16u, j * kWG * 16u, s2[j]);
+            if (a.write_dense) buffer_store_slot(out, threadIdx.x * 16u, j * kWG * 16u, sum);
+        }
+        if (threadIdx.x < (n & 3u)) {
+            const uint64_t e = ut.elem_base + whole + threadIdx.x;
+            const float sum = s_acc[whole + threadIdx.x];
+            float wc = a.weights[e], s1c = a.state1[e], s2c = MODE == 2 ? a.state2[e] : 0.f;
+            apply_update<MODE>(a, sum, wc, s1c, s2c);
+            a.weights[e] = wc; a.state1[e] = s1c;
+            if (MODE == 2) a.state2[e] = s2c;
+            if (a.write_dense) a.dense[e] = sum;
+        }
+    }
+};
+template <>
+struct TileState<0> {
+    __device__ __forceinline__ void fetch(const UnpackArgs &, const UTileDev &) {}
+    __device__ __forceinline__ void step(const UnpackArgs &a, const UTileDev &ut, float *const s_acc) { unpack_write_out(a, ut, s_acc); }
+};
+
+// Group number g of the launch, and its first tile.  Arguments, group, tile: a round of scalar loads each, 0.25 us, and what the
+// packets are asked for stands in the tile's record (so far a round more for the layer's, and the compiler fetched the
+// arguments where it used them).  The record is kept whole: taken apart, its short fields come through vector loads.
+struct GroupAndTile {
+    UGroupDev grp;
+    UTileDev tile;
+};
+__device__ __forceinline__ UTileDev utile_record(const UTileDev *p)
+{
+    vuint8 v = *(const __attribute__((address_space(4))) vuint8 *)p;
+    asm volatile("" : "+s"(v));
+    return __builtin_bit_cast(UTileDev, v);
+}
+__device__ __forceinline__ GroupAndTile first_records(const UnpackArgs &a, const uint32_t g)
+{
+    const UTileDev *tiles = a.tiles;
+    const UGroupDev *groups = a.groups;
+    uint32_t n_groups = a.n_groups;
+    asm volatile("" : "+s"(tiles), "+s"(groups), "+s"(n_groups));
+    GroupAndTile r;
+    r.grp = groups == nullptr ? UGroupDev{single_tile(g, n_groups), 1u} : table_record<vuint2>(groups + g);
+    r.tile = utile_record(tiles + r.grp.first_tile);
+    return r;
 }
 
 // MODE 0: dense_out <- sum.  MODE 1 / 2: also (or only) the SGD / Adam step on weights and state.
@@ -2295,26 +2409,22 @@ __device__ __forceinline__ void unpack_write_out(const UnpackArgs &a, const UTil
 // layer says which).  Large tables get one launch per kind: each path alone needs fewer registers
 // than a kernel that holds both, which buys resident workgroups (8 % of the 16-bit path's time on
 // the 125 M-element table).  Small tables, where a second launch would cost more than that, use
-// the kernel that holds both.  The single-width kernels are held to 80 registers (6 waves per
-// SIMD, what the LDS tile allows; the 16-bit path spills two).
-template <int MODE, int KIND, uint32_t LG>
-__device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
-                                             uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
+// the kernel that holds both, one path after a branch.  The single-width kernels are held to 80 registers (6 waves per
+// SIMD, what the LDS tile allows).
+// EARLY: weights and moments are asked for ahead of the adds and kept through them, in up to 128 registers.
+template <int MODE, bool W8, uint32_t LG, bool EARLY>
+__device__ __forceinline__ void unpack_tiles(const UnpackArgs &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc,
+                                             uint32_t (*const s_off)[kOffStride<LG>], uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
     // A workgroup serves a group of consecutive tiles that lie in one 64-bin chunk (or are slices
     // of one long bin).  With up to LG learners the tables of phase 1 are built once for the group.
-    const UGroupDev grp = a.groups[group];
-    const UTileDev ut0 = a.tiles[grp.first_tile];
-    const UTileDev ut_last = a.tiles[grp.first_tile + grp.n_tiles - 1u];
-    const uint32_t layer = ut0.layer();
-    const LayerDev ld = a.layers[layer];
-    const uint32_t row0_bin = ut0.first_bin, scan_end = ut_last.first_bin + ut_last.n_bins;
+    const uint32_t row0_bin = ut0.first_bin, chunk_end = (row0_bin & ~63u) + ut0.chunk_bins;
+    const uint32_t bins = ut0.L_T > kUnpackTileElems ? 1u : ut0.n_bins * grp.n_tiles;   // (the last tile may have fewer)
+    const uint32_t scan_end = row0_bin + bins < chunk_end ? row0_bin + bins : chunk_end;
     const bool tables_once = a.n_learners <= LG;
-    const bool w8 = KIND == 2 ? ld.word_bytes == 1u : KIND == 1;
-
 
   for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
-    const UTileDev ut = ti == 0u ? ut0 : a.tiles[grp.first_tile + ti];
+    const UTileDev ut = ti == 0u ? ut0 : utile_record(a.tiles + grp.first_tile + ti);
     const uint32_t n = ut.n_elems;
     const bool vec = ut.aligned();
     float *__restrict__ out = a.dense + ut.elem_base;
@@ -2322,24 +2432,42 @@ __device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t
     __syncthreads();  // the previous tile has been written out and its adds are done with the tables
     unpack_clear(a, n, vec, out, s_acc);
 
-    for (uint32_t k0 = 0; k0 < a.n_learners; k0 += LG) {
+    TileState<MODE> state;
+    auto round = [&](const uint32_t k0, auto words_on_their_way) {
         if (!tables_once || ti == 0u) {
             if (k0 != 0u) __syncthreads();  // the adds of the previous learners are done with the tables
-            if (w8) unpack_tables<true, LG>(a, ld, layer, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
-            else unpack_tables<false, LG>(a, ld, layer, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
+            unpack_tables<W8, LG>(a, ut0, row0_bin, scan_end, k0, s_off, s_cnt, s_scale, &s_cmax);
         }
         __syncthreads();  // tables filled, accumulators initialised
-        if (w8) unpack_adds<true, LG>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax);
-        else unpack_adds<false, LG>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax);
+        unpack_adds<W8, LG>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax, words_on_their_way);
+    };
+    uint32_t k0 = 0;
+    if constexpr (EARLY) {
+        for (; k0 + LG < a.n_learners; k0 += LG) round(k0, NoHook());
+        round(k0, [&] { state.fetch(a, ut); });
+    } else {
+        for (; k0 < a.n_learners; k0 += LG) round(k0, NoHook());
+        state.fetch(a, ut);
     }
     __syncthreads();
 
-    unpack_write_out<MODE>(a, ut, s_acc);
+    state.step(a, ut, s_acc);
   }  // tiles of the group
 }
 
-template <int MODE, int KIND, uint32_t LG>
-__global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const UnpackArgs a)
+template <int MODE, int KIND, uint32_t LG, bool EARLY>
+__device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
+                                             uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
+{
+    const GroupAndTile first = first_records(a, group);
+    const UGroupDev grp = first.grp;
+    const UTileDev ut0 = first.tile;
+    if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_tiles<MODE, true, LG, EARLY>(a, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
+    else unpack_tiles<MODE, false, LG, EARLY>(a, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
+}
+
+template <int MODE, int KIND, uint32_t LG, bool EARLY>
+__global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UnpackArgs a)
 {
     if (blockIdx.x >= a.n_groups) return;
     __shared__ float s_acc[kUnpackTileElems];
@@ -2347,7 +2475,7 @@ __global__ __launch_bounds__(kWG, (KIND == 2 ? 4 : 6)) void k_unpack(const Unpac
     __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64][kCntStride];
     __shared__ __attribute__((aligned(16))) float s_scale[LG];
     __shared__ uint32_t s_cmax;                                                // largest word count of a (bin, learner) in the tables
-    unpack_group<MODE, KIND, LG>(a, blockIdx.x, s_acc, s_off, s_cnt, s_scale, s_cmax);
+    unpack_group<MODE, KIND, LG, EARLY>(a, blockIdx.x, s_acc, s_off, s_cnt, s_scale, s_cmax);
 }
 
 // ==============================================================================================
@@ -2364,44 +2492,42 @@ constexpr uint32_t kFewLearners = 4;
 // take this form for up to two learners (ResNet-50's table, k_unpack's form / this one: 1 packet 20.3 / 20.0 us, 2 22.1 /
 // 20.9, but 4 25.2 / 26.7).
 constexpr uint32_t kFewInLaunch8 = 2;
-template <int MODE, bool W8>
-__device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGroupDev grp, const UTileDev ut0, const LayerDev ld, float *const s_acc)
+template <int MODE, bool W8, bool MANY, uint32_t NK>
+__device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc)
 {
     typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const uint32_t layer = ut0.layer(), chunk = ut0.first_bin >> 6, bin = (chunk << 6) + lane;
+    constexpr bool EARLY = MODE != 0 && MANY;
+    const uint32_t chunk = ut0.first_bin >> 6;
+    const bool in_chunk = lane < ut0.chunk_bins;
 
-    constexpr uint32_t NK = kFewLearners;
     // word count and first word (counted from the packet's start) of the lane's bin, for every learner
     uint32_t c[NK], off[NK];
     float scale[NK];
+    PacketChunk pc[NK];
 #pragma unroll
     for (uint32_t k = 0; k < NK; ++k) {
         const uint8_t *const pk = a.packets[k < a.n_learners ? k : 0u];
-        c[k] = reinterpret_cast<const word_t *>(pk + ld.counts_offset)[bin < ld.n_bins ? bin : 0u];
+        c[k] = reinterpret_cast<const word_t *>(pk + ut0.counts_offset)[in_chunk ? (chunk << 6) + lane : 0u];
+        pc[k].fetch(pk, ut0.layer(), ut0.chunks_offset, chunk);
     }
+    if constexpr (W8 || !MANY) settle(pc);
+    else settle_heads(pc, c);
 #pragma unroll
     for (uint32_t k = 0; k < NK; ++k) {
-        const uint8_t *const pk = a.packets[k < a.n_learners ? k : 0u];
-        const vuint4 hv = packet_field<vuint4>(pk);        // magic, version, status, n_layers
-        const vuint2 tb = packet_field<vuint2>(pk + 16);   // total_bytes
-        const bool ok = (k < a.n_learners) & (hv.x == ADACOMP_PACKET_MAGIC) & (hv.y == ADACOMP_PACKET_VERSION) &
-                        (hv.z == ADACOMP_STATUS_COMPLETE) & (hv.w == a.n_layers) & (tb.y == 0u);
-        const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
-        const uint32_t words = uint32_t(packet_field<uint64_t>(rec + offsetof(adacomp_packet_layer_t, words_offset)) / sizeof(word_t));
-        const uint32_t before = packet_field<uint32_t>(pk + ld.chunks_offset + 4u * chunk);
-        scale[k] = packet_field<float>(rec + offsetof(adacomp_packet_layer_t, scale));
-        const uint32_t ck = ok && bin < ld.n_bins ? c[k] : 0u;   // a packet that does not match contributes nothing
+        scale[k] = pc[k].scale;
+        const uint32_t ck = ((k < a.n_learners) & pc[k].fits(a) & in_chunk) ? c[k] : 0u;   // a packet that does not match contributes nothing
         // nor does a bin whose words would lie past the packet's total_bytes
-        const uint64_t first = uint64_t(words) + before + (wave_incl_scan(ck) - ck);
-        c[k] = first + ck <= tb.x / uint32_t(sizeof(word_t)) ? ck : 0u;
+        const uint64_t first = pc[k].first_word(uint32_t(sizeof(word_t))) + (wave_incl_scan(ck) - ck);
+        c[k] = first + ck <= pc[k].total_bytes.x / uint32_t(sizeof(word_t)) ? ck : 0u;
         off[k] = uint32_t(first);
     }
 
     for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
-        const UTileDev ut = ti == 0u ? ut0 : table_record<vuint8>(a.tiles + grp.first_tile + ti);
+        const UTileDev ut = ti == 0u ? ut0 : utile_record(a.tiles + grp.first_tile + ti);
         const uint32_t n = ut.n_elems, T = ut.L_T, nb = ut.n_bins, bin0 = ut.first_bin & 63u;
         if (ti != 0u) __syncthreads();   // the previous tile has been written out
+        TileState<MODE> state;
         unpack_clear(a, n, ut.aligned(), a.dense + ut.elem_base, s_acc);
         __syncthreads();
         if (W8) {
@@ -2421,6 +2547,7 @@ __device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGro
                 if (cc[k] != 0u && 4u * sub < (at[k] & 3u) + cc[k])
                     packed[k] = reinterpret_cast<const uint32_t *>(a.packets[k < a.n_learners ? k : 0u])[(at[k] >> 2) + sub];
             }
+            if (EARLY) state.fetch(a, ut);
 #pragma unroll
             for (uint32_t k = 0; k < NK; ++k) {
                 if (k >= a.n_learners) break;   // uniform
@@ -2465,22 +2592,28 @@ __device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGro
         // lanes per bin: what makes use of all threads, more if a bin of the tile has more words
         uint32_t glog = nb >= 16u ? 4u : nb >= 8u ? 5u : 6u;
         while (glog < 6u && __builtin_amdgcn_ballot_w64(lane >= bin0 && lane < bin0 + nb && most > (1u << glog)) != 0ull) ++glog;
-        const uint32_t gsz = 1u << glog;
-        for (uint32_t s = tid; s < (((nb << glog) + 63u) & ~63u); s += kWG) {   // (whole waves: the permutes need all lanes)
-            const uint32_t lb = s >> glog, sub = s & (gsz - 1u);
-            const uint32_t from = (bin0 + lb) & 63u;
-            const bool live = lb < nb;
-            const uint32_t span = live ? (T < n - lb * T ? T : n - lb * T) : 0u;   // elements of this bin held by the tile
-            float *const acc = s_acc + lb * T;
-            uint32_t cc[NK], word[NK], cmax = 0u;
+        const uint32_t gsz = 1u << glog, slots = ((nb << glog) + 63u) & ~63u;   // (whole waves: the permutes need all lanes)
+        uint32_t cc[NK], word[NK], cmax;
+        auto fetch = [&](const uint32_t s) {
+            const uint32_t lb = s >> glog, sub = s & (gsz - 1u), from = (bin0 + lb) & 63u;
+            cmax = 0u;
 #pragma unroll
             for (uint32_t k = 0; k < NK; ++k) {
                 cc[k] = uint32_t(__shfl(int(c[k]), int(from), 64));
                 const uint32_t at = uint32_t(__shfl(int(off[k]), int(from), 64)) + sub;
                 cmax = cc[k] > cmax ? cc[k] : cmax;
                 word[k] = 0u;
-                if (live && sub < cc[k]) word[k] = reinterpret_cast<const word_t *>(a.packets[k < a.n_learners ? k : 0u])[at];
+                if (lb < nb && sub < cc[k]) word[k] = reinterpret_cast<const word_t *>(a.packets[k < a.n_learners ? k : 0u])[at];
             }
+        };
+        if (EARLY) { fetch(tid); state.fetch(a, ut); }
+        for (uint32_t s = tid; s < slots; s += kWG) {
+            if (!EARLY || s != tid) fetch(s);
+            const uint32_t lb = s >> glog, sub = s & (gsz - 1u);
+            const uint32_t from = (bin0 + lb) & 63u;
+            const bool live = lb < nb;
+            const uint32_t span = live ? (T < n - lb * T ? T : n - lb * T) : 0u;   // elements of this bin held by the tile
+            float *const acc = s_acc + lb * T;
             if (__builtin_amdgcn_ballot_w64(live && cmax > gsz) == 0ull) {
 #pragma unroll
                 for (uint32_t k = 0; k < NK; ++k) {
@@ -2499,21 +2632,26 @@ __device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGro
             }
         }
         }
+        if (!EARLY) state.fetch(a, ut);
         __syncthreads();
-        unpack_write_out<MODE>(a, ut, s_acc);
+        state.step(a, ut, s_acc);
     }
 }
 
-// KIND as in k_unpack
-template <int MODE, int KIND>
-__global__ __launch_bounds__(kWG, 6) void k_unpack_few(const UnpackArgs a)
+// KIND as in k_unpack.  MANY: for launches of many workgroups.  With the optimizer's step it asks for weights and moments ahead of the adds
+// (unpack_early_for); with 16-bit words it does not insist on all packets' records at once, which shortens the chain of a
+// workgroup and costs those that queue for the scalar caches.  Insisting / not, in us, 4 packets, L_T 500: 0.4 M elements 4.6 / 4.8, 2 M
+// 5.65 / 5.7, 8 M 10.1 / 9.95, 25 M 24.5 / 24.2, 500 and 9000 24.1 / 23.6; 60 M, 64 and 200 in k_unpack8's launch, 1 packet 51.9 /
+// 47.1; 8-bit words, 8 M 13.4 / 15.3, 25 M with 500 28.4 / 30.8.
+template <int MODE, int KIND, bool MANY, uint32_t NK>
+__global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(const UnpackArgs a)
 {
     __shared__ __attribute__((aligned(16))) float s_acc[kUnpackTileElems];
-    const UGroupDev grp = table_record<vuint2>(a.groups + blockIdx.x);
-    const UTileDev ut0 = table_record<vuint8>(a.tiles + grp.first_tile);
-    const LayerDev ld = table_record<vuint16>(a.layers + ut0.layer());
-    if (KIND == 1 || (KIND == 2 && ld.word_bytes == 1u)) unpack_group_few<MODE, true>(a, grp, ut0, ld, s_acc);
-    else unpack_group_few<MODE, false>(a, grp, ut0, ld, s_acc);
+    const GroupAndTile first = first_records(a, blockIdx.x);
+    const UGroupDev grp = first.grp;
+    const UTileDev ut0 = first.tile;
+    if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_group_few<MODE, true, MANY, NK>(a, grp, ut0, s_acc);
+    else unpack_group_few<MODE, false, MANY, NK>(a, grp, ut0, s_acc);
 }
 
 // ==============================================================================================
@@ -2535,9 +2673,8 @@ template <int MODE>
 __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_t group, float *acc_chunk)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const UTileDev ut = table_record<vuint8>(a.tiles + table_record<vuint2>(a.groups + group).first_tile);
+    const UTileDev ut = utile_record(a.tiles + table_record<vuint2>(a.groups + group).first_tile);
     const uint32_t layer = ut.layer(), n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
-    const LayerDev ld = table_record<vuint16>(a.layers + layer);
     float *const out = a.dense + ut.elem_base;
     const uint32_t chunk = ut.first_bin >> 6;
 
@@ -2557,7 +2694,7 @@ __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_
 #pragma unroll
         for (uint32_t k = 0; k < kBatch; ++k) {
             c[k] = 0u;
-            if (k < nk && lane < nb) c[k] = (a.packets[h0 + k] + ld.counts_offset)[ut.first_bin + lane];
+            if (k < nk && lane < nb) c[k] = (a.packets[h0 + k] + ut.counts_offset)[ut.first_bin + lane];
         }
 #pragma unroll
         for (uint32_t k = 0; k < kBatch; ++k) {
@@ -2570,7 +2707,7 @@ __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_
                             (hv.w == a.n_layers) & (tb.y == 0u);
             const uint8_t *const rec = pk + sizeof(adacomp_packet_header_t) + sizeof(adacomp_packet_layer_t) * layer;
             const uint32_t words = packet_field<uint32_t>(rec + offsetof(adacomp_packet_layer_t, words_offset));   // packets stay below 2^32 bytes (host check)
-            const uint32_t before = packet_field<uint32_t>(pk + ld.chunks_offset + 4u * chunk);
+            const uint32_t before = packet_field<uint32_t>(pk + ut.chunks_offset + 4u * chunk);
             const uint32_t ck = ok ? c[k] : 0u;   // a packet that does not match contributes nothing
             // a bin whose words would lie past the packet's total_bytes contributes nothing either
             const uint64_t first = uint64_t(words) + before + (wave_incl_scan(ck) - ck);
@@ -2670,11 +2807,11 @@ __global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackArgs a)
     if (blockIdx.x < a.n_groups) {
         if constexpr (LG == kFewLearners) {
             const UGroupDev grp = table_record<vuint2>(a.groups + a.first16 + blockIdx.x);
-            const UTileDev ut0 = table_record<vuint8>(a.tiles + grp.first_tile);
-            unpack_group_few<MODE, false>(a, grp, ut0, table_record<vuint16>(a.layers + ut0.layer()), reinterpret_cast<float *>(s_dyn));
+            const UTileDev ut0 = utile_record(a.tiles + grp.first_tile);
+            unpack_group_few<MODE, false, MODE == 0, kFewInLaunch8>(a, grp, ut0, reinterpret_cast<float *>(s_dyn));
         } else {
             UnpackLds<LG> &lds = *reinterpret_cast<UnpackLds<LG> *>(s_dyn);
-            unpack_group<MODE, 0, LG>(a, a.first16 + blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+            unpack_group<MODE, 0, LG, false>(a, a.first16 + blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
         }
         return;
     }
@@ -2827,11 +2964,12 @@ int launch_place(const CompressArgs &a, void *stream)
     return check_launch();
 }
 
-// resident: workgroups per compute unit that the launch is held to (5 or 4), or 0.
-int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream)
+// resident: workgroups per compute unit that the launch is held to (5 or 4), or 0.  early: unpack_early_for.
+int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, bool early, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (a.n_groups == 0 && kind != 3) return ADACOMP_OK;
+    if (early && (a.mode == 0u || kind == 3 || (a.n_learners > 8u && kind != 0))) return ADACOMP_EINVAL;   // the host asks for it where there is a kernel
     const dim3 grid(a.n_groups), wg(kWG);
     uint32_t lds = 0;
     auto launch = [&](const dim3 &workgroups, auto kernel) { hipLaunchKernelGGL(kernel, workgroups, wg, lds, s, a); };
@@ -2846,7 +2984,7 @@ int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream
     if (resident != 0u && arrays < kResidentLds[resident == 4u]) lds = kResidentLds[resident == 4u] - arrays;   // LDS that no kernel touches
     if (kind == 3) {
         const uint32_t wg_log = a.chunk_lds & 63u, chunk_elems = a.chunk_lds & ~63u;
-        if (a.n_groups8 == 0 || chunk_elems == 0 || chunk_elems > 64u * 64u || wg_log > 2u) return ADACOMP_EINVAL;
+        if (a.n_groups8 == 0 || chunk_elems == 0 || chunk_elems > 64u * 64u || wg_log > 2u || (a.mode != 0u && !eight)) return ADACOMP_EINVAL;
         const dim3 both(a.n_groups + ((a.n_groups8 + (1u << wg_log) - 1u) >> wg_log));
         const bool two = a.n_learners != 0u && a.n_learners <= kFewInLaunch8;
         const uint32_t groups = a.n_groups == 0u ? 0u : two ? 4u * kUnpackTileElems : uint32_t(eight ? sizeof(UnpackLds<8>) : sizeof(UnpackLds<16>));
@@ -2855,7 +2993,7 @@ int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream
             constexpr int M = decltype(mode)::value;
             if (two) launch(both, k_unpack8<M, kFewLearners>);
             else if (eight) launch(both, k_unpack8<M, 8>);
-            else launch(both, k_unpack8<M, 16>);
+            else if constexpr (M == 0) launch(both, k_unpack8<M, 16>);
         });
         return check_launch();
     }
@@ -2866,9 +3004,16 @@ int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream
             else if (kind == 1) launch(grid, k1);
             else launch(grid, k2);
         };
-        if (few) width(k_unpack_few<M, 0>, k_unpack_few<M, 1>, k_unpack_few<M, 2>);
-        else if (eight) width(k_unpack<M, 0, 8>, k_unpack<M, 1, 8>, k_unpack<M, 2, 8>);
-        else width(k_unpack<M, 0, 16>, k_unpack<M, 1, 16>, k_unpack<M, 2, 16>);
+        auto kernels = [&](auto how) {
+            constexpr bool B = decltype(how)::value, E = M != 0 && B;
+            if (few && a.n_learners <= 2u) width(k_unpack_few<M, 0, B, 2>, k_unpack_few<M, 1, E, 2>, k_unpack_few<M, 2, B, 2>);
+            else if (few) width(k_unpack_few<M, 0, B, 4>, k_unpack_few<M, 1, E, 4>, k_unpack_few<M, 2, B, 4>);
+            else if (eight) width(k_unpack<M, 0, 8, E>, k_unpack<M, 1, 8, E>, k_unpack<M, 2, 8, E>);
+            else if constexpr (E) launch(grid, k_unpack<M, 0, 16, E>);
+            else width(k_unpack<M, 0, 16, E>, k_unpack<M, 1, 16, E>, k_unpack<M, 2, 16, E>);
+        };
+        if (M != 0 ? early : a.n_groups > kFewTilesTogether) kernels(std::integral_constant<bool, true>());
+        else kernels(std::integral_constant<bool, false>());
     });
     return check_launch();
 }

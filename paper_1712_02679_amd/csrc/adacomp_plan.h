@@ -55,18 +55,22 @@ struct TileDev {
 static_assert(sizeof(TileDev) == 32, "TileDev layout");
 
 // One workgroup's share of adacomp_unpack_accumulate: up to 64 whole bins inside one 64-bin
-// chunk, or a slice [idx_lo, idx_lo + n_elems) of a single bin longer than the tile (32 bytes).
+// chunk, or a slice [idx_lo, idx_lo + n_elems) of a single bin longer than the tile (32 bytes).  With what the kernels need to
+// know about the layer, so that they do not have to fetch its record behind this one.
 struct UTileDev {
     uint64_t elem_base;
-    uint32_t n_elems;
-    uint32_t L_T;
-    uint32_t n_bins;
     uint32_t first_bin;
-    uint32_t idx_lo;
     uint32_t layer_flags; // bits 0..23 layer, 24..27 log2(lanes per bin), bit 31 aligned
+    uint32_t counts_offset, chunks_offset;   // of the layer, in a packet (which stays below 2^32 bytes)
+    uint16_t n_elems;     // <= kUnpackTileElems
+    uint16_t L_T;
+    uint16_t idx_lo;
+    uint8_t n_bins;       // <= 64
+    uint8_t chunk_bins;   // bins of the layer in the tile's 64-bin chunk
     __host__ __device__ uint32_t layer() const { return layer_flags & 0xFFFFFFu; }
     __host__ __device__ uint32_t group_log2() const { return (layer_flags >> 24) & 15u; }
     __host__ __device__ bool aligned() const { return (layer_flags >> 31) != 0; }
+    __host__ __device__ bool words8() const { return L_T <= 64u; }
 };
 static_assert(sizeof(UTileDev) == 32, "UTileDev layout");
 
@@ -75,6 +79,12 @@ struct UGroupDev {
     uint32_t first_tile, n_tiles;
 };
 static_assert(sizeof(UGroupDev) == 8, "UGroupDev layout");
+// The tile of group g where every group is a tile.  Workgroups are dealt to the 8 XCDs round-robin, so inside each 64 the
+// order is transposed and the 8 tiles of a chunk, which read the same count and offset lines of every packet, share an L2.
+__host__ __device__ inline uint32_t single_tile(uint32_t g, uint32_t n_tiles)
+{
+    return g < (n_tiles & ~63u) ? ((g & ~63u) | ((g & 7u) << 3) | ((g >> 3) & 7u)) : g;
+}
 constexpr uint32_t kUnpackGroupTiles = 8;   // at most this many tiles per group
 constexpr uint32_t kUnpackMinGroups = 2048;  // groups of more than one tile only while this many workgroups remain (8 per compute unit)
 // Tables with both word widths: one launch per width on tables of more tiles than this and with more packets than
@@ -101,6 +111,8 @@ constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workg
 //          186, 16 194 / 190 / 189; 13 M, L_T 500, 8 65.4 / 64.2 / 65.3
 constexpr uint32_t kResidentLds[2] = {32000, 40900};   // bytes of LDS that leave five, four workgroups on a compute unit
 constexpr uint64_t kResidentElems = 11600000, kResidentElemsSum = 23200000, kResidentElemsSumMany = 32000000;   // from which on: with the optimizer; sums of up to 4 packets; of more
+constexpr uint64_t kEarlyElems = 1500000;   // elements of a launch from which on the optimizer's state is fetched ahead of the adds (unpack_early_for)
+constexpr uint32_t kFewTilesTogether = 1024;   // groups up to which a plain sum of few packets waits for all packets' records together (k_unpack_few)
 constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table that go alone (3 per compute unit)
 
 // What k_fused leaves per tile for k_scan and k_place: one 16-byte record, so that a tile makes one
@@ -189,6 +201,7 @@ struct Plan {
     uint32_t layer_tiles_max = 0;  // compress tiles of the layer that has most
     uint32_t short_bin_max = 0;    // longest L_T <= 64
     bool has_tiny_bins = false;    // some layer has L_T < 4
+    bool groups_single = false;    // the groups of the plain sum are single tiles too (of a plan with tables)
     bool has_shifted_tiles = false;  // some tile of the larger class has skip != 0
     WorkspaceLayout ws;
     SyncPlace sync;   // of a registered workspace
@@ -337,7 +350,7 @@ static_assert(sizeof(CompressArgs) <= 1024, "kernel arguments");
 
 struct UnpackArgs {
     const UTileDev *tiles;
-    const UGroupDev *groups;
+    const UGroupDev *groups;           // null: a tile each, single_tile
     const LayerDev *layers;
     float *dense;
     uint32_t n_groups;                 // workgroups that take a group each (kind 3: of the layers with 16-bit words)
@@ -361,6 +374,7 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
 bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units);
 uint32_t place_lanes_for(const Plan &p);
 uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint32_t n_learners, uint32_t mode);
+bool unpack_early_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, bool words8, uint32_t n_learners, uint32_t mode);
 uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);
 int launch_fused(const CompressArgs &a, int jcode, void *stream);
 int launch_scan(const CompressArgs &a, void *stream);
@@ -368,7 +382,7 @@ int launch_place(const CompressArgs &a, void *stream);
 // what a k_place launch does: everything (the default); the words, offsets and header only, leaving
 // the residue corrections waiting; or those corrections only
 constexpr uint32_t kPlaceEager = 0, kPlaceWords = 1, kPlaceResidue = 2;
-int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, void *stream);  // kind 0: 16-bit words, 1: 8-bit, 2: both, 3: both, k_unpack8
+int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, bool early, void *stream);  // kind 0: 16-bit words, 1: 8-bit, 2: both, 3: both, k_unpack8
 int launch_copy(float *dst, const float *src, size_t n, void *stream);
 int launch_triad(float *x, const float *y, size_t n, uint32_t resident, void *stream);   // n a multiple of 4, below 2^44; resident 3 .. 8
 int launch_fill(float *x, float value, size_t n, void *stream);
