@@ -32,6 +32,7 @@
 // and the per-bin bookkeeping.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "adacomp_plan.h"
@@ -1952,7 +1953,7 @@ struct PacketChunk {
         before = packet_field<uint32_t>(pk + chunks_offset + 4u * chunk);
     }
     // whether the packet is one that this call can read
-    __device__ __forceinline__ bool fits(const UnpackArgs &a) const
+    __device__ __forceinline__ bool fits(const UnpackHead &a) const
     {
         return (head.x == ADACOMP_PACKET_MAGIC) & (head.y == ADACOMP_PACKET_VERSION) & (head.z == ADACOMP_STATUS_COMPLETE) & (head.w == a.n_layers) & (total_bytes.y == 0u);
     }
@@ -1987,8 +1988,8 @@ __device__ __forceinline__ void settle(PacketChunk (&p)[N])
 // Phase 1 for learners k0 .. k0 + LG - 1 (LG = 8 or 16) and the bins [row0_bin, scan_end) of one 64-bin chunk: word
 // count and position of the first word of every (bin, learner), into the LDS tables (row = bin -
 // row0_bin).  The caller has a barrier before (the tables are free) and after (they are filled).
-template <bool W8, uint32_t LG>
-__device__ __forceinline__ void unpack_tables(const UnpackArgs &a, const UTileDev &ut0,
+template <bool W8, uint32_t LG, class Args>
+__device__ __forceinline__ void unpack_tables(const Args &a, const UTileDev &ut0,
                                               const uint32_t row0_bin, const uint32_t scan_end, const uint32_t k0,
                                               uint32_t (*s_off)[kOffStride<LG>], uint16_t (*s_cnt)[kCntStride],
                                               float *s_scale, uint32_t *s_cmax)
@@ -2067,8 +2068,8 @@ __device__ __forceinline__ void lds_add(float *acc, const uint32_t idx, const fl
 struct NoHook {
     __device__ __forceinline__ void operator()() const {}
 };
-template <bool W8, uint32_t LG, class Hook>
-__device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev &ut, const uint32_t row0, const uint32_t k0,
+template <bool W8, uint32_t LG, class Hook, class Args>
+__device__ __forceinline__ void unpack_adds(const Args &a, const UTileDev &ut, const uint32_t row0, const uint32_t k0,
                                             float *s_acc, uint32_t (*s_off)[kOffStride<LG>],
                                             uint16_t (*s_cnt)[kCntStride], const float *s_scale, const uint32_t *s_cmax, Hook words_on_their_way)
 {
@@ -2226,7 +2227,7 @@ __device__ __forceinline__ void unpack_adds(const UnpackArgs &a, const UTileDev 
 // operation is a separate float32 operation (contraction is off), division and square root are
 // the correctly rounded ones.
 template <int MODE>
-__device__ __forceinline__ void apply_update(const UnpackArgs &a, float sum, float &w, float &s1, float &s2)
+__device__ __forceinline__ void apply_update(const UnpackHead &a, float sum, float &w, float &s1, float &s2)
 {
     const float g = sum / a.n_average;
     if (MODE == 1) {  // SGD with momentum: v <- mu v + g; w <- w - lr v
@@ -2264,7 +2265,7 @@ struct UnpackLds {
 };
 
 // Clears the accumulators of a tile of n elements, or loads the partial sum of an earlier launch.
-__device__ __forceinline__ void unpack_clear(const UnpackArgs &a, const uint32_t n, const bool vec, const float *__restrict__ out, float *const s_acc)
+__device__ __forceinline__ void unpack_clear(const UnpackHead &a, const uint32_t n, const bool vec, const float *__restrict__ out, float *const s_acc)
 {
     const uint32_t tid = threadIdx.x;
     for (uint32_t i = tid * 4u; i < n; i += kWG * 4u) {
@@ -2283,7 +2284,7 @@ __device__ __forceinline__ void unpack_clear(const UnpackArgs &a, const uint32_t
 }
 
 // Writes the finished sum of a tile out.
-__device__ __forceinline__ void unpack_write_out(const UnpackArgs &a, const UTileDev &ut, float *const s_acc)
+__device__ __forceinline__ void unpack_write_out(const UnpackHead &a, const UTileDev &ut, float *const s_acc)
 {
     const uint32_t tid = threadIdx.x;
     const uint32_t n = ut.n_elems;
@@ -2327,7 +2328,7 @@ struct TileState {
     static constexpr uint32_t kSlots = kUnpackTileElems / (4u * kWG);
     vfloat4 w[kSlots], s1[kSlots], s2[MODE == 2 ? kSlots : 1u];
 
-    __device__ __forceinline__ void fetch(const UnpackArgs &a, const UTileDev &ut)
+    __device__ __forceinline__ void fetch(const UnpackHead &a, const UTileDev &ut)
     {
         const uint32_t whole = ut.n_elems & ~3u;
         const __amdgpu_buffer_rsrc_t wb = tile_buffer(a.weights + ut.elem_base, whole), b1 = tile_buffer(a.state1 + ut.elem_base, whole);
@@ -2339,7 +2340,7 @@ struct TileState {
             if (MODE == 2) s2[j] = buffer_load_slot(b2, threadIdx.x * 16u, j * kWG * 16u);
         }
     }
-    __device__ __forceinline__ void step(const UnpackArgs &a, const UTileDev &ut, const float *const s_acc)
+    __device__ __forceinline__ void step(const UnpackHead &a, const UTileDev &ut, const float *const s_acc)
     {
         const uint32_t n = ut.n_elems, whole = n & ~3u;
         const __amdgpu_buffer_rsrc_t wb = tile_buffer(a.weights + ut.elem_base, whole), b1 = tile_buffer(a.state1 + ut.elem_base, whole);
@@ -2375,9 +2376,13 @@ struct TileState {
 };
 template <>
 struct TileState<0> {
-    __device__ __forceinline__ void fetch(const UnpackArgs &, const UTileDev &) {}
-    __device__ __forceinline__ void step(const UnpackArgs &a, const UTileDev &ut, float *const s_acc) { unpack_write_out(a, ut, s_acc); }
+    __device__ __forceinline__ void fetch(const UnpackHead &, const UTileDev &) {}
+    __device__ __forceinline__ void step(const UnpackHead &a, const UTileDev &ut, float *const s_acc) { unpack_write_out(a, ut, s_acc); }
 };
+
+// Packets of a launch whose tables are for LG of them: 16 do for any number, as many at a time.
+template <uint32_t LG>
+constexpr uint32_t packets_of = LG <= 8u ? LG : kMaxPacketArgs;
 
 // Group number g of the launch, and its first tile.  Arguments, group, tile: a round of scalar loads each, 0.25 us, and what the
 // packets are asked for stands in the tile's record (so far a round more for the layer's, and the compiler fetched the
@@ -2392,7 +2397,7 @@ __device__ __forceinline__ UTileDev utile_record(const UTileDev *p)
     asm volatile("" : "+s"(v));
     return __builtin_bit_cast(UTileDev, v);
 }
-__device__ __forceinline__ GroupAndTile first_records(const UnpackArgs &a, const uint32_t g)
+__device__ __forceinline__ GroupAndTile first_records(const UnpackHead &a, const uint32_t g)
 {
     const UTileDev *tiles = a.tiles;
     const UGroupDev *groups = a.groups;
@@ -2412,8 +2417,8 @@ __device__ __forceinline__ GroupAndTile first_records(const UnpackArgs &a, const
 // the kernel that holds both, one path after a branch.  The single-width kernels are held to 80 registers (6 waves per
 // SIMD, what the LDS tile allows).
 // EARLY: weights and moments are asked for ahead of the adds and kept through them, in up to 128 registers.
-template <int MODE, bool W8, uint32_t LG, bool EARLY>
-__device__ __forceinline__ void unpack_tiles(const UnpackArgs &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc,
+template <int MODE, bool W8, uint32_t LG, bool EARLY, class Args>
+__device__ __forceinline__ void unpack_tiles(const Args &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc,
                                              uint32_t (*const s_off)[kOffStride<LG>], uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
     // A workgroup serves a group of consecutive tiles that lie in one 64-bin chunk (or are slices
@@ -2455,8 +2460,8 @@ __device__ __forceinline__ void unpack_tiles(const UnpackArgs &a, const UGroupDe
   }  // tiles of the group
 }
 
-template <int MODE, int KIND, uint32_t LG, bool EARLY>
-__device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
+template <int MODE, int KIND, uint32_t LG, bool EARLY, class Args>
+__device__ __forceinline__ void unpack_group(const Args &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
                                              uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
     const GroupAndTile first = first_records(a, group);
@@ -2467,7 +2472,7 @@ __device__ __forceinline__ void unpack_group(const UnpackArgs &a, const uint32_t
 }
 
 template <int MODE, int KIND, uint32_t LG, bool EARLY>
-__global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UnpackArgs a)
+__global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UnpackPackets<packets_of<LG>> a)
 {
     if (blockIdx.x >= a.n_groups) return;
     __shared__ float s_acc[kUnpackTileElems];
@@ -2492,8 +2497,8 @@ constexpr uint32_t kFewLearners = 4;
 // take this form for up to two learners (ResNet-50's table, k_unpack's form / this one: 1 packet 20.3 / 20.0 us, 2 22.1 /
 // 20.9, but 4 25.2 / 26.7).
 constexpr uint32_t kFewInLaunch8 = 2;
-template <int MODE, bool W8, bool MANY, uint32_t NK>
-__device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc)
+template <int MODE, bool W8, bool MANY, uint32_t NK, class Args>
+__device__ __forceinline__ void unpack_group_few(const Args &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc)
 {
     typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -2644,7 +2649,7 @@ __device__ __forceinline__ void unpack_group_few(const UnpackArgs &a, const UGro
 // 5.65 / 5.7, 8 M 10.1 / 9.95, 25 M 24.5 / 24.2, 500 and 9000 24.1 / 23.6; 60 M, 64 and 200 in k_unpack8's launch, 1 packet 51.9 /
 // 47.1; 8-bit words, 8 M 13.4 / 15.3, 25 M with 500 28.4 / 30.8.
 template <int MODE, int KIND, bool MANY, uint32_t NK>
-__global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(const UnpackArgs a)
+__global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(const UnpackPackets<NK> a)
 {
     __shared__ __attribute__((aligned(16))) float s_acc[kUnpackTileElems];
     const GroupAndTile first = first_records(a, blockIdx.x);
@@ -2669,8 +2674,8 @@ __global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(c
 // All adds to one element come from one lane in program order, and the LDS unit executes a wave's
 // operations in order: the sum is taken learner 0 first.
 // ==============================================================================================
-template <int MODE>
-__device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_t group, float *acc_chunk)
+template <int MODE, class Args>
+__device__ __forceinline__ void unpack8_chunk(const Args &a, const uint32_t group, float *acc_chunk)
 {
     const uint32_t lane = threadIdx.x & 63u;
     const UTileDev ut = utile_record(a.tiles + table_record<vuint2>(a.groups + group).first_tile);
@@ -2801,7 +2806,7 @@ __device__ __forceinline__ void unpack8_chunk(const UnpackArgs &a, const uint32_
 // The first n_groups workgroups take a group of the 16-bit layers each, the others up to four chunks of the
 // 8-bit ones.  Dynamic LDS: launch_unpack.  LG: 4 (k_unpack_few), 8 or 16 learners to a group of the former.
 template <int MODE, uint32_t LG>
-__global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackArgs a)
+__global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackPackets<(LG == kFewLearners ? kFewInLaunch8 : packets_of<LG>)> a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
     if (blockIdx.x < a.n_groups) {
@@ -2964,6 +2969,12 @@ int launch_place(const CompressArgs &a, void *stream)
     return check_launch();
 }
 
+template <class K>
+struct KernelArgs;
+template <class A>
+struct KernelArgs<void (*)(A)> {
+    using type = typename std::remove_const<A>::type;
+};
 // resident: workgroups per compute unit that the launch is held to (5 or 4), or 0.  early: unpack_early_for.
 int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, bool early, void *stream)
 {
@@ -2972,7 +2983,12 @@ int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, bool early, 
     if (early && (a.mode == 0u || kind == 3 || (a.n_learners > 8u && kind != 0))) return ADACOMP_EINVAL;   // the host asks for it where there is a kernel
     const dim3 grid(a.n_groups), wg(kWG);
     uint32_t lds = 0;
-    auto launch = [&](const dim3 &workgroups, auto kernel) { hipLaunchKernelGGL(kernel, workgroups, wg, lds, s, a); };
+    auto launch = [&](const dim3 &workgroups, auto kernel) {
+        typename KernelArgs<decltype(kernel)>::type args;
+        static_cast<UnpackHead &>(args) = a;
+        std::copy_n(a.packets, sizeof(args.packets) / sizeof(args.packets[0]), args.packets);
+        hipLaunchKernelGGL(kernel, workgroups, wg, lds, s, args);
+    };
     auto with_mode = [&](auto &&go) {
         if (a.mode == 1) go(std::integral_constant<int, 1>());
         else if (a.mode == 2) go(std::integral_constant<int, 2>());

@@ -348,7 +348,7 @@ struct CompressArgs {
 // before it (968, and 1184, do not): the kernels do without the hidden ones.
 static_assert(sizeof(CompressArgs) <= 1024, "kernel arguments");
 
-struct UnpackArgs {
+struct UnpackHead {
     const UTileDev *tiles;
     const UGroupDev *groups;           // null: a tile each, single_tile
     const LayerDev *layers;
@@ -363,12 +363,19 @@ struct UnpackArgs {
     float n_average;                   // learner count the sum is divided by
     float lr, p1, p2, one_minus_p1, one_minus_p2, eps, bias1, bias2;
     uint32_t chunk_lds;                // kind 3: floats of LDS per chunk, 64 times the longest of the 8-bit layers' bins, + log2 of the chunks per workgroup
-    const uint8_t *packets[kMaxPacketArgs];
 };
+// With N packets: a kernel takes no more of them than it can have.  Small sums are bound by what a launch costs the host, which
+// goes by its arguments too: 0.4 M elements, 1 packet, 144 bytes of them instead of 640 4.25 us a call on a box where what was before
+// took 4.75; 4.0 where it took 4.2 with 640.
+template <uint32_t N>
+struct UnpackPackets : UnpackHead {
+    const uint8_t *packets[N];
+};
+using UnpackArgs = UnpackPackets<kMaxPacketArgs>;
 // Workgroups start with the scalar loads of these arguments, and the first of a launch wait for every line
 // of them.  With 16 bytes more before `packets`, whose lines then no longer began with it, k_unpack took
 // 1.5 to 2 % longer (4 M elements, 4 packets 8.85 -> 9.04 us; 20 M, 8 packets 31.5 -> 32.1).
-static_assert(sizeof(UnpackArgs) == 640 && offsetof(UnpackArgs, packets) == 128, "kernel arguments");
+static_assert(sizeof(UnpackHead) == 128 && sizeof(UnpackArgs) == 640, "kernel arguments");
 
 uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units, bool lazy = false);
 bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units);
