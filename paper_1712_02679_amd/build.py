@@ -14,6 +14,8 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off",                                     # no fused multiply-add, no reassociation
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",  # no packed-FP32 instructions
+    # scalar arguments ahead of a kernel's structure are in registers when its workgroups start (k_pack, the unpack kernels)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wextra",
 ]
 

@@ -1091,40 +1091,59 @@ __device__ __forceinline__ uint32_t take_max_from(const uint32_t v, const bool f
     return from && o > v ? o : v;
 }
 
+// What a workgroup needs for its first loads, ahead of the structure (kOneTable).
+struct PackFirst {
+    const TileDev *tiles;
+    uint8_t *sync;
+    uint32_t sync_stride, o_epoch, n_tiles, first;
+};
 template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
-__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80))) void k_pack(const CompressArgs a)
+__device__ __forceinline__ void pack_tile(const PackFirst &ahead, const CompressArgs &a)
 {
     constexpr uint32_t WG = uint32_t(WAVES) * 64u, kRow = WG * 4u;   // J 16-byte slots to a thread: slot j of thread t is number j * WG + t of the tile
     constexpr int P = (J + 1) / 2;   // pairs of rows
     static_assert(WG * uint32_t(J) <= 4096u && J <= 4, "tiles of at most 16384 elements, words counted in 15 bits");
     // Two rounds of scalar loads: arguments, then what they point to.  (Left to the compiler, which fetches what a
-    // branch needs behind the branch, there are five, 0.25 us each, before the first load of the tile.)
-    const TileDev *tiles = a.tiles;
-    const LayerDev *layers = a.layers;
-    uint8_t *sync = a.sync;
-    uint64_t sync_stride = a.sync_stride;
-    uint32_t o_rec = a.o_sync_rec, o_tile = a.o_sync_tile, o_layer = a.o_sync_layer, o_epoch = a.o_sync_epoch;
-    uint32_t n_tiles = a.class_count, lr = a.fused_first;
-    asm volatile("" : "+s"(tiles), "+s"(layers), "+s"(sync), "+s"(sync_stride), "+s"(o_rec), "+s"(o_tile), "+s"(o_layer), "+s"(o_epoch), "+s"(n_tiles), "+s"(lr));
+    // branch needs behind the branch, there are five, 0.25 us each, before the first load of the tile.)  kOneTable, where the
+    // chain is what counts: one, since what the loads of the second need is there when the workgroup starts, in scalar
+    // registers (the arguments before the structure, see the build's preload count; as structure / ahead of it, in us: 397 k elements
+    // 6.24 / 6.03, the CIFAR table 8.83 / 8.38, 4 learners with unpack 19.98 / 19.79, bins of 800 and 8000 19.95 / 19.39; kOneLayers, ResNet-50's
+    // table 58.5 / 59.5, with six more scalar registers spilled).
+    constexpr bool kAhead = ONE == kOneTable;
+    const TileDev *tiles = ahead.tiles;
+    uint8_t *sync = ahead.sync;
+    uint64_t sync_stride = ahead.sync_stride;
+    uint32_t o_epoch = ahead.o_epoch, n_tiles = ahead.n_tiles, lr = ahead.first, o_rec = 0u, o_tile = 0u, o_layer = 0u;
+    const LayerDev *layers = nullptr;
+    if constexpr (!kAhead) {
+        tiles = a.tiles; layers = a.layers; sync = a.sync; sync_stride = a.sync_stride;
+        o_rec = a.o_sync_rec; o_tile = a.o_sync_tile; o_layer = a.o_sync_layer; o_epoch = a.o_sync_epoch;
+        n_tiles = a.class_count; lr = a.fused_first;
+        asm volatile("" : "+s"(tiles), "+s"(layers), "+s"(sync), "+s"(sync_stride), "+s"(o_rec), "+s"(o_tile), "+s"(o_layer), "+s"(o_epoch), "+s"(n_tiles), "+s"(lr));
+    }
     // learner-major: one workgroup per tile, within runs of 64 transposed as in k_fused, then the one that writes the header
     uint32_t tile = blockIdx.x;
     const bool heads = tile == n_tiles;
     lr += blockIdx.y;
     if (tile < (n_tiles & ~63u)) tile = (tile & ~63u) | ((tile & 7u) << 3) | ((tile >> 3) & 7u);
+    uint8_t *const area = sync + uint64_t(lr) * sync_stride;
     SyncArea sy;
-    {
-        uint8_t *const area = sync + uint64_t(lr) * sync_stride;
+    auto set_sync = [&]() {
         sy.rec = reinterpret_cast<uint64_t *>(area + o_rec);
         sy.tile = reinterpret_cast<uint64_t *>(area + o_tile);
         sy.layer = reinterpret_cast<uint64_t *>(area + o_layer);
-        sy.epoch = reinterpret_cast<uint32_t *>(area + o_epoch);
-    }
+    };
+    if constexpr (!kAhead) set_sync();
+    sy.epoch = reinterpret_cast<uint32_t *>(area + o_epoch);
     vuint8 tile_words = *(const __attribute__((address_space(4))) vuint8 *)(tiles + (heads ? 0u : tile));
     uint32_t epoch = *(const __attribute__((address_space(4))) uint32_t *)(sy.epoch + tile);
     uint8_t *packet = a.packet[lr];
     float *residue = a.residue[lr];
     const float *grad = a.grad[lr];
-    asm volatile("" : "+s"(tile_words), "+s"(epoch), "+s"(packet), "+s"(residue), "+s"(grad));
+    if constexpr (kAhead) { layers = a.layers; o_rec = a.o_sync_rec; o_tile = a.o_sync_tile; o_layer = a.o_sync_layer; }
+    if constexpr (kAhead) asm volatile("" : "+s"(tile_words), "+s"(epoch), "+s"(packet), "+s"(residue), "+s"(grad), "+s"(layers), "+s"(o_rec), "+s"(o_tile), "+s"(o_layer));
+    else asm volatile("" : "+s"(tile_words), "+s"(epoch), "+s"(packet), "+s"(residue), "+s"(grad));
+    if constexpr (kAhead) set_sync();
     ++epoch;   // (count_call)
     const TileDev td = __builtin_bit_cast(TileDev, tile_words);
 
@@ -1535,6 +1554,23 @@ __global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LA
     // chunks[c] = words of the layer in bins < 64 c, for the chunk starts inside this tile
     for (uint32_t t = t0 + 64u * tid; t < nb; t += 64u * WG)
         reinterpret_cast<uint32_t *>(packet + ld.chunks_offset)[(td.first_bin + t) >> 6] = base + s_chunk[t >> 6];
+}
+
+// kOneTable, kOneLayers
+template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
+__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80)))
+void k_pack(const TileDev *const tiles, uint8_t *const sync, const uint32_t sync_stride, const uint32_t o_epoch, const uint32_t n_tiles,
+            const uint32_t first, const CompressArgs a)
+{
+    static_assert(ONE == kOneTable, "arguments ahead of the structure");
+    pack_tile<VARIANT, ONE, WAVES, J, LAZY>(PackFirst{tiles, sync, sync_stride, o_epoch, n_tiles, first}, a);
+}
+template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
+__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80)))
+void k_pack(const CompressArgs a)
+{
+    static_assert(ONE == kOneLayers, "the structure alone");
+    pack_tile<VARIANT, ONE, WAVES, J, LAZY>(PackFirst{}, a);
 }
 
 // ==============================================================================================
@@ -2384,9 +2420,9 @@ struct TileState<0> {
 template <uint32_t LG>
 constexpr uint32_t packets_of = LG <= 8u ? LG : kMaxPacketArgs;
 
-// Group number g of the launch, and its first tile.  Arguments, group, tile: a round of scalar loads each, 0.25 us, and what the
-// packets are asked for stands in the tile's record (so far a round more for the layer's, and the compiler fetched the
-// arguments where it used them).  The record is kept whole: taken apart, its short fields come through vector loads.
+// Group number g of the launch, and its first tile.  Group and tile: a round of scalar loads each, 0.25 us, without one for the
+// arguments (see k_pack), and what the packets are asked for stands in the tile's record (so far a round more for the layer's, and
+// the compiler fetched the arguments where it used them).  The record is kept whole: taken apart, its short fields come through vector loads.
 struct GroupAndTile {
     UGroupDev grp;
     UTileDev tile;
@@ -2397,12 +2433,8 @@ __device__ __forceinline__ UTileDev utile_record(const UTileDev *p)
     asm volatile("" : "+s"(v));
     return __builtin_bit_cast(UTileDev, v);
 }
-__device__ __forceinline__ GroupAndTile first_records(const UnpackHead &a, const uint32_t g)
+__device__ __forceinline__ GroupAndTile first_records(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups, const uint32_t g)
 {
-    const UTileDev *tiles = a.tiles;
-    const UGroupDev *groups = a.groups;
-    uint32_t n_groups = a.n_groups;
-    asm volatile("" : "+s"(tiles), "+s"(groups), "+s"(n_groups));
     GroupAndTile r;
     r.grp = groups == nullptr ? UGroupDev{single_tile(g, n_groups), 1u} : table_record<vuint2>(groups + g);
     r.tile = utile_record(tiles + r.grp.first_tile);
@@ -2461,10 +2493,9 @@ __device__ __forceinline__ void unpack_tiles(const Args &a, const UGroupDev grp,
 }
 
 template <int MODE, int KIND, uint32_t LG, bool EARLY, class Args>
-__device__ __forceinline__ void unpack_group(const Args &a, const uint32_t group, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
+__device__ __forceinline__ void unpack_group(const Args &a, const GroupAndTile &first, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
                                              uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
-    const GroupAndTile first = first_records(a, group);
     const UGroupDev grp = first.grp;
     const UTileDev ut0 = first.tile;
     if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_tiles<MODE, true, LG, EARLY>(a, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
@@ -2472,15 +2503,15 @@ __device__ __forceinline__ void unpack_group(const Args &a, const uint32_t group
 }
 
 template <int MODE, int KIND, uint32_t LG, bool EARLY>
-__global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UnpackPackets<packets_of<LG>> a)
+__global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
+                                                                                                      const UnpackPackets<packets_of<LG>> a)
 {
-    if (blockIdx.x >= a.n_groups) return;
     __shared__ float s_acc[kUnpackTileElems];
     __shared__ __attribute__((aligned(16))) uint32_t s_off[64][kOffStride<LG>];  // first word of (bin, learner), counted from the packet start
     __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64][kCntStride];
     __shared__ __attribute__((aligned(16))) float s_scale[LG];
     __shared__ uint32_t s_cmax;                                                // largest word count of a (bin, learner) in the tables
-    unpack_group<MODE, KIND, LG, EARLY>(a, blockIdx.x, s_acc, s_off, s_cnt, s_scale, s_cmax);
+    unpack_group<MODE, KIND, LG, EARLY>(a, first_records(tiles, groups, n_groups, blockIdx.x), s_acc, s_off, s_cnt, s_scale, s_cmax);
 }
 
 // ==============================================================================================
@@ -2649,10 +2680,11 @@ __device__ __forceinline__ void unpack_group_few(const Args &a, const UGroupDev 
 // 5.65 / 5.7, 8 M 10.1 / 9.95, 25 M 24.5 / 24.2, 500 and 9000 24.1 / 23.6; 60 M, 64 and 200 in k_unpack8's launch, 1 packet 51.9 /
 // 47.1; 8-bit words, 8 M 13.4 / 15.3, 25 M with 500 28.4 / 30.8.
 template <int MODE, int KIND, bool MANY, uint32_t NK>
-__global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(const UnpackPackets<NK> a)
+__global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
+                                                                             const UnpackPackets<NK> a)
 {
     __shared__ __attribute__((aligned(16))) float s_acc[kUnpackTileElems];
-    const GroupAndTile first = first_records(a, blockIdx.x);
+    const GroupAndTile first = first_records(tiles, groups, n_groups, blockIdx.x);
     const UGroupDev grp = first.grp;
     const UTileDev ut0 = first.tile;
     if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_group_few<MODE, true, MANY, NK>(a, grp, ut0, s_acc);
@@ -2675,10 +2707,9 @@ __global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(c
 // operations in order: the sum is taken learner 0 first.
 // ==============================================================================================
 template <int MODE, class Args>
-__device__ __forceinline__ void unpack8_chunk(const Args &a, const uint32_t group, float *acc_chunk)
+__device__ __forceinline__ void unpack8_chunk(const Args &a, const UTileDev &ut, float *acc_chunk)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const UTileDev ut = utile_record(a.tiles + table_record<vuint2>(a.groups + group).first_tile);
     const uint32_t layer = ut.layer(), n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
     float *const out = a.dense + ut.elem_base;
     const uint32_t chunk = ut.first_bin >> 6;
@@ -2806,27 +2837,27 @@ __device__ __forceinline__ void unpack8_chunk(const Args &a, const uint32_t grou
 // The first n_groups workgroups take a group of the 16-bit layers each, the others up to four chunks of the
 // 8-bit ones.  Dynamic LDS: launch_unpack.  LG: 4 (k_unpack_few), 8 or 16 learners to a group of the former.
 template <int MODE, uint32_t LG>
-__global__ __launch_bounds__(kWG, 4) void k_unpack8(const UnpackPackets<(LG == kFewLearners ? kFewInLaunch8 : packets_of<LG>)> a)
+__global__ __launch_bounds__(kWG, 4) void k_unpack8(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
+                                                   const UnpackPackets<(LG == kFewLearners ? kFewInLaunch8 : packets_of<LG>)> a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
-    if (blockIdx.x < a.n_groups) {
+    if (blockIdx.x < n_groups) {
         if constexpr (LG == kFewLearners) {
-            const UGroupDev grp = table_record<vuint2>(a.groups + a.first16 + blockIdx.x);
-            const UTileDev ut0 = utile_record(a.tiles + grp.first_tile);
-            unpack_group_few<MODE, false, MODE == 0, kFewInLaunch8>(a, grp, ut0, reinterpret_cast<float *>(s_dyn));
+            const GroupAndTile first = first_records(tiles, groups, 0u, a.first16 + blockIdx.x);
+            unpack_group_few<MODE, false, MODE == 0, kFewInLaunch8>(a, first.grp, first.tile, reinterpret_cast<float *>(s_dyn));
         } else {
             UnpackLds<LG> &lds = *reinterpret_cast<UnpackLds<LG> *>(s_dyn);
-            unpack_group<MODE, 0, LG, false>(a, a.first16 + blockIdx.x, lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+            unpack_group<MODE, 0, LG, false>(a, first_records(tiles, groups, 0u, a.first16 + blockIdx.x), lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
         }
         return;
     }
-    uint32_t r = blockIdx.x - a.n_groups;
+    uint32_t r = blockIdx.x - n_groups;
     const uint32_t wg_log = a.chunk_lds & 63u, wg_chunks = 1u << wg_log;
     const uint32_t n_runs = (a.n_groups8 + wg_chunks - 1u) >> wg_log;
     if (r < (n_runs & ~63u)) r = (r & ~63u) | ((r & 7u) << 3) | ((r >> 3) & 7u);   // neighbouring chunks share an XCD's L2
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t chunk = (r << wg_log) + wave;
-    if (wave < wg_chunks && chunk < a.n_groups8) unpack8_chunk<MODE>(a, chunk, reinterpret_cast<float *>(s_dyn) + wave * (a.chunk_lds & ~63u));
+    if (wave < wg_chunks && chunk < a.n_groups8) unpack8_chunk<MODE>(a, first_records(tiles, groups, 0u, chunk).tile, reinterpret_cast<float *>(s_dyn) + wave * (a.chunk_lds & ~63u));
 }
 
 // ==============================================================================================
@@ -2906,9 +2937,18 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
         const dim3 grid(a.class_count + 1u, a.fused_count);   // a learner's tiles and the workgroup that writes the header
         auto method = [&](auto waves, auto slots, auto form) {
             constexpr int W = decltype(waves)::value, J = decltype(slots)::value, F = decltype(form)::value;
-            if (lazy) hipLaunchKernelGGL((k_pack<false, F, W, J, true>), grid, dim3(W * 64), 0, s, a);
-            else if (variant) hipLaunchKernelGGL((k_pack<true, F, W, J, false>), grid, dim3(W * 64), 0, s, a);
-            else hipLaunchKernelGGL((k_pack<false, F, W, J, false>), grid, dim3(W * 64), 0, s, a);
+            auto go = [&](auto variant_, auto lazy_) {
+                constexpr bool V = decltype(variant_)::value, L = decltype(lazy_)::value;
+                if constexpr (F == kOneTable)
+                    hipLaunchKernelGGL(static_cast<void (*)(const TileDev *, uint8_t *, uint32_t, uint32_t, uint32_t, uint32_t, CompressArgs)>(k_pack<V, F, W, J, L>),
+                                       grid, dim3(W * 64), 0, s, a.tiles, a.sync, uint32_t(a.sync_stride), a.o_sync_epoch, a.class_count, a.fused_first, a);
+                else hipLaunchKernelGGL(static_cast<void (*)(CompressArgs)>(k_pack<V, F, W, J, L>), grid, dim3(W * 64), 0, s, a);
+            };
+            const std::integral_constant<bool, true> yes;
+            const std::integral_constant<bool, false> no;
+            if (lazy) go(no, yes);
+            else if (variant) go(yes, no);
+            else go(no, no);
         };
         const std::integral_constant<int, 4> four;
         const std::integral_constant<int, kOneTable> all_records;
@@ -2972,7 +3012,7 @@ int launch_place(const CompressArgs &a, void *stream)
 template <class K>
 struct KernelArgs;
 template <class A>
-struct KernelArgs<void (*)(A)> {
+struct KernelArgs<void (*)(const UTileDev *, const UGroupDev *, uint32_t, A)> {
     using type = typename std::remove_const<A>::type;
 };
 // resident: workgroups per compute unit that the launch is held to (5 or 4), or 0.  early: unpack_early_for.
@@ -2987,7 +3027,7 @@ int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, bool early, 
         typename KernelArgs<decltype(kernel)>::type args;
         static_cast<UnpackHead &>(args) = a;
         std::copy_n(a.packets, sizeof(args.packets) / sizeof(args.packets[0]), args.packets);
-        hipLaunchKernelGGL(kernel, workgroups, wg, lds, s, args);
+        hipLaunchKernelGGL(kernel, workgroups, wg, lds, s, a.tiles, a.groups, a.n_groups, args);
     };
     auto with_mode = [&](auto &&go) {
         if (a.mode == 1) go(std::integral_constant<int, 1>());

@@ -348,7 +348,7 @@ struct CompressArgs {
 // before it (968, and 1184, do not): the kernels do without the hidden ones.
 static_assert(sizeof(CompressArgs) <= 1024, "kernel arguments");
 
-struct UnpackHead {
+struct alignas(64) UnpackHead {
     const UTileDev *tiles;
     const UGroupDev *groups;           // null: a tile each, single_tile
     const LayerDev *layers;
