@@ -1097,9 +1097,14 @@ struct PackFirst {
     uint8_t *sync;
     uint32_t sync_stride, o_epoch, n_tiles, first;
 };
-template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
-__device__ __forceinline__ void pack_tile(const PackFirst &ahead, const CompressArgs &a)
+// Ahead: the types of PackFirst's members in their order (kOneTable), or none.  (As a function that two kernels call, kOneLayers
+// reads back 14 more spilled scalar registers.)
+template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY, class... Ahead>
+__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80)))
+void k_pack(const Ahead... first_args, const CompressArgs a)
 {
+    static_assert((ONE == kOneTable) == (sizeof...(Ahead) != 0), "arguments ahead of the structure");
+    const PackFirst ahead{first_args...};
     constexpr uint32_t WG = uint32_t(WAVES) * 64u, kRow = WG * 4u;   // J 16-byte slots to a thread: slot j of thread t is number j * WG + t of the tile
     constexpr int P = (J + 1) / 2;   // pairs of rows
     static_assert(WG * uint32_t(J) <= 4096u && J <= 4, "tiles of at most 16384 elements, words counted in 15 bits");
@@ -1554,23 +1559,6 @@ __device__ __forceinline__ void pack_tile(const PackFirst &ahead, const Compress
     // chunks[c] = words of the layer in bins < 64 c, for the chunk starts inside this tile
     for (uint32_t t = t0 + 64u * tid; t < nb; t += 64u * WG)
         reinterpret_cast<uint32_t *>(packet + ld.chunks_offset)[(td.first_bin + t) >> 6] = base + s_chunk[t >> 6];
-}
-
-// kOneTable, kOneLayers
-template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
-__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80)))
-void k_pack(const TileDev *const tiles, uint8_t *const sync, const uint32_t sync_stride, const uint32_t o_epoch, const uint32_t n_tiles,
-            const uint32_t first, const CompressArgs a)
-{
-    static_assert(ONE == kOneTable, "arguments ahead of the structure");
-    pack_tile<VARIANT, ONE, WAVES, J, LAZY>(PackFirst{tiles, sync, sync_stride, o_epoch, n_tiles, first}, a);
-}
-template <bool VARIANT, int ONE, int WAVES, int J, bool LAZY>
-__global__ __launch_bounds__(WAVES * 64, ONE == kOneTable && WAVES == 8 ? 4 : LAZY && WAVES == 4 && ONE == kOneTable ? 6 : 8) __attribute__((amdgpu_num_sgpr(80)))
-void k_pack(const CompressArgs a)
-{
-    static_assert(ONE == kOneLayers, "the structure alone");
-    pack_tile<VARIANT, ONE, WAVES, J, LAZY>(PackFirst{}, a);
 }
 
 // ==============================================================================================
@@ -2940,9 +2928,9 @@ int launch_fused(const CompressArgs &a, int jcode, void *stream)
             auto go = [&](auto variant_, auto lazy_) {
                 constexpr bool V = decltype(variant_)::value, L = decltype(lazy_)::value;
                 if constexpr (F == kOneTable)
-                    hipLaunchKernelGGL(static_cast<void (*)(const TileDev *, uint8_t *, uint32_t, uint32_t, uint32_t, uint32_t, CompressArgs)>(k_pack<V, F, W, J, L>),
+                    hipLaunchKernelGGL((k_pack<V, F, W, J, L, const TileDev *, uint8_t *, uint32_t, uint32_t, uint32_t, uint32_t>),
                                        grid, dim3(W * 64), 0, s, a.tiles, a.sync, uint32_t(a.sync_stride), a.o_sync_epoch, a.class_count, a.fused_first, a);
-                else hipLaunchKernelGGL(static_cast<void (*)(CompressArgs)>(k_pack<V, F, W, J, L>), grid, dim3(W * 64), 0, s, a);
+                else hipLaunchKernelGGL((k_pack<V, F, W, J, L>), grid, dim3(W * 64), 0, s, a);
             };
             const std::integral_constant<bool, true> yes;
             const std::integral_constant<bool, false> no;
