@@ -73,9 +73,14 @@ __device__ __forceinline__ vfloat4 buffer_load_slot(__amdgpu_buffer_rsrc_t rsrc,
 {
     return __builtin_bit_cast(vfloat4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(lane_at), int(row_at), kAuxStream));
 }
+// A store of 16 bytes reads its registers after it has been issued.  The compiler keeps what overwrites them two wait states away, but not
+// from a store that has its offset in a scalar register, as these have: built with such an overwrite right behind the store, lanes
+// 12 .. 15 of each 16 stored the new value in place of the first of their four now and then, on a busy GPU.  The s_nop is those wait
+// states, and names the registers, so that nothing can write them before it.
 __device__ __forceinline__ void buffer_store_slot(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_at, uint32_t row_at, vfloat4 v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vuint4, v), rsrc, int(lane_at), int(row_at), kAuxStream);
+    asm volatile("s_nop 1" :: "v"(v));
 }
 // one element through the same descriptor (the first and last slot of a tile that is not 16-byte aligned)
 __device__ __forceinline__ float buffer_load1(__amdgpu_buffer_rsrc_t rsrc, uint32_t elem)
