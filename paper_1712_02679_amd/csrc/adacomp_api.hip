@@ -463,16 +463,28 @@ static bool unpack_hold_early(uint64_t n_elems, uint64_t n_tiles, uint32_t n_lea
     return n_learners <= 4u && n_elems >= kResidentElems && n_elems >= 2900u * n_tiles;
 }
 
-// Plain sums of one or two packets over layers with 8-bit words that k_unpack_few takes: how many workgroups per compute unit they
-// are held to.  Full tiles and next to no words to add: the launch is a stream of stores, which HBM takes at a higher rate with fewer
-// in flight.  8 workgroups / 5 / 4, in us: L_T 64, 1 packet, 25 M 22.7 / 21.2 / 19.9, 40 M 34.8 / 33.9 / 29.3, 60 M 52.0 / 50.9 / 41.4; with 30 % of
-// the elements at L_T 200 22.2 / 21.5 / 21.5, 35.9 / 34.4 / 31.6, 53.6 / 53.0 / 45.6; L_T 54 and 4000 21.4 / 21.4 / 22.9, 34.5 / 31.5 / 33.9, 53.2 / 45.5 /
-// 49.2; 13 M, 64, 11.3 / 11.7 / 12.9.  2 packets: 64, 25 M 22.5 / 21.1 / 23.8, 40 M 35.7 / 31.2 / 35.6, 60 M 52.5 / 44.3 / 51.1; 64 and 200
-// 21.6 / 21.8 / 23.5, 35.1 / 33.5 / 35.9, 51.7 / 50.0 / 52.3; 54 and 4000, 40 M 32.7 / 35.8 / 39.4.  4 packets 54.1 / 64.2 / 74.5.
-static uint32_t unpack_hold_sum8(uint64_t elems8, uint64_t tiles8, uint64_t n_elems, uint32_t n_learners)
+// Plain sums of one or two packets over layers with 8-bit words that k_unpack_few takes, in a launch of their own or together with the
+// 16-bit layers: how many workgroups per compute unit they are held to.  Full tiles and next to no words to add: the launch is a stream of
+// stores, which HBM takes at a higher rate with fewer in flight.  As many as fit / 5 / 4, in us (or as 1):
+//   8-bit words alone, 1 packet, L_T 64, 25 M elements 22.7 / 21.2 / 19.9, 40 M 34.8 / 33.9 / 29.3, 60 M 52.0 / 50.9 / 41.4, 13 M 11.3 / 11.7 / 12.9; 63, 60 M
+//     48.8 / 44.9 / 42.7; 60 49.7 / 44.0 / 42.3; 55 48.2 / 44.4 / 45.2.  2 packets: 64, 25 M 22.5 / 21.1 / 23.8, 40 M 35.7 / 31.2 / 35.6, 60 M 52.5 / 44.3 / 51.1; 60, 60 M 44.5 / 46.4 / 53.1, 55 44.4 / 50.4 / 58.5.
+//     4 packets 54.1 / 64.2 / 74.5.
+//   Tiles of fewer elements have bins of fewer, and more words to add, which other workgroups cover: 95 % at L_T 20 and 5 % at 64, 1 packet, 25 M
+//     1 / 1.16 / 1.35, 60 M 1 / 1.32 / 1.56; half and half (1950 to a tile), 60 M 1 / 1.11 / 1.18; 33 and 64 (2830) 1 / 1.06 / 1.12; 45 % at 20, 5 % at 64 and the
+//     rest at 500 1 / 1.05 / 1.14.
+//   With 16-bit layers, 5 % at L_T 64, 60 M, 1 packet: the rest at 65 51.9 / 49.4 / 57.5, 72 1 / 0.85 / 0.98, 84 1 / 0.89 / 0.88, 129 59.3 / 55.7 / 48.9, 500 59.4 /
+//     56.9 / 55.1; half of them at 65 52.2 / 47.7 / 50.5, 80 51.3 / 48.9 / 45.8, a quarter at 65 51.7 / 47.4 / 46.4.  2 packets: 65 46.6 / 59.7, 72 1 / 1.08, 76 1 / 0.99, 84 1 / 0.85,
+//     129 59.2 / 54.7; half of them at 65 45.1 / 51.5, 84 1 / 0.93, 129 50.4 / 52.3; 25 M, 72 1 / 0.91, 84 1 / 0.88, 500 27.4 / 26.6, a quarter of the
+//     elements at 64 26.8 / 25.7, half of them 23.9 / 24.6.
+uint32_t unpack_hold_sum8(uint64_t elems8, uint64_t tiles8, uint64_t elems16, uint64_t bins16, uint32_t n_learners)
 {
-    if (n_learners == 1u && n_elems >= kResidentElemsSum) return elems8 >= 3700u * tiles8 ? 4u : 5u;
-    return n_learners == 2u && n_elems >= kResidentElemsSumMany && elems8 >= 3900u * tiles8 ? 5u : 0u;
+    const uint64_t n = elems8 + elems16;
+    if (n_learners == 0u || n_learners > 2u || n < (n_learners == 1u || 4u * elems8 <= n ? kResidentElemsSum : kResidentElemsSumMany)) return 0u;
+    if (8u * elems8 > n && elems8 < 3200u * tiles8) return 0u;
+    // bins not far beyond 64 elements in more than a third of the table, or an eighth
+    const bool short16 = n_learners == 1u ? 3u * elems16 > n && elems16 < 78u * bins16 : 8u * elems16 > n && elems16 < 71u * bins16;
+    if (n_learners == 2u) return !short16 && (elems8 >= 3900u * tiles8 || 4u * elems8 <= n) ? 5u : 0u;
+    return !short16 && elems8 >= 3700u * tiles8 ? 4u : 5u;
 }
 
 // Layers with 8-bit words in k_unpack8 (a wave per chunk of 64 bins), or in k_unpack and k_unpack_few (a workgroup)?
@@ -1007,7 +1019,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         if (early16 && resident16 != 0u) resident16 = 4u;
         uint32_t resident8 = early8 && unpack_hold_early(elems8, p.n_usingles8, now) ? 4u : 0u;
         uint32_t resident_both = early_both && unpack_hold_early(p.n_elems_total, p.n_utiles, now) && p.n_elems16 >= 60u * uint64_t(now) * p.n_bins16 ? 4u : 0u;
-        if (a.mode == 0u) resident8 = resident_both = unpack_hold_sum8(elems8, p.n_usingles8, p.n_elems_total, now);
+        if (a.mode == 0u) resident8 = resident_both = unpack_hold_sum8(elems8, p.n_usingles8, p.n_elems16, p.n_bins16, now);   // (up to two packets: one launch)
         // Launches over all groups take single tiles without a look at the table, a round of scalar loads; over both word widths only
         // while every tile has a compute unit to itself, since those of short bins, which take longest, stand first in it (2 M elements,
         // 50 and 500, 16 packets: by the table 13.8 us, without 14.4; 0.4 M 13.0 / 12.6).

@@ -381,6 +381,7 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
 bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units);
 uint32_t place_lanes_for(const Plan &p);
 uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint32_t n_learners, uint32_t mode);
+uint32_t unpack_hold_sum8(uint64_t elems8, uint64_t tiles8, uint64_t elems16, uint64_t bins16, uint32_t n_learners);
 bool unpack_early_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, bool words8, uint32_t n_learners, uint32_t mode);
 uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);
 int launch_fused(const CompressArgs &a, int jcode, void *stream);

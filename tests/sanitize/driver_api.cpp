@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdint>
 #include <cstdlib>
+#include <utility>
 #include <vector>
 
 #include <hip/hip_runtime.h>
@@ -433,6 +434,24 @@ int main()
         if (held(40 * M, 700, 4, 1) != 5 || held(40 * M, 700, 5, 1) != 0 || held(40 * M, 3000, 8, 1) != 5 || held(11 * M, 500, 1, 1) != 0 || held(12 * M, 500, 1, 1) != 5) return 73;
         if (held(24 * M, 500, 4, 0) != 5 || held(24 * M, 500, 5, 0) != 0 || held(40 * M, 500, 8, 0) != 5 || held(40 * M, 500, 9, 0) != 0 || held(23 * M, 500, 4, 0) != 0) return 74;
         if (held(40 * M, 100, 2, 0) != 5 || held(40 * M, 100, 3, 0) != 0 || held(40 * M, 65, 1, 0) != 0 || held(40 * M, 200, 4, 0) != 5 || held(40 * M, 9000, 5, 0) != 0 || held(40 * M, 300, 4, 0) != 5 || held(40 * M, 150, 4, 0) != 0) return 75;
+    }
+    {   // ... and of sums of one or two packets over 8-bit layers, alone or with 16-bit ones in the launch: fewer only where the tiles of
+        // the former are full, and 4 (with two packets any) only where bins of the latter are not short too
+        using namespace adacomp;
+        auto held = [](uint64_t elems8, uint32_t lt8, uint64_t elems16, uint32_t lt16, uint32_t learners, uint64_t elems8b = 0, uint32_t lt8b = 64) {
+            std::vector<adacomp_layer_t> t;
+            uint64_t off = 0;
+            for (auto l : {std::make_pair(elems8, lt8), std::make_pair(elems16, lt16), std::make_pair(elems8b, lt8b)})
+                if (l.first != 0) { t.push_back(adacomp_layer_t{off, l.first, l.second, 0}); off += (l.first + 3) / 4 * 4; }
+            Plan p;
+            if (build_plan(t.data(), uint32_t(t.size()), true, p) != ADACOMP_OK) return 99u;
+            return unpack_hold_sum8(p.n_elems_total - p.n_elems16, p.n_usingles8, p.n_elems16, p.n_bins16, learners);
+        };
+        const uint64_t M = 1000000;
+        if (held(25 * M, 64, 0, 0, 1) != 4 || held(25 * M, 54, 0, 0, 1) != 5 || held(23 * M, 64, 0, 0, 1) != 0 || held(33 * M, 64, 0, 0, 2) != 5 || held(25 * M, 64, 0, 0, 2) != 0 || held(2 * M, 64, 22 * M, 500, 2) != 5 || held(2 * M, 64, 21 * M, 500, 2) != 0 || held(8 * M, 64, 17 * M, 500, 2) != 0 || held(60 * M, 60, 0, 0, 2) != 0 || held(8 * M, 33, 32 * M, 500, 2) != 0 || held(60 * M, 64, 0, 0, 3) != 0 || held(60 * M, 64, 0, 0, 0) != 0) return 76;
+        if (held(30 * M, 20, 0, 0, 1, 30 * M) != 0 || held(57 * M, 20, 0, 0, 1, 3 * M) != 0 || held(20 * M, 33, 0, 0, 1, 20 * M) != 0 || held(27 * M, 20, 30 * M, 500, 1, 3 * M) != 0 || held(6 * M, 20, 53 * M, 2000, 1, M) != 5) return 77;
+        if (held(2 * M, 64, 38 * M, 65, 1) != 5 || held(2 * M, 64, 38 * M, 77, 1) != 5 || held(2 * M, 64, 38 * M, 79, 1) != 4 || held(30 * M, 64, 10 * M, 65, 1) != 4 || held(2 * M, 64, 38 * M, 129, 1) != 4 || held(20 * M, 64, 20 * M, 65, 1) != 5 || held(38 * M, 64, 2 * M, 65, 1) != 4) return 78;
+        if (held(2 * M, 64, 38 * M, 65, 2) != 0 || held(20 * M, 64, 20 * M, 70, 2) != 0 || held(2 * M, 64, 38 * M, 76, 2) != 5 || held(2 * M, 64, 38 * M, 500, 2) != 5 || held(38 * M, 64, 2 * M, 65, 2) != 5) return 79;
     }
     if (adacomp_selftest_binindex() != 0) return 9;
     for (int c = 1; c > -9; --c) if (!adacomp_strerror(c)) return 10;
