@@ -980,7 +980,6 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
     char *ws = static_cast<char *>(workspace);
     UnpackArgs a;
     a.tiles = reinterpret_cast<const UTileDev *>(ws + p.ws.utiles);
-    a.layers = reinterpret_cast<const LayerDev *>(ws + p.ws.layers);
     a.dense = dense_out;
     a.n_layers = p.n_layers;
     a.weights = weights; a.state1 = state1; a.state2 = state2;

@@ -2455,7 +2455,7 @@ __device__ __forceinline__ GroupAndTile first_records(const UTileDev *const tile
 // SIMD, what the LDS tile allows).
 // EARLY: weights and moments are asked for ahead of the adds and kept through them, in up to 128 registers.
 template <int MODE, bool W8, uint32_t LG, bool EARLY, class Args>
-__device__ __forceinline__ void unpack_tiles(const Args &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc,
+__device__ __forceinline__ void unpack_tiles(const Args &a, const UTileDev *const tiles, const UGroupDev grp, const UTileDev ut0, float *const s_acc,
                                              uint32_t (*const s_off)[kOffStride<LG>], uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
     // A workgroup serves a group of consecutive tiles that lie in one 64-bin chunk (or are slices
@@ -2466,7 +2466,7 @@ __device__ __forceinline__ void unpack_tiles(const Args &a, const UGroupDev grp,
     const bool tables_once = a.n_learners <= LG;
 
   for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
-    const UTileDev ut = ti == 0u ? ut0 : utile_record(a.tiles + grp.first_tile + ti);
+    const UTileDev ut = ti == 0u ? ut0 : utile_record(tiles + grp.first_tile + ti);
     const uint32_t n = ut.n_elems;
     const bool vec = ut.aligned();
     float *__restrict__ out = a.dense + ut.elem_base;
@@ -2498,13 +2498,13 @@ __device__ __forceinline__ void unpack_tiles(const Args &a, const UGroupDev grp,
 }
 
 template <int MODE, int KIND, uint32_t LG, bool EARLY, class Args>
-__device__ __forceinline__ void unpack_group(const Args &a, const GroupAndTile &first, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
+__device__ __forceinline__ void unpack_group(const Args &a, const UTileDev *const tiles, const GroupAndTile &first, float *const s_acc, uint32_t (*const s_off)[kOffStride<LG>],
                                              uint16_t (*const s_cnt)[kCntStride], float *const s_scale, uint32_t &s_cmax)
 {
     const UGroupDev grp = first.grp;
     const UTileDev ut0 = first.tile;
-    if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_tiles<MODE, true, LG, EARLY>(a, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
-    else unpack_tiles<MODE, false, LG, EARLY>(a, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
+    if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_tiles<MODE, true, LG, EARLY>(a, tiles, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
+    else unpack_tiles<MODE, false, LG, EARLY>(a, tiles, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
 }
 
 template <int MODE, int KIND, uint32_t LG, bool EARLY>
@@ -2516,7 +2516,7 @@ __global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) v
     __shared__ __attribute__((aligned(16))) uint16_t s_cnt[64][kCntStride];
     __shared__ __attribute__((aligned(16))) float s_scale[LG];
     __shared__ uint32_t s_cmax;                                                // largest word count of a (bin, learner) in the tables
-    unpack_group<MODE, KIND, LG, EARLY>(a, first_records(tiles, groups, n_groups, blockIdx.x), s_acc, s_off, s_cnt, s_scale, s_cmax);
+    unpack_group<MODE, KIND, LG, EARLY>(a, tiles, first_records(tiles, groups, n_groups, blockIdx.x), s_acc, s_off, s_cnt, s_scale, s_cmax);
 }
 
 // ==============================================================================================
@@ -2534,7 +2534,7 @@ constexpr uint32_t kFewLearners = 4;
 // 20.9, but 4 25.2 / 26.7).
 constexpr uint32_t kFewInLaunch8 = 2;
 template <int MODE, bool W8, bool MANY, uint32_t NK, class Args>
-__device__ __forceinline__ void unpack_group_few(const Args &a, const UGroupDev grp, const UTileDev ut0, float *const s_acc)
+__device__ __forceinline__ void unpack_group_few(const Args &a, const UTileDev *const tiles, const UGroupDev grp, const UTileDev ut0, float *const s_acc)
 {
     typedef typename std::conditional<W8, uint8_t, uint16_t>::type word_t;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -2565,7 +2565,7 @@ __device__ __forceinline__ void unpack_group_few(const Args &a, const UGroupDev 
     }
 
     for (uint32_t ti = 0; ti < grp.n_tiles; ++ti) {
-        const UTileDev ut = ti == 0u ? ut0 : utile_record(a.tiles + grp.first_tile + ti);
+        const UTileDev ut = ti == 0u ? ut0 : utile_record(tiles + grp.first_tile + ti);
         const uint32_t n = ut.n_elems, T = ut.L_T, nb = ut.n_bins, bin0 = ut.first_bin & 63u;
         if (ti != 0u) __syncthreads();   // the previous tile has been written out
         TileState<MODE> state;
@@ -2692,8 +2692,8 @@ __global__ __launch_bounds__(kWG, MODE != 0 && MANY ? 4 : 6) void k_unpack_few(c
     const GroupAndTile first = first_records(tiles, groups, n_groups, blockIdx.x);
     const UGroupDev grp = first.grp;
     const UTileDev ut0 = first.tile;
-    if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_group_few<MODE, true, MANY, NK>(a, grp, ut0, s_acc);
-    else unpack_group_few<MODE, false, MANY, NK>(a, grp, ut0, s_acc);
+    if (KIND == 1 || (KIND == 2 && ut0.words8())) unpack_group_few<MODE, true, MANY, NK>(a, tiles, grp, ut0, s_acc);
+    else unpack_group_few<MODE, false, MANY, NK>(a, tiles, grp, ut0, s_acc);
 }
 
 // ==============================================================================================
@@ -2849,10 +2849,10 @@ __global__ __launch_bounds__(kWG, 4) void k_unpack8(const UTileDev *const tiles,
     if (blockIdx.x < n_groups) {
         if constexpr (LG == kFewLearners) {
             const GroupAndTile first = first_records(tiles, groups, 0u, a.first16 + blockIdx.x);
-            unpack_group_few<MODE, false, MODE == 0, kFewInLaunch8>(a, first.grp, first.tile, reinterpret_cast<float *>(s_dyn));
+            unpack_group_few<MODE, false, MODE == 0, kFewInLaunch8>(a, tiles, first.grp, first.tile, reinterpret_cast<float *>(s_dyn));
         } else {
             UnpackLds<LG> &lds = *reinterpret_cast<UnpackLds<LG> *>(s_dyn);
-            unpack_group<MODE, 0, LG, false>(a, first_records(tiles, groups, 0u, a.first16 + blockIdx.x), lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
+            unpack_group<MODE, 0, LG, false>(a, tiles, first_records(tiles, groups, 0u, a.first16 + blockIdx.x), lds.acc, lds.off, lds.cnt, lds.scale, lds.cmax);
         }
         return;
     }

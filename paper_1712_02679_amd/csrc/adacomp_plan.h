@@ -348,34 +348,40 @@ struct CompressArgs {
 // before it (968, and 1184, do not): the kernels do without the hidden ones.
 static_assert(sizeof(CompressArgs) <= 1024, "kernel arguments");
 
-struct alignas(64) UnpackHead {
-    const UTileDev *tiles;
-    const UGroupDev *groups;           // null: a tile each, single_tile
-    const LayerDev *layers;
+// What an unpack kernel has behind its three scalar arguments (the tiles' records, the table of groups, null: a tile each, single_tile,
+// and the number of groups, kind 3: of the layers with 16-bit words), which take 24 bytes.
+struct UnpackHead {
     float *dense;
-    uint32_t n_groups;                 // workgroups that take a group each (kind 3: of the layers with 16-bit words)
-    uint32_t n_groups8;                // kind 3: groups of the layers with 8-bit words, a chunk each, the first of `groups`
+    uint32_t n_groups8;                // kind 3: groups of the layers with 8-bit words, a chunk each, the first of the table
     uint32_t n_layers, n_learners, accumulate;
     uint32_t write_dense;              // 0: the sum is only consumed by the update
     uint32_t mode;                     // 0: sum only; 1: SGD with momentum; 2: Adam (applied by this launch)
-    uint32_t first16;                  // kind 3: where in `groups` those of the layers with 16-bit words begin
     float *weights, *state1, *state2;  // momentum buffer, or Adam's m and v
     float n_average;                   // learner count the sum is divided by
     float lr, p1, p2, one_minus_p1, one_minus_p2, eps, bias1, bias2;
     uint32_t chunk_lds;                // kind 3: floats of LDS per chunk, 64 times the longest of the 8-bit layers' bins, + log2 of the chunks per workgroup
+    uint32_t first16;                  // kind 3: where in the table the groups of the layers with 16-bit words begin
 };
 // With N packets: a kernel takes no more of them than it can have.  Small sums are bound by what a launch costs the host, which
-// goes by its arguments too: 0.4 M elements, 1 packet, 144 bytes of them instead of 640 4.25 us a call on a box where what was before
-// took 4.75; 4.0 where it took 4.2 with 640.
+// goes by its arguments too: 144 bytes of them for 1 and 2 packets, 640 for 64.  256 and 704, with this structure aligned to 64 bytes and
+// the scalar arguments in it a second time / as it is, in us: 0.4 M elements, L_T 50, and 0.6 M, 500, 2 packets 4.64 / 4.46, 4 5.88 /
+// 5.68; 4 M and 4 M, 1 packet 7.70 / 7.50, SGD with 2 23.65 / 22.52.  k_unpack8 for two packets had 66 vector registers instead of 32.
 template <uint32_t N>
 struct UnpackPackets : UnpackHead {
     const uint8_t *packets[N];
 };
-using UnpackArgs = UnpackPackets<kMaxPacketArgs>;
+// What the host fills.
+struct UnpackArgs : UnpackPackets<kMaxPacketArgs> {
+    const UTileDev *tiles;
+    const UGroupDev *groups;
+    uint32_t n_groups;                 // workgroups that take a group each
+};
 // Workgroups start with the scalar loads of these arguments, and the first of a launch wait for every line
 // of them.  With 16 bytes more before `packets`, whose lines then no longer began with it, k_unpack took
 // 1.5 to 2 % longer (4 M elements, 4 packets 8.85 -> 9.04 us; 20 M, 8 packets 31.5 -> 32.1).
-static_assert(sizeof(UnpackHead) == 128 && sizeof(UnpackArgs) == 640, "kernel arguments");
+static_assert(24 + sizeof(UnpackHead) == 128 && alignof(UnpackHead) == 8, "a line of kernel arguments ends where the packets begin");
+static_assert(sizeof(UnpackPackets<2>) == sizeof(UnpackHead) + 16 && sizeof(UnpackPackets<4>) == sizeof(UnpackHead) + 32 &&
+              sizeof(UnpackPackets<8>) == sizeof(UnpackHead) + 64, "kernel arguments end with the last packet");
 
 uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes, uint32_t compute_units, bool lazy = false);
 bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units);
