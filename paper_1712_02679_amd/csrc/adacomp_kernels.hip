@@ -2507,8 +2507,10 @@ __device__ __forceinline__ void unpack_group(const Args &a, const UTileDev *cons
     else unpack_tiles<MODE, false, LG, EARLY>(a, tiles, grp, ut0, s_acc, s_off, s_cnt, s_scale, s_cmax);
 }
 
+// SGD on 8-bit words with 5 to 8 packets, behind the adds: held to 96 scalar registers, with which a SIMD has room for 7 waves, not 6 (25 M
+// elements, L_T 20, 5 packets 100.5 us, so 92.5, 8 packets 112.9 / 104.4; L_T 33, 8 packets 82.0 / 77.2).
 template <int MODE, int KIND, uint32_t LG, bool EARLY>
-__global__ __launch_bounds__(kWG, (KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
+__global__ __launch_bounds__(kWG, (MODE == 1 && KIND == 1 && LG == 8u && !EARLY ? 7 : KIND == 2 || (MODE != 0 && EARLY) ? 4 : 6)) void k_unpack(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
                                                                                                       const UnpackPackets<packets_of<LG>> a)
 {
     __shared__ float s_acc[kUnpackTileElems];
@@ -2715,7 +2717,11 @@ template <int MODE, class Args>
 __device__ __forceinline__ void unpack8_chunk(const Args &a, const UTileDev &ut, float *acc_chunk)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t layer = ut.layer(), n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
+    const uint32_t layer = ut.layer();
+    // As numbers of 32 bits: from 16 bits the compiler concludes that the loop of the write-out cannot overflow, and takes what does not
+    // fill its unrolled body first, one slot after the other (Adam, 25 M elements, L_T 12, 8 packets 150.7 us, so 143.5).
+    uint32_t n = ut.n_elems, T = ut.L_T, nb = ut.n_bins;
+    asm volatile("" : "+s"(n), "+s"(T), "+s"(nb));
     float *const out = a.dense + ut.elem_base;
     const uint32_t chunk = ut.first_bin >> 6;
 
@@ -2841,8 +2847,13 @@ __device__ __forceinline__ void unpack8_chunk(const Args &a, const UTileDev &ut,
 
 // The first n_groups workgroups take a group of the 16-bit layers each, the others up to four chunks of the
 // 8-bit ones.  Dynamic LDS: launch_unpack.  LG: 4 (k_unpack_few), 8 or 16 learners to a group of the former.
+// With 3 to 8 packets and the optimizer's step it is held to 72 vector registers and 96 scalar ones, with which 7 workgroups are resident: from 97
+// scalar ones on a SIMD has room for 6 waves only, from 73 vector ones too.  In us, 106 scalar registers and, Adam, 81 vector ones /
+// as it is: 25 M elements, L_T 12, SGD, 8 packets 104.9 / 98.5, Adam 150.7 / 130.4; L_T 16 103.3 / 93.0, 142.3 / 128.5; 30 M, L_T 8, and 30 M, 500
+// 213.8 / 202.9, 316.5 / 280.9; 6 M, L_T 8, SGD, 4 25.3 / 22.8; 54 M with 4 M at L_T 16 153.1 / 153.7, 227.7 / 229.2; at the worst 4 M, L_T 16, and
+// 4 M, 500, SGD, 4 26.9 / 28.7, where the last workgroups fall into a round of their own.
 template <int MODE, uint32_t LG>
-__global__ __launch_bounds__(kWG, 4) void k_unpack8(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
+__global__ __launch_bounds__(kWG, MODE != 0 && LG == 8u ? 7 : 4) void k_unpack8(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
                                                    const UnpackPackets<(LG == kFewLearners ? kFewInLaunch8 : packets_of<LG>)> a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
