@@ -441,8 +441,12 @@ uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint3
 // (k_unpack's and k_unpack_few's EARLY), or behind the adds?  Ahead, they are on their way while the adds run, and take 32 or 48 registers
 // through them, which leaves fewer workgroups: 7 instead of 8 with up to 4 packets (Adam 5 / 6), 4 or 5 instead of 6 or 7 with more.  That
 // pays in full tiles with few words, and where there is work for all compute units.  Behind / ahead, in us:
-//   up to 4 packets: 0.4 M elements, L_T 500, SGD, 1 packet 5.9 / 5.9, Adam, 4 8.4 / 8.5; 2 M, 50 and 500, SGD, 4 9.3 / 8.6; 25 M, 500, 1
-//     71.7 / 70.7, 4 73.0 / 70.6, Adam 114.2 / 109.9, 114.0 / 110.8; tiles of 2080 elements (L_T 65), Adam, 4 110.7 / 112.1; of 1280
+//   1 and 2 packets: 0.4 M elements, L_T 500, SGD, 1 packet 5.9 / 5.9; 2 M, 50 6.7 / 5.7, 65 8.5 / 7.4, 500 6.8 / 6.6; 1.6 M, 20 5.5 / 5.7; 4 M, 65
+//     12.3 / 12.7; 8 M, 20 22.4 / 23.7, 50 and 500, 2 packets 23.3 / 22.6; 13 M, 500 35.2 / 36.6.  With SGD the larger ones are ahead behind them, as far as bins are
+//     short: 25 M, 16 68.1 / 72.0, 50 64.4 / 65.6, 100 64.5 / 66.8, 500 65.0 / 67.0; 60 M, 65 152.9 / 162.4, 500 153.9 / 161.5; 125 M, 500 323 / 340; 40 M, 1000
+//     103.9 / 108.5, 1100 117.7 / 112.9, 1365 113.4 / 107.3, 2100 118.7 / 112.3, 4096 103.8 / 103.5, 5000 136.9 / 131.9.  With Adam: 25 M, 14 107.8 / 115.6, 20 100.8 / 102.4,
+//     50 100.5 / 100.2, 65 100.9 / 104.7, 9000 112.2 / 109.4; 8 M, 50 and 500 36.9 / 36.0; 125 M, 500 502 / 496;
+//   3 and 4: 2 M, 50 and 500, SGD, 4 9.3 / 8.6; 25 M, 500, 4 73.0 / 70.6, Adam 114.0 / 110.8; tiles of 2080 elements (L_T 65), Adam, 4 110.7 / 112.1; of 1280
 //     (L_T 20, and 200), SGD, 4 85.1 / 80.2, Adam, 4 122 / 120, 60 M 286 / 287;
 //   8: 25 M, L_T 500 73.8 / 70.6, L_T 50 85.7 / 75.9, 65 76.1 / 80.4, 20 and 200 106 / 128; Adam 116.6 / 113.8, 123 / 114, 113 / 124, 152 / 165;
 //   16: 25 M, 500 78.4 / 72.8, 250 75.7 / 74.3, 170 75.7 / 82.7, 100 83.6 / 95.6, 50 101 / 122; Adam 121 / 117, 118 / 114, 114 / 115, 121 /
@@ -450,15 +454,17 @@ uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint3
 bool unpack_early_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, bool words8, uint32_t n_learners, uint32_t mode)
 {
     if (mode == 0u || n_elems < kEarlyElems) return false;
+    if (n_learners <= 2u && mode == 1u) return n_elems < kResidentElems ? n_elems >= 1700u * n_tiles : n_elems >= 1050u * n_bins;
+    if (n_learners <= 2u) return n_elems >= 2300u * n_tiles;
     if (n_learners <= 4u) return mode == 1u || n_elems >= 2300u * n_tiles;
     if (n_learners <= 8u) return n_elems >= 2900u * n_tiles;
     return n_learners <= 16u && !words8 && n_elems >= 2900u * n_tiles && n_elems >= 200u * n_bins;
 }
 
-// Is a launch with 8-bit words that fetches ahead held to 4 workgroups per compute unit?  Up to 4 packets, whose kernels
-// leave 5 or 6; as many as fit / 4, in us: 25 M elements, L_T 50, SGD, 4 packets 71.8 / 70.3, Adam 111.5 / 109.1; 50 and 500 71.0 / 69.5,
+// Is a launch of up to 4 packets with 8-bit words and the optimizer's step, whose kernels leave 5 or 6 workgroups to a compute unit, held to
+// 4?  As many as fit / 4, in us: 25 M elements, L_T 50, SGD, 4 packets 71.8 / 70.3, Adam 111.5 / 109.1; 50 and 500 71.0 / 69.5,
 // 111.0 / 109.3; 60 M, Adam 260 / 256, 260 / 256; tiles of 2080 elements, 25 M, SGD 70.7 / 78.3.
-static bool unpack_hold_early(uint64_t n_elems, uint64_t n_tiles, uint32_t n_learners)
+static bool unpack_hold_few(uint64_t n_elems, uint64_t n_tiles, uint32_t n_learners)
 {
     return n_learners <= 4u && n_elems >= kResidentElems && n_elems >= 2900u * n_tiles;
 }
@@ -1015,9 +1021,9 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         const bool early16 = unpack_early_for(p.n_elems16, p.n_bins16, tiles16, false, now, a.mode), early8 = unpack_early_for(elems8, bins8, p.n_usingles8, true, now, a.mode);
         const bool early_both = unpack_early_for(p.n_elems_total, p.n_bins_total, p.n_utiles, true, now, a.mode);
         uint32_t resident16 = resident_for(p.n_elems16, p.n_bins16, tiles16, now, a.mode);
-        if (early16 && resident16 != 0u) resident16 = 4u;
-        uint32_t resident8 = early8 && unpack_hold_early(elems8, p.n_usingles8, now) ? 4u : 0u;
-        uint32_t resident_both = early_both && unpack_hold_early(p.n_elems_total, p.n_utiles, now) && p.n_elems16 >= 60u * uint64_t(now) * p.n_bins16 ? 4u : 0u;
+        if (resident16 != 0u && a.mode != 0u && (early16 || now <= 2u)) resident16 = 4u;
+        uint32_t resident8 = unpack_hold_few(elems8, p.n_usingles8, now) ? 4u : 0u;
+        uint32_t resident_both = unpack_hold_few(p.n_elems_total, p.n_utiles, now) && p.n_elems16 >= 60u * uint64_t(now) * p.n_bins16 ? 4u : 0u;
         if (a.mode == 0u) resident8 = resident_both = unpack_hold_sum8(elems8, p.n_usingles8, p.n_elems16, p.n_bins16, now);   // (up to two packets: one launch)
         // Launches over all groups take single tiles without a look at the table, a round of scalar loads; over both word widths only
         // while every tile has a compute unit to itself, since those of short bins, which take longest, stand first in it (2 M elements,

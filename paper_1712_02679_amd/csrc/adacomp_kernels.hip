@@ -2369,6 +2369,12 @@ struct TileState {
     static constexpr uint32_t kSlots = kUnpackTileElems / (4u * kWG);
     vfloat4 w[kSlots], s1[kSlots], s2[MODE == 2 ? kSlots : 1u];
 
+    // SKIP: not the slots past the tile, whose loads the hardware drops after they have cost their issue.  Behind the adds of up to two
+    // packets, where it pays in tiles of few elements and costs nothing in others; elsewhere the branches spill registers.  All slots /
+    // without those past the tile, in us, 25 M elements: L_T 14, Adam, 1 packet 125 / 107.8, 2 133.2 / 112.5; L_T 20, 1 104.8 / 100.8, 2 110.9 /
+    // 103.9; 12 M, L_T 20, and 13 M, 65, 2 106.2 / 103.7, with the 16-bit tiles' too 104.4; but 3 packets, L_T 18 123.0 / 129.3, k_unpack, SGD, L_T 33, 8
+    // packets 82.0 / 98.1.
+    template <bool SKIP>
     __device__ __forceinline__ void fetch(const UnpackHead &a, const UTileDev &ut)
     {
         const uint32_t whole = ut.n_elems & ~3u;
@@ -2376,6 +2382,7 @@ struct TileState {
         const __amdgpu_buffer_rsrc_t b2 = tile_buffer(MODE == 2 ? a.state2 + ut.elem_base : a.weights, MODE == 2 ? whole : 0u);
 #pragma unroll
         for (uint32_t j = 0; j < kSlots; ++j) {
+            if (SKIP && j * kWG * 4u >= whole) break;
             w[j] = buffer_load_slot(wb, threadIdx.x * 16u, j * kWG * 16u);
             s1[j] = buffer_load_slot(b1, threadIdx.x * 16u, j * kWG * 16u);
             if (MODE == 2) s2[j] = buffer_load_slot(b2, threadIdx.x * 16u, j * kWG * 16u);
@@ -2417,6 +2424,7 @@ struct TileState {
 };
 template <>
 struct TileState<0> {
+    template <bool SKIP>
     __device__ __forceinline__ void fetch(const UnpackHead &, const UTileDev &) {}
     __device__ __forceinline__ void step(const UnpackHead &a, const UTileDev &ut, float *const s_acc) { unpack_write_out(a, ut, s_acc); }
 };
@@ -2486,10 +2494,10 @@ __device__ __forceinline__ void unpack_tiles(const Args &a, const UTileDev *cons
     uint32_t k0 = 0;
     if constexpr (EARLY) {
         for (; k0 + LG < a.n_learners; k0 += LG) round(k0, NoHook());
-        round(k0, [&] { state.fetch(a, ut); });
+        round(k0, [&] { state.template fetch<false>(a, ut); });
     } else {
         for (; k0 < a.n_learners; k0 += LG) round(k0, NoHook());
-        state.fetch(a, ut);
+        state.template fetch<false>(a, ut);
     }
     __syncthreads();
 
@@ -2590,7 +2598,7 @@ __device__ __forceinline__ void unpack_group_few(const Args &a, const UTileDev *
                 if (cc[k] != 0u && 4u * sub < (at[k] & 3u) + cc[k])
                     packed[k] = reinterpret_cast<const uint32_t *>(a.packets[k < a.n_learners ? k : 0u])[(at[k] >> 2) + sub];
             }
-            if (EARLY) state.fetch(a, ut);
+            if (EARLY) state.template fetch<false>(a, ut);
 #pragma unroll
             for (uint32_t k = 0; k < NK; ++k) {
                 if (k >= a.n_learners) break;   // uniform
@@ -2649,7 +2657,7 @@ __device__ __forceinline__ void unpack_group_few(const Args &a, const UTileDev *
                 if (lb < nb && sub < cc[k]) word[k] = reinterpret_cast<const word_t *>(a.packets[k < a.n_learners ? k : 0u])[at];
             }
         };
-        if (EARLY) { fetch(tid); state.fetch(a, ut); }
+        if (EARLY) { fetch(tid); state.template fetch<false>(a, ut); }
         for (uint32_t s = tid; s < slots; s += kWG) {
             if (!EARLY || s != tid) fetch(s);
             const uint32_t lb = s >> glog, sub = s & (gsz - 1u);
@@ -2675,7 +2683,7 @@ __device__ __forceinline__ void unpack_group_few(const Args &a, const UTileDev *
             }
         }
         }
-        if (!EARLY) state.fetch(a, ut);
+        if (!EARLY) state.template fetch<NK == 2u && (W8 || MODE == 1)>(a, ut);
         __syncthreads();
         state.step(a, ut, s_acc);
     }

@@ -453,6 +453,22 @@ int main()
         if (held(2 * M, 64, 38 * M, 65, 1) != 5 || held(2 * M, 64, 38 * M, 77, 1) != 5 || held(2 * M, 64, 38 * M, 79, 1) != 4 || held(30 * M, 64, 10 * M, 65, 1) != 4 || held(2 * M, 64, 38 * M, 129, 1) != 4 || held(20 * M, 64, 20 * M, 65, 1) != 5 || held(38 * M, 64, 2 * M, 65, 1) != 4) return 78;
         if (held(2 * M, 64, 38 * M, 65, 2) != 0 || held(20 * M, 64, 20 * M, 70, 2) != 0 || held(2 * M, 64, 38 * M, 76, 2) != 5 || held(2 * M, 64, 38 * M, 500, 2) != 5 || held(38 * M, 64, 2 * M, 65, 2) != 5) return 79;
     }
+    {   // where weights and moments are fetched ahead of the adds: tables of one layer, both sides of each line
+        using namespace adacomp;
+        auto early = [](uint64_t elems, uint32_t lt, uint32_t learners, uint32_t mode) {
+            std::vector<adacomp_layer_t> t{{0, elems, lt, 0}};
+            Plan p;
+            if (build_plan(t.data(), 1, true, p) != ADACOMP_OK) return false;
+            return unpack_early_for(elems, p.n_bins_total, p.n_utiles, lt <= 64, learners, mode);
+        };
+        const uint64_t M = 1000000;
+        for (uint32_t n = 1; n <= 16; ++n) if (early(M, 500, n, 1) || early(M, 500, n, 2) || early(2 * M, 500, n, 0)) return 80;
+        for (uint32_t n = 1; n <= 2; ++n) {
+            if (!early(2 * M, 500, n, 1) || !early(11 * M, 500, n, 1) || early(12 * M, 500, n, 1) || early(125 * M, 500, n, 1) || early(25 * M, 1023, n, 1) || !early(25 * M, 1365, n, 1) || !early(60 * M, 9000, n, 1)) return 81;
+            if (early(8 * M, 20, n, 1) || !early(8 * M, 33, n, 1) || early(25 * M, 14, n, 1) || early(25 * M, 64, n, 1)) return 82;
+            if (!early(2 * M, 500, n, 2) || !early(125 * M, 500, n, 2) || early(25 * M, 20, n, 2) || !early(25 * M, 50, n, 2) || early(25 * M, 65, n, 2) || !early(25 * M, 100, n, 2)) return 83;
+        }
+    }
     if (adacomp_selftest_binindex() != 0) return 9;
     for (int c = 1; c > -9; --c) if (!adacomp_strerror(c)) return 10;
     std::printf("api sanitizer driver ok, checksum %llu, %llu tiles and %llu groups checked\n", (unsigned long long)checksum,
