@@ -2491,12 +2491,10 @@ __device__ __forceinline__ void unpack_tiles(const Args &a, const UTileDev *cons
         __syncthreads();  // tables filled, accumulators initialised
         unpack_adds<W8, LG>(a, ut, ut.first_bin - row0_bin, k0, s_acc, s_off, s_cnt, s_scale, &s_cmax, words_on_their_way);
     };
-    uint32_t k0 = 0;
-    if constexpr (EARLY) {
-        for (; k0 + LG < a.n_learners; k0 += LG) round(k0, NoHook());
-        round(k0, [&] { state.template fetch<false>(a, ut); });
+    if constexpr (EARLY) {   // the launch has no more packets than the tables
+        round(0u, [&] { state.template fetch<false>(a, ut); });
     } else {
-        for (; k0 < a.n_learners; k0 += LG) round(k0, NoHook());
+        for (uint32_t k0 = 0; k0 < a.n_learners; k0 += LG) round(k0, NoHook());
         state.template fetch<false>(a, ut);
     }
     __syncthreads();
@@ -3044,7 +3042,7 @@ int launch_unpack(const UnpackArgs &a, int kind, uint32_t resident, bool early, 
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (a.n_groups == 0 && kind != 3) return ADACOMP_OK;
-    if (early && (a.mode == 0u || kind == 3 || (a.n_learners > 8u && kind != 0))) return ADACOMP_EINVAL;   // the host asks for it where there is a kernel
+    if (early && (a.mode == 0u || kind == 3 || a.n_learners == 0u || a.n_learners > (kind == 0 ? 16u : 8u))) return ADACOMP_EINVAL;   // the host asks for it where there is a kernel
     const dim3 grid(a.n_groups), wg(kWG);
     uint32_t lds = 0;
     auto launch = [&](const dim3 &workgroups, auto kernel) {

@@ -453,6 +453,13 @@ int main()
         if (held(2 * M, 64, 38 * M, 65, 1) != 5 || held(2 * M, 64, 38 * M, 77, 1) != 5 || held(2 * M, 64, 38 * M, 79, 1) != 4 || held(30 * M, 64, 10 * M, 65, 1) != 4 || held(2 * M, 64, 38 * M, 129, 1) != 4 || held(20 * M, 64, 20 * M, 65, 1) != 5 || held(38 * M, 64, 2 * M, 65, 1) != 4) return 78;
         if (held(2 * M, 64, 38 * M, 65, 2) != 0 || held(20 * M, 64, 20 * M, 70, 2) != 0 || held(2 * M, 64, 38 * M, 76, 2) != 5 || held(2 * M, 64, 38 * M, 500, 2) != 5 || held(38 * M, 64, 2 * M, 65, 2) != 5) return 79;
     }
+    {   // launches that fetch weights and moments ahead of the adds, of which there are none: refused before anything is launched
+        using namespace adacomp;
+        UnpackArgs a{};
+        a.n_groups = 1;
+        auto refused = [&a](uint32_t learners, uint32_t mode, int kind) { a.n_learners = learners; a.mode = mode; return launch_unpack(a, kind, 0u, true, nullptr) == ADACOMP_EINVAL; };
+        if (!refused(17, 1, 0) || !refused(64, 2, 0) || !refused(9, 1, 1) || !refused(9, 2, 2) || !refused(0, 1, 0) || !refused(4, 0, 0) || !refused(4, 1, 3)) return 84;
+    }
     {   // where weights and moments are fetched ahead of the adds: tables of one layer, both sides of each line
         using namespace adacomp;
         auto early = [](uint64_t elems, uint32_t lt, uint32_t learners, uint32_t mode) {
