@@ -447,16 +447,19 @@ uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint3
 //     103.9 / 108.5, 1100 117.7 / 112.9, 1365 113.4 / 107.3, 2100 118.7 / 112.3, 4096 103.8 / 103.5, 5000 136.9 / 131.9.  With Adam: 25 M, 14 107.8 / 115.6, 20 100.8 / 102.4,
 //     50 100.5 / 100.2, 65 100.9 / 104.7, 9000 112.2 / 109.4; 8 M, 50 and 500 36.9 / 36.0; 125 M, 500 502 / 496;
 //   3 and 4: 2 M, 50 and 500, SGD, 4 9.3 / 8.6; 25 M, 500, 4 73.0 / 70.6, Adam 114.0 / 110.8; tiles of 2080 elements (L_T 65), Adam, 4 110.7 / 112.1; of 1280
-//     (L_T 20, and 200), SGD, 4 85.1 / 80.2, Adam, 4 122 / 120, 60 M 286 / 287;
+//     (L_T 20, and 200), SGD, 4 85.1 / 80.2, Adam, 4 122 / 120, 60 M 286 / 287.  8-bit words, Adam: 2 M, 18, 3 14.7 / 13.6; 25 M, 18, 3 123.7 / 116.1, 4 124.4 / 125.9,
+//     28, 3 103.7 / 100.2, 4 106.7 / 102.3; 60 M, 18, 3 289.6 / 276.5, 4 292.1 / 299.4; with 16-bit ones, 3: 20 M, 18, and 5 M, 65 122.6 / 117.0; 12 M, 20, and 13 M,
+//     500 110.7 / 107.0, 65 110.0 / 108.1; 7 M, 20, and 18 M, 65 109.9 / 112.7;
 //   8: 25 M, L_T 500 73.8 / 70.6, L_T 50 85.7 / 75.9, 65 76.1 / 80.4, 20 and 200 106 / 128; Adam 116.6 / 113.8, 123 / 114, 113 / 124, 152 / 165;
 //   16: 25 M, 500 78.4 / 72.8, 250 75.7 / 74.3, 170 75.7 / 82.7, 100 83.6 / 95.6, 50 101 / 122; Adam 121 / 117, 118 / 114, 114 / 115, 121 /
 //     130, 132 / 154; 24 packets, 10 M, 170 45.6 / 52.8.
+// (words8: the launch's words, or of a launch over both widths and up to 8 packets those of a third of its elements, have 8 bits)
 bool unpack_early_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, bool words8, uint32_t n_learners, uint32_t mode)
 {
     if (mode == 0u || n_elems < kEarlyElems) return false;
     if (n_learners <= 2u && mode == 1u) return n_elems < kResidentElems ? n_elems >= 1700u * n_tiles : n_elems >= 1050u * n_bins;
     if (n_learners <= 2u) return n_elems >= 2300u * n_tiles;
-    if (n_learners <= 4u) return mode == 1u || n_elems >= 2300u * n_tiles;
+    if (n_learners <= 4u) return mode == 1u || words8 || n_elems >= 2300u * n_tiles;
     if (n_learners <= 8u) return n_elems >= 2900u * n_tiles;
     return n_learners <= 16u && !words8 && n_elems >= 2900u * n_tiles && n_elems >= 200u * n_bins;
 }
@@ -1019,7 +1022,7 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         // workgroups per compute unit they are held.
         const uint64_t tiles16 = p.n_utiles - p.n_usingles8, elems8 = p.n_elems_total - p.n_elems16, bins8 = p.n_bins_total - p.n_bins16;
         const bool early16 = unpack_early_for(p.n_elems16, p.n_bins16, tiles16, false, now, a.mode), early8 = unpack_early_for(elems8, bins8, p.n_usingles8, true, now, a.mode);
-        const bool early_both = unpack_early_for(p.n_elems_total, p.n_bins_total, p.n_utiles, true, now, a.mode);
+        const bool early_both = now <= 8u && unpack_early_for(p.n_elems_total, p.n_bins_total, p.n_utiles, 3u * elems8 >= p.n_elems_total, now, a.mode);
         uint32_t resident16 = resident_for(p.n_elems16, p.n_bins16, tiles16, now, a.mode);
         if (resident16 != 0u && a.mode != 0u && (early16 || now <= 2u)) resident16 = 4u;
         uint32_t resident8 = unpack_hold_few(elems8, p.n_usingles8, now) ? 4u : 0u;

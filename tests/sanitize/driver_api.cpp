@@ -475,6 +475,9 @@ int main()
             if (early(8 * M, 20, n, 1) || !early(8 * M, 33, n, 1) || early(25 * M, 14, n, 1) || early(25 * M, 64, n, 1)) return 82;
             if (!early(2 * M, 500, n, 2) || !early(125 * M, 500, n, 2) || early(25 * M, 20, n, 2) || !early(25 * M, 50, n, 2) || early(25 * M, 65, n, 2) || !early(25 * M, 100, n, 2)) return 83;
         }
+        for (uint32_t n = 3; n <= 4; ++n) if (!early(2 * M, 18, n, 1) || !early(2 * M, 18, n, 2) || !early(60 * M, 64, n, 2) || early(60 * M, 65, n, 2) || !early(60 * M, 65, n, 1) || !early(60 * M, 100, n, 2)) return 85;
+        for (uint32_t n = 5; n <= 8; ++n) for (uint32_t m = 1; m <= 2; ++m) if (early(25 * M, 33, n, m) || !early(25 * M, 50, n, m) || early(25 * M, 65, n, m) || !early(25 * M, 500, n, m)) return 86;
+        for (uint32_t n : {9u, 16u}) for (uint32_t m = 1; m <= 2; ++m) if (early(25 * M, 64, n, m) || early(25 * M, 150, n, m) || !early(25 * M, 500, n, m) || early(25 * M, 500, 17, m)) return 87;
     }
     if (adacomp_selftest_binindex() != 0) return 9;
     for (int c = 1; c > -9; --c) if (!adacomp_strerror(c)) return 10;
