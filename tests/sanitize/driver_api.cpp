@@ -88,6 +88,9 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
         }
         if (ut.group_log2() < 3 || ut.group_log2() > 6) return 127;
         if (ut.aligned() != (ut.elem_base % 4 == 0)) return 128;
+        // what the record holds of its layer, whose own the unpack kernels do not read
+        if (ut.counts_offset != ld.counts_offset || ut.chunks_offset != ld.chunks_offset || ut.words8() != (ld.word_bytes == 1)) return 151;
+        if (ut.chunk_bins != std::min<uint32_t>(64u, ld.n_bins - (ut.first_bin & ~63u)) || (ut.first_bin & 63u) + ut.n_bins > ut.chunk_bins) return 152;
     }
     for (uint32_t l = 0; l < p.n_layers; ++l)
         if (covered[l] != p.layers[l].n_elems) return 129;
@@ -104,6 +107,10 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
             if (ut.L_T <= kUnpackTileElems ? (ut.first_bin >> 6) != (a.first_bin >> 6) : ut.first_bin != a.first_bin) return 133;
             if (ut.first_bin < a.first_bin || ut.first_bin + ut.n_bins - a.first_bin > 64) return 134;
         }
+        // the end of the group's bins, as k_unpack works it out from the first tile's record
+        const UTileDev &last = p.utiles[g.first_tile + g.n_tiles - 1u];
+        const uint32_t bins = a.L_T > kUnpackTileElems ? 1u : a.n_bins * g.n_tiles;
+        if (std::min(a.first_bin + bins, (a.first_bin & ~63u) + a.chunk_bins) != last.first_bin + last.n_bins) return 153;
     }
     for (uint32_t i = 0; i < p.n_utiles; ++i)
         if (seen[i] != 1) return 135;
@@ -117,6 +124,19 @@ static int check_plan(const std::vector<adacomp_layer_t> &t)
     for (const UGroupDev &g : p.usingles) {
         if (g.n_tiles != 1 || g.first_tile >= p.n_utiles || seen[g.first_tile]++) return 136;
     }
+    // launches without a table of groups: the tile from the workgroup's number, each tile once; of one word width in the table's order
+    std::fill(seen.begin(), seen.end(), 0);
+    const bool mixed = p.n_usingles8 != 0 && p.n_usingles8 != p.n_utiles;
+    for (uint32_t i = 0; i < p.n_utiles; ++i) {
+        const uint32_t t = single_tile(i, p.n_utiles);
+        if (t >= p.n_utiles || seen[t]++ || (!mixed && p.usingles[i].first_tile != t)) return 154;
+    }
+    if (p.groups_single) {
+        if (p.n_ugroups != p.n_utiles) return 155;
+        for (uint32_t i = 0; i < p.n_ugroups; ++i)
+            if (p.ugroups[i].n_tiles != 1 || p.ugroups[i].first_tile != p.usingles[i].first_tile) return 156;
+    }
+    if (p.ws.sync_stride >> 32) return 157;   // k_pack takes it in 32 bits
     // workspace layout: sections in order, inside the advertised size
     const WorkspaceLayout &w = p.ws;
     if (w.cclass + 4 * size_t(p.n_ctiles) > w.utiles) return 144;
@@ -458,7 +478,7 @@ int main()
         UnpackArgs a{};
         a.n_groups = 1;
         auto refused = [&a](uint32_t learners, uint32_t mode, int kind) { a.n_learners = learners; a.mode = mode; return launch_unpack(a, kind, 0u, true, nullptr) == ADACOMP_EINVAL; };
-        if (!refused(17, 1, 0) || !refused(64, 2, 0) || !refused(9, 1, 1) || !refused(9, 2, 2) || !refused(0, 1, 0) || !refused(4, 0, 0) || !refused(4, 1, 3)) return 84;
+        if (!refused(17, 1, 0) || !refused(64, 2, 0) || !refused(9, 1, 1) || !refused(9, 2, 2) || !refused(0, 1, 0) || !refused(4, 0, 0) || !refused(4, 1, 3)) return 164;
     }
     {   // where weights and moments are fetched ahead of the adds: tables of one layer, both sides of each line
         using namespace adacomp;
@@ -469,15 +489,15 @@ int main()
             return unpack_early_for(elems, p.n_bins_total, p.n_utiles, lt <= 64, learners, mode);
         };
         const uint64_t M = 1000000;
-        for (uint32_t n = 1; n <= 16; ++n) if (early(M, 500, n, 1) || early(M, 500, n, 2) || early(2 * M, 500, n, 0)) return 80;
+        for (uint32_t n = 1; n <= 16; ++n) if (early(M, 500, n, 1) || early(M, 500, n, 2) || early(2 * M, 500, n, 0)) return 160;
         for (uint32_t n = 1; n <= 2; ++n) {
-            if (!early(2 * M, 500, n, 1) || !early(11 * M, 500, n, 1) || early(12 * M, 500, n, 1) || early(125 * M, 500, n, 1) || early(25 * M, 1023, n, 1) || !early(25 * M, 1365, n, 1) || !early(60 * M, 9000, n, 1)) return 81;
-            if (early(8 * M, 20, n, 1) || !early(8 * M, 33, n, 1) || early(25 * M, 14, n, 1) || early(25 * M, 64, n, 1)) return 82;
-            if (!early(2 * M, 500, n, 2) || !early(125 * M, 500, n, 2) || early(25 * M, 20, n, 2) || !early(25 * M, 50, n, 2) || early(25 * M, 65, n, 2) || !early(25 * M, 100, n, 2)) return 83;
+            if (!early(2 * M, 500, n, 1) || !early(11 * M, 500, n, 1) || early(12 * M, 500, n, 1) || early(125 * M, 500, n, 1) || early(25 * M, 1023, n, 1) || !early(25 * M, 1365, n, 1) || !early(60 * M, 9000, n, 1)) return 161;
+            if (early(8 * M, 20, n, 1) || !early(8 * M, 33, n, 1) || early(25 * M, 14, n, 1) || early(25 * M, 64, n, 1)) return 162;
+            if (!early(2 * M, 500, n, 2) || !early(125 * M, 500, n, 2) || early(25 * M, 20, n, 2) || !early(25 * M, 50, n, 2) || early(25 * M, 65, n, 2) || !early(25 * M, 100, n, 2)) return 163;
         }
-        for (uint32_t n = 3; n <= 4; ++n) if (!early(2 * M, 18, n, 1) || !early(2 * M, 18, n, 2) || !early(60 * M, 64, n, 2) || early(60 * M, 65, n, 2) || !early(60 * M, 65, n, 1) || !early(60 * M, 100, n, 2)) return 85;
-        for (uint32_t n = 5; n <= 8; ++n) for (uint32_t m = 1; m <= 2; ++m) if (early(25 * M, 33, n, m) || !early(25 * M, 50, n, m) || early(25 * M, 65, n, m) || !early(25 * M, 500, n, m)) return 86;
-        for (uint32_t n : {9u, 16u}) for (uint32_t m = 1; m <= 2; ++m) if (early(25 * M, 64, n, m) || early(25 * M, 150, n, m) || !early(25 * M, 500, n, m) || early(25 * M, 500, 17, m)) return 87;
+        for (uint32_t n = 3; n <= 4; ++n) if (!early(2 * M, 18, n, 1) || !early(2 * M, 18, n, 2) || !early(60 * M, 64, n, 2) || early(60 * M, 65, n, 2) || !early(60 * M, 65, n, 1) || !early(60 * M, 100, n, 2)) return 165;
+        for (uint32_t n = 5; n <= 8; ++n) for (uint32_t m = 1; m <= 2; ++m) if (early(25 * M, 33, n, m) || !early(25 * M, 50, n, m) || early(25 * M, 65, n, m) || !early(25 * M, 500, n, m)) return 166;
+        for (uint32_t n : {9u, 16u}) for (uint32_t m = 1; m <= 2; ++m) if (early(25 * M, 64, n, m) || early(25 * M, 150, n, m) || !early(25 * M, 500, n, m) || early(25 * M, 500, 17, m)) return 167;
     }
     if (adacomp_selftest_binindex() != 0) return 9;
     for (int c = 1; c > -9; --c) if (!adacomp_strerror(c)) return 10;
