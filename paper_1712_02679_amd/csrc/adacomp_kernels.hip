@@ -2853,13 +2853,14 @@ __device__ __forceinline__ void unpack8_chunk(const Args &a, const UTileDev &ut,
 
 // The first n_groups workgroups take a group of the 16-bit layers each, the others up to four chunks of the
 // 8-bit ones.  Dynamic LDS: launch_unpack.  LG: 4 (k_unpack_few), 8 or 16 learners to a group of the former.
-// With 3 to 8 packets and the optimizer's step it is held to 72 vector registers and 96 scalar ones, with which 7 workgroups are resident: from 97
+// With 3 to 8 packets and the optimizer's step, and with more than 8, it is held to 72 vector registers and 96 scalar ones, with which 7 workgroups are resident: from 97
 // scalar ones on a SIMD has room for 6 waves only, from 73 vector ones too.  In us, 106 scalar registers and, Adam, 81 vector ones /
 // as it is: 25 M elements, L_T 12, SGD, 8 packets 104.9 / 98.5, Adam 150.7 / 130.4; L_T 16 103.3 / 93.0, 142.3 / 128.5; 30 M, L_T 8, and 30 M, 500
 // 213.8 / 202.9, 316.5 / 280.9; 6 M, L_T 8, SGD, 4 25.3 / 22.8; 54 M with 4 M at L_T 16 153.1 / 153.7, 227.7 / 229.2; at the worst 4 M, L_T 16, and
-// 4 M, 500, SGD, 4 26.9 / 28.7, where the last workgroups fall into a round of their own.
+// 4 M, 500, SGD, 4 26.9 / 28.7, where the last workgroups fall into a round of their own.  Sums: 25 M, L_T 8, 16 packets 181.4 / 170.4, 9 110.9 / 104.5;
+// 60 M, L_T 16, 24 340.0 / 321.7; 12 M, L_T 16, and 12 M, 500, 16 70.3 / 70.3.
 template <int MODE, uint32_t LG>
-__global__ __launch_bounds__(kWG, MODE != 0 && LG == 8u ? 7 : 4) void k_unpack8(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
+__global__ __launch_bounds__(kWG, (MODE != 0 && LG == 8u) || LG == 16u ? 7 : 4) void k_unpack8(const UTileDev *const tiles, const UGroupDev *const groups, const uint32_t n_groups,
                                                    const UnpackPackets<(LG == kFewLearners ? kFewInLaunch8 : packets_of<LG>)> a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];

@@ -51,7 +51,7 @@ def test_the_launch_of_two_packets_has_few_registers(kernels):
 
 
 # A SIMD has 512 vector registers, given out by 8, and 800 scalar ones, given out by 16 and with 16 more to a wave than it names.
-@pytest.mark.parametrize("kernel", [("k_unpack8", 1, 8), ("k_unpack8", 2, 8), ("k_unpack", 1, 1, 8, 0)])
+@pytest.mark.parametrize("kernel", [("k_unpack8", 1, 8), ("k_unpack8", 2, 8), ("k_unpack8", 0, 16), ("k_unpack", 1, 1, 8, 0)])
 def test_seven_workgroups_of_short_bins_fit_a_compute_unit(kernels, kernel):
     d = kernels[kernel]
     scalar = d["next_free_sgpr"] + 6   # vcc, flat scratch and xnack mask
