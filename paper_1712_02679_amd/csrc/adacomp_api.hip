@@ -141,6 +141,7 @@ int build_plan(const adacomp_layer_t *layers, uint32_t n_layers, bool tables, Pl
         ld.chunk_start = uint32_t(chunks_total);
         bins_total += n_bins;
         if (wb == 2u) { p.n_elems16 += n; p.n_bins16 += n_bins; }
+        else if (layers[l].elem_offset % 32u == 0u) p.n_elems8_lines += n;
         chunks_total += n_chunks;
         if (bins_total >= (uint64_t(1) << 32)) return ADACOMP_EINVAL;
         p.elem_span = std::max<uint64_t>(p.elem_span, layers[l].elem_offset + n);
@@ -390,7 +391,7 @@ int find_plan(const adacomp_layer_t *layers, uint32_t n_layers, const void *work
     // copy the scalars only; the tables already live on the device
     out.n_layers = p.n_layers; out.n_ctiles = p.n_ctiles; out.crowd_tiles = p.crowd_tiles; out.n_utiles = p.n_utiles; out.n_ugroups = p.n_ugroups; out.n_ugroups8 = p.n_ugroups8; out.n_usingles8 = p.n_usingles8;
     out.n_bins_total = p.n_bins_total; out.n_chunks_total = p.n_chunks_total;
-    out.n_elems16 = p.n_elems16; out.n_bins16 = p.n_bins16;
+    out.n_elems16 = p.n_elems16; out.n_bins16 = p.n_bins16; out.n_elems8_lines = p.n_elems8_lines;
     out.elem_span = p.elem_span; out.n_elems_total = p.n_elems_total; out.stage_entries = p.stage_entries;
     out.fixed_bytes = p.fixed_bytes; out.bound_bytes = p.bound_bytes;
     for (int c = 0; c < 2; ++c) out.n_class_tiles[c] = p.n_class_tiles[c];
@@ -472,12 +473,22 @@ static bool unpack_hold_few(uint64_t n_elems, uint64_t n_tiles, uint32_t n_learn
     return n_learners <= 4u && n_elems >= kResidentElems && n_elems >= 2900u * n_tiles;
 }
 
-// Plain sums of one or two packets over layers with 8-bit words that k_unpack_few takes, in a launch of their own or together with the
-// 16-bit layers: how many workgroups per compute unit they are held to.  Full tiles and next to no words to add: the launch is a stream of
-// stores, which HBM takes at a higher rate with fewer in flight.  As many as fit / 5 / 4, in us (or as 1):
-//   8-bit words alone, 1 packet, L_T 64, 25 M elements 22.7 / 21.2 / 19.9, 40 M 34.8 / 33.9 / 29.3, 60 M 52.0 / 50.9 / 41.4, 13 M 11.3 / 11.7 / 12.9; 63, 60 M
-//     48.8 / 44.9 / 42.7; 60 49.7 / 44.0 / 42.3; 55 48.2 / 44.4 / 45.2.  2 packets: 64, 25 M 22.5 / 21.1 / 23.8, 40 M 35.7 / 31.2 / 35.6, 60 M 52.5 / 44.3 / 51.1; 60, 60 M 44.5 / 46.4 / 53.1, 55 44.4 / 50.4 / 58.5.
-//     4 packets 54.1 / 64.2 / 74.5.
+// Plain sums of one or two packets over layers with 8-bit words and nothing else, in k_unpack_few: how many workgroups per compute unit they are
+// held to.  Full tiles and few words to add: the launch is a stream of stores, which HBM takes at a higher rate with fewer in flight, if the
+// workgroups' tiles share lines of 128 bytes above all (layers that do not begin on one).  As many as fit / 5 / 4, in us:
+//   tiles on lines, 1 packet: L_T 64, 14 M elements 11.3 / 11.2 / 12.2, 20 M 15.5 / 14.5 / 16.0, 25 M 18.9 / 17.1 / 18.9, 60 M 42.5 / 36.5 / 39.8, 125 M 90.8 / 76.5 / 80.9; 58, 60 M
+//     43.8 / 36.6 / 42.6; 55 43.1 / 37.9 / 44.2.  2 packets: 64, 25 M 17.6 / 20.4 / 22.9, 60 M 36.5 / 43.7 / 50.4, 125 M 76.2 / 98.6 / 117; 55, 60 M 40.4 / 49.7 / 58.3;
+//   off lines, 1 packet: 64, 14 M 12.9 / 12.3 / 12.7, 20 M 18.0 / 17.1 / 16.5, 25 M 22.0 / 21.0 / 19.7, 60 M 51.7 / 49.9 / 44.8, 125 M 107 / 104 / 94; 58, 60 M 52.1 / 50.1 /
+//     43.0; 55 51.8 / 49.8 / 44.6; 54, 33 M 28.8 / 26.2 / 26.6, 60 M 52.0 / 47.2 / 45.2, 125 M 107 / 89 / 100.  2 packets: 64, 14 M 12.5 / 13.4 / 15.0, 20 M 18.7 / 17.8 / 19.6, 25 M
+//     22.7 / 20.7 / 23.1, 60 M 50.9 / 43.7 / 50.5, 125 M 98.5 / 98.2 / 117; 60, 60 M 54.9 / 45.9 / 53.0; 58 48.1 / 47.6 / 55.4, 125 M 92 / 108 / 129; 55, 60 M 46.5 / 49.4 / 57.7.
+uint32_t unpack_hold_sum8_alone(uint64_t elems8, uint64_t tiles8, bool on_lines, uint32_t n_learners)
+{
+    if (elems8 < kHoldSum8Elems || elems8 < 3200u * tiles8) return 0u;   // (emptier tiles have more words to add: unpack_hold_sum8)
+    if (n_learners == 1u) return !on_lines && elems8 >= 3500u * tiles8 ? 4u : 5u;
+    return n_learners == 2u && !on_lines && elems8 >= 3800u * tiles8 ? 5u : 0u;
+}
+
+// ... and over them together with 16-bit layers, in one launch (tiles8 .. bins16: of either).  As many as fit / 5 / 4, in us (or as 1):
 //   Tiles of fewer elements have bins of fewer, and more words to add, which other workgroups cover: 95 % at L_T 20 and 5 % at 64, 1 packet, 25 M
 //     1 / 1.16 / 1.35, 60 M 1 / 1.32 / 1.56; half and half (1950 to a tile), 60 M 1 / 1.11 / 1.18; 33 and 64 (2830) 1 / 1.06 / 1.12; 45 % at 20, 5 % at 64 and the
 //     rest at 500 1 / 1.05 / 1.14.
@@ -1027,7 +1038,11 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         if (resident16 != 0u && a.mode != 0u && (early16 || now <= 2u)) resident16 = 4u;
         uint32_t resident8 = unpack_hold_few(elems8, p.n_usingles8, now) ? 4u : 0u;
         uint32_t resident_both = unpack_hold_few(p.n_elems_total, p.n_utiles, now) && p.n_elems16 >= 60u * uint64_t(now) * p.n_bins16 ? 4u : 0u;
-        if (a.mode == 0u) resident8 = resident_both = unpack_hold_sum8(elems8, p.n_usingles8, p.n_elems16, p.n_bins16, now);   // (up to two packets: one launch)
+        if (a.mode == 0u) {
+            const bool on_lines = 2u * p.n_elems8_lines >= elems8 && reinterpret_cast<uintptr_t>(dense_out) % 128u == 0u;
+            resident8 = p.n_elems16 == 0u ? unpack_hold_sum8_alone(elems8, p.n_usingles8, on_lines, now) : 0u;
+            resident_both = unpack_hold_sum8(elems8, p.n_usingles8, p.n_elems16, p.n_bins16, now);
+        }
         // Launches over all groups take single tiles without a look at the table, a round of scalar loads; over both word widths only
         // while every tile has a compute unit to itself, since those of short bins, which take longest, stand first in it (2 M elements,
         // 50 and 500, 16 packets: by the table 13.8 us, without 14.4; 0.4 M 13.0 / 12.6).

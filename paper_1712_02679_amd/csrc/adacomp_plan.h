@@ -111,6 +111,7 @@ constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workg
 //          186, 16 194 / 190 / 189; 13 M, L_T 500, 8 65.4 / 64.2 / 65.3
 constexpr uint32_t kResidentLds[2] = {32000, 40900};   // bytes of LDS that leave five, four workgroups on a compute unit
 constexpr uint64_t kResidentElems = 11600000, kResidentElemsSum = 23200000, kResidentElemsSumMany = 32000000;   // from which on: with the optimizer; sums of up to 4 packets; of more
+constexpr uint64_t kHoldSum8Elems = 18000000;   // elements of layers with 8-bit words from which on sums of one or two packets over nothing else are held (unpack_hold_sum8_alone)
 constexpr uint64_t kEarlyElems = 1500000;   // elements of a launch from which on the optimizer's state is fetched ahead of the adds (unpack_early_for)
 constexpr uint32_t kFewTilesTogether = 1024;   // groups up to which a plain sum of few packets waits for all packets' records together (k_unpack_few)
 constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table that go alone (3 per compute unit)
@@ -192,6 +193,7 @@ struct Plan {
     uint64_t n_elems16 = 0, n_bins16 = 0;   // of the layers with 16-bit words
     uint64_t elem_span = 0;     // max over layers of elem_offset + n_elems
     uint64_t n_elems_total = 0;
+    uint64_t n_elems8_lines = 0;  // of the layers with 8-bit words that begin on a line of 128 bytes: all of their tiles do then
     uint64_t stage_entries = 0; // entries of the staging array: sum over the compress tiles of their element counts rounded up to 4
     uint64_t fixed_bytes = 0;   // packet bytes before the first word
     uint64_t bound_bytes = 0;   // packet bytes with every element sent
@@ -387,6 +389,7 @@ uint32_t one_launch_for(const Plan &p, size_t n_learners, size_t workspace_bytes
 bool pack_wide_for(const Plan &p, size_t n_learners, uint32_t compute_units);
 uint32_t place_lanes_for(const Plan &p);
 uint32_t resident_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, uint32_t n_learners, uint32_t mode);
+uint32_t unpack_hold_sum8_alone(uint64_t elems8, uint64_t tiles8, bool on_lines, uint32_t n_learners);
 uint32_t unpack_hold_sum8(uint64_t elems8, uint64_t tiles8, uint64_t elems16, uint64_t bins16, uint32_t n_learners);
 bool unpack_early_for(uint64_t n_elems, uint64_t n_bins, uint64_t n_tiles, bool words8, uint32_t n_learners, uint32_t mode);
 uint32_t unpack8_wg_log(const Plan &p, uint32_t n_chunks, uint32_t n_groups16, uint32_t n_learners);

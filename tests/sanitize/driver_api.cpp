@@ -473,6 +473,25 @@ int main()
         if (held(2 * M, 64, 38 * M, 65, 1) != 5 || held(2 * M, 64, 38 * M, 77, 1) != 5 || held(2 * M, 64, 38 * M, 79, 1) != 4 || held(30 * M, 64, 10 * M, 65, 1) != 4 || held(2 * M, 64, 38 * M, 129, 1) != 4 || held(20 * M, 64, 20 * M, 65, 1) != 5 || held(38 * M, 64, 2 * M, 65, 1) != 4) return 78;
         if (held(2 * M, 64, 38 * M, 65, 2) != 0 || held(20 * M, 64, 20 * M, 70, 2) != 0 || held(2 * M, 64, 38 * M, 76, 2) != 5 || held(2 * M, 64, 38 * M, 500, 2) != 5 || held(38 * M, 64, 2 * M, 65, 2) != 5) return 79;
     }
+    {   // ... over 8-bit layers alone: by the lines of 128 bytes that the layers begin on, the tiles' fill and the number of elements
+        using namespace adacomp;
+        auto held = [](uint64_t elems, uint32_t lt, uint32_t layers, uint64_t first, uint32_t learners) {   // layers of equal size, the next `first` elements after the end of one
+            std::vector<adacomp_layer_t> t;
+            const uint64_t each = elems / layers / 32 * 32;
+            for (uint32_t i = 0; i < layers; ++i) t.push_back(adacomp_layer_t{first + i * (each + first), each, lt, 0});
+            Plan p;
+            if (build_plan(t.data(), layers, true, p) != ADACOMP_OK) return 99u;
+            return unpack_hold_sum8_alone(p.n_elems_total, p.n_usingles8, 2 * p.n_elems8_lines >= p.n_elems_total, learners);
+        };
+        const uint64_t M = 1000000;
+        for (uint64_t on : {uint64_t(0), uint64_t(32), uint64_t(64)})
+            if (held(19 * M, 64, 10, on, 1) != 5 || held(17 * M, 64, 10, on, 1) != 0 || held(60 * M, 55, 10, on, 1) != 5 || held(125 * M, 64, 3, on, 2) != 0 || held(25 * M, 48, 10, on, 1) != 0) return 168;
+        for (uint64_t off : {uint64_t(4), uint64_t(20)}) {
+            if (held(19 * M, 64, 1, off, 1) != 4 || held(60 * M, 55, 1, off, 1) != 4 || held(60 * M, 54, 1, off, 1) != 5 || held(17 * M, 64, 1, off, 1) != 0) return 169;
+            if (held(19 * M, 64, 1, off, 2) != 5 || held(17 * M, 64, 1, off, 2) != 0 || held(60 * M, 60, 1, off, 2) != 5 || held(60 * M, 59, 1, off, 2) != 0 || held(60 * M, 64, 1, off, 3) != 0 || held(60 * M, 64, 1, off, 0) != 0) return 170;
+        }
+        if (held(25 * M, 64, 8, 4, 2) != 5 || held(25 * M, 64, 2, 4, 2) != 5 || held(25 * M, 20, 4, 4, 1) != 0) return 171;
+    }
     {   // launches that fetch weights and moments ahead of the adds, of which there are none: refused before anything is launched
         using namespace adacomp;
         UnpackArgs a{};
