@@ -1037,6 +1037,9 @@ static int unpack_common(const adacomp_layer_t *layers, uint32_t n_layers, const
         uint32_t resident16 = resident_for(p.n_elems16, p.n_bins16, tiles16, now, a.mode);
         if (resident16 != 0u && a.mode != 0u && (early16 || now <= 2u)) resident16 = 4u;
         uint32_t resident8 = unpack_hold_few(elems8, p.n_usingles8, now) ? 4u : 0u;
+        // Over both widths: early as over one (behind / ahead, us, 12 M, L_T 50, and 13 M, 500: SGD, 4 packets 71.3 / 66.3, 8 76.1 / 69.9, Adam, 8 112.2 / 107.6); and held where the
+        // 16-bit layers have few words to a bin (as many as fit / 4: 12 M and 13 M, SGD, 4 67.5 / 66.3; 30 M, 50, and 30 M, 4000, SGD, 4 161.0 / 156.0, Adam, 3 241.5 / 238.3; 5 M, 50,
+        // and 45 M, 500, Adam, 3 205.0 / 201.1; not by this line, 20 M, 50, and 20 M, 200, SGD, 4 107.0 / 103.5; with tiles less full 5 M, 20, and 20 M, 65, SGD, 2 65.9 / 71.1).
         uint32_t resident_both = unpack_hold_few(p.n_elems_total, p.n_utiles, now) && p.n_elems16 >= 60u * uint64_t(now) * p.n_bins16 ? 4u : 0u;
         if (a.mode == 0u) {
             const bool on_lines = 2u * p.n_elems8_lines >= elems8 && reinterpret_cast<uintptr_t>(dense_out) % 128u == 0u;

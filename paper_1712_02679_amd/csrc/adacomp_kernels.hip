@@ -47,11 +47,9 @@ typedef float vfloat4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ vfloat4 load_stream4(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const vfloat4 *>(p)); }
 __device__ __forceinline__ void store_stream4(float *p, vfloat4 v) { __builtin_nontemporal_store(v, reinterpret_cast<vfloat4 *>(p)); }
 
-// The same accesses as raw buffer instructions, for the Adam epilogue of k_unpack, which streams
-// three arrays in and out per tile: addressing through a descriptor (scalar base, 32-bit offset)
-// takes fewer registers there than 64-bit addresses, enough to stay within 80 without spilling,
-// and the pass runs 4 % faster (k_fused and the plain sum measured the same with them, the
-// SGD epilogue 4 % slower, so those keep global accesses).  A descriptor covers one tile:
+// The same accesses as raw buffer instructions, for k_pack and for the optimizer's epilogues, which stream two or three arrays in and out per
+// tile: addressing through a descriptor (scalar base, 32-bit offset) takes fewer registers there than 64-bit addresses, and needs no
+// alignment but the element's (k_fused and the plain sum measured the same with them).  A descriptor covers one tile:
 // base = the tile's first element, size = its bytes; an access past the tile is dropped by the
 // hardware.
 typedef uint32_t vuint4 __attribute__((ext_vector_type(4)));
@@ -2456,11 +2454,8 @@ __device__ __forceinline__ GroupAndTile first_records(const UTileDev *const tile
 
 // MODE 0: dense_out <- sum.  MODE 1 / 2: also (or only) the SGD / Adam step on weights and state.
 // KIND 0 / 1: all groups of this launch belong to layers with 16-bit / 8-bit words; 2: either (the
-// layer says which).  Large tables get one launch per kind: each path alone needs fewer registers
-// than a kernel that holds both, which buys resident workgroups (8 % of the 16-bit path's time on
-// the 125 M-element table).  Small tables, where a second launch would cost more than that, use
-// the kernel that holds both, one path after a branch.  The single-width kernels are held to 80 registers (6 waves per
-// SIMD, what the LDS tile allows).
+// layer says which), one path after a branch; kUnpackSplitTiles has where one launch for both is taken and where one per kind.
+// The single-width kernels are held to 80 registers (6 waves per SIMD, what the LDS tile allows).
 // EARLY: weights and moments are asked for ahead of the adds and kept through them, in up to 128 registers.
 template <int MODE, bool W8, uint32_t LG, bool EARLY, class Args>
 __device__ __forceinline__ void unpack_tiles(const Args &a, const UTileDev *const tiles, const UGroupDev grp, const UTileDev ut0, float *const s_acc,

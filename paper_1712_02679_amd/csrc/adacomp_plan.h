@@ -88,9 +88,11 @@ __host__ __device__ inline uint32_t single_tile(uint32_t g, uint32_t n_tiles)
 constexpr uint32_t kUnpackGroupTiles = 8;   // at most this many tiles per group
 constexpr uint32_t kUnpackMinGroups = 2048;  // groups of more than one tile only while this many workgroups remain (8 per compute unit)
 // Tables with both word widths: one launch per width on tables of more tiles than this and with more packets than
-// that.  The kernel for both has registers for both, which costs the one for 16 packets a workgroup or two per compute unit,
-// the others none; and two launches are two ends.  Two / one, in us: ResNet-50's table, SGD, 8 packets 91 / 85, 16 113 / 116, 1
-// 77 / 72; 30 M, L_T 64 and 500, sum of 8 42 / 35; 10 M, 50 and 500, SGD with 8 43.6 / 37.4, sum of 6 18.5 / 13.6.
+// that: two launches are two ends, and the kernel for both and 16 packets had registers for fewer workgroups than those for one width.
+// It has 75 now, as few as those, and one launch would be the faster one for more packets too, up to some 60 M elements.  Two / one, in us:
+//   up to 8 packets: ResNet-50's table, SGD, 8 91 / 85, 1 77 / 72; 30 M, L_T 64 and 500, sum of 8 42 / 35; 10 M, 50 and 500, SGD with 8 43.6 / 37.4, sum of 6 18.5 / 13.6;
+//   more, as it is / as one: 4 M, 50, and 8 M, 500, sum of 9 27.1 / 21.8, 16 31.1 / 24.1, SGD 51.2 / 44.5, Adam 71.6 / 64.3; 10 M and 15 M, sum of 16 61.3 / 48.9, SGD 91.5 / 84.0;
+//   30 M, 64, and 30 M, 500, 16 110.3 / 99.7, 187.5 / 183.5, 267.7 / 267.6; 60 M, 50, and 65 M, 500, 16 241 / 232, 382 / 386, 553 / 573.
 constexpr uint32_t kUnpackSplitTiles = 2048;
 constexpr uint32_t kUnpackTogether = 8;
 constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workgroups on a compute unit
@@ -98,7 +100,8 @@ constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workg
 // flight than the workgroups that fit put there (as it does k_fused, below): LDS that no kernel touches holds them to 5
 // or 4 to a compute unit.  That needs full tiles, since a workgroup in one of 2080 elements (L_T 65; 2400 at 150 and 300, 2800 at
 // 700, 3000 at 3000 and 9000, 3200 at 100 and 200, 4000 at 500) has half of them in flight, and few words to each: what hides the
-// adds is other workgroups.  As many as fit (8, 7 or 6: up to 4, 8 or more packets) / 5 / 4, in us, 40 M elements:
+// adds is other workgroups.  As many as fit (8, 7 or 6: up to 4, 8 or more packets) / 5 / 4, in us, 40 M elements (SGD and
+// Adam: behind the adds, one slot after the other, as these launches were when this was measured; as they are, below):
 //   sum    L_T 65, 1 packet 34 / 43 / 51, 4 50 / 63 / 74, 8 76 / 86 / 98; 100, 1 38.6 / 35.3 / 36.2, 4 37.9 / 46.9 / 54; 200, 4
 //          42.2 / 39.2 / 39.3, 8 40.6 / 43.4 / 48.7; 300, 4 42.3 / 41.6 / 39.6, 8 41.5 / 44.4 / 51.6; 500, 1 42.2 / 41.5 / 40.5, 4 43.4 /
 //          41.8 / 41.8, 8 46.6 / 42.0 / 42.2, 16 47.9 / 48.8 / 53; 9000, 4 38.5 / 36.3 / 36.1, 8 38.0 / 39.2 / 42.8; 24 M, L_T 500, 4 25.2 /
@@ -109,11 +112,19 @@ constexpr uint32_t kUnpackLdsFull = 27306;  // bytes of LDS that leave six workg
 //   Adam   L_T 65, 4 185 / 189 / 205, 8 193 / 207 / 228; 100, 4 194 / 189 / 191, 8 191 / 193 / 202; 200, 8 192 / 190 / 194; 300, 4 184 / 182 /
 //          187, 8 183 / 185 / 194; 500, 1 205 / 203 / 188, 8 204 / 195 / 189, 16 202 / 198 / 193 (125 M 519 / 512 / 520); 9000, 8 193 / 189 /
 //          186, 16 194 / 190 / 189; 13 M, L_T 500, 8 65.4 / 64.2 / 65.3
+//   launches that fetch ahead, and those of 1 and 2 packets, are held to 4 where others are held to 5 (as many as fit: 5 or 4, for 1 and 2 packets 6 or 7).  60 M
+//   elements: SGD    300, 1 154.2 / 150.0 / 151.3; 500, 1 156.3 / 154.4 / 152.1, 8 154.5 / 154.7 / 152.7, 16 155.5 / 155.8 / 156.0; 700, 1 170.1 / 161.2 / 160.8, 4 167.8 / 161.0 / 158.9; 3000, 1
+//          182.9 / 172.3 / 168.1, 8 163.6 / 163.3 / 160.1; 9000, 4 172.1 / 164.9 / 160.7; 125 M, 500, 4 332 / 339 / 334, 8 326 / 326 / 319
+//          Adam   500, 1 243.0 / 239.2 / 236.7, 4 243.0 / 243.0 / 239.5, 8 238.3 / 238.1 / 237.8; 3000, 4 258.4 / 258.7 / 252.1; 125 M, 500, 1 521 / 512 / 500, 4 520 / 520 / 508, 16 498 / 502 / 498
+//   others, not held by the lines of tiles and bins: SGD 700, 8 170.5 / 168.0 / 164.5; Adam 300, 8 244.9 / 237.8 / 240.0, 700, 8 263.5 / 263.9 / 257.3
 constexpr uint32_t kResidentLds[2] = {32000, 40900};   // bytes of LDS that leave five, four workgroups on a compute unit
 constexpr uint64_t kResidentElems = 11600000, kResidentElemsSum = 23200000, kResidentElemsSumMany = 32000000;   // from which on: with the optimizer; sums of up to 4 packets; of more
 constexpr uint64_t kHoldSum8Elems = 18000000;   // elements of layers with 8-bit words from which on sums of one or two packets over nothing else are held (unpack_hold_sum8_alone)
 constexpr uint64_t kEarlyElems = 1500000;   // elements of a launch from which on the optimizer's state is fetched ahead of the adds (unpack_early_for)
-constexpr uint32_t kFewTilesTogether = 1024;   // groups up to which a plain sum of few packets waits for all packets' records together (k_unpack_few)
+// Groups up to which a plain sum of few packets waits for all packets' records together (k_unpack_few).  Together / not, in us: 4 packets, L_T 500, 2 M elements
+// 4.46 / 4.58, 4 M (1000 groups) 5.67 / 5.79, 8 M 7.89 / 7.87, 25 M 22.8 / 22.5; 100, 4 M 7.65 / 7.64; 1 M, L_T 50, and 1.5 M, 500 6.34 / 6.47; 2.4 M and 3.6 M (1670) 9.17 / 8.30, 6.4 M and
+// 9.6 M 17.9 / 17.4.
+constexpr uint32_t kFewTilesTogether = 1024;
 constexpr uint32_t kUnpackTaperTiles = 768;  // tiles at the end of the table that go alone (3 per compute unit)
 
 // What k_fused leaves per tile for k_scan and k_place: one 16-byte record, so that a tile makes one
